@@ -5,23 +5,32 @@
 //     p_u  = exp(z_u - lse)                     dp_u = <dO, v_u>             Delta = <dO, O> (= sum_u p_u dp_u)
 //     dz_u = p_u (dp_u - Delta)                 dq   = scale * sum_u dz_u k_u
 //     dk_u += scale * dz_u q                    dv_u += p_u dO               (summed over rows and over the group)
-// This file: fp32 arithmetic on the vector units for any G <= 16, d in {64, 128}, fp32 or bf16 data (the paper's
-// head shape in bf16 takes the matrix-core path of attn_bwd_mfma.hip instead), in three kernels:
+// This file: any G <= 16, d in {64, 128}, fp32 or bf16 data (the paper's head shape in bf16 takes the matrix-core path of
+// attn_bwd_mfma.hip instead).  All weights and sums are fp32; the products run on the matrix cores as described in
+// gen_unit.h.  Three kernels:
 //   delta : Delta per (row, query head)
-//   dq    : one workgroup per (row, KV head), the loop of the forward generic kernel
-//   dkv   : one workgroup per (KV block, chunk of 256 later tokens, KV head): finds the tokens of its chunk that
-//           selected the block, accumulates the block's 64 rows of dK and dV in registers and adds them to the
-//           float32 result with atomics (one add per element and workgroup; the order of the adds, and with it the
-//           last bits of dK and dV, can differ from run to run).
+//   dq    : the workgroup and block walk of the generic forward kernel: per block S^T = K Q^T and dP^T = V dO^T
+//           (keys x columns), dZ^T in registers, dQ^T += K^T dZ^T
+//   dkv   : one workgroup of 4 wavefronts per (KV block, chunk of later tokens, KV head): lists the tokens of its chunk
+//           that selected the block and takes 16 / G of them at a time, 16 rows of Q and dO; wavefront w holds keys
+//           16 w .. 16 w + 15 (their K and V rows stay in registers): S = Q K^T, dP = dO V^T (rows x keys), then
+//           dV += P^T dO and dK += dZ^T Q, contracted over the 16 rows.  The block's 64 rows of dK and dV are added to
+//           the float32 result with atomics (one add per element and workgroup; the order of the adds, and with it
+//           the last bits of dK and dV, can differ from run to run).
+// Measured, bf16, 1985 tokens, 8 heads on 2, d 128, 16 blocks: dq 1681 -> 86 us, dkv 5636 -> 107 us (vector arithmetic
+// before; with its atomic adds as the accumulators lie in registers instead of through LDS dkv took 490 us).
 #include <algorithm>
 
-#include "common.h"
+#include "gen_unit.h"
 
 namespace ifv2 {
 
 namespace {
 
-constexpr int BWD_CHUNK = 256;      // tokens per dkv workgroup
+using namespace gen;
+
+constexpr int NW = 4;               // wavefronts per workgroup of the dq and dkv kernels
+constexpr int BWD_CHUNK = 256;      // most tokens a dkv workgroup looks at
 
 template <typename T>
 struct BwdArgs {
@@ -51,80 +60,98 @@ __global__ void __launch_bounds__(256) bwd_delta_kernel(BwdArgs<T> a) {
 }
 
 template <typename T, int D>
-__global__ void __launch_bounds__(256) bwd_dq_kernel(BwdArgs<T> a) {
-    const int row = blockIdx.x, h = blockIdx.y;
-    const int G = a.hq / a.map.num_kv_heads;
-    const RowLoc loc = locate(a.map, row);
-    const int t = loc.pos, bt = t / kBlock;
-    const bool dense = a.idx == nullptr || loc.len < a.dense_below;
-    const int32_t *my_idx = dense ? nullptr : a.idx + head_row(a.map, h, row) * a.topk_total;
-    const int nsteps = dense ? bt + 1 : a.topk_total;
-
-    __shared__ float qs[kMaxGroup][D], gs[kMaxGroup][D];      // scale * q, dO
-    __shared__ float dzs[kMaxGroup][kBlock];
-    __shared__ float lse_s[kMaxGroup], delta_s[kMaxGroup];
+__global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
+    constexpr int N = D / 16;
+    __shared__ Union un;
+    __shared__ float o_s[NW][kCols][D + 4];
+    __shared__ int s_tile[2];
+    const int h = blockIdx.y, G = a.hq / a.map.num_kv_heads;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    for (int e = tid; e < kMaxGroup * D; e += 256) {
-        const int g = e / D, c = e % D;
-        const int64_t off = ((int64_t)row * a.hq + h * G + g) * D + c;
-        qs[g][c] = g < G ? Elem<T>::load(a.q + off) * a.scale : 0.f;
-        gs[g][c] = g < G ? Elem<T>::load(a.dout + off) : 0.f;
-    }
-    if (tid < kMaxGroup) {
-        lse_s[tid] = tid < G ? a.lse[qhead_row(a.map, h * G + tid, a.hq, row)] : 0.f;
-        delta_s[tid] = tid < G ? a.delta[qhead_row(a.map, h * G + tid, a.hq, row)] : 0.f;
-    }
-    __syncthreads();
-    const T *kb = a.k + loc.kv_base + (int64_t)h * a.map.kv_head_stride;
-    const T *vb = a.v + loc.kv_base + (int64_t)h * a.map.kv_head_stride;
-    constexpr int NACC = kMaxGroup * D / 256;
-    float acc[NACC];
-#pragma unroll
-    for (int x = 0; x < NACC; ++x) acc[x] = 0.f;
+    Tile t;
+    if (!find_tile(a.map, gridDim.x - 1 - blockIdx.x, tile_tokens(a.map, G), t, s_tile)) return;
+    const bool dense = a.idx == nullptr || t.len < a.dense_below;
+    const int32_t *lists = dense ? nullptr : a.idx + head_row(a.map, h, t.row0) * a.topk_total;
+    const int nblk = (t.t0 + t.ntok - 1) / kBlock + 1;
+    const T *kb = a.k + t.kv_base + (int64_t)h * a.map.kv_head_stride;
+    const T *vb = a.v + t.kv_base + (int64_t)h * a.map.kv_head_stride;
 
-    for (int s = 0; s < nsteps; ++s) {
-        const int j = dense ? s : my_idx[s];
-        if (j < 0 || j > bt) continue;
-        const int u = j * kBlock + lane;
-        const bool valid = u <= t;
-        float z[4] = {0.f, 0.f, 0.f, 0.f}, dp[4] = {0.f, 0.f, 0.f, 0.f};     // heads w, w+4, w+8, w+12
-        if (valid) {
-            const T *kr = kb + (int64_t)u * a.map.kv_tok_stride, *vr = vb + (int64_t)u * a.map.kv_tok_stride;
-            for (int c = 0; c < D; ++c) {
-                const float kv = Elem<T>::load(kr + c), vv = Elem<T>::load(vr + c);
+    const int m = lane & 15, g = lane >> 4;
+    const int ti = m / G;
+    const bool used = ti < t.ntok;
+    const int row = t.row0 + (used ? ti : 0), qh = h * G + (used ? m - ti * G : 0);
+    RowFrag<T, D> qf, gf;
+    qf.load(a.q + ((int64_t)row * a.hq + qh) * D, g);
+    gf.load(a.dout + ((int64_t)row * a.hq + qh) * D, g);
+    const float lse = a.lse[qhead_row(a.map, qh, a.hq, row)], delta = a.delta[qhead_row(a.map, qh, a.hq, row)];
+
+    // as in the forward kernel: one pass for all tokens of the tile, and again token by token with the K rows that a
+    // token does not see taken as 0 if something came out that is not finite (0 x infinity)
+    uint32_t all = (1u << t.ntok) - 1u;
+    int solo = -1;
+    for (;;) {
+        const int solo_t = t.t0 + solo;
+        f32x4 acc[N];                                    // dQ^T: dim N (4 g + r) + j, this lane's column
 #pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    z[x] += qs[w + 4 * x][c] * kv;
-                    dp[x] += gs[w + 4 * x][c] * vv;
+        for (int j = 0; j < N; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int c0 = 0; c0 < nblk; c0 += kChunk) {
+            un.build(lists, a.topk_total, t, c0, nblk, all, tid, NW * 64);
+            const int count = un.count;
+            for (int e = w; e < count; e += NW) {
+                const int2 ent = un.list[e];
+                const int u0 = ent.x * kBlock;
+                const int lim = used && ((ent.y >> ti) & 1) ? t.t0 + ti - u0 : -1;
+                f32x4 s[4], dp[4];
+#pragma unroll
+                for (int kt = 0; kt < 4; ++kt) {
+                    const int64_t off = (int64_t)min(u0 + 16 * kt + m, t.len - 1) * a.map.kv_tok_stride;
+                    RowFrag<T, D> kf, vf;
+                    kf.load(kb + off, g);
+                    vf.load(vb + off, g);
+                    s[kt] = row_product<D>(kf, qf);
+                    dp[kt] = row_product<D>(vf, gf);
+                }
+#pragma unroll
+                for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float p = exp2_fast(__builtin_fmaf(s[kt][r], a.scale, -lse) * kLog2e);
+                        s[kt][r] = 16 * kt + 4 * g + r <= lim ? p * (dp[kt][r] - delta) : 0.f;
+                    }
+#pragma unroll
+                for (int kt = 0; kt < 4; ++kt) {
+                    Spread<T, D> kr[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int u = u0 + 16 * kt + 4 * g + r;
+                        kr[r].load(kb + (int64_t)min(u, t.len - 1) * a.map.kv_tok_stride, m);
+                        if (solo >= 0 && u > solo_t) kr[r].zero();
+                    }
+                    weighted_rows<false, D>(acc, s[kt], kr);
                 }
             }
+            __syncthreads();
         }
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const int g = w + 4 * x;
-            const float p = valid ? __expf(z[x] - lse_s[g]) : 0.f;
-            dzs[g][lane] = p * (dp[x] - delta_s[g]);
-        }
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < N; ++j) o_s[w][m][N * (4 * g + r) + j] = acc[j][r];
         __syncthreads();
-        const int nkeys = min(kBlock, t - j * kBlock + 1);
+        static_assert(NW * 64 == kCols * 16, "sixteen threads per column");
+        const int col = tid >> 4, d0 = (tid & 15) * N, tc = col / G;
+        float y[N];
+        bool bad = false;
 #pragma unroll
-        for (int x = 0; x < NACC; ++x) {
-            const int o = tid + x * 256;
-            const int g = o / D, c = o % D;
-            if (g < G) {
-                float sacc = 0.f;
-                for (int kk = 0; kk < nkeys; ++kk)
-                    sacc += dzs[g][kk] * Elem<T>::load(kb + (int64_t)(j * kBlock + kk) * a.map.kv_tok_stride + c);
-                acc[x] += sacc;
-            }
+        for (int j = 0; j < N; ++j) {
+            y[j] = ((o_s[0][col][d0 + j] + o_s[1][col][d0 + j]) + (o_s[2][col][d0 + j] + o_s[3][col][d0 + j])) * a.scale;
+            bad |= !finite(y[j]);
         }
+        const bool mine = tc < t.ntok && ((all >> tc) & 1u);
+        const bool again = solo < 0 && __syncthreads_or(mine && bad);
+        if (!again && mine) store_row<T, N>(a.dq + ((int64_t)(t.row0 + tc) * a.hq + h * G + col - tc * G) * D + d0, y);
+        if (solo < 0 && !again) return;
+        if (++solo >= t.ntok) return;
+        all = 1u << solo;
         __syncthreads();
-    }
-#pragma unroll
-    for (int x = 0; x < NACC; ++x) {
-        const int o = tid + x * 256;
-        const int g = o / D, c = o % D;
-        if (g < G) Elem<T>::store(a.dq + ((int64_t)row * a.hq + h * G + g) * D + c, acc[x] * a.scale);
     }
 }
 
@@ -140,36 +167,24 @@ __device__ inline bool list_has(const int32_t *e, int n, int j) {
 }
 
 template <typename T, int D>
-__global__ void __launch_bounds__(256) bwd_dkv_kernel(BwdArgs<T> a, int num_blocks) {
-    extern __shared__ float lds[];
-    constexpr int DS = D + 1;                                  // padded row: lanes read different rows
-    float *ks = lds, *vs = lds + kBlock * DS;                  // the block's K and V rows
-    float *qs = vs + kBlock * DS, *gs = qs + kMaxGroup * D;     // scale * q, dO of the current token
-    float *ps = gs + kMaxGroup * D, *dzs = ps + kMaxGroup * kBlock;
-    __shared__ int s_seq, s_j, s_list[BWD_CHUNK], s_wave_cnt[4];
-    __shared__ float lse_s[kMaxGroup], delta_s[kMaxGroup];
+__global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chunk) {
+    constexpr int N = D / 16;
+    __shared__ __attribute__((aligned(16))) T rows_s[2][2][kCols][D + 16 / sizeof(T)];      // [buffer][Q, dO][row]
+    __shared__ float lse_s[2][kCols], delta_s[2][kCols];
+    __shared__ int t_s[2][kCols];
+    __shared__ int s_tile[2], s_list[BWD_CHUNK], s_wave_cnt[NW];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int h = blockIdx.z, G = a.hq / a.map.num_kv_heads;
-    if (tid == 0) {
-        int rem = blockIdx.y, s = 0;
-        for (; s < a.map.batch; ++s) {
-            const int nb = (a.map.cu[s + 1] - a.map.cu[s] + kBlock - 1) / kBlock;
-            if (rem < nb) break;
-            rem -= nb;
-        }
-        s_seq = s;
-        s_j = rem;
-    }
-    __syncthreads();
-    const int seq = s_seq, j = s_j;
+    int j;
+    const int seq = find_seq_tile(a.map.cu, a.map.batch, kBlock, blockIdx.y, j, s_tile);
     if (seq >= a.map.batch) return;
     const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;
     // tokens of this chunk that can see the block: [max(chunk start, 64 j), min(chunk end, len))
-    const int c0 = blockIdx.x * BWD_CHUNK, c1 = min(c0 + BWD_CHUNK, len);
+    const int c0 = blockIdx.x * chunk, c1 = min(c0 + chunk, len);
     if (c1 <= j * kBlock || c0 >= len) return;
     const bool dense = a.idx == nullptr || len < a.dense_below;
 
-    // ---- which tokens of the chunk selected the block (in token order)
+    // ---- which tokens of the chunk selected the block (in token order); a chunk has at most one token per thread
     const int t_mine = c0 + tid;
     bool sel = t_mine < c1 && t_mine >= j * kBlock;
     if (sel && !dense) sel = list_has(a.idx + head_row(a.map, h, tok0 + t_mine) * a.topk_total, a.topk_total, j);
@@ -177,77 +192,108 @@ __global__ void __launch_bounds__(256) bwd_dkv_kernel(BwdArgs<T> a, int num_bloc
     if (lane == 0) s_wave_cnt[w] = __popcll(bal);
     __syncthreads();
     int base = 0, total = 0;
-    for (int x = 0; x < 4; ++x) {
+    for (int x = 0; x < NW; ++x) {
         if (x < w) base += s_wave_cnt[x];
         total += s_wave_cnt[x];
     }
     if (sel) s_list[base + __popcll(bal & ((1ull << lane) - 1ull))] = t_mine;
     if (total == 0) return;
-
-    // ---- the block's K and V rows (zero past the end of the sequence)
-    const int64_t kv_base = (int64_t)tok0 * a.map.kv_tok_stride + (int64_t)h * a.map.kv_head_stride;
-    for (int e = tid; e < kBlock * D; e += 256) {
-        const int r = e / D, c = e % D, u = j * kBlock + r;
-        const int64_t off = kv_base + (int64_t)u * a.map.kv_tok_stride + c;
-        ks[r * DS + c] = u < len ? Elem<T>::load(a.k + off) : 0.f;
-        vs[r * DS + c] = u < len ? Elem<T>::load(a.v + off) : 0.f;
-    }
-    // this thread accumulates key `lane`, channels w * D/4 .. + D/4
-    constexpr int NC = D / 4;
-    float acc_k[NC], acc_v[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc_k[c] = acc_v[c] = 0.f;
     __syncthreads();
 
-    for (int it = 0; it < total; ++it) {
-        const int t = s_list[it], row = tok0 + t;
-        for (int e = tid; e < kMaxGroup * D; e += 256) {
-            const int g = e / D, c = e % D;
-            const int64_t off = ((int64_t)row * a.hq + h * G + g) * D + c;
-            qs[e] = g < G ? Elem<T>::load(a.q + off) * a.scale : 0.f;
-            gs[e] = g < G ? Elem<T>::load(a.dout + off) : 0.f;
-        }
-        if (tid < kMaxGroup) {
-            lse_s[tid] = tid < G ? a.lse[qhead_row(a.map, h * G + tid, a.hq, row)] : 0.f;
-            delta_s[tid] = tid < G ? a.delta[qhead_row(a.map, h * G + tid, a.hq, row)] : 0.f;
-        }
-        __syncthreads();
-        const bool valid = j * kBlock + lane <= t;             // causal (t < len, so also inside the sequence)
-        float z[4] = {0.f, 0.f, 0.f, 0.f}, dp[4] = {0.f, 0.f, 0.f, 0.f};     // heads w, w+4, w+8, w+12 of key `lane`
-        for (int c = 0; c < D; ++c) {
-            const float kv = ks[lane * DS + c], vv = vs[lane * DS + c];
+    // ---- the wavefront's 16 keys: K and V rows as operands (past the end of the sequence: the last row, never visible)
+    const int m = lane & 15, g = lane >> 4;
+    const int key = j * kBlock + 16 * w + m;
+    const int64_t kv_off = (int64_t)(tok0 + min(key, len - 1)) * a.map.kv_tok_stride + (int64_t)h * a.map.kv_head_stride;
+    RowFrag<T, D> kf, vf;
+    kf.load(a.k + kv_off, g);
+    vf.load(a.v + kv_off, g);
+    f32x4 acc_k[N], acc_v[N];                                  // keys 16 w + 4 g + r, dim N m + i
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                z[x] += qs[(w + 4 * x) * D + c] * kv;
-                dp[x] += gs[(w + 4 * x) * D + c] * vv;
-            }
+    for (int i = 0; i < N; ++i) acc_k[i] = acc_v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // A group is the list's next `tokens` entries with their G heads: row x is entry x / G, head x % G.  The four
+    // wavefronts need the same 16 rows of Q and dO twice (as row operands and spread over lanes), so they pass through
+    // LDS once: thread (row, part) brings a sixteenth of its row, the next group's in flight in registers while the
+    // current one is computed; one barrier per group.  Unused rows hold zeros and see no key.
+    const int tokens = kCols / G;
+    const int x_row = tid >> 4, x_slot = x_row / G, x_head = h * G + x_row - x_slot * G;
+    struct Pre { Spread<T, D> q, g; float lse, delta; int t; };
+    auto fetch = [&](int it) -> Pre {
+        Pre pr;
+        const bool used = x_slot < min(tokens, total - it);
+        const int t = s_list[used ? it + x_slot : 0];
+        const int64_t off = ((int64_t)(tok0 + t) * a.hq + (used ? x_head : h * G)) * D;
+        pr.q.load(a.q + off, tid & 15);
+        pr.g.load(a.dout + off, tid & 15);
+        const int64_t lr = qhead_row(a.map, used ? x_head : h * G, a.hq, tok0 + t);
+        pr.lse = a.lse[lr];
+        pr.delta = a.delta[lr];
+        pr.t = used ? t : -1;
+        if (!used) { pr.q.zero(); pr.g.zero(); }
+        return pr;
+    };
+    auto stage = [&](int buf, const Pre &pr) {
+        pr.q.store_lds(&rows_s[buf][0][x_row][0], tid & 15);
+        pr.g.store_lds(&rows_s[buf][1][x_row][0], tid & 15);
+        if ((tid & 15) == 0) {
+            lse_s[buf][x_row] = pr.lse;
+            delta_s[buf][x_row] = pr.delta;
+            t_s[buf][x_row] = pr.t;
         }
+    };
+    stage(0, fetch(0));
+    __syncthreads();
+    int buf = 0;
+    for (int it = 0; it < total; it += tokens, buf ^= 1) {
+        const bool more = it + tokens < total;
+        Pre nxt = {};
+        if (more) nxt = fetch(it + tokens);
+        RowFrag<T, D> qf, gf;
+        qf.load_lds(&rows_s[buf][0][m][0], g);
+        gf.load_lds(&rows_s[buf][1][m][0], g);
+        const f32x4 s = row_product<D>(qf, kf);
+        const f32x4 dp = row_product<D>(gf, vf);
+        f32x4 p, dz;
+        Spread<T, D> qr[4], gr[4];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const int g = w + 4 * x;
-            const float p = valid && g < G ? __expf(z[x] - lse_s[g]) : 0.f;
-            ps[g * kBlock + lane] = p;
-            dzs[g * kBlock + lane] = p * (dp[x] - delta_s[g]);
+        for (int r = 0; r < 4; ++r) {
+            const int x = 4 * g + r;
+            const bool vis = key <= t_s[buf][x];
+            p[r] = vis ? exp2_fast(__builtin_fmaf(s[r], a.scale, -lse_s[buf][x]) * kLog2e) : 0.f;
+            dz[r] = vis ? p[r] * (dp[r] - delta_s[buf][x]) : 0.f;
+            qr[r].load_lds(&rows_s[buf][0][x][0], m);
+            gr[r].load_lds(&rows_s[buf][1][x][0], m);
         }
-        __syncthreads();
-        for (int g = 0; g < G; ++g) {
-            const float p = ps[g * kBlock + lane], dz = dzs[g * kBlock + lane];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                acc_v[c] += p * gs[g * D + w * NC + c];
-                acc_k[c] += dz * qs[g * D + w * NC + c];        // qs carries the scale
-            }
-        }
+        weighted_rows<true, D>(acc_v, p, gr);
+        weighted_rows<true, D>(acc_k, dz, qr);
+        if (more) stage(buf ^ 1, nxt);
         __syncthreads();
     }
-    const int u = j * kBlock + lane;
-    if (u < len) {
-        float *dk = a.dk + ((int64_t)h * a.map.total_rows + tok0 + u) * D + w * NC;
-        float *dv = a.dv + ((int64_t)h * a.map.total_rows + tok0 + u) * D + w * NC;
+    // Results through LDS (the row stages are free now), so that the 64 lanes of an atomic add cover consecutive
+    // addresses: as the accumulators lie, neighbouring lanes are N floats apart and an add would touch a cache line per
+    // two lanes.
+    float *tr = reinterpret_cast<float *>(&rows_s[0][0][0][0]) + w * (4 * (D + 4));
+    static_assert(sizeof(rows_s) >= NW * 4 * (D + 4) * sizeof(float), "four rows per wavefront");
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            atomicAdd(dk + c, acc_k[c]);
-            atomicAdd(dv + c, acc_v[c]);
+    for (int which = 0; which < 2; ++which) {
+        float *dst = which ? a.dv : a.dk;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {                              // keys 16 w + 4 g + r, g = 0 .. 3
+#pragma unroll
+            for (int i = 0; i < N; ++i) tr[g * (D + 4) + N * m + i] = which ? acc_v[i][r] : acc_k[i][r] * a.scale;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const int u = j * kBlock + 16 * w + 4 * y + r;
+                if (u < len) {
+                    float *p = dst + ((int64_t)h * a.map.total_rows + tok0 + u) * D;
+#pragma unroll
+                    for (int d0 = 0; d0 < D; d0 += 64) unsafeAtomicAdd(p + d0 + lane, tr[y * (D + 4) + d0 + lane]);    // the L2's own float add
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
     }
 }
@@ -274,18 +320,16 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 4096)), dim3(256), 0, L.stream,
                        (float4 *)a.dv, n4);
     hipLaunchKernelGGL((bwd_delta_kernel<T, D>), dim3((unsigned)((rows * a.hq + 3) / 4)), dim3(256), 0, L.stream, a);
-    hipLaunchKernelGGL((bwd_dq_kernel<T, D>), dim3((unsigned)rows, hkv), dim3(256), 0, L.stream, a);
-    const size_t lds = ((size_t)2 * kBlock * (D + 1) + 2 * kMaxGroup * D + 2 * kMaxGroup * kBlock) * sizeof(float);
-    auto kern = bwd_dkv_kernel<T, D>;
-    hipError_t e = hipSuccess;
-    if (lds > 48 * 1024)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess) {
-        const unsigned chunks = (unsigned)((L.max_len + BWD_CHUNK - 1) / BWD_CHUNK);
-        hipLaunchKernelGGL(kern, dim3(chunks, (unsigned)nblocks, hkv), dim3(256), lds, L.stream, a, (int)nblocks);
-        e = hipGetLastError();
-    }
-    return hip_status(e);
+    // at most this many tiles (every sequence may end with a partial one)
+    const int tokens = tile_tokens(L.map, a.hq / hkv);
+    hipLaunchKernelGGL((bwd_dq_kernel<T, D>), dim3((unsigned)(rows / tokens + L.map.batch), hkv), dim3(NW * 64), 0, L.stream, a);
+    // Tokens per dkv workgroup: 256, or down to 64 while the launch would leave CUs without a second workgroup (half of the
+    // (block, chunk) pairs of a causal sequence are empty)
+    int chunk = BWD_CHUNK;
+    while (chunk > 64 && nblocks * ((L.max_len + chunk - 1) / chunk) * hkv < 2048) chunk /= 2;
+    const unsigned chunks = (unsigned)((L.max_len + chunk - 1) / chunk);
+    hipLaunchKernelGGL((bwd_dkv_kernel<T, D>), dim3(chunks, (unsigned)nblocks, hkv), dim3(NW * 64), 0, L.stream, a, chunk);
+    return hip_status(hipGetLastError());
 }
 
 template <typename T>

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "infllmv2.h"
 
 namespace ifv2 {
@@ -115,6 +117,43 @@ __device__ inline float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
+}
+
+// Which sequence the tile-th tile of a packed batch belongs to, when every sequence is cut into tiles of `tokens` tokens,
+// and which of its tiles that is (rem).  Called by every thread of a workgroup; the first wave looks at 64 sequences
+// per step instead of one (a walk in one thread is a dependent trip to memory per sequence, in front of everything else
+// a workgroup does) and shares the answer through two ints of LDS.  One barrier; returns >= batch past the last tile.
+__device__ inline int find_seq_tile(const int32_t *cu, int batch, int tokens, int tile, int &rem, int *s_out) {
+    if (batch == 1) {
+        rem = tile;
+        return tile < (cu[1] - cu[0] + tokens - 1) / tokens ? 0 : 1;
+    }
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        int before = 0, seq = batch, r = 0;
+        for (int s0 = 0; s0 < batch; s0 += 64) {
+            const int s = s0 + lane;
+            const int n = s < batch ? (cu[s + 1] - cu[s] + tokens - 1) / tokens : 0;
+            int incl = n;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int up = __shfl_up(incl, o);
+                if (lane >= o) incl += up;
+            }
+            const uint64_t hit = __ballot(before + incl > tile);
+            if (hit) {
+                const int l = __ffsll((long long)hit) - 1;
+                seq = s0 + l;
+                r = tile - before - __shfl(incl - n, l);
+                break;
+            }
+            before += __shfl(incl, 63);
+        }
+        if (lane == 0) { s_out[0] = seq; s_out[1] = r; }
+    }
+    __syncthreads();
+    rem = s_out[1];
+    return s_out[0];
 }
 
 // ---------------------------------------------------------------- launchers implemented per stage
