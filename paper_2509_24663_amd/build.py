@@ -27,6 +27,8 @@ FLAGS = [
 # every temporary MFMA (a hundred v_accvgpr moves per token).  Keeping MFMA results in VGPRs avoids that.
 EXTRA_FLAGS = {
     "attn_bwd_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    # (its long-lived sums are placed in AGPRs by hand)
+    "attn_bwd_dkv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

@@ -1,0 +1,38 @@
+// What the kernels of the matrix-core backward (attn_bwd_mfma.hip, attn_bwd_dkv.hip) share.
+#pragma once
+#include "common.h"
+
+namespace ifv2 {
+
+struct BwdM {
+    const uint16_t *q, *k, *v, *out, *dout;
+    const float *lse;
+    const int32_t *idx;          // nullptr: dense
+    int topk_total, dense_below, hq;
+    float scale;
+    RowMap map;
+    // scratch
+    float *nlse, *ndelta;        // [T][hq]: -lse / scale and -<dO, O>, the seeds of the products q k and dO v
+    uint16_t *kt;                // [hkv][blocks][128][64]
+    int64_t nblocks;             // 64-key blocks over all sequences
+    uint32_t *sel_bits;          // [hkv][sel_words]: per sequence and key block, one bit per token that selected it
+    int64_t sel_words;           //   (block-major, rows of ceil(len / 32) words); nullptr: not built (too large)
+    // results
+    uint16_t *dq;
+    float *dk, *dv;
+};
+
+// words of the selection bitmap before sequence seq
+__device__ inline int64_t sel_base(const RowMap &m, int seq) {
+    int64_t w = 0;
+    for (int s = 0; s < seq; ++s) {
+        const int len = m.cu[s + 1] - m.cu[s];
+        w += (int64_t)((len + kBlock - 1) / kBlock) * ((len + 31) / 32);
+    }
+    return w;
+}
+
+// dK, dV (attn_bwd_dkv.hip); nothing else of the call depends on it
+int launch_bwd_dkv(const BwdM &a, int32_t max_len, hipStream_t stream);
+
+}  // namespace ifv2

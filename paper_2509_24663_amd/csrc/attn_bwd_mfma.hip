@@ -4,27 +4,19 @@
 //     P = exp(z - lse),  dP = dO V^T,  dZ = P o (dP - Delta),  dQ = scale dZ K,  dK = scale dZ^T Q,  dV = P^T dO.
 // Every product is an MFMA with the 16 heads of a token as one matrix dimension.  Operands go from global
 // memory through LDS stages into MFMA registers.  Two small pre-passes write into stream-ordered scratch:
-//   prep : Delta = <dO, O> and lse * log2(e) per (token, query head), token-major
+//   prep : -<dO, O> = -Delta and -lse / scale per (token, query head), token-major
 //   kt   : per 64-key block K^T as [128 dims][64 keys]
 //   dq   : one wavefront per (token, KV head), a workgroup of consecutive tokens walking the union of their
 //          block lists with each block's K, V, K^T staged once in LDS.  Per 16 keys:
 //          S^T = K Q^T and dP^T = V dO^T (4 + 4 MFMA 16x16x32: keys x heads), dZ^T in registers with one head per
 //          lane, dQ^T += K^T dZ^T (8 MFMA 16x16x16: dims x heads).
-//   dkv  : one workgroup of 4 wavefronts per (64-key block, chunk of later tokens, KV head); wavefront w owns keys
-//          16 w .. 16 w + 15 with their K and V fragments in registers.  The workgroup lists the tokens of its
-//          chunk that selected the block; per token S = Q K^T and dP = dO V^T (heads x keys), then
-//          dV += P^T dO and dK += dZ^T Q (8 + 8 MFMA 16x16x16: keys x dims, contraction over the 16 heads; the
-//          B operands, heads x dims, are read from the same row-major tiles with the transposing LDS read).
-//          The four wavefronts share each token's Q and dO rows (8 KB) through a double-buffered LDS stage,
-//          two tokens per barrier, the next two in flight in registers.  Results are added to the float32 outputs with
-//          the L2's float atomics, one add per element and workgroup.
-// Measured at 131072 tokens, 64 selected blocks: dq 31 ms, dkv 45 ms (the forward attention kernel: 12.6 ms; 3.5x
-// its flops).  dkv is bound by the 8 KB of Q and dO rows it fetches per (token, block) -- tokens that selected a
-// given block are scattered, so nothing is shared between blocks -- and dq by LDS traffic and barriers.
+//   dkv  : attn_bwd_dkv.hip.
+// Measured at 32768 tokens, 64 selected blocks: dq 5.5 ms, dkv 5.1 ms (the forward attention kernel: 2.35 ms; together 3.5x
+// its flops).  dq is bound by LDS traffic and its barrier per block.
 #include <algorithm>
 
 #include <cstdlib>
-#include "common.h"
+#include "attn_bwd_mfma.h"
 
 namespace ifv2 {
 
@@ -32,7 +24,6 @@ namespace {
 
 constexpr int D = 128, G = 16;
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr int DKV_CHUNK = 2048;          // tokens per dkv workgroup
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
@@ -46,24 +37,6 @@ __device__ inline short4v to_bf16x4(float a, float b, float c, float d) {
     return __builtin_bit_cast(short4v, r);
 }
 
-struct BwdM {
-    const uint16_t *q, *k, *v, *out, *dout;
-    const float *lse;
-    const int32_t *idx;          // nullptr: dense
-    int topk_total, dense_below, hq;
-    float scale;
-    RowMap map;
-    // scratch
-    float *lse2, *delta;         // [T][hq]
-    uint16_t *kt;                // [hkv][blocks][128][64]
-    int64_t nblocks;             // 64-key blocks over all sequences
-    uint32_t *sel_bits;          // [hkv][sel_words]: per sequence and key block, one bit per token that selected it
-    int64_t sel_words;           //   (block-major, rows of ceil(len / 32) words); nullptr: not built (too large)
-    // results
-    uint16_t *dq;
-    float *dk, *dv;
-};
-
 // first 64-key block of sequence seq in the packed block numbering
 __device__ inline int block_base(const RowMap &m, int seq) {
     int b = 0;
@@ -73,7 +46,7 @@ __device__ inline int block_base(const RowMap &m, int seq) {
 
 // ------------------------------------------------------------------------------------------ pre-passes
 __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdM a) {
-    // 16 threads per (token, query head): Delta = <dO, O>, and lse in the log2 domain, both token-major
+    // 16 threads per (token, query head): minus Delta = <dO, O> and minus lse / scale, both token-major
     const int row = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
     const int head = tid >> 4, d0 = (tid & 15) * 8;
     const int64_t off = ((int64_t)row * a.hq + h * G + head) * D + d0;
@@ -90,23 +63,13 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdM a) {
     for (int o = 1; o < 16; o <<= 1) dot += __shfl_xor(dot, o);
     if ((tid & 15) == 0) {
         const int qh = h * G + head;
-        a.delta[(int64_t)row * a.hq + qh] = dot;
-        a.lse2[(int64_t)row * a.hq + qh] = a.lse[qhead_row(a.map, qh, a.hq, row)] * LOG2E;
+        a.ndelta[(int64_t)row * a.hq + qh] = -dot;
+        a.nlse[(int64_t)row * a.hq + qh] = -a.lse[qhead_row(a.map, qh, a.hq, row)] / a.scale;
     }
-}
-
-// words of the selection bitmap before sequence seq
-__device__ inline int64_t sel_base(const RowMap &m, int seq) {
-    int64_t w = 0;
-    for (int s = 0; s < seq; ++s) {
-        const int len = m.cu[s + 1] - m.cu[s];
-        w += (int64_t)((len + kBlock - 1) / kBlock) * ((len + 31) / 32);
-    }
-    return w;
 }
 
 // Inverse of the block lists: bit t of row j says that token t selected key block j.  The dK/dV kernel then gets
-// the tokens of a (block, 2048-token chunk) pair with one 256-byte read instead of searching every token's list.
+// the tokens of a (block, token chunk) pair with one short read instead of searching every token's list.
 // One workgroup per 256 tokens of a sequence; a wavefront reads a token's list with one coalesced load (lane =
 // list entry) and takes its 64 tokens in turn.
 __global__ void __launch_bounds__(256) bwd_sel_bits_kernel(BwdM a) {
@@ -265,8 +228,8 @@ __global__ void __launch_bounds__(NT * 64) bwd_dq_mfma_kernel(BwdM a, int num_ti
             gf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(gp + ks * 32));
         }
     }
-    const float nlse2 = -a.lse2[(int64_t)row * a.hq + qh], delta = a.delta[(int64_t)row * a.hq + qh];
     const float c = a.scale * LOG2E;
+    const float nlse2 = a.nlse[(int64_t)row * a.hq + qh] * c, delta = -a.ndelta[(int64_t)row * a.hq + qh];
     const uint16_t *kb = a.k + (int64_t)tok0 * a.map.kv_tok_stride + (int64_t)h * a.map.kv_head_stride;
     const uint16_t *vb = a.v + (int64_t)tok0 * a.map.kv_tok_stride + (int64_t)h * a.map.kv_head_stride;
     const uint16_t *ktb = a.kt + ((int64_t)h * a.nblocks + block_base(a.map, seq)) * (D * kBlock);
@@ -358,203 +321,6 @@ __global__ void __launch_bounds__(NT * 64) bwd_dq_mfma_kernel(BwdM a, int num_ti
     }
 }
 
-// ------------------------------------------------------------------------------------------ dK, dV
-// is block j in the ascending, -1 padded list e[0 .. n)?
-__device__ inline bool list_has(const int32_t *e, int n, int j) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const int x = e[mid];
-        if (x >= 0 && x < j) lo = mid + 1; else hi = mid;
-    }
-    return lo < n && e[lo] == j;
-}
-
-constexpr int DKV_QS = D + 8;                                   // padded row of the row-major Q / dO tiles
-constexpr int DKV_TOK_ELEMS = 2 * G * DKV_QS;                   // Q and dO rows of one token
-constexpr int DKV_TB = 2;                                       // tokens per barrier (and per prefetch)
-
-__global__ void __launch_bounds__(256) bwd_dkv_mfma_kernel(BwdM a) {
-    constexpr int QS = DKV_QS, TOK_ELEMS = DKV_TOK_ELEMS, TB = DKV_TB;
-    __shared__ __attribute__((aligned(16))) uint16_t tok_s[2 * TB * TOK_ELEMS];     // [2 buffers][TB tokens]
-    __shared__ __attribute__((aligned(16))) float f_s[2][TB][32];  // lse * log2(e) and Delta of the 16 heads
-    __shared__ int s_seq, s_j, s_list[DKV_CHUNK], s_wave_cnt[4];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int h = blockIdx.z;
-    if (tid == 0) {
-        int rem = blockIdx.y, s = 0;
-        for (; s < a.map.batch; ++s) {
-            const int nb = (a.map.cu[s + 1] - a.map.cu[s] + kBlock - 1) / kBlock;
-            if (rem < nb) break;
-            rem -= nb;
-        }
-        s_seq = s;
-        s_j = rem;
-    }
-    __syncthreads();
-    const int seq = s_seq, j = s_j;
-    if (seq >= a.map.batch) return;
-    const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;
-    const int c0 = blockIdx.x * DKV_CHUNK, c1 = min(c0 + DKV_CHUNK, len);
-    if (c1 <= j * kBlock || c0 >= len) return;
-    const bool dense = a.idx == nullptr || len < a.dense_below;
-
-    // ---- tokens of the chunk that selected the block, in token order
-    int total = 0;
-    if (!dense && a.sel_bits != nullptr) {
-        // from the selection bitmap: the chunk is 64 words of the block's row; thread tid expands byte tid of them
-        static_assert(DKV_CHUNK == 8 * 256, "one byte of the chunk's bits per thread");
-        const int words = (len + 31) / 32;
-        const uint32_t *row = a.sel_bits + (int64_t)h * a.sel_words + sel_base(a.map, seq) + (int64_t)j * words + (c0 >> 5);
-        const int nw = (c1 - c0 + 31) >> 5;
-        const uint32_t wv = (tid >> 2) < nw ? row[tid >> 2] : 0u;
-        const uint32_t bits = (wv >> (8 * (tid & 3))) & 0xffu;
-        const int cnt = __popc(bits);
-        int incl = cnt;                                        // inclusive prefix inside the wave
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(incl, o);
-            if (lane >= o) incl += up;
-        }
-        if (lane == 63) s_wave_cnt[w] = incl;
-        __syncthreads();
-        int base = incl - cnt;
-        for (int x = 0; x < 4; ++x) {
-            if (x < w) base += s_wave_cnt[x];
-            total += s_wave_cnt[x];
-        }
-        for (uint32_t rest = bits; rest; rest &= rest - 1) s_list[base++] = c0 + 8 * tid + __ffs(rest) - 1;
-        __syncthreads();
-    } else
-    for (int r0 = c0; r0 < c1; r0 += 256) {
-        const int t_mine = r0 + tid;
-        bool sel = t_mine < c1 && t_mine >= j * kBlock;
-        if (sel && !dense) sel = list_has(a.idx + head_row(a.map, h, tok0 + t_mine) * a.topk_total, a.topk_total, j);
-        const uint64_t bal = __ballot(sel);
-        if (lane == 0) s_wave_cnt[w] = __popcll(bal);
-        __syncthreads();
-        int base = total;
-        for (int x = 0; x < 4; ++x) {
-            if (x < w) base += s_wave_cnt[x];
-            total += s_wave_cnt[x];
-        }
-        if (sel) s_list[base + __popcll(bal & ((1ull << lane) - 1ull))] = t_mine;
-        __syncthreads();
-    }
-    if (total == 0) return;
-
-    const int n16 = lane & 15, g = lane >> 4;
-    // K and V rows of key 16 w + n16 as B operands (k = 8 dims at 32 ks + 8 g); rows past the sequence are never
-    // visible to any token (causal), their contributions are masked to zero
-    const int key = j * kBlock + 16 * w + n16;
-    bf16x8 kf[4], vf[4];
-    {
-        const int64_t base = (int64_t)tok0 * a.map.kv_tok_stride + (int64_t)h * a.map.kv_head_stride +
-                             (int64_t)min(key, len - 1) * a.map.kv_tok_stride + g * 8;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            kf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(a.k + base + ks * 32));
-            vf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(a.v + base + ks * 32));
-        }
-    }
-    const float c = a.scale * LOG2E;
-    f32x4 acc_k[8], acc_v[8];                  // rows: keys 16 w + 4 g + r; columns: dims 16 dt + n16
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-        acc_k[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        acc_v[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    // The four wavefronts need the same per-token data, so it goes through LDS once: Q and dO rows (row-major,
-    // padded: A operands), Q^T and dO^T ([dims][heads]: B operands), Delta and lse.  Double buffered, the next
-    // token's 16 KB are in flight in registers while the current token is computed; one barrier per token.
-    struct TokPre { uint4 q, g; float f; };
-    auto gload = [&](int t) -> TokPre {
-        TokPre pr;
-        const int row = tok0 + t;
-        const int64_t off = ((int64_t)row * a.hq + h * G + (tid >> 4)) * D + (tid & 15) * 8;
-        pr.q = *reinterpret_cast<const uint4 *>(a.q + off);
-        pr.g = *reinterpret_cast<const uint4 *>(a.dout + off);
-        pr.f = (tid < 16 ? a.lse2 : a.delta)[(int64_t)row * a.hq + h * G + (tid & 15)];    // used by threads 0..31
-        return pr;
-    };
-    auto lstore = [&](int buf, int slot, const TokPre &pr) {
-        uint16_t *b = tok_s + (buf * TB + slot) * TOK_ELEMS;
-        *reinterpret_cast<uint4 *>(b + (tid >> 4) * QS + (tid & 15) * 8) = pr.q;
-        *reinterpret_cast<uint4 *>(b + G * QS + (tid >> 4) * QS + (tid & 15) * 8) = pr.g;
-        if (tid < 32) f_s[buf][slot][tid] = pr.f;
-    };
-    // B operands of the two head-contractions come from the same row-major tiles through the transposing LDS
-    // read: in each group of 16 lanes, lane L points at dims 4 (L % 4) .. + 3 of row L / 4 of a 4 x 16 block and
-    // receives column L of it.  Block = heads 4 g .. 4 g + 3, dims 16 dt .. 16 dt + 15.
-    typedef __attribute__((address_space(3))) short4v lds_s4;
-    const int tr_off = (4 * g + (n16 >> 2)) * QS + 4 * (n16 & 3);
-    // batches of TB tokens: batch i = list entries TB i .. TB i + TB - 1 (entries past the end repeat the last one
-    // and are not computed)
-    const int nbatch = (total + TB - 1) / TB;
-    TokPre nxt[TB];
-#pragma unroll
-    for (int sl = 0; sl < TB; ++sl) lstore(0, sl, gload(s_list[min(sl, total - 1)]));
-    __syncthreads();
-    for (int ib = 0; ib < nbatch; ++ib) {
-#pragma unroll
-        for (int sl = 0; sl < TB; ++sl) nxt[sl] = gload(s_list[min((ib + 1) * TB + sl, total - 1)]);
-#pragma unroll
-        for (int sl = 0; sl < TB; ++sl) {
-            const int it = ib * TB + sl;
-            if (it >= total) break;                                  // uniform
-            const int t = s_list[it];
-            const uint16_t *b = tok_s + ((ib & 1) * TB + sl) * TOK_ELEMS;
-            // A operands: Q and dO rows of head n16
-            f32x4 sacc = f32x4{0.f, 0.f, 0.f, 0.f}, dpacc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const bf16x8 qa = *reinterpret_cast<const bf16x8 *>(b + n16 * QS + g * 8 + ks * 32);
-                const bf16x8 ga = *reinterpret_cast<const bf16x8 *>(b + G * QS + n16 * QS + g * 8 + ks * 32);
-                sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa, kf[ks], sacc, 0, 0, 0);
-                dpacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga, vf[ks], dpacc, 0, 0, 0);
-            }
-            // element r: head 4 g + r, key n16 of this wave's tile
-            const float4 l2 = *reinterpret_cast<const float4 *>(&f_s[ib & 1][sl][4 * g]);
-            const float4 dl = *reinterpret_cast<const float4 *>(&f_s[ib & 1][sl][16 + 4 * g]);
-            const float l2a[4] = {l2.x, l2.y, l2.z, l2.w}, dla[4] = {dl.x, dl.y, dl.z, dl.w};
-            const bool visible = key <= t;
-            float p[4], dz[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                p[r] = visible ? exp2_fast(__builtin_fmaf(sacc[r], c, -l2a[r])) : 0.f;
-                dz[r] = p[r] * (dpacc[r] - dla[r]);
-            }
-            const short4v pb = to_bf16x4(p[0], p[1], p[2], p[3]), dzb = to_bf16x4(dz[0], dz[1], dz[2], dz[3]);
-            // dV (keys x dims) += P^T (keys x heads) dO (heads x dims); B: dim 16 dt + n16, heads 4 g .. 4 g + 3
-#pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
-                const short4v qb = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(b + tr_off + 16 * dt));
-                const short4v gb = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(b + G * QS + tr_off + 16 * dt));
-                acc_v[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pb, gb, acc_v[dt], 0, 0, 0);
-                acc_k[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(dzb, qb, acc_k[dt], 0, 0, 0);
-            }
-        }
-        if (ib + 1 < nbatch) {
-#pragma unroll
-            for (int sl = 0; sl < TB; ++sl) lstore((ib + 1) & 1, sl, nxt[sl]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int u = j * kBlock + 16 * w + 4 * g + r;
-        if (u < len) {
-            float *dk = a.dk + ((int64_t)h * a.map.total_rows + tok0 + u) * D + n16;
-            float *dv = a.dv + ((int64_t)h * a.map.total_rows + tok0 + u) * D + n16;
-#pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
-                unsafeAtomicAdd(dk + 16 * dt, acc_k[dt][r] * a.scale);       // the L2's own float add, no CAS loop
-                unsafeAtomicAdd(dv + 16 * dt, acc_v[dt][r]);
-            }
-        }
-    }
-}
-
 }  // namespace
 
 bool bwd_mfma_params(const infllmv2_params *p) {
@@ -616,8 +382,8 @@ int launch_attn_bwd_mfma(const Launch &L, const void *q, const void *k, const vo
     a.hq = hq;
     a.scale = p->softmax_scale;
     a.map = L.map;
-    a.lse2 = (float *)ws;
-    a.delta = (float *)(ws + b_f);
+    a.nlse = (float *)ws;
+    a.ndelta = (float *)(ws + b_f);
     a.kt = (uint16_t *)(ws + 2 * b_f);
     a.nblocks = nblocks;
     a.sel_bits = use_bits ? (uint32_t *)(ws + 2 * b_f + b_kt) : nullptr;
@@ -646,9 +412,8 @@ int launch_attn_bwd_mfma(const Launch &L, const void *q, const void *k, const vo
         return INFLLMV2_ERR_HIP;
     hipLaunchKernelGGL(bwd_dq_mfma_kernel<DQ_NT>, dim3((unsigned)dq_tiles, hkv), dim3(DQ_NT * 64), dq_lds, L.stream, a,
                        (int)dq_tiles);
-    const unsigned chunks = (unsigned)((L.max_len + DKV_CHUNK - 1) / DKV_CHUNK);
-    hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3(chunks, (unsigned)nblocks, hkv), dim3(256), 0, L.stream, a);
-    return hip_status(hipGetLastError());
+    if (hipGetLastError() != hipSuccess) return INFLLMV2_ERR_HIP;
+    return launch_bwd_dkv(a, L.max_len, L.stream);
 }
 
 }  // namespace ifv2
