@@ -109,18 +109,16 @@ int infllmv2_compress_k(const infllmv2_params *p, const void *k_d, int64_t kv_to
     st = check_cu(cu_seqlens_h, cu_seqlens_d, batch, &total, &max_len);
     if (st) return st;
     if (cu_seqlens_c_d == nullptr) return INFLLMV2_ERR_INVALID_ARGUMENT;
-    if (total == 0) return launch_cu_c(p, cu_seqlens_d, batch, cu_seqlens_c_d, (hipStream_t)stream);
-    if (k_d == nullptr || kc_d == nullptr) return INFLLMV2_ERR_INVALID_ARGUMENT;
-    if (kv_tok_stride < p->head_dim || kv_head_stride < p->head_dim) return INFLLMV2_ERR_INVALID_ARGUMENT;
-    int64_t need = 0;
-    for (int s = 0; s < batch; ++s) need += num_cmp(cu_seqlens_h[s + 1] - cu_seqlens_h[s], p->cmp_len, p->cmp_stride);
-    if (total_c < need || total_c >= (1ll << 31)) return INFLLMV2_ERR_INVALID_ARGUMENT;
-    hipStream_t s = (hipStream_t)stream;
-    st = launch_cu_c(p, cu_seqlens_d, batch, cu_seqlens_c_d, s);
-    if (st) return st;
-    Launch L{p, prefill_map(p, cu_seqlens_d, cu_seqlens_c_d, batch, total, kv_tok_stride, kv_head_stride, total_c), s,
-             max_len, nullptr, 0};
-    return launch_compress_k(L, k_d, kc_d, need);
+    if (total > 0) {
+        if (k_d == nullptr || kc_d == nullptr) return INFLLMV2_ERR_INVALID_ARGUMENT;
+        if (kv_tok_stride < p->head_dim || kv_head_stride < p->head_dim) return INFLLMV2_ERR_INVALID_ARGUMENT;
+        int64_t need = 0;
+        for (int s = 0; s < batch; ++s) need += num_cmp(cu_seqlens_h[s + 1] - cu_seqlens_h[s], p->cmp_len, p->cmp_stride);
+        if (total_c < need || total_c >= (1ll << 31)) return INFLLMV2_ERR_INVALID_ARGUMENT;
+    }
+    Launch L{p, prefill_map(p, cu_seqlens_d, nullptr, batch, total, kv_tok_stride, kv_head_stride, total_c),
+             (hipStream_t)stream, max_len, nullptr, 0};
+    return launch_compress_k(L, k_d, kc_d, cu_seqlens_c_d, cu_seqlens_h);
 }
 
 int infllmv2_compress_k_append(const infllmv2_params *p, const void *k_cache_d, int64_t kv_batch_stride,

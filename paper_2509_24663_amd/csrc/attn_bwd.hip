@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
     constexpr int N = D / 16;
     __shared__ Union un;
     __shared__ float o_s[NW][kCols][D + 4];
-    __shared__ int s_tile[2];
+    __shared__ int s_tile[3];
     const int h = blockIdx.y, G = a.hq / a.map.num_kv_heads;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     Tile t;
@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
     __shared__ __attribute__((aligned(16))) T rows_s[2][2][kCols][D + 16 / sizeof(T)];      // [buffer][Q, dO][row]
     __shared__ float lse_s[2][kCols], delta_s[2][kCols];
     __shared__ int t_s[2][kCols];
-    __shared__ int s_tile[2], s_list[BWD_CHUNK], s_wave_cnt[NW];
+    __shared__ int s_tile[3], s_list[BWD_CHUNK], s_wave_cnt[NW];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int h = blockIdx.z, G = a.hq / a.map.num_kv_heads;
     int j;

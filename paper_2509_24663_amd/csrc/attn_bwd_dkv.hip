@@ -199,7 +199,7 @@ __device__ inline void pair_step(State &acc, const bf16x8 (&kf)[2][8], const bf1
 __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, int groups) {
     __shared__ __attribute__((aligned(1024))) char smem[2 * kPairStride];      // two buffers of a pair of tokens
     __shared__ uint16_t s_list[MAX_CHUNK];                             // tokens of the chunk that selected the block
-    __shared__ int s_tile[2];
+    __shared__ int s_tile[3];
     const int lane = threadIdx.x;
     const int nb = (int)a.nblocks;
     // XCD x (= workgroup id mod 8) takes the (chunk, KV head) groups x, x + 8, ...; the first block, whose list holds every

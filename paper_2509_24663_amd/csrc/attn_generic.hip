@@ -31,7 +31,7 @@ attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *_
     constexpr int N = D / 16;
     __shared__ Union un;
     __shared__ float o_s[NW][kCols][D + 4], m_s[NW][kCols], l_s[NW][kCols];
-    __shared__ int s_tile[2];
+    __shared__ int s_tile[3];
     const int h = blockIdx.y, G = hq / map.num_kv_heads;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     Tile t;

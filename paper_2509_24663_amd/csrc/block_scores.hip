@@ -41,7 +41,7 @@ block_scores_generic(const T *__restrict__ q, const float *__restrict__ kc, RowM
     __shared__ float red_m[GS_WAVES][kCols], red_l[GS_WAVES][kCols];
     __shared__ float ps[GS_WAVES][16][kCols + 1];          // probabilities of one key tile, per wavefront
     __shared__ float sh[kCols][GS_CHUNK];                  // group scores of the chunk, per token
-    __shared__ int s_tile[2];
+    __shared__ int s_tile[3];
     const int h = blockIdx.y, G = hq / map.num_kv_heads;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     Tile t;

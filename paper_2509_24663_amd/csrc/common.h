@@ -119,41 +119,55 @@ __device__ inline float wave_sum(float v) {
     return v;
 }
 
-// Which sequence the tile-th tile of a packed batch belongs to, when every sequence is cut into tiles of `tokens` tokens,
-// and which of its tiles that is (rem).  Called by every thread of a workgroup; the first wave looks at 64 sequences
-// per step instead of one (a walk in one thread is a dependent trip to memory per sequence, in front of everything else
-// a workgroup does) and shares the answer through two ints of LDS.  One barrier; returns >= batch past the last tile.
-__device__ inline int find_seq_tile(const int32_t *cu, int batch, int tokens, int tile, int &rem, int *s_out) {
+// Which sequence the tile-th tile of a packed batch belongs to, when a sequence of n tokens is cut into count(n) tiles, and
+// which of its tiles that is (rem); before: the sum of weight(n) over the sequences in front of it.  Called by every thread
+// of a workgroup; the first wave looks at 64 sequences per step instead of one (a walk in one thread is a dependent trip
+// to memory per sequence, in front of everything else a workgroup does) and shares the answer through three ints of LDS.
+// One barrier; returns >= batch past the last tile.
+template <class Count, class Weight>
+__device__ inline int find_seq_count(const int32_t *cu, int batch, int tile, int &rem, int &before, int *s_out, Count count,
+                                     Weight weight) {
     if (batch == 1) {
         rem = tile;
-        return tile < (cu[1] - cu[0] + tokens - 1) / tokens ? 0 : 1;
+        before = 0;
+        return tile < count(cu[1] - cu[0]) ? 0 : 1;
     }
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
-        int before = 0, seq = batch, r = 0;
+        int tiles = 0, sum = 0, seq = batch, r = 0, bef = 0;
         for (int s0 = 0; s0 < batch; s0 += 64) {
             const int s = s0 + lane;
-            const int n = s < batch ? (cu[s + 1] - cu[s] + tokens - 1) / tokens : 0;
-            int incl = n;
+            const int len = s < batch ? cu[s + 1] - cu[s] : 0;
+            const int n = s < batch ? count(len) : 0, wt = s < batch ? weight(len) : 0;
+            int incl = n, wincl = wt;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
-                const int up = __shfl_up(incl, o);
-                if (lane >= o) incl += up;
+                const int up = __shfl_up(incl, o), wup = __shfl_up(wincl, o);
+                if (lane >= o) { incl += up; wincl += wup; }
             }
-            const uint64_t hit = __ballot(before + incl > tile);
+            const uint64_t hit = __ballot(tiles + incl > tile);
             if (hit) {
                 const int l = __ffsll((long long)hit) - 1;
                 seq = s0 + l;
-                r = tile - before - __shfl(incl - n, l);
+                r = tile - tiles - __shfl(incl - n, l);
+                bef = sum + __shfl(wincl - wt, l);
                 break;
             }
-            before += __shfl(incl, 63);
+            tiles += __shfl(incl, 63);
+            sum += __shfl(wincl, 63);
         }
-        if (lane == 0) { s_out[0] = seq; s_out[1] = r; }
+        if (lane == 0) { s_out[0] = seq; s_out[1] = r; s_out[2] = bef; }
     }
     __syncthreads();
     rem = s_out[1];
+    before = s_out[2];
     return s_out[0];
+}
+// tiles of `tokens` tokens
+__device__ inline int find_seq_tile(const int32_t *cu, int batch, int tokens, int tile, int &rem, int *s_out) {
+    int before;
+    return find_seq_count(cu, batch, tile, rem, before, s_out, [&](int n) { return (n + tokens - 1) / tokens; },
+                          [](int) { return 0; });
 }
 
 // ---------------------------------------------------------------- launchers implemented per stage
@@ -166,8 +180,8 @@ struct Launch {
     size_t ws_bytes;
 };
 
-int launch_cu_c(const infllmv2_params *p, const int32_t *cu_d, int batch, int32_t *cu_c_d, hipStream_t s);
-int launch_compress_k(const Launch &L, const void *k, float *kc, int64_t total_c_rows);
+// also writes cu_c [batch + 1]; cu_h may hold no tokens at all (k, kc are not touched then)
+int launch_compress_k(const Launch &L, const void *k, float *kc, int32_t *cu_c, const int32_t *cu_h);
 int launch_compress_k_append(const infllmv2_params *p, const void *k, int64_t kv_batch_stride, int64_t kv_head_stride,
                              int64_t kv_tok_stride, float *kc, int64_t kc_head_stride, const int32_t *prev_d,
                              const int32_t *ctx_d, int batch, int max_new, hipStream_t stream);

@@ -35,6 +35,7 @@ struct Unaligned {
 typedef Unaligned<uint16_t, 8>::type u16x8_u;
 typedef Unaligned<uint16_t, 4>::type u16x4_u;
 typedef Unaligned<float, 4>::type f32x4_u;
+typedef Unaligned<float, 8>::type f32x8_u;
 
 // One row (key, token-head or compressed key) as an operand of a row product: lane (m, g) holds a quarter of row m.
 // Which elements a lane group takes does not matter as long as both operands agree.
@@ -206,7 +207,7 @@ struct Tile {
 __host__ __device__ inline int tile_tokens(const RowMap &m, int G) { return m.ctx ? 1 : kCols / G; }
 
 // wave 0 looks the tile up (64 sequences per step), every thread gets it; two barriers.  false: past the last tile
-__device__ inline bool find_tile(const RowMap &m, int tile, int tokens, Tile &t, int *s_tile /* 2 ints of LDS */) {
+__device__ inline bool find_tile(const RowMap &m, int tile, int tokens, Tile &t, int *s_tile /* 3 ints of LDS */) {
     if (m.ctx) {
         t.seq = tile;
         t.len = m.ctx[tile];
