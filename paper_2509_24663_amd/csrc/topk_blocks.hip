@@ -1,4 +1,7 @@
-// Stage 3 kernel: one wavefront per (token, KV head) row; the selection itself is in topk_row.h.
+// Stage 3 kernel: one wavefront per (token, KV head) row; the selection itself is in topk_row.h.  Bound by instruction
+// issue: at 131072 tokens (pooled scores, 2048 blocks) the vector unit was busy 71% of the time with 865 instructions per
+// row while 2.2 TB/s were read.  With the code chosen by the row's own length and rows read through a buffer descriptor
+// (topk_row.h): 492 -> 332 us; 65536 tokens 175 -> 145 us; 20011 tokens from unpooled scores 44 -> 39 us.
 #include "topk_row.h"
 
 namespace ifv2 {
@@ -10,7 +13,7 @@ topk_blocks_kernel(const float *__restrict__ s_shared, int64_t row_stride, RowMa
                    int32_t *__restrict__ idx, int lds_keys_per_wave) {
     extern __shared__ uint32_t lds_keys[];
     __shared__ uint2 cand[NCH > kCandChunks ? 4 * kCandPerWave : 1];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = blockIdx.x * 4 + w, h = blockIdx.y;
     if (row >= map.total_rows) return;
     const RowLoc loc = locate(map, row);
@@ -19,8 +22,18 @@ topk_blocks_kernel(const float *__restrict__ s_shared, int64_t row_stride, RowMa
         for (int j = lane; j < a.topk_total; j += 64) out[j] = -1;
         return;
     }
-    topk_row<NCH, MODE>(s_shared + head_row(map, h, row) * row_stride, loc.pos, a, out,
-                  lds_keys + (size_t)w * lds_keys_per_wave, cand + (NCH > kCandChunks ? w * kCandPerWave : 0), lane);
+    const float *srow = s_shared + head_row(map, h, row) * row_stride;
+    // A row takes the code for its own number of 64-block chunks, in steps of a quarter of the longest row's: the rows of a
+    // causal sequence are half as long as the longest on average, and the work is per chunk.
+    uint2 *cd = cand + (NCH > kCandChunks ? w * kCandPerWave : 0);
+    uint32_t *lk = lds_keys + (size_t)w * lds_keys_per_wave;
+    if constexpr (NCH >= 8) {
+        const int nch = __builtin_amdgcn_readfirstlane((loc.pos / kBlock + 64) >> 6);
+        if (nch <= NCH / 4) return topk_row<NCH / 4, MODE>(srow, loc.pos, a, out, lk, cd, lane);
+        if (nch <= NCH / 2) return topk_row<NCH / 2, MODE>(srow, loc.pos, a, out, lk, cd, lane);
+        if (nch <= NCH / 4 * 3) return topk_row<NCH / 4 * 3, MODE>(srow, loc.pos, a, out, lk, cd, lane);
+    }
+    topk_row<NCH, MODE>(srow, loc.pos, a, out, lk, cd, lane);
 }
 
 template <int NCH>

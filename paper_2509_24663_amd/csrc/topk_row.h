@@ -52,6 +52,7 @@ constexpr int kBoundBits = 12;          // leading key bits (below the sign) res
 template <int NCH, int MODE = TOPK_POOL_ANY>
 __device__ inline void topk_row(const float *srow, int t, const TopkArgs &a, int32_t *out, uint32_t *lk, uint2 *cand,
                                 int lane) {
+    t = __builtin_amdgcn_readfirstlane(t);             // (one row per wavefront: what derives from its position is uniform)
     const int bt = t / kBlock, nblk = bt + 1;
     const int v = visible_cmp(t, a.lc, a.sc);
     const int nch = (nblk + 63) >> 6;
@@ -107,6 +108,12 @@ __device__ inline void topk_row(const float *srow, int t, const TopkArgs &a, int
 #pragma unroll
             for (int c = c0; c < c0 + 8 && c < NCH; ++c) {
                 const int j = c * 64 + lane, i0 = 4 * j;
+                if (c * 64 >= f_init && c * 64 + 64 <= f_lo && 4 * (c * 64 + 63) + 4 < v) {
+                    // every window of the chunk is visible and none of its blocks is forced
+                    keys[c] = __float_as_uint(fmaxf(fmaxf(fmaxf(q4[c - c0].x, q4[c - c0].y), fmaxf(q4[c - c0].z, q4[c - c0].w)),
+                                                    fmaxf(f5[c - c0], 0.f)));
+                    continue;
+                }
                 float m = 0.f;
                 m = i0 < v ? fmaxf(m, q4[c - c0].x) : m;
                 m = i0 + 1 < v ? fmaxf(m, q4[c - c0].y) : m;
@@ -118,17 +125,17 @@ __device__ inline void topk_row(const float *srow, int t, const TopkArgs &a, int
             }
         }
     } else if (NCH > 0 && MODE == TOPK_POOLED) {
-        // all loads first, addresses clamped into the row (entry bt always exists); undefined, forced and
-        // out-of-range entries are masked afterwards
-        float x[NCH > 0 ? NCH : 1];
+        // Live are the blocks [f_init, j_end): not forced and with a visible key in their window.  The row is read through a
+        // buffer descriptor that ends at j_end, so everything from there on (past the row, too) arrives as 0 without an
+        // address or a mask being computed for it; the initial blocks are masked in the chunks that hold any.
+        const int j_end = v > 0 ? (int)min((int64_t)f_lo, ((int64_t)v + a.pool_pad + a.pool_stride - 1) / a.pool_stride) : 0;
+        const __amdgpu_buffer_rsrc_t row =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(srow), 0, j_end * (int)sizeof(float), 0x00020000);
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) x[c] = srow[min(c * 64 + lane, bt)];
+        for (int c = 0; c < NCH; ++c) keys[c] = __builtin_amdgcn_raw_buffer_load_b32(row, lane * 4 + c * 256, 0, 0);
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int j = c * 64 + lane;
-            const bool dead = j >= nblk || j < f_init || j >= f_lo || !(max(a.pool_stride * j - a.pool_pad, 0) < v);
-            keys[c] = dead ? 0u : __float_as_uint(x[c]);
-        }
+        for (int c = 0; c < NCH; ++c)
+            if (c == 0 || c * 64 < f_init) keys[c] = c * 64 + lane >= f_init ? keys[c] : 0u;
     } else if (NCH > 0) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
@@ -160,14 +167,17 @@ __device__ inline void topk_row(const float *srow, int t, const TopkArgs &a, int
             const uint64_t below = (1ull << lane) - 1ull;
             int total = 0;
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const bool in = keys[c] >= L;                    // dead slots hold 0 < L
-                const uint64_t bal = __ballot(in);
-                const int pos = total + __popcll(bal & below);
-                if (in && pos < kCandPerWave) cand[pos] = make_uint2(keys[c], (uint32_t)(c * 64 + lane));
-                total += __popcll(bal);
-            }
+            for (int c = 0; c < NCH; ++c) total += __popcll(__ballot(keys[c] >= L));      // dead slots hold 0 < L
             if (total <= kCandPerWave) {
+                int at = 0;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    const bool in = keys[c] >= L;
+                    const uint64_t bal = __ballot(in);
+                    const int pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, at));
+                    if (in) cand[pos] = make_uint2(keys[c], (uint32_t)(c * 64 + lane));
+                    at += __popcll(bal);
+                }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 uint32_t ck[kCandChunks], cj[kCandChunks];
