@@ -62,9 +62,9 @@ struct TileKernel {
     static constexpr int T = NW;
     static constexpr int NTHR = NW * 64;
     static constexpr int NSTAGE = 2 * SLOTS;        // double buffering of an interval's blocks
-    static constexpr int PPW = 32 / NW;             // one-KB load pieces per wave and block
+    static constexpr int PPW = 16 / NW;             // one-KB pieces of each of a block's two tiles per wave
     static constexpr int NONE = 0xffff;            // no block (block numbers are kept in 16 bits)
-    static_assert(32 % NW == 0, "32 one-KB load instructions are dealt round-robin to the waves");
+    static_assert(16 % NW == 0, "sixteen one-KB pieces per tile are dealt round-robin to the waves");
     static_assert(SLOTS == 1 || SLOTS == 2, "one or two entries per interval");
 
     // which of the CU's four SIMDs this wave runs on (hardware id register, bits 5:4)
@@ -239,7 +239,7 @@ struct TileKernel {
         };
 
         // ---- loads: a block is 32 one-KB pieces (16 of the K tile: 4 rows each; 16 of the V^T tile: 8 rows each); wave w
-        // copies K piece w and V^T piece w of every block.  A piece's source is a wave-uniform base (sequence, head,
+        // copies K and V^T pieces w, w + NW, ... of every block.  A piece's source is a wave-uniform base (sequence, head,
         // block, piece: scalar arithmetic) plus a per-lane byte offset that never changes, except that the sequence's
         // last, partial K block re-reads its last valid row (finite data, always masked by causality); that block can
         // only be the tile's own, which is alone in the last interval.  The V^T copy is zero-padded instead.
@@ -248,25 +248,30 @@ struct TileKernel {
         // next interval's copies -- address arithmetic included -- delays that unit, and the interval lasts as long as
         // its slowest wave: the code below is the shortest there is for four copies (every piece offset folded into
         // per-wave constants, 32-bit block stride, the partial block handled by the last interval's own function).
-        static_assert(NW == 16, "wave w copies piece w of the 16 pieces of a tile");
-        constexpr uint32_t kTileBytes = TILE_ELEMS * 2, kStageBytes = STAGE_ELEMS * 2;
+        // (The V^T tile's swizzle repeats after 4 pieces, the K tile's after 8: with 4 waves a wave's pieces alternate between
+        // two K offsets.)
+        static_assert(NW == 16 || NW == 8 || NW == 4, "pieces 2 NW (K) and NW (V^T) apart have the same swizzle");
+        constexpr int KOFF = NW == 4 ? 2 : 1;
+        constexpr uint32_t kTileBytes = TILE_ELEMS * 2, kStageBytes = STAGE_ELEMS * 2, kPieceStep = NW * 1024u;
         const uint32_t blk_bytes = (uint32_t)a.map.kv_tok_stride * (uint32_t)(kBlock * sizeof(uint16_t));   // < 2^31: the stride is < 2^24
         const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(stages));
         const int own_rows = len - bt * kBlock;          // rows of the tile's own block that exist (1..64 counts)
-        uint32_t off_k_w, off_v_w;
-        {
+        uint32_t off_k_w[KOFF];
+#pragma unroll
+        for (int u = 0; u < KOFF; ++u) {
             int row, chunk;
-            k_piece_src(w, lane, row, chunk);
-            off_k_w = (uint32_t)((row - 4 * w) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
-            off_v_w = vt_piece_src_bytes(w, lane) - (uint32_t)w * 1024u;
+            k_piece_src(w + u * NW, lane, row, chunk);
+            off_k_w[u] = (uint32_t)((row - 4 * (w + u * NW)) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
         }
+        const uint32_t off_v_w = vt_piece_src_bytes(w, lane) - (uint32_t)w * 1024u;
+        const uint32_t k_step = blk_bytes / PPW;          // K bytes between a wave's pieces of a block
         const char *kb_w = reinterpret_cast<const char *>(kb) + (uint64_t)w * (blk_bytes / 16u);
         const char *vtb_w = reinterpret_cast<const char *>(vtb) + (uint32_t)w * 1024u;
         const uint32_t lds_w = lds0 + (uint32_t)w * 1024u;
 #ifdef ATTN_TIMING_NO_LOADS
         bool timing_fill = false;
 #endif
-        // this wave's sixteenth of the interval whose blocks are jj (two 16-bit block numbers), into buffer buf
+        // this wave's share of the interval whose blocks are jj (two 16-bit block numbers), into buffer buf
         auto issue = [&](uint32_t jj, int buf) {
 #ifdef ATTN_TIMING_NO_LOADS
             if (!timing_fill) return;                   // timing experiment only (results are garbage)
@@ -278,11 +283,17 @@ struct TileKernel {
             j1 %= ATTN_TIMING_NEAR;
 #endif
             const uint32_t dst = lds_w + (uint32_t)buf * (SLOTS * kStageBytes);
-            async_copy16(kb_w + (uint64_t)j0 * blk_bytes, off_k_w, dst);
-            async_copy16(vtb_w + (j0 << 14), off_v_w, dst + kTileBytes);
+#pragma unroll
+            for (int u = 0; u < PPW; ++u) {
+                async_copy16(kb_w + (uint64_t)j0 * blk_bytes + u * k_step, off_k_w[u % KOFF], dst + u * kPieceStep);
+                async_copy16(vtb_w + (j0 << 14) + u * kPieceStep, off_v_w, dst + kTileBytes + u * kPieceStep);
+            }
             if (two) {
-                async_copy16(kb_w + (uint64_t)j1 * blk_bytes, off_k_w, dst + kStageBytes);
-                async_copy16(vtb_w + (j1 << 14), off_v_w, dst + kStageBytes + kTileBytes);
+#pragma unroll
+                for (int u = 0; u < PPW; ++u) {
+                    async_copy16(kb_w + (uint64_t)j1 * blk_bytes + u * k_step, off_k_w[u % KOFF], dst + kStageBytes + u * kPieceStep);
+                    async_copy16(vtb_w + (j1 << 14) + u * kPieceStep, off_v_w, dst + kStageBytes + kTileBytes + u * kPieceStep);
+                }
             }
         };
         // the last interval: the tile's own block alone, possibly the sequence's partial last block
@@ -291,11 +302,14 @@ struct TileKernel {
             if (!timing_fill) return;
 #endif
             const uint32_t dst = lds_w + (uint32_t)buf * (SLOTS * kStageBytes);
-            int row, chunk;
-            k_piece_src(w, lane, row, chunk);
-            const uint32_t off = (uint32_t)(min(row, own_rows - 1) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
-            async_copy16(reinterpret_cast<const char *>(kb) + (uint64_t)bt * blk_bytes, off, dst);
-            async_copy16(vtb_w + ((uint32_t)bt << 14), off_v_w, dst + kTileBytes);
+#pragma unroll
+            for (int u = 0; u < PPW; ++u) {
+                int row, chunk;
+                k_piece_src(w + u * NW, lane, row, chunk);
+                const uint32_t off = (uint32_t)(min(row, own_rows - 1) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
+                async_copy16(reinterpret_cast<const char *>(kb) + (uint64_t)bt * blk_bytes, off, dst + u * kPieceStep);
+                async_copy16(vtb_w + ((uint32_t)bt << 14) + u * kPieceStep, off_v_w, dst + kTileBytes + u * kPieceStep);
+            }
         };
         int2 r_cur = ni > 0 ? interval(0) : make_int2(0, 0);
 #ifdef ATTN_TIMING_NO_LOADS
@@ -541,8 +555,20 @@ int launch_attn_mfma(const Launch &L, const void *q, const void *k, const void *
     if (rc == INFLLMV2_OK) {
         // Two entries per interval when the four LDS stages that needs fit next to the block masks (with block lists:
         // sequences up to about 384K tokens; dense calls keep no masks), else one.
+        // Tiles of 16 tokens, or of 8 or 4 while even those leave CUs without a workgroup (one fits a CU): a block in LDS
+        // then serves fewer tokens, but there is nobody else to serve, and an interval takes as long as its units.
+        // (777 tokens, 2 KV heads: 28.9 us with 16, 20.7 with 8; dense, 1000 tokens: 36.4 and 27.4, 200 tokens 17.3 and,
+        // with 4, 13.5)
+        const int64_t most = 256 / L.p->num_kv_heads;
+        int64_t tiles4 = 0, tiles8 = 0;
+        for (int s = 0; s < L.map.batch; ++s) {
+            tiles4 += (cu_h[s + 1] - cu_h[s] + 3) / 4;
+            tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
+        }
         rc = INFLLMV2_ERR_UNSUPPORTED;
-        rc = launch_tile<16, 2>(L, a, cu_h);
+        if (tiles4 <= most) rc = launch_tile<4, 2>(L, a, cu_h);
+        else if (tiles8 <= most) rc = launch_tile<8, 2>(L, a, cu_h);
+        if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 2>(L, a, cu_h);
         if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 1>(L, a, cu_h);
     }
     return rc;

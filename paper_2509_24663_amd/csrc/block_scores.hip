@@ -746,6 +746,12 @@ int launch_scores_mfma(const Launch &L, ScoreArgs a, const int32_t *cu_h) {
     return hip_status(hipGetLastError());
 }
 
+template <int NW, int TPW>
+int launch_scores_pool(const Launch &L, const ScoreArgs &a, const int32_t *cu_h, int pool) {
+    if (pool < 0) return launch_scores_mfma<NW, TPW, -1>(L, a, cu_h);
+    return pool == 0 ? launch_scores_mfma<NW, TPW, 0>(L, a, cu_h) : launch_scores_mfma<NW, TPW, 1>(L, a, cu_h);
+}
+
 bool scores_mfma_params(const infllmv2_params *p, bool pooled) {
     // the tiled kernel pools on chip only for the paper's window (l = 5, s = 4), unshifted or shifted by one, with
     // four compressed keys per selection block (block j's window then starts at key 4j of its tile row)
@@ -771,8 +777,18 @@ int launch_block_scores(const Launch &L, const void *q, const float *kc, float *
         (((uintptr_t)q | (uintptr_t)kc) & 15) == 0) {
         ScoreArgs a{(const uint16_t *)q, kc, HalfTiles{}, HalfTiles{}, s_shared, L.map, L.p->num_q_heads, L.p->cmp_len, L.p->cmp_stride,
                     L.p->dense_threshold, L.p->lse_mode, L.p->softmax_scale, row_stride};
-        if (!pooled) return launch_scores_mfma<8, 4, -1>(L, a, cu_h);
-        return pool.pad == 0 ? launch_scores_mfma<8, 4, 0>(L, a, cu_h) : launch_scores_mfma<8, 4, 1>(L, a, cu_h);
+        // Four tokens per wavefront, so that a key fragment read from LDS feeds four products; two or one while even that
+        // leaves CUs without a workgroup (a short prompt is one chain of loads and products per token of a wavefront: 777
+        // tokens on 2 KV heads 14.9 us with four, 8.2 with one).
+        const int64_t most = 256 / L.p->num_kv_heads;
+        int64_t tiles8 = 0, tiles16 = 0;
+        for (int s = 0; s < L.map.batch; ++s) {
+            tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
+            tiles16 += (cu_h[s + 1] - cu_h[s] + 15) / 16;
+        }
+        if (tiles8 <= most) return launch_scores_pool<8, 1>(L, a, cu_h, pooled ? pool.pad : -1);
+        if (tiles16 <= most) return launch_scores_pool<8, 2>(L, a, cu_h, pooled ? pool.pad : -1);
+        return launch_scores_pool<8, 4>(L, a, cu_h, pooled ? pool.pad : -1);
     }
     if (L.p->head_dim == 128)
         return bf ? launch_generic<bf16_t, 128>(L, q, kc, s_shared, row_stride, pool)
