@@ -142,8 +142,7 @@ def _workspace(op: int, p: Params, cu_h: torch.Tensor, device, given: Optional[t
     if given is not None:
         return given
     batch = cu_h.numel() - 1
-    max_len = int((cu_h[1:] - cu_h[:-1]).max()) if batch else 0
-    need = workspace_bytes(op, p, batch, int(cu_h[-1]), max_len)
+    need = workspace_bytes(op, p, batch, int(cu_h[-1]), _max_len(cu_h))
     return torch.empty(need, dtype=torch.uint8, device=device) if need else None
 
 
@@ -168,6 +167,11 @@ def _cu_pair(cu_seqlens):
     """host int32 tensor + device copy (pass a SeqInfo to avoid the copy on every call)"""
     si = cu_seqlens if isinstance(cu_seqlens, SeqInfo) else SeqInfo(cu_seqlens)
     return si.cu_h, si.cu_d
+
+
+def _max_len(cu_h: torch.Tensor) -> int:
+    """Longest sequence; only where a buffer is made here (a few microseconds of tensor arithmetic)."""
+    return int((cu_h[1:] - cu_h[:-1]).max()) if cu_h.numel() > 1 else 0
 
 
 def _kv_strides(k: torch.Tensor):
@@ -216,9 +220,8 @@ def block_scores(p: Params, q: torch.Tensor, kc: torch.Tensor, cu_seqlens, cu_se
     assert q.is_contiguous() and kc.is_contiguous()
     cu_h, cu_d = _cu_pair(cu_seqlens)
     batch = cu_h.numel() - 1
-    max_len = int((cu_h[1:] - cu_h[:-1]).max()) if batch else 0
-    rs = max(4, (num_cmp(p, max_len) + 3) // 4 * 4)
     if out is None:
+        rs = max(4, (num_cmp(p, _max_len(cu_h)) + 3) // 4 * 4)
         out = torch.empty((p.num_kv_heads, q.shape[0], rs), dtype=torch.float32, device=q.device)
     ws = _workspace(OP_BLOCK_SCORES, p, cu_h, q.device, workspace)
     st = lib().infllmv2_block_scores(ctypes.byref(p), _ptr(q), _ptr(kc), kc.shape[1], _ptr(cu_h), _ptr(cu_d),
@@ -245,9 +248,8 @@ def block_scores_pooled(p: Params, q: torch.Tensor, kc: torch.Tensor, cu_seqlens
     a row is written iff the block's pooling window holds a visible key."""
     cu_h, cu_d = _cu_pair(cu_seqlens)
     batch = cu_h.numel() - 1
-    max_len = int((cu_h[1:] - cu_h[:-1]).max()) if batch else 0
     if out is None:
-        rs = max(1, (max_len + p.block_size - 1) // p.block_size)
+        rs = max(1, (_max_len(cu_h) + p.block_size - 1) // p.block_size)
         out = torch.empty((p.num_kv_heads, q.shape[0], rs), dtype=torch.float32, device=q.device)
     assert q.is_contiguous() and kc.is_contiguous()
     ws = _workspace(OP_BLOCK_SCORES_POOLED, p, cu_h, q.device, workspace)
@@ -318,7 +320,7 @@ def sparse_attn_bwd(p: Params, q, k, v, block_idx, out, lse, dout, cu_seqlens, d
     assert dout.is_contiguous() and out.is_contiguous() and dq.is_contiguous() and dk.is_contiguous() and dv.is_contiguous()
     assert q.is_contiguous() and lse.is_contiguous()
     if workspace is None:
-        max_len = int((cu_h[1:] - cu_h[:-1]).max()) if batch else 0
+        max_len = _max_len(cu_h)
         full = workspace_bytes(OP_SPARSE_ATTN_BWD, p, batch, T, max_len)
         least = workspace_bytes(OP_SPARSE_ATTN_BWD_MIN, p, batch, T, max_len)
         need = full if block_idx is not None and full - least <= sel_bitmap_max_bytes else least
