@@ -127,8 +127,8 @@ typedef enum infllmv2_op {
  * all and none longer than max_seqlen (for INFLLMV2_OP_SPARSE_DECODE: `batch` sequences with contexts of at most
  * max_seqlen tokens; total_tokens is ignored).  The inputs of Alg. 1 and Appendix Alg. 2 / 3 and their outputs
  * live in HBM buffers of the caller; so does everything the kernels keep between their launches: a transposed
- * copy of V for the attention calls, a half-precision copy of the compressed keys for the score calls, K^T and
- * per-row terms for the backward call, partial results for decode.  Returns 0 for calls that need none, and 0
+ * copy of V for the attention calls, a half-precision copy of the compressed keys for the score calls, per-row terms
+ * for the backward call, partial results for decode.  Returns 0 for calls that need none, and 0
  * for parameters that infllmv2_* calls reject.  Host helper, no GPU needed.
  */
 size_t infllmv2_workspace_bytes(int op, const infllmv2_params *p, int32_t batch, int64_t total_tokens,

@@ -22,12 +22,9 @@ FLAGS = [
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 
-# Per-file additions.  The backward kernels keep 64 accumulator registers plus short-lived ones; with the default
-# split of the register file the compiler parks accumulators in AGPRs and then shuffles them through VGPRs around
-# every temporary MFMA (a hundred v_accvgpr moves per token).  Keeping MFMA results in VGPRs avoids that.
+# Per-file additions.  The dK/dV kernel keeps 256 accumulator registers, placed in AGPRs by hand, next to 240 others; with
+# the default form the compiler wants AGPRs for its short-lived MFMA results as well and spills.
 EXTRA_FLAGS = {
-    "attn_bwd_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-    # (its long-lived sums are placed in AGPRs by hand)
     "attn_bwd_dkv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 

@@ -13,7 +13,6 @@ struct BwdM {
     RowMap map;
     // scratch
     float *nlse, *ndelta;        // [T][hq]: -lse / scale and -<dO, O>, the seeds of the products q k and dO v
-    uint16_t *kt;                // [hkv][blocks][128][64]
     int64_t nblocks;             // 64-key blocks over all sequences
     uint32_t *sel_bits;          // [hkv][sel_words]: per sequence and key block, one bit per token that selected it
     int64_t sel_words;           //   (block-major, rows of ceil(len / 32) words); nullptr: not built (too large)
@@ -32,7 +31,9 @@ __device__ inline int64_t sel_base(const RowMap &m, int seq) {
     return w;
 }
 
-// dK, dV (attn_bwd_dkv.hip); nothing else of the call depends on it
+// dQ: the forward's tile kernel with another unit (attn_mfma.hip)
+int launch_bwd_dq(const Launch &L, const BwdM &a, const int32_t *cu_h);
+// dK, dV (attn_bwd_dkv.hip)
 int launch_bwd_dkv(const BwdM &a, int32_t max_len, hipStream_t stream);
 
 }  // namespace ifv2

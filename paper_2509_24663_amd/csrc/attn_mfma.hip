@@ -34,6 +34,7 @@
 // ATTN_TIMING_DROP_PRIVATE=C leaves the union entries with at most C consumers out of the walk (what do they cost?).
 #include <type_traits>
 
+#include "attn_bwd_mfma.h"
 #include "attn_unit.h"
 
 namespace ifv2 {
@@ -46,6 +47,8 @@ struct AttnArgs {
     const uint16_t *q, *k, *v;
     const uint16_t *vt;      // V^T blocks: [kv head][block of the batch][128 dims][64 keys]
     int nblk_total;          // blocks of the whole batch (sum over sequences of ceil(len / 64))
+    const uint16_t *dout;    // backward form only: dO, -lse / scale and -<dO, O> per (token, query head); out is dQ
+    const float *nlse, *ndelta;
     const int32_t *idx;
     uint16_t *out;
     float *lse;
@@ -56,8 +59,9 @@ struct AttnArgs {
     int list_cap;      // entries reserved for the union list
 };
 
-// NW waves with one token each, SLOTS union entries per barrier interval.
-template <int NW, int SLOTS>
+// NW waves with one token each, SLOTS union entries per barrier interval.  BWD: the backward's dQ for the same tiles and
+// walk: the second tile of a stage is the block's V rows instead of V^T, and the unit is unit_bwd.
+template <int NW, int SLOTS, bool BWD = false>
 struct TileKernel {
     static constexpr int T = NW;
     static constexpr int NTHR = NW * 64;
@@ -66,6 +70,11 @@ struct TileKernel {
     static constexpr int NONE = 0xffff;            // no block (block numbers are kept in 16 bits)
     static_assert(16 % NW == 0, "sixteen one-KB pieces per tile are dealt round-robin to the waves");
     static_assert(SLOTS == 1 || SLOTS == 2, "one or two entries per interval");
+
+    __device__ static inline void piece_src(int q, int lane, int &row, int &chunk) {
+        if (BWD) bwd_piece_src(q, lane, row, chunk);
+        else k_piece_src(q, lane, row, chunk);
+    }
 
     // which of the CU's four SIMDs this wave runs on (hardware id register, bits 5:4)
     __device__ static inline int simd_id() { return (int)__builtin_amdgcn_s_getreg(4 | (4 << 6) | (1 << 11)); }
@@ -158,7 +167,8 @@ struct TileKernel {
         const bool dense = a.idx == nullptr || len < a.dense_below;
         const int row0 = tok0 + t0;                      // packed row of the tile's first token
         const uint16_t *kb = a.k + (int64_t)tok0 * a.map.kv_tok_stride + (int64_t)h * a.map.kv_head_stride;
-        const uint16_t *vtb = a.vt + ((int64_t)h * a.nblk_total + __builtin_amdgcn_readfirstlane(s_blk0)) * VT_TILE_ELEMS;
+        const uint16_t *vtb = BWD ? a.v + (kb - a.k)
+                                  : a.vt + ((int64_t)h * a.nblk_total + __builtin_amdgcn_readfirstlane(s_blk0)) * VT_TILE_ELEMS;
         const uint32_t full = ntok >= 32 ? 0xffffffffu : ((1u << ntok) - 1u);
 
         // ---- union of the tile's block lists: masks[j] has bit ti set if token ti selected block j.  The tile's
@@ -260,13 +270,17 @@ struct TileKernel {
 #pragma unroll
         for (int u = 0; u < KOFF; ++u) {
             int row, chunk;
-            k_piece_src(w + u * NW, lane, row, chunk);
+            piece_src(w + u * NW, lane, row, chunk);
             off_k_w[u] = (uint32_t)((row - 4 * (w + u * NW)) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
         }
         const uint32_t off_v_w = vt_piece_src_bytes(w, lane) - (uint32_t)w * 1024u;
         const uint32_t k_step = blk_bytes / PPW;          // K bytes between a wave's pieces of a block
         const char *kb_w = reinterpret_cast<const char *>(kb) + (uint64_t)w * (blk_bytes / 16u);
-        const char *vtb_w = reinterpret_cast<const char *>(vtb) + (uint32_t)w * 1024u;
+        const char *vtb_w = reinterpret_cast<const char *>(vtb) + (BWD ? (uint64_t)w * (blk_bytes / 16u) : (uint64_t)w * 1024u);
+        auto copy_v = [&](uint32_t j, int u, uint32_t dst) {
+            if (BWD) async_copy16(vtb_w + (uint64_t)j * blk_bytes + u * k_step, off_k_w[u % KOFF], dst);
+            else async_copy16(vtb_w + (j << 14) + u * kPieceStep, off_v_w, dst);
+        };
         const uint32_t lds_w = lds0 + (uint32_t)w * 1024u;
 #ifdef ATTN_TIMING_NO_LOADS
         bool timing_fill = false;
@@ -286,13 +300,13 @@ struct TileKernel {
 #pragma unroll
             for (int u = 0; u < PPW; ++u) {
                 async_copy16(kb_w + (uint64_t)j0 * blk_bytes + u * k_step, off_k_w[u % KOFF], dst + u * kPieceStep);
-                async_copy16(vtb_w + (j0 << 14) + u * kPieceStep, off_v_w, dst + kTileBytes + u * kPieceStep);
+                copy_v(j0, u, dst + kTileBytes + u * kPieceStep);
             }
             if (two) {
 #pragma unroll
                 for (int u = 0; u < PPW; ++u) {
                     async_copy16(kb_w + (uint64_t)j1 * blk_bytes + u * k_step, off_k_w[u % KOFF], dst + kStageBytes + u * kPieceStep);
-                    async_copy16(vtb_w + (j1 << 14) + u * kPieceStep, off_v_w, dst + kStageBytes + kTileBytes + u * kPieceStep);
+                    copy_v(j1, u, dst + kStageBytes + kTileBytes + u * kPieceStep);
                 }
             }
         };
@@ -305,10 +319,11 @@ struct TileKernel {
 #pragma unroll
             for (int u = 0; u < PPW; ++u) {
                 int row, chunk;
-                k_piece_src(w + u * NW, lane, row, chunk);
+                piece_src(w + u * NW, lane, row, chunk);
                 const uint32_t off = (uint32_t)(min(row, own_rows - 1) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
                 async_copy16(reinterpret_cast<const char *>(kb) + (uint64_t)bt * blk_bytes, off, dst + u * kPieceStep);
-                async_copy16(vtb_w + ((uint32_t)bt << 14) + u * kPieceStep, off_v_w, dst + kTileBytes + u * kPieceStep);
+                if (BWD) async_copy16(reinterpret_cast<const char *>(vtb) + (uint64_t)bt * blk_bytes, off, dst + kTileBytes + u * kPieceStep);
+                else async_copy16(vtb_w + ((uint32_t)bt << 14) + u * kPieceStep, off_v_w, dst + kTileBytes + u * kPieceStep);
             }
         };
         int2 r_cur = ni > 0 ? interval(0) : make_int2(0, 0);
@@ -323,14 +338,31 @@ struct TileKernel {
         else if (ni > 1) issue((uint32_t)__builtin_amdgcn_readfirstlane(r_cur.x), 0);
 
         // ---- this wave's token
-        Tok st;
+        typename std::conditional<BWD, TokBwd, Tok>::type st;
         const int m16 = lane & 15, g = lane >> 4;
         const int ti = w;
-        {
+        const int64_t qrow = (int64_t)(row0 + ti) * a.hq + h * G + m16;        // (token, query head) of this lane
+        if constexpr (BWD) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                uint4 q4 = make_uint4(0, 0, 0, 0), g4 = q4;
+                if (ti < ntok) {
+                    q4 = *reinterpret_cast<const uint4 *>(a.q + qrow * D + g * 8 + s * 32);
+                    g4 = *reinterpret_cast<const uint4 *>(a.dout + qrow * D + g * 8 + s * 32);
+                }
+                st.qf[s] = __builtin_bit_cast(bf16x8, q4);
+                st.gf[s] = __builtin_bit_cast(bf16x8, g4);
+            }
+            st.nlse = ti < ntok ? a.nlse[qrow] : 0.f;
+            st.ndelta = ti < ntok ? a.ndelta[qrow] : 0.f;
+            st.c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.scale * LOG2E)));
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) st.o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        } else {
             float cm;
             int ce;
             split_scale(a.scale * LOG2E, cm, ce);
-            const uint16_t *qp = a.q + ((int64_t)(row0 + ti) * a.hq + h * G + m16) * D + g * 8;
+            const uint16_t *qp = a.q + qrow * D + g * 8;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 uint4 raw = ti < ntok ? *reinterpret_cast<const uint4 *>(qp + s * 32) : make_uint4(0, 0, 0, 0);
@@ -338,7 +370,7 @@ struct TileKernel {
             }
             tok_init(st, __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, cm))));
         }
-        const uint32_t kx = k_lane_bytes(lane), vx = v_lane_bytes(lane);
+        const uint32_t kx = BWD ? bwd_row_bytes(lane) : k_lane_bytes(lane), vx = BWD ? bwd_trans_bytes(lane) : v_lane_bytes(lane);
 
         // Main loop: while interval i is consumed from one buffer, the blocks of interval i + 1 land in the other
         // (every wave left that buffer before the barrier that ended interval i - 1).  The interval records are
@@ -380,8 +412,13 @@ struct TileKernel {
             const uint32_t stage = lds0 + (uint32_t)(((i & 1) * SLOTS) * STAGE_ELEMS * 2);
             // (consecutive tests rather than the arms of one branch: the compiler would otherwise merge the
             // identical operand reads of the two units above the branch and run out of registers)
-            if (u0) unit<OWN>(st, stage, kx, vx, lane, t0 + w - j0 * kBlock, issue_now);
-            if (u1) unit<false>(st, stage + STAGE_ELEMS * 2, kx, vx, lane, 0, issue_now);
+            if constexpr (BWD) {
+                if (u0) unit_bwd<OWN>(st, stage, kx, vx, lane, t0 + w - j0 * kBlock, issue_now);
+                if (u1) unit_bwd<false>(st, stage + STAGE_ELEMS * 2, kx, vx, lane, 0, issue_now);
+            } else {
+                if (u0) unit<OWN>(st, stage, kx, vx, lane, t0 + w - j0 * kBlock, issue_now);
+                if (u1) unit<false>(st, stage + STAGE_ELEMS * 2, kx, vx, lane, 0, issue_now);
+            }
 #ifdef ATTN_TIMING_CLOCK
             const uint64_t ck2 = wall_clock64();
             ck_units += ck2 - ck1;
@@ -409,11 +446,16 @@ struct TileKernel {
 
         // ---- normalise and store
         if (ti < ntok) {
-            float l = st.l;
-            l += __shfl_xor(l, 16);
-            l += __shfl_xor(l, 32);
-            const float inv = l > 0.f ? 1.0f / l : 0.f;
-            uint16_t *op = a.out + ((int64_t)(row0 + ti) * a.hq + h * G + m16) * D + g * 4;
+            float l = 0.f, inv = a.scale;
+            if constexpr (!BWD) {
+                l = st.l;
+                l += __shfl_xor(l, 16);
+                l += __shfl_xor(l, 32);
+                inv = l > 0.f ? 1.0f / l : 0.f;
+            }
+            int lane_end = lane;
+            asm volatile("" : "+v"(lane_end));           // the address is formed here, not kept in registers over the loop
+            uint16_t *op = a.out + ((int64_t)(row0 + ti) * a.hq + h * G + (lane_end & 15)) * D + (lane_end >> 4) * 4;
 #pragma unroll
             for (int dt = 0; dt < 8; ++dt) {
                 uint2 pk;
@@ -421,6 +463,8 @@ struct TileKernel {
                 pk.y = (uint32_t)float_to_bf16(st.o[dt][2] * inv) | ((uint32_t)float_to_bf16(st.o[dt][3] * inv) << 16);
                 *reinterpret_cast<uint2 *>(op + dt * 16) = pk;
             }
+            if constexpr (BWD) return;
+            else {
             // log-sum-exp in natural units: the reference and the row sum are kept in powers of two
 #ifdef ATTN_TIMING_CLOCK
             // timing experiment: instead of lse, heads 0-6 of the group get this wave's 100 MHz ticks spent issuing
@@ -434,6 +478,7 @@ struct TileKernel {
             if (a.lse != nullptr && g == 0)
                 a.lse[(int64_t)(h * G + m16) * a.map.total_rows + row0 + ti] = (__log2f(l) - st.nr) * 0.6931471805599453f;
 #endif
+            }
         }
     }
 };
@@ -482,8 +527,12 @@ template <int NW, int SLOTS>
 __global__ void __launch_bounds__(NW * 64) attn_tile_kernel(AttnArgs a, int num_tiles) {
     TileKernel<NW, SLOTS>::run(a, num_tiles);
 }
-
 template <int NW, int SLOTS>
+__global__ void __launch_bounds__(NW * 64) bwd_dq_mfma_kernel(AttnArgs a, int num_tiles) {
+    TileKernel<NW, SLOTS, true>::run(a, num_tiles);
+}
+
+template <int NW, int SLOTS, bool BWD = false>
 int launch_tile(const Launch &L, const AttnArgs &a0, const int32_t *cu_h) {
     constexpr int T = NW;
     AttnArgs a = a0;
@@ -498,7 +547,7 @@ int launch_tile(const Launch &L, const AttnArgs &a0, const int32_t *cu_h) {
                        (size_t)a.nb_cap * 4 + (size_t)a.list_cap * 8;
     if (lds > 160 * 1024 - 256 || nb_max >= 0xffff) return INFLLMV2_ERR_UNSUPPORTED;     // does not fit: the caller pairs nothing
     if (SLOTS == 2 && a.list_cap / 2 + 1 > NW * 64) return INFLLMV2_ERR_UNSUPPORTED;      // one thread packs one interval record
-    auto kern = attn_tile_kernel<NW, SLOTS>;
+    auto kern = BWD ? bwd_dq_mfma_kernel<NW, SLOTS> : attn_tile_kernel<NW, SLOTS>;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -507,6 +556,28 @@ int launch_tile(const Launch &L, const AttnArgs &a0, const int32_t *cu_h) {
     dim3 grid((unsigned)tiles, L.p->num_kv_heads);
     hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, L.stream, a, (int)tiles);
     return hip_status(hipGetLastError());
+}
+
+template <bool BWD>
+int launch_tiles(const Launch &L, const AttnArgs &a, const int32_t *cu_h) {
+    // Two entries per interval when the four LDS stages that needs fit next to the block masks (with block lists:
+    // sequences up to about 384K tokens; dense calls keep no masks), else one.
+    // Tiles of 16 tokens, or of 8 or 4 while even those leave CUs without a workgroup (one fits a CU): a block in LDS
+    // then serves fewer tokens, but there is nobody else to serve, and an interval takes as long as its units.
+    // (777 tokens, 2 KV heads: 28.9 us with 16, 20.7 with 8; dense, 1000 tokens: 36.4 and 27.4, 200 tokens 17.3 and,
+    // with 4, 13.5)
+    const int64_t most = 256 / L.p->num_kv_heads;
+    int64_t tiles4 = 0, tiles8 = 0;
+    for (int s = 0; s < L.map.batch; ++s) {
+        tiles4 += (cu_h[s + 1] - cu_h[s] + 3) / 4;
+        tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
+    }
+    int rc = INFLLMV2_ERR_UNSUPPORTED;
+    if (tiles4 <= most) rc = launch_tile<4, 2, BWD>(L, a, cu_h);
+    else if (tiles8 <= most) rc = launch_tile<8, 2, BWD>(L, a, cu_h);
+    if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 2, BWD>(L, a, cu_h);
+    if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 1, BWD>(L, a, cu_h);
+    return rc;
 }
 
 }  // namespace
@@ -553,25 +624,28 @@ int launch_attn_mfma(const Launch &L, const void *q, const void *k, const void *
                        a.v, (uint16_t *)ws, L.map, (int)nblk_total);
     int rc = hip_status(hipGetLastError());
     if (rc == INFLLMV2_OK) {
-        // Two entries per interval when the four LDS stages that needs fit next to the block masks (with block lists:
-        // sequences up to about 384K tokens; dense calls keep no masks), else one.
-        // Tiles of 16 tokens, or of 8 or 4 while even those leave CUs without a workgroup (one fits a CU): a block in LDS
-        // then serves fewer tokens, but there is nobody else to serve, and an interval takes as long as its units.
-        // (777 tokens, 2 KV heads: 28.9 us with 16, 20.7 with 8; dense, 1000 tokens: 36.4 and 27.4, 200 tokens 17.3 and,
-        // with 4, 13.5)
-        const int64_t most = 256 / L.p->num_kv_heads;
-        int64_t tiles4 = 0, tiles8 = 0;
-        for (int s = 0; s < L.map.batch; ++s) {
-            tiles4 += (cu_h[s + 1] - cu_h[s] + 3) / 4;
-            tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
-        }
-        rc = INFLLMV2_ERR_UNSUPPORTED;
-        if (tiles4 <= most) rc = launch_tile<4, 2>(L, a, cu_h);
-        else if (tiles8 <= most) rc = launch_tile<8, 2>(L, a, cu_h);
-        if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 2>(L, a, cu_h);
-        if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 1>(L, a, cu_h);
+        rc = launch_tiles<false>(L, a, cu_h);
     }
     return rc;
+}
+
+// dQ of the backward (declared in attn_bwd_mfma.h)
+int launch_bwd_dq(const Launch &L, const BwdM &b, const int32_t *cu_h) {
+    AttnArgs a{};
+    a.q = b.q;
+    a.k = b.k;
+    a.v = b.v;
+    a.idx = b.idx;
+    a.out = b.dq;
+    a.map = b.map;
+    a.hq = b.hq;
+    a.topk_total = b.topk_total;
+    a.dense_below = b.dense_below;
+    a.scale = b.scale;
+    a.dout = b.dout;
+    a.nlse = b.nlse;
+    a.ndelta = b.ndelta;
+    return launch_tiles<true>(L, a, cu_h);
 }
 
 }  // namespace ifv2

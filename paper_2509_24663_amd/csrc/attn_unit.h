@@ -429,5 +429,102 @@ __device__ inline void unit(Tok &t, uint32_t stage, uint32_t kx, uint32_t vx, in
     }
 }
 
+// =====================================================================================================
+// Backward unit (dQ): one K/V block against the token held by this wave.  Per half of 32 keys S^T = K Q^T and dP^T = V dO^T
+// (keys x heads, seeded with -lse / scale and -Delta, so that the products come out subtracted), dZ = P dP, and
+// dQ^T += K^T dZ^T, whose first operand is the K tile read back transposed.  Key rows are assigned to product rows as in
+// the prefill unit, so a lane's eight dZ are the eight consecutive keys it must supply.  Both tiles are row-major, 256-byte
+// rows, 16-byte chunk c of row r at chunk c ^ bwd_swizzle(r): the sixteen rows of an operand read take sixteen positions,
+// and so do the 8 rows x 2 chunks that half a wave touches in a transposing read.
+__device__ inline int bwd_swizzle(int r) { return 4 * (r & 3) + 2 * ((r >> 3) & 1) + ((r >> 4) & 1); }
+
+// K or V piece q (rows 4q .. 4q+3 of the block): lane l fills (row 4q + l / 16, physical chunk l % 16)
+__device__ inline void bwd_piece_src(int q, int lane, int &row, int &chunk) {
+    row = 4 * q + (lane >> 4);
+    chunk = (lane & 15) ^ bwd_swizzle(row);
+}
+// row operand of key tile 0, k-step 0 (as k_lane_bytes)
+__device__ inline uint32_t bwd_row_bytes(int lane) {
+    const int m16 = lane & 15, g = lane >> 4, row = 8 * (m16 >> 2) + (m16 & 3);
+    return (uint32_t)(row * D * 2 + ((g ^ bwd_swizzle(row)) << 4));
+}
+// transposing read of the 4 x 16 piece (rows 8 g + L / 4, dims 4 (L % 4) ..) of each 16-lane group
+__device__ inline uint32_t bwd_trans_bytes(int lane) {
+    const int L = lane & 15, g = lane >> 4, row = 8 * g + (L >> 2);
+    return (uint32_t)(row * D * 2 + ((((L & 3) >> 1) ^ bwd_swizzle(row)) << 4) + (L & 1) * 8);
+}
+// K^T operand of dim tile dt and half h: keys 32 h + 8 g .. + 7 of dim 16 dt + lane % 16
+__device__ inline bf16x8 bwd_kt_frag(uint32_t tb, int dt, int h) {
+    typedef __attribute__((address_space(3))) short4v lds_s4;
+    const uint32_t x = (tb ^ (uint32_t)(32 * dt)) + (uint32_t)(32 * h * D * 2);
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)x);
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)(x + 4 * D * 2));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+struct TokBwd {
+    bf16x8 qf[4], gf[4];   // Q_t and dO_t as second operands: head = lane % 16, dims ks*32 + (lane/16)*8 ..
+    f32x4 o[8];            // dQ_t^T / scale: dim tile dt, dims dt*16 + 4*(lane/16) + r, head = lane % 16
+    float nlse, ndelta;    // -lse / scale and -Delta of this lane's head
+    float c;               // softmax_scale * log2(e)
+};
+
+template <bool OWN, class Mid = NoMid>
+__device__ inline void unit_bwd(TokBwd &t, uint32_t stage, uint32_t rx, uint32_t tx, int lane, int key_limit, Mid mid = Mid()) {
+    const uint32_t kb = stage + rx, tb = stage + tx;
+    constexpr int W = 4;
+    bf16x8 f[W];
+    // fragment n of the unit, 24 per half: K and V rows of a key tile's four k-steps in turn, two tiles, then K^T
+    auto frag = [&](int n) -> bf16x8 {
+        const int h = n / 24, i = n % 24;
+        if (i < 16) {
+            const int kt = 2 * h + (i >> 3), s = (i >> 1) & 3;      // (as k_frag; the V tile lies behind the K tile)
+            return lds_read16((kb ^ (uint32_t)(64 * s)) + (uint32_t)((32 * (kt >> 1) + 4 * (kt & 1)) * D * 2 + (i & 1) * TILE_ELEMS * 2));
+        }
+        return bwd_kt_frag(tb, i - 16, h);
+    };
+#pragma unroll
+    for (int n = 0; n < W; ++n) f[n] = frag(n);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        u32x4 zb;
+        // (products in pairs, the later-fetched fragment first: see unit().  One key tile at a time: with both tiles' sums
+        // in flight the wave needs more than the 128 registers that sixteen of them leave it.)
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+            f32x4 s = {t.nlse, t.nlse, t.nlse, t.nlse}, d = {t.ndelta, t.ndelta, t.ndelta, t.ndelta};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const int n = 24 * h + 8 * kt + 2 * ks;
+                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(n + 1) % W], t.gf[ks], d, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[n % W], t.qf[ks], s, 0, 0, 0);
+                f[n % W] = frag(n + W);
+                f[(n + 1) % W] = frag(n + 1 + W);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (h == 0 && kt == 1) mid();
+            float z[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool hidden = OWN && 32 * h + 8 * (lane >> 4) + 4 * kt + e > key_limit;
+                z[e] = hidden ? 0.f : fast_exp2(s[e] * t.c) * d[e];
+            }
+            zb[2 * kt] = pack_bf16(z[0], z[1]);
+            zb[2 * kt + 1] = pack_bf16(z[2], z[3]);
+        }
+#pragma unroll
+        for (int dt = 0; dt < 8; dt += 2) {
+            const int n = 24 * h + 16 + dt;
+            t.o[dt + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(n + 1) % W], __builtin_bit_cast(bf16x8, zb), t.o[dt + 1], 0, 0, 0);
+            t.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[n % W], __builtin_bit_cast(bf16x8, zb), t.o[dt], 0, 0, 0);
+            if (n + W < 48) {
+                f[n % W] = frag(n + W);
+                f[(n + 1) % W] = frag(n + 1 + W);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
 }  // namespace attn_unit
 }  // namespace ifv2
