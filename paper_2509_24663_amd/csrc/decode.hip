@@ -553,7 +553,7 @@ __global__ void __launch_bounds__(AW * 64) dec_attn_kernel(DecArgs a) {
 //            (a few KB, redundantly), normalises and group-sums its own keys, max-pools them to its 64 blocks
 //   attend : grid (splits, pairs)  every workgroup first selects (radix select over the pair's <= a few thousand
 //            pooled keys: no trip through memory between selection and attention), then attends to its eight
-//            blocks of the top-k list
+//            blocks of the top-k list; for large batches the selection is a kernel of its own (dec_pick_kernel)
 //   merge  : as above, over forced + top-k partials.
 // The serial selection kernel is gone from the chain; what it did is spread over many workgroups (pool) or repeated
 // by each of the few workgroups that need the result (attend).
@@ -711,9 +711,187 @@ constexpr int kSelMax = 1024;               // top-k entries (topk_total <= 1024
 constexpr int kPkLds = 4096;                // pooled keys a workgroup keeps in registers (contexts up to 262144 tokens;
                                             // longer rows are re-read from memory by every pass)
 
+// The selection of one pair by a workgroup of NW waves: on return (after a barrier) sel[0 .. kr) holds the top-k blocks
+// without the forced ones, ascending.  hist: [4][256] of LDS.
+template <int NW>
+__device__ inline void pick_blocks(const DecArgs &a, int pair, const Forced &fo, int *sel, int (*hist)[256], int *wave_tot,
+                                   uint32_t *s_prefix, int *s_k) {
+    constexpr int NT = NW * 64;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (fo.nblk <= kPkLds) {
+        // ---- radix select (4 x 8 bits) of the kr-th largest pooled key among the live blocks; selection rule
+        // and tie order as in the prefill: keys above it, then the first `need` keys equal to it by block number.
+        // A thread keeps `per` consecutive blocks' keys in registers (one trip to memory, no copy in LDS); every
+        // wave reduces the histogram of a pass by itself (data-parallel scan, no LDS round trips), so a pass costs
+        // one barrier.
+        constexpr int KPT = kPkLds / NT;
+        const uint32_t *pk = a.pk + (int64_t)pair * a.pk_cap;
+        const int per = (fo.nblk + NT - 1) / NT, jb0 = tid * per;
+        uint32_t kreg[KPT];
+        uint32_t live = 0u;                              // bit u: block jb0 + u exists and takes part in the top-k
+#pragma unroll
+        for (int u = 0; u < KPT; ++u) {
+            const int jb = jb0 + u;
+            const bool lv = u < per && jb < fo.nblk && !fo.is_forced(jb);
+            kreg[u] = lv ? pk[jb] : 0u;
+            live |= lv ? 1u << u : 0u;
+        }
+        for (int i = tid; i < 4 * 256; i += NT) (&hist[0][0])[i] = 0;
+        __syncthreads();
+        uint32_t prefix = 0u;
+        int k = fo.kr;
+        for (int pass = 3; pass >= 0; --pass) {
+            const int hi_shift = 8 * (pass + 1);
+#pragma unroll
+            for (int u = 0; u < KPT; ++u)
+                if (((live >> u) & 1u) && (pass == 3 || (kreg[u] >> hi_shift) == prefix))
+                    atomicAdd(&hist[pass][(kreg[u] >> (8 * pass)) & 255u], 1);
+            __syncthreads();
+            // lane l owns digits 255 - 4l .. 252 - 4l, largest first; above = number of keys with a larger digit
+            int c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[u] = hist[pass][255 - 4 * lane - u];
+            const int mine = c[0] + c[1] + c[2] + c[3];
+            int above = wave_inclusive_sum(mine) - mine;
+            int digit = 0, knew = 0;
+            bool found = false;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (above < k && k <= above + c[u]) {
+                    found = true;
+                    digit = 255 - 4 * lane - u;
+                    knew = k - above;
+                }
+                above += c[u];
+            }
+            const int src = max(__ffsll((long long)__ballot(found)) - 1, 0);     // exactly one lane (kr >= 1 keys exist)
+            prefix = (prefix << 8) | (uint32_t)__builtin_amdgcn_readlane(digit, src);
+            k = __builtin_amdgcn_readlane(knew, src);
+        }
+        const uint32_t thr = prefix;                     // the kr-th largest key; `need` of the keys equal to it are taken
+        const int need = k;
+        // emission in ascending block order: one prefix count over the threads for (keys above, keys equal)
+        int ca = 0, cb = 0;
+#pragma unroll
+        for (int u = 0; u < KPT; ++u) {
+            const bool lv = ((live >> u) & 1u) != 0u;
+            ca += lv && kreg[u] > thr ? 1 : 0;
+            cb += lv && kreg[u] == thr ? 1 : 0;
+        }
+        const int packed = ca | (cb << 16);
+        const int incl = wave_inclusive_sum(packed);
+        if (lane == 63) wave_tot[w] = incl;
+        __syncthreads();
+        int before = incl - packed;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) before += q < w ? wave_tot[q] : 0;
+        int eq_before = before >> 16;
+        int pos = (before & 0xffff) + min(eq_before, need);
+#pragma unroll
+        for (int u = 0; u < KPT; ++u) {
+            if (!((live >> u) & 1u)) continue;
+            bool take = kreg[u] > thr;
+            if (kreg[u] == thr) {
+                take = eq_before < need;
+                ++eq_before;
+            }
+            if (take) sel[pos++] = jb0 + u;
+        }
+        __syncthreads();
+    } else {
+        // the same for rows too long for the registers: every pass re-reads the pooled keys from memory
+        const uint32_t *pk = a.pk + (int64_t)pair * a.pk_cap;
+        for (int i = tid; i < 4 * 256; i += NT) (&hist[0][0])[i] = 0;
+        if (tid == 0) { *s_prefix = 0u; *s_k = fo.kr; }
+        __syncthreads();
+        for (int pass = 3; pass >= 0; --pass) {
+            const uint32_t prefix = *s_prefix;
+            const int hi_shift = 8 * (pass + 1);
+            for (int jb = tid; jb < fo.nblk; jb += NT) {
+                if (fo.is_forced(jb)) continue;
+                const uint32_t key = pk[jb];
+                if (pass == 3 || (key >> hi_shift) == prefix) atomicAdd(&hist[pass][(key >> (8 * pass)) & 255u], 1);
+            }
+            __syncthreads();
+            if (w == 0) {
+                // lane l owns digits 4l .. 4l+3; above = number of keys with a larger digit
+                const int k = *s_k;
+                int c[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) c[u] = hist[pass][4 * lane + u];
+                const int mine = c[0] + c[1] + c[2] + c[3];
+                int run = mine;                          // inclusive suffix sum over lanes
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int other = __shfl_down(run, o);
+                    if (lane + o < 64) run += other;
+                }
+                int above = run - mine;
+#pragma unroll
+                for (int u = 3; u >= 0; --u) {
+                    if (above < k && k <= above + c[u]) {
+                        *s_prefix = (prefix << 8) | (uint32_t)(4 * lane + u);
+                        *s_k = k - above;
+                    }
+                    above += c[u];
+                }
+            }
+            __syncthreads();
+        }
+        const uint32_t thr = *s_prefix;               // the kr-th largest key; `need` of the keys equal to it are taken
+        const int need = *s_k;
+        int written = 0, eq_seen = 0;
+        for (int base = 0; base < fo.nblk; base += NT) {
+            const int jb = base + tid;
+            const bool lv = jb < fo.nblk && !fo.is_forced(jb);
+            const uint32_t key = lv ? pk[jb] : 0u;
+            int eq_tot, sel_tot;
+            const int eq_rank = eq_seen + wg_prefix_count_n<NW>(lv && key == thr, wave_tot, tid, eq_tot);
+            const bool take = lv && (key > thr || (key == thr && eq_rank < need));
+            const int pos = written + wg_prefix_count_n<NW>(take, wave_tot, tid, sel_tot);
+            if (take) sel[pos] = jb;
+            written += sel_tot;
+            eq_seen += eq_tot;
+        }
+        __syncthreads();
+    }
+}
+
+// The whole list of a sparse pair, ascending: initial blocks, the top-k, the local blocks, then -1 (sel: nullptr when every
+// block up to the query's is kept).
+__device__ inline void write_list(const Forced &fo, const int *sel, int32_t *out, int topk_total, int nt) {
+    const int n_loc = fo.n_forced - fo.f_init;
+    for (int i = threadIdx.x; i < topk_total; i += nt) {
+        int val = -1;
+        if (sel == nullptr) val = i < fo.nblk ? i : -1;
+        else if (i < fo.f_init) val = i;
+        else if (i < fo.f_init + fo.kr) val = sel[i - fo.f_init];
+        else if (i < fo.f_init + fo.kr + n_loc) val = fo.forced_block(i - fo.kr);
+        out[i] = val;
+    }
+}
+
+// The selection as a kernel of its own, one workgroup per pair (see DecLayout::picked).
+__global__ void __launch_bounds__(AW * 64) dec_pick_kernel(DecArgs a) {
+    __shared__ int sel[kSelMax], hist[4][256], wave_tot[AW], s_k;
+    __shared__ uint32_t s_prefix;
+    const int pair = blockIdx.x, L = a.ctx[pair / a.hkv];
+    const Forced fo(a.tk, L);
+    int32_t *out = a.idx + (int64_t)pair * a.tk.topk_total;
+    if (L < a.tk.dense_below) {
+        for (int i = threadIdx.x; i < a.tk.topk_total; i += AW * 64) out[i] = -1;
+    } else if (fo.kr == fo.n_rest) {
+        write_list(fo, nullptr, out, a.tk.topk_total, AW * 64);
+    } else {
+        if (fo.kr > 0) pick_blocks<AW>(a, pair, fo, sel, hist, wave_tot, &s_prefix, &s_k);
+        write_list(fo, sel, out, a.tk.topk_total, AW * 64);
+    }
+}
+
 // NW waves (= blocks) per workgroup: 8 when the launch has at most one workgroup per CU anyway, 4 when it has more
 // (64 KB of V tiles instead of 128: two workgroups share a CU and one's selection overlaps the other's loads).
-template <int NW>
+// PICKED: dec_pick_kernel has written the lists to a.idx; otherwise every workgroup selects for itself.
+template <int NW, bool PICKED>
 __global__ void __launch_bounds__(NW * 64) dec_attn2_kernel(DecArgs a) {
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];     // NW V tiles of 16 KB, one per wave
     __shared__ float wm[NW][16], wl[NW][16];
@@ -728,186 +906,28 @@ __global__ void __launch_bounds__(NW * 64) dec_attn2_kernel(DecArgs a) {
     const int split = blockIdx.x, pair = blockIdx.y;
     const int b = pair / a.hkv;
     const int L = a.ctx[b];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, w = tid >> 6;
     const Forced fo(a.tk, L);
     const bool dense = L < a.tk.dense_below;
-    int32_t *out = a.idx != nullptr ? a.idx + (int64_t)pair * a.tk.topk_total : nullptr;
+    int32_t *list = a.idx != nullptr ? a.idx + (int64_t)pair * a.tk.topk_total : nullptr;
+    int32_t *out = !PICKED && split == 0 ? list : nullptr;       // this workgroup writes the pair's list
     int j = -1;
     const int e = w < a.bpw ? split * a.bpw + w : 1 << 30;       // (waves past bpw attend to nothing)
     if (dense) {
         j = e <= fo.bt ? e : -1;
-        if (out != nullptr && split == 0)
+        if (out != nullptr)
             for (int i = tid; i < a.tk.topk_total; i += NT) out[i] = -1;
     } else if (fo.kr == fo.n_rest) {
         // everything up to the query's block is kept: the blocks between the initial and the local ones
         j = e < fo.kr ? fo.f_init + e : -1;
-        if (out != nullptr && split == 0)
-            for (int i = tid; i < a.tk.topk_total; i += NT) out[i] = i < fo.nblk ? i : -1;
-    } else {
-        if (split * a.bpw >= fo.kr && !(out != nullptr && split == 0)) {
-            j = -1;                                        // nothing for this workgroup: an empty partial
-        } else if (fo.nblk <= kPkLds) {
-            // ---- radix select (4 x 8 bits) of the kr-th largest pooled key among the live blocks; selection rule
-            // and tie order as in the prefill: keys above it, then the first `need` keys equal to it by block number.
-            // A thread keeps `per` consecutive blocks' keys in registers (one trip to memory, no copy in LDS); every
-            // wave reduces the histogram of a pass by itself (data-parallel scan, no LDS round trips), so a pass costs
-            // one barrier.
-            constexpr int KPT = kPkLds / NT;
-            const uint32_t *pk = a.pk + (int64_t)pair * a.pk_cap;
-            const int per = (fo.nblk + NT - 1) / NT, jb0 = tid * per;
-            uint32_t kreg[KPT];
-            uint32_t live = 0u;                              // bit u: block jb0 + u exists and takes part in the top-k
-#pragma unroll
-            for (int u = 0; u < KPT; ++u) {
-                const int jb = jb0 + u;
-                const bool lv = u < per && jb < fo.nblk && !fo.is_forced(jb);
-                kreg[u] = lv ? pk[jb] : 0u;
-                live |= lv ? 1u << u : 0u;
-            }
-            for (int i = tid; i < 4 * 256; i += NT) (&hist[0][0])[i] = 0;
-            __syncthreads();
-            uint32_t prefix = 0u;
-            int k = fo.kr;
-            for (int pass = 3; pass >= 0; --pass) {
-                const int hi_shift = 8 * (pass + 1);
-#pragma unroll
-                for (int u = 0; u < KPT; ++u)
-                    if (((live >> u) & 1u) && (pass == 3 || (kreg[u] >> hi_shift) == prefix))
-                        atomicAdd(&hist[pass][(kreg[u] >> (8 * pass)) & 255u], 1);
-                __syncthreads();
-                // lane l owns digits 255 - 4l .. 252 - 4l, largest first; above = number of keys with a larger digit
-                int c[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) c[u] = hist[pass][255 - 4 * lane - u];
-                const int mine = c[0] + c[1] + c[2] + c[3];
-                int above = wave_inclusive_sum(mine) - mine;
-                int digit = 0, knew = 0;
-                bool found = false;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (above < k && k <= above + c[u]) {
-                        found = true;
-                        digit = 255 - 4 * lane - u;
-                        knew = k - above;
-                    }
-                    above += c[u];
-                }
-                const int src = max(__ffsll((long long)__ballot(found)) - 1, 0);     // exactly one lane (kr >= 1 keys exist)
-                prefix = (prefix << 8) | (uint32_t)__builtin_amdgcn_readlane(digit, src);
-                k = __builtin_amdgcn_readlane(knew, src);
-            }
-            const uint32_t thr = prefix;                     // the kr-th largest key; `need` of the keys equal to it are taken
-            const int need = k;
-            // emission in ascending block order: one prefix count over the threads for (keys above, keys equal)
-            int ca = 0, cb = 0;
-#pragma unroll
-            for (int u = 0; u < KPT; ++u) {
-                const bool lv = ((live >> u) & 1u) != 0u;
-                ca += lv && kreg[u] > thr ? 1 : 0;
-                cb += lv && kreg[u] == thr ? 1 : 0;
-            }
-            const int packed = ca | (cb << 16);
-            const int incl = wave_inclusive_sum(packed);
-            if (lane == 63) wave_tot[w] = incl;
-            __syncthreads();
-            int before = incl - packed;
-#pragma unroll
-            for (int q = 0; q < NW; ++q) before += q < w ? wave_tot[q] : 0;
-            int eq_before = before >> 16;
-            int pos = (before & 0xffff) + min(eq_before, need);
-#pragma unroll
-            for (int u = 0; u < KPT; ++u) {
-                if (!((live >> u) & 1u)) continue;
-                bool take = kreg[u] > thr;
-                if (kreg[u] == thr) {
-                    take = eq_before < need;
-                    ++eq_before;
-                }
-                if (take) sel[pos++] = jb0 + u;
-            }
-            __syncthreads();
-            j = e < fo.kr ? sel[e] : -1;
-            if (out != nullptr && split == 0) {
-                // the whole list, ascending: initial blocks, the top-k, the local blocks, then -1
-                const int n_loc = fo.n_forced - fo.f_init;
-                for (int i = tid; i < a.tk.topk_total; i += NT) {
-                    int val = -1;
-                    if (i < fo.f_init) val = i;
-                    else if (i < fo.f_init + fo.kr) val = sel[i - fo.f_init];
-                    else if (i < fo.f_init + fo.kr + n_loc) val = fo.forced_block(i - fo.kr);
-                    out[i] = val;
-                }
-            }
-            __syncthreads();                             // the V tiles may overwrite the selection's state now
-        } else {
-            // the same for rows too long for the registers: every pass re-reads the pooled keys from memory
-            const uint32_t *pk = a.pk + (int64_t)pair * a.pk_cap;
-            for (int i = tid; i < 4 * 256; i += NT) (&hist[0][0])[i] = 0;
-            if (tid == 0) { s_prefix = 0u; s_k = fo.kr; }
-            __syncthreads();
-            for (int pass = 3; pass >= 0; --pass) {
-                const uint32_t prefix = s_prefix;
-                const int hi_shift = 8 * (pass + 1);
-                for (int jb = tid; jb < fo.nblk; jb += NT) {
-                    if (fo.is_forced(jb)) continue;
-                    const uint32_t key = pk[jb];
-                    if (pass == 3 || (key >> hi_shift) == prefix) atomicAdd(&hist[pass][(key >> (8 * pass)) & 255u], 1);
-                }
-                __syncthreads();
-                if (w == 0) {
-                    // lane l owns digits 4l .. 4l+3; above = number of keys with a larger digit
-                    const int k = s_k;
-                    int c[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) c[u] = hist[pass][4 * lane + u];
-                    const int mine = c[0] + c[1] + c[2] + c[3];
-                    int run = mine;                          // inclusive suffix sum over lanes
-#pragma unroll
-                    for (int o = 1; o < 64; o <<= 1) {
-                        const int other = __shfl_down(run, o);
-                        if (lane + o < 64) run += other;
-                    }
-                    int above = run - mine;
-#pragma unroll
-                    for (int u = 3; u >= 0; --u) {
-                        if (above < k && k <= above + c[u]) {
-                            s_prefix = (prefix << 8) | (uint32_t)(4 * lane + u);
-                            s_k = k - above;
-                        }
-                        above += c[u];
-                    }
-                }
-                __syncthreads();
-            }
-            const uint32_t thr = s_prefix;               // the kr-th largest key; `need` of the keys equal to it are taken
-            const int need = s_k;
-            int written = 0, eq_seen = 0;
-            for (int base = 0; base < fo.nblk; base += NT) {
-                const int jb = base + tid;
-                const bool lv = jb < fo.nblk && !fo.is_forced(jb);
-                const uint32_t key = lv ? pk[jb] : 0u;
-                int eq_tot, sel_tot;
-                const int eq_rank = eq_seen + wg_prefix_count_n<NW>(lv && key == thr, wave_tot, tid, eq_tot);
-                const bool take = lv && (key > thr || (key == thr && eq_rank < need));
-                const int pos = written + wg_prefix_count_n<NW>(take, wave_tot, tid, sel_tot);
-                if (take) sel[pos] = jb;
-                written += sel_tot;
-                eq_seen += eq_tot;
-            }
-            __syncthreads();
-            j = e < fo.kr ? sel[e] : -1;
-            if (out != nullptr && split == 0) {
-                const int n_loc = fo.n_forced - fo.f_init;
-                for (int i = tid; i < a.tk.topk_total; i += NT) {
-                    int val = -1;
-                    if (i < fo.f_init) val = i;
-                    else if (i < fo.f_init + fo.kr) val = sel[i - fo.f_init];
-                    else if (i < fo.f_init + fo.kr + n_loc) val = fo.forced_block(i - fo.kr);
-                    out[i] = val;
-                }
-            }
-            __syncthreads();                             // the V tiles may overwrite the selection's state now
-        }
+        if (out != nullptr) write_list(fo, nullptr, out, a.tk.topk_total, NT);
+    } else if (PICKED) {
+        j = e < fo.kr ? list[fo.f_init + e] : -1;
+    } else if (split * a.bpw < fo.kr || out != nullptr) {         // (otherwise nothing here: an empty partial)
+        if (fo.kr > 0) pick_blocks<NW>(a, pair, fo, sel, hist, wave_tot, &s_prefix, &s_k);
+        j = e < fo.kr ? sel[e] : -1;
+        if (out != nullptr) write_list(fo, sel, out, a.tk.topk_total, NT);
+        __syncthreads();                                         // the V tiles may overwrite the selection's state now
     }
     if (j > fo.bt) j = -1;
     attend_partial<NW>(a, pair, L, a.fsplit + split, j, smem, wm, wl);
@@ -980,6 +1000,7 @@ struct DecLayout {
     bool staged;
     int aw;                     // waves per attend workgroup
     int bpw;                    // blocks per attend workgroup (<= aw)
+    bool picked;                // the selection runs as a kernel of its own in front of the attend kernel
     int fsplit, nslot, pk_cap;
     size_t off_pk;
 };
@@ -1016,6 +1037,10 @@ DecLayout dec_layout(const infllmv2_params *p, int batch, int max_ctx, int dense
             d.bpw = (entries + ns - 1) / ns;
         }
     }
+    // Once an attend workgroup is one of several on its CU, selecting again in each of a pair's dozen workgroups costs more
+    // than a launch: batch 128 (256 pairs x 14) attend 124 -> 96 us for a 6.4 us kernel; batch 20 (40 x 14) 61 -> 58.6 us a
+    // step.  With at most one workgroup per CU the launch would cost more than it saves (selection there: ~4 us).
+    d.picked = d.staged && d.aw != AW;
     d.fsplit = d.staged ? (p->n_init + p->n_local + FW - 1) / FW : 0;
     d.nslot = d.fsplit + d.nsplit;
     d.pk_cap = (int)align_up((size_t)(max_ctx + kBlock - 1) / kBlock + 4, 4);
@@ -1097,20 +1122,19 @@ int launch_decode_mfma(const infllmv2_params *p, const void *q, const void *k, c
     if (d.staged) {
         // Larger-than-default dynamic LDS has to be enabled per kernel; the same fixed limit is set on every call,
         // so nothing has to be remembered between calls.
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(dec_attn2_kernel<AW>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(dec_attn2_kernel<AW / 2>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds / 2) != hipSuccess)
+        const auto attn = d.picked ? dec_attn2_kernel<AW / 2, true> : d.aw == AW ? dec_attn2_kernel<AW, false> : dec_attn2_kernel<AW / 2, false>;
+        const size_t lds = attn_lds / (AW / d.aw);
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(attn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+            hipSuccess)
             return INFLLMV2_ERR_HIP;
-        a.idx = idx_out;                     // written by the attend kernel only when the caller wants the list
+        // written by the attend kernel only when the caller wants the list; by the pick kernel always
+        a.idx = idx_out || !d.picked ? idx_out : (int32_t *)(base + d.off_idx);
         const int groups = ((max_ctx + kBlock - 1) / kBlock + PB - 1) / PB;
         hipLaunchKernelGGL(dec_front_kernel, dim3(d.nchunk + d.fsplit, pairs), dim3(256),
                            (size_t)FW * TILE_ELEMS * sizeof(uint16_t), stream, a);
         hipLaunchKernelGGL(dec_pool_kernel, dim3(groups, pairs), dim3(256), 0, stream, a);
-        if (d.aw == AW)
-            hipLaunchKernelGGL(dec_attn2_kernel<AW>, dim3(d.nsplit, pairs), dim3(AW * 64), attn_lds, stream, a);
-        else
-            hipLaunchKernelGGL(dec_attn2_kernel<AW / 2>, dim3(d.nsplit, pairs), dim3(AW * 32), attn_lds / 2, stream, a);
+        if (d.picked) hipLaunchKernelGGL(dec_pick_kernel, dim3(pairs), dim3(AW * 64), 0, stream, a);
+        hipLaunchKernelGGL(attn, dim3(d.nsplit, pairs), dim3(d.aw * 64), lds, stream, a);
         hipLaunchKernelGGL(dec_merge_kernel, dim3(pairs), dim3(kMergeThreads), 0, stream, a);
         return hip_status(hipGetLastError());
     }
