@@ -225,7 +225,8 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
         const int words = (len + 31) / 32, n = chunk / 64;
         const uint32_t *row = a.sel_bits + (int64_t)h * a.sel_words + sel_base(a.map, seq) + (int64_t)j * words + (c0 >> 5);
         const int wd = (lane * n) >> 5;
-        const uint32_t word = wd < ((c1 - c0 + 31) >> 5) ? row[wd] : 0u;
+        // (words of tokens in front of the block are not written)
+        const uint32_t word = wd < ((c1 - c0 + 31) >> 5) && c0 + 32 * wd >= j * kBlock ? row[wd] : 0u;
         const uint32_t bits = (word >> ((lane * n) & 31)) & ((1u << n) - 1u);
         const int cnt = __popc(bits);
         int incl = cnt;                                        // inclusive prefix
