@@ -298,7 +298,8 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
     }
 }
 
-__global__ void __launch_bounds__(256) bwd_zero_kernel(float4 *p, int64_t n4) {
+__global__ void __launch_bounds__(256) bwd_zero_kernel(float4 *dk, float4 *dv, int64_t n4) {
+    float4 *p = blockIdx.y ? dv : dk;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256)
         p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
@@ -315,10 +316,8 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     if (ws == nullptr || L.ws_bytes < (size_t)rows * a.hq * sizeof(float)) return INFLLMV2_ERR_WORKSPACE_TOO_SMALL;
     a.delta = (float *)ws;
     const int64_t n4 = rows * hkv * D / 4;
-    hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 4096)), dim3(256), 0, L.stream,
-                       (float4 *)a.dk, n4);
-    hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 4096)), dim3(256), 0, L.stream,
-                       (float4 *)a.dv, n4);
+    hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 4096), 2), dim3(256), 0, L.stream,
+                       (float4 *)a.dk, (float4 *)a.dv, n4);
     hipLaunchKernelGGL((bwd_delta_kernel<T, D>), dim3((unsigned)((rows * a.hq + 3) / 4)), dim3(256), 0, L.stream, a);
     // at most this many tiles (every sequence may end with a partial one)
     const int tokens = tile_tokens(L.map, a.hq / hkv);
