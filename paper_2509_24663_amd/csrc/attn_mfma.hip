@@ -172,7 +172,7 @@ struct TileKernel {
         const uint32_t full = ntok >= 32 ? 0xffffffffu : ((1u << ntok) - 1u);
 
         // ---- union of the tile's block lists: masks[j] has bit ti set if token ti selected block j.  The tile's
-        // own block is the largest one any of its tokens selects, and every token selects it: it is the last entry.
+        // own block, if any of its tokens selected it (lists may leave it out), is the last entry.
         int ni;                                          // number of barrier intervals
         if (!dense) {
             for (int j = tid; j < nblk; j += NTHR) masks[j] = 0u;
@@ -210,7 +210,8 @@ struct TileKernel {
         }
         // Interval i -> its blocks and consumer masks (unused slot: block NONE, mask 0).  With SLOTS == 2 an
         // interval covers two consecutive entries of the union, so that a SIMD usually has two or more units to
-        // overlap between one pair of barriers; the tile's own block (the last entry) is alone in the last interval.
+        // overlap between one pair of barriers; the last entry (where the tile's own block is, if listed) is alone in the
+        // last interval.
         const int ne = dense ? nblk : __builtin_amdgcn_readfirstlane(s_ne);
         // (packed into two words -- block numbers and consumer masks in 16 bits each -- because the record of the next
         // interval waits in vector registers while a unit runs)
@@ -252,7 +253,7 @@ struct TileKernel {
         // copies K and V^T pieces w, w + NW, ... of every block.  A piece's source is a wave-uniform base (sequence, head,
         // block, piece: scalar arithmetic) plus a per-lane byte offset that never changes, except that the sequence's
         // last, partial K block re-reads its last valid row (finite data, always masked by causality); that block can
-        // only be the tile's own, which is alone in the last interval.  The V^T copy is zero-padded instead.
+        // only be the tile's own and so only be in the last interval.  The V^T copy is zero-padded instead.
         //
         // A wave's instructions issue in order, so whatever a wave with a unit in the current interval spends on the
         // next interval's copies -- address arithmetic included -- delays that unit, and the interval lasts as long as
@@ -265,7 +266,6 @@ struct TileKernel {
         constexpr uint32_t kTileBytes = TILE_ELEMS * 2, kStageBytes = STAGE_ELEMS * 2, kPieceStep = NW * 1024u;
         const uint32_t blk_bytes = (uint32_t)a.map.kv_tok_stride * (uint32_t)(kBlock * sizeof(uint16_t));   // < 2^31: the stride is < 2^24
         const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(stages));
-        const int own_rows = len - bt * kBlock;          // rows of the tile's own block that exist (1..64 counts)
         uint32_t off_k_w[KOFF];
 #pragma unroll
         for (int u = 0; u < KOFF; ++u) {
@@ -310,20 +310,21 @@ struct TileKernel {
                 }
             }
         };
-        // the last interval: the tile's own block alone, possibly the sequence's partial last block
-        auto issue_last = [&](int buf) {
+        // the last interval: block j alone, possibly the tile's own and then possibly the sequence's partial last block
+        auto issue_last = [&](uint32_t j, int buf) {
 #ifdef ATTN_TIMING_NO_LOADS
             if (!timing_fill) return;
 #endif
             const uint32_t dst = lds_w + (uint32_t)buf * (SLOTS * kStageBytes);
+            const int last_row = len - (int)j * kBlock - 1;          // (63 and more: the block is whole)
 #pragma unroll
             for (int u = 0; u < PPW; ++u) {
                 int row, chunk;
                 piece_src(w + u * NW, lane, row, chunk);
-                const uint32_t off = (uint32_t)(min(row, own_rows - 1) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
-                async_copy16(reinterpret_cast<const char *>(kb) + (uint64_t)bt * blk_bytes, off, dst + u * kPieceStep);
-                if (BWD) async_copy16(reinterpret_cast<const char *>(vtb) + (uint64_t)bt * blk_bytes, off, dst + kTileBytes + u * kPieceStep);
-                else async_copy16(vtb_w + ((uint32_t)bt << 14) + u * kPieceStep, off_v_w, dst + kTileBytes + u * kPieceStep);
+                const uint32_t off = (uint32_t)(min(row, last_row) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
+                async_copy16(reinterpret_cast<const char *>(kb) + (uint64_t)j * blk_bytes, off, dst + u * kPieceStep);
+                if (BWD) async_copy16(reinterpret_cast<const char *>(vtb) + (uint64_t)j * blk_bytes, off, dst + kTileBytes + u * kPieceStep);
+                else async_copy16(vtb_w + (j << 14) + u * kPieceStep, off_v_w, dst + kTileBytes + u * kPieceStep);
             }
         };
         int2 r_cur = ni > 0 ? interval(0) : make_int2(0, 0);
@@ -334,7 +335,7 @@ struct TileKernel {
         for (int b2 = 0; b2 < 2; ++b2) issue(0u, b2);
         timing_fill = false;
 #endif
-        if (ni == 1) issue_last(0);
+        if (ni == 1) issue_last((uint32_t)__builtin_amdgcn_readfirstlane(r_cur.x) & 0xffffu, 0);
         else if (ni > 1) issue((uint32_t)__builtin_amdgcn_readfirstlane(r_cur.x), 0);
 
         // ---- this wave's token
@@ -383,7 +384,7 @@ struct TileKernel {
         __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
         __syncthreads();
         auto step = [&](auto own, int i) {
-            constexpr bool OWN = decltype(own)::value;
+            constexpr bool OWN = decltype(own)::value;       // the last interval (a block before the own one: nothing is masked)
             const int j0 = __builtin_amdgcn_readfirstlane(r_cur.x) & 0xffff;
             const uint32_t mks = (uint32_t)__builtin_amdgcn_readfirstlane(r_cur.y);
             const uint32_t mk0 = mks & 0xffffu, mk1 = SLOTS == 2 ? mks >> 16 : 0u;
@@ -398,7 +399,7 @@ struct TileKernel {
             int mode = i + 1 >= ni ? 0 : i + 2 == ni ? 1 : 2;
             const uint32_t jj_next = (uint32_t)__builtin_amdgcn_readfirstlane(r_next.x);
             auto issue_now = [&]() {
-                if (mode == 1) issue_last((i + 1) & 1);
+                if (mode == 1) issue_last(jj_next & 0xffffu, (i + 1) & 1);
                 if (mode == 2) issue(jj_next, (i + 1) & 1);
                 mode = 0;
             };
