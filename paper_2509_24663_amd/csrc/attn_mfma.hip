@@ -77,16 +77,12 @@ struct TileKernel {
         else k_piece_src(q, lane, row, chunk);
     }
 
-    // which of the CU's four SIMDs this wave runs on (hardware id register, bits 5:4)
-    __device__ static inline int simd_id() { return (int)__builtin_amdgcn_s_getreg(4 | (4 << 6) | (1 << 11)); }
-
     __device__ static void run(const AttnArgs &a, int num_tiles) {
         extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
         uint16_t *stages = smem;
         uint32_t *masks = reinterpret_cast<uint32_t *>(smem + NSTAGE * STAGE_ELEMS);
         int2 *rec = reinterpret_cast<int2 *>(masks + a.nb_cap);          // union list: (block, token mask) per entry
         __shared__ int s_seq, s_tile, s_blk0, s_ne, s_ni;
-        __shared__ uint32_t s_simd_waves[4];                             // waves (= tokens) resident on each SIMD
 #ifdef ATTN_TIMING_CLOCK
         __shared__ uint32_t s_busy_ticks[2][NW];                         // per interval parity: each wave's ticks from the
                                                                          // barrier to its arrival at the next one
@@ -119,10 +115,8 @@ struct TileKernel {
             s_seq = s;
             s_tile = rem;
             s_blk0 = blk0;
-            for (int i = 0; i < 4; ++i) s_simd_waves[i] = 0u;
         }
         __syncthreads();
-        if (SLOTS == 2 && lane == 0) atomicOr(&s_simd_waves[simd_id()], 1u << w);     // read after later barriers
         const int seq = __builtin_amdgcn_readfirstlane(s_seq);
         if (seq >= a.map.batch) return;
         const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;
@@ -167,7 +161,7 @@ struct TileKernel {
             __syncthreads();
             ni = __builtin_amdgcn_readfirstlane(s_ni);
             if (SLOTS == 2) {
-                pair_entries<NW>(rec, __builtin_amdgcn_readfirstlane(s_ne) - 1, w, lane, s_simd_waves);
+                pair_entries<NW>(rec, __builtin_amdgcn_readfirstlane(s_ne) - 1, w, lane);
                 __syncthreads();
             }
         } else {

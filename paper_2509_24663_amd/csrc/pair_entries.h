@@ -10,10 +10,12 @@ namespace ifv2 {
 // sized range of entries and repeatedly joins its first remaining entry to the one that raises the pair's
 // busiest SIMD the least.  Partners stay a few entries apart, so the walk remains nearly ascending
 // (neighbouring tiles then touch the same blocks at about the same time, which the L2 likes).
-// rec: (block, token mask) per entry; body: entries in front of the last one; simd_waves[s]: bit w set if wave w runs on
-// SIMD s.  Whatever that table says, every entry stays in the list exactly once.
+// Waves w, w + 4, w + 8, ... are taken to share a SIMD: that is how a workgroup's waves are dealt out (checked for 4, 8 and 16
+// waves on idle and full chips).  The hardware's own record of it is not asked, because the order of a token's blocks, and
+// with it the last bits of its result, must not depend on where the waves happened to run.
+// rec: (block, token mask) per entry; body: entries in front of the last one.
 template <int NW>
-__device__ inline void pair_entries(int2 *rec, int body, int w, int lane, const uint32_t *simd_waves) {
+__device__ inline void pair_entries(int2 *rec, int body, int w, int lane) {
     const int pairs = body / 2;
     const int lo = 2 * (pairs * w / NW), hi = 2 * (pairs * (w + 1) / NW);
     const int n = hi - lo;
@@ -22,7 +24,7 @@ __device__ inline void pair_entries(int2 *rec, int body, int w, int lane, const 
     const int2 r = live ? rec[lo + lane] : make_int2(0, 0);
     uint32_t loads = 0u;                                // consumers per SIMD, one byte each
 #pragma unroll
-    for (int sd = 0; sd < 4; ++sd) loads |= (uint32_t)__popc((uint32_t)r.y & simd_waves[sd]) << (8 * sd);
+    for (int sd = 0; sd < 4; ++sd) loads |= (uint32_t)__popc((uint32_t)r.y & (0x1111u << sd)) << (8 * sd);
     auto max_byte = [](uint32_t x) -> int {
         return (int)max(max(x & 0xffu, (x >> 8) & 0xffu), max((x >> 16) & 0xffu, x >> 24));
     };
@@ -32,8 +34,8 @@ __device__ inline void pair_entries(int2 *rec, int body, int w, int lane, const 
         const int first = __ffsll((long long)__ballot(live)) - 1;
         const uint32_t lf = (uint32_t)__builtin_amdgcn_readlane((int)loads, first);
         if (lane == first) { rec[pos] = r; live = false; }
-        // second: the live entry whose company costs the least beyond what it would cost alone (0 .. NW: at most what the
-        // first one costs; n is even, so there is one)
+        // second: the live entry whose company costs the least beyond what it would cost alone (at most what the first one
+        // costs; n is even, so there is one)
         const int extra = max_byte(lf + loads) - own_max;
         uint64_t least = 0u;
         for (int c = 0; c <= NW && least == 0u; ++c) least = __ballot(live && extra == c);

@@ -1,5 +1,5 @@
 """The pairing of a tile's union list (csrc/pair_entries.h), compiled for the host with a wavefront of 64 threads that meet at
-every ballot and lane read: the list keeps every entry exactly once, wherever the hardware puts the waves."""
+every ballot and lane read: the list keeps every entry exactly once, in an order that follows from the list alone."""
 import ctypes
 import os
 import subprocess
@@ -35,20 +35,20 @@ static int __builtin_amdgcn_readlane(int v, int l) { put((uint32_t)v); const int
 static int __ffsll(long long x) { return __builtin_ffsll(x); }
 static int __popc(uint32_t x) { return __builtin_popcount(x); }
 #include "pair_entries.h"
-template <int NW> static void run(int2 *rec, int body, const uint32_t *simd_waves) {
+template <int NW> static void run(int2 *rec, int body) {
     pthread_barrier_init(&meet, nullptr, 64);
     for (int w = 0; w < NW; ++w) {
         std::vector<std::thread> lanes;
         for (int l = 0; l < 64; ++l)
-            lanes.emplace_back([=] { self = l; ifv2::pair_entries<NW>(rec, body, w, l, simd_waves); });
+            lanes.emplace_back([=] { self = l; ifv2::pair_entries<NW>(rec, body, w, l); });
         for (auto &t : lanes) t.join();
     }
     pthread_barrier_destroy(&meet);
 }
-extern "C" void pair(int nw, int *rec, int body, const uint32_t *simd_waves) {
-    if (nw == 4) run<4>((int2 *)rec, body, simd_waves);
-    else if (nw == 8) run<8>((int2 *)rec, body, simd_waves);
-    else run<16>((int2 *)rec, body, simd_waves);
+extern "C" void pair(int nw, int *rec, int body) {
+    if (nw == 4) run<4>((int2 *)rec, body);
+    else if (nw == 8) run<8>((int2 *)rec, body);
+    else run<16>((int2 *)rec, body);
 }
 """
 
@@ -61,29 +61,44 @@ def pair(tmp_path_factory):
                            os.path.join(ROOT, "paper_2509_24663_amd", "csrc"), "-o", str(d / "h.so"), str(d / "harness.cpp")])
     lib = ctypes.CDLL(str(d / "h.so"))
 
-    def call(nw, masks, simd_of_wave):
+    def call(nw, masks):
         """The list (block numbers 0 ..) after the pairing; the last entry is not part of it."""
-        table = np.zeros(4, np.uint32)
-        for w, sd in enumerate(simd_of_wave):
-            table[sd] |= np.uint32(1 << w)
         rec = np.stack([np.arange(len(masks)), masks], 1).astype(np.int32)
-        lib.pair(nw, rec.ctypes.data_as(ctypes.c_void_p), len(masks) - 1, table.ctypes.data_as(ctypes.c_void_p))
+        lib.pair(nw, rec.ctypes.data_as(ctypes.c_void_p), len(masks) - 1)
         return rec
     return call
 
 
-PLACEMENTS = {4: [[0, 1, 2, 3], [0, 0, 1, 2], [3, 3, 3, 3]],
-              8: [[0, 1, 2, 3] * 2, [0, 0, 0, 1, 1, 2, 2, 3], [2] * 8],
-              16: [[0, 1, 3, 2] * 4, [0] * 6 + [1] * 4 + [2] * 4 + [3] * 2, [1] * 16]}
+def _paired(nw, masks):
+    """The rule in plain words: inside each wave's range the first entry left is joined to the one that adds the least to what
+    it costs alone; an entry costs as many units as its busiest SIMD has, waves w, w + 4, ... sharing one."""
+    loads = np.array([[bin(int(mk) & (0x1111 << sd) & 0xffff).count("1") for sd in range(4)] for mk in masks])
+    order = list(range(len(masks)))
+    pairs = (len(masks) - 1) // 2
+    for w in range(nw):
+        lo, hi = 2 * (pairs * w // nw), 2 * (pairs * (w + 1) // nw)
+        if 4 <= hi - lo <= 64:
+            left, out = list(range(lo, hi)), []
+            while left:
+                first = left.pop(0)
+                second = min(left, key=lambda e: ((loads[first] + loads[e]).max() - loads[e].max(), e))
+                left.remove(second)
+                out += [first, second]
+            order[lo:hi] = out
+    return order
 
 
 @pytest.mark.parametrize("nw", [4, 8, 16])
-def test_every_entry_stays_in_the_list_once(pair, nw):
+def test_every_entry_once_in_the_order_of_the_rule(pair, nw):
     rng = np.random.default_rng(nw)
     full = (1 << nw) - 1
-    for n in (1, 2, nw * 4, nw * 4 + 1, nw * 5 + 2):
-        for masks in (np.full(n, full), rng.integers(1, full + 1, n)):
-            for simd_of_wave in PLACEMENTS[nw]:
-                rec = pair(nw, masks, simd_of_wave)
-                assert sorted(rec[:, 0].tolist()) == list(range(n)), (n, simd_of_wave, rec[:, 0].tolist())
-                assert rec[-1, 0] == n - 1 and (rec[:, 1] == masks[rec[:, 0]]).all()
+    for n in (1, 2, nw * 4, nw * 4 + 1, nw * 5 + 2, nw * 13 + 1):
+        for masks in (np.full(n, full), rng.integers(1, full + 1, n), 1 << rng.integers(0, nw, n)):
+            rec = pair(nw, masks)
+            assert sorted(rec[:, 0].tolist()) == list(range(n)) and (rec[:, 1] == masks[rec[:, 0]]).all()
+            assert rec[:, 0].tolist() == _paired(nw, masks), n
+
+
+def test_no_kernel_asks_where_its_waves_run():
+    csrc = os.path.join(ROOT, "paper_2509_24663_amd", "csrc")
+    assert [f for f in sorted(os.listdir(csrc)) if "s_getreg" in open(os.path.join(csrc, f)).read()] == []
