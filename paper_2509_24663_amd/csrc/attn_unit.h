@@ -462,6 +462,15 @@ __device__ inline bf16x8 bwd_kt_frag(uint32_t tb, int dt, int h) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// an operand of the K^T products with the keys the token does not see taken as 0 (their dZ is 0, but 0 times an infinity in
+// their K rows would not be): keys 0 .. last of the lane's eight are visible
+__device__ inline bf16x8 visible_keys(bf16x8 f, int last) {
+    u32x4 x = __builtin_bit_cast(u32x4, f);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = last > 2 * i ? x[i] : last == 2 * i ? x[i] & 0xffffu : 0u;
+    return __builtin_bit_cast(bf16x8, x);
+}
+
 struct TokBwd {
     bf16x8 qf[4], gf[4];   // Q_t and dO_t as second operands: head = lane % 16, dims ks*32 + (lane/16)*8 ..
     f32x4 o[8];            // dQ_t^T / scale: dim tile dt, dims dt*16 + 4*(lane/16) + r, head = lane % 16
@@ -515,6 +524,11 @@ __device__ inline void unit_bwd(TokBwd &t, uint32_t stage, uint32_t rx, uint32_t
 #pragma unroll
         for (int dt = 0; dt < 8; dt += 2) {
             const int n = 24 * h + 16 + dt;
+            if (OWN) {
+                const int last = key_limit - 32 * h - 8 * (lane >> 4);
+                f[n % W] = visible_keys(f[n % W], last);
+                f[(n + 1) % W] = visible_keys(f[(n + 1) % W], last);
+            }
             t.o[dt + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(n + 1) % W], __builtin_bit_cast(bf16x8, zb), t.o[dt + 1], 0, 0, 0);
             t.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[n % W], __builtin_bit_cast(bf16x8, zb), t.o[dt], 0, 0, 0);
             if (n + W < 48) {
