@@ -114,8 +114,7 @@ __device__ inline void pair_step(State &acc, const bf16x8 (&kf)[2][8], const bf1
         return __builtin_bit_cast(bf16x8, r);
     };
     // Seeds: element e is row 8 (e / 4) + 4 kg + e % 4 of the 32 (token, head) rows.  Minus lse / scale and minus Delta of
-    // its token and head, so that the products come out subtracted; a key the token does not see (yet: the token then lies
-    // in the block itself) gets minus infinity, i.e. probability 0.
+    // its token and head, so that the products come out subtracted.
     const uint32_t sa = buf + 2 * kTokBytes + (uint32_t)(kg * 16);
     auto seed = [&](int which) -> f32x16 {
         typedef __attribute__((address_space(3))) const f32x4 lds_f4;
@@ -128,11 +127,16 @@ __device__ inline void pair_step(State &acc, const bf16x8 (&kf)[2][8], const bf1
         }
         return r;
     };
-    auto hide = [&](f32x16 &x, int key) {
+    // A key the token does not see (yet: the token then lies in the block itself) gets probability 0 and dP 0.  In the
+    // finished products: a seed of minus infinity would not hide a key whose row holds infinities.
+    auto hide = [&](f32x16 &x, f32x16 &y, int key) {
         if (!diag) return;                                 // (uniform)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            if (key > (e < 8 ? t0 : t1)) x[e] = -INFINITY;
+            if (key > (e < 8 ? t0 : t1)) {
+                x[e] = -INFINITY;
+                y[e] = 0.f;
+            }
     };
     f32x16 s[2], dp[2];
     u32x4 pw[2][2], zw[2][2];       // [half][token]: eight bf16
@@ -154,7 +158,6 @@ __device__ inline void pair_step(State &acc, const bf16x8 (&kf)[2][8], const bf1
     dp[0] = seed(1);
 #pragma unroll
     for (int i = 0; i < W1 - 1; ++i) fetch1(i);
-    hide(s[0], key0);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int kt = i >> 3, ks = i & 7;
@@ -164,13 +167,13 @@ __device__ inline void pair_step(State &acc, const bf16x8 (&kf)[2][8], const bf1
             s[1] = seed(0);
             dp[1] = seed(1);
         }
-        if (i == 8) hide(s[1], key0 + 32);
         s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[i % W1], kf[kt][ks], s[kt], 0, 0, 0);
         dp[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga[i % W1], vf[kt][ks], dp[kt], 0, 0, 0);
         if (i < 8) {
             copy(2 * i);
             copy(2 * i + 1);
         }
+        if (i == 8) hide(s[0], dp[0], key0);
         if (kt == 1) {
             uint32_t p, z;
             prob_pair(s[0], dp[0], 2 * ks, c, p, z);
@@ -186,6 +189,7 @@ __device__ inline void pair_step(State &acc, const bf16x8 (&kf)[2][8], const bf1
         if (i + W2 - 1 < 16) fetch2(i + W2 - 1);
         accumulate(acc.v[kt][dt], pw[kt][a], gb[i % W2]);
         accumulate(acc.k[kt][dt], zw[kt][a], qb[i % W2]);
+        if (i == 0) hide(s[1], dp[1], key0 + 32);
         if (kt == 0) {
             uint32_t p, z;
             prob_pair(s[1], dp[1], 2 * i, c, p, z);
@@ -286,9 +290,8 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
         const uint32_t voff = (uint32_t)((lane >> 4) * 256 + (((lane & 15) ^ swz(lane >> 4)) << 4));
         auto entry = [&](int i) -> int { return (int)s_list[min(i, total - 1)]; };
         auto uniform = [&](int x) -> int { return c0 + __builtin_amdgcn_readfirstlane(x); };
-        // requests a sixteenth of the rows of the pair (ta, tb) into a buffer.  An odd last token's partner is a token of
-        // zeros (the copies repeat the last token and are overwritten): its probabilities are 1 and its rows are 0, which
-        // adds nothing.
+        // requests a sixteenth of the rows of the pair (ta, tb) into a buffer.  An odd last token's partner is a token that
+        // sees no key, with rows of zeros (the copies repeat the last token and are overwritten).
         auto copy_share = [&](int ta, int tb, uint32_t buf, int x) {
             const int64_t row = (int64_t)(tok0 + (x & 8 ? tb : ta)) * a.hq + h * G;
             const uint16_t *src = (x & 4 ? a.dout : a.q) + row * D;
@@ -319,16 +322,15 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
             lb = entry(2 * pn + 3);
             __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);           // this pair's rows (and, at first, K and V) are there
             asm volatile("" ::: "memory");
-            if (2 * pi + 1 == total) {
+            const bool odd = 2 * pi + 1 == total;
+            if (odd) {
                 typedef __attribute__((address_space(3))) u32x4 lds_u4;
-                typedef __attribute__((address_space(3))) float lds_fw;
 #pragma unroll
                 for (int x = 0; x < 8; ++x) *(lds_u4 *)(uintptr_t)(cur + kTokBytes + x * 1024u + (uint32_t)lane * 16u) = (u32x4)0u;
-                if (lane >= 32) *(lds_fw *)(uintptr_t)(cur + 2 * kTokBytes + (uint32_t)lane * 4u) = 0.f;
                 asm volatile("" ::: "memory");
             }
             // (the other buffer's last readers were the products of the previous step)
-            pair_step(acc, kf, vf, cur, lane, c, key0, ta, tb, ta < j * kBlock + kBlock - 1, [&](int x) {
+            pair_step(acc, kf, vf, cur, lane, c, key0, ta, odd ? -1 : tb, odd || ta < j * kBlock + kBlock - 1, [&](int x) {
                 if (pn < pairs) copy_share(na, nbt, nxt, x);
             });
             asm volatile("" ::: "memory");
