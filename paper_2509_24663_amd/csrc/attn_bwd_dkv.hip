@@ -374,7 +374,7 @@ int launch_bwd_dkv(const BwdM &a, int32_t max_len, hipStream_t stream) {
     while (chunk > 64 && a.nblocks * ((max_len + chunk - 1) / chunk) * a.map.num_kv_heads < 4096) chunk /= 2;
     const int groups = (max_len + chunk - 1) / chunk * a.map.num_kv_heads;
     const int64_t wgs = 8ll * ((groups + 7) / 8) * a.nblocks;
-    if (wgs > 0x7fffffff) return INFLLMV2_ERR_UNSUPPORTED;
+    if (wgs > 0xffffffffll / 64) return INFLLMV2_ERR_UNSUPPORTED;       // (a launch has fewer than 2^32 threads in x)
     hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3((unsigned)wgs), dim3(64), 0, stream, a, chunk, groups);
     return hip_status(hipGetLastError());
 }
