@@ -871,7 +871,7 @@ __device__ inline void write_list(const Forced &fo, const int *sel, int32_t *out
     }
 }
 
-// The selection as a kernel of its own, one workgroup per pair (see DecLayout::picked).
+// The selection as a kernel of its own, one workgroup per pair (see DecLayout::aw).
 __global__ void __launch_bounds__(AW * 64) dec_pick_kernel(DecArgs a) {
     __shared__ int sel[kSelMax], hist[4][256], wave_tot[AW], s_k;
     __shared__ uint32_t s_prefix;
@@ -888,11 +888,12 @@ __global__ void __launch_bounds__(AW * 64) dec_pick_kernel(DecArgs a) {
     }
 }
 
-// NW waves (= blocks) per workgroup: 8 when the launch has at most one workgroup per CU anyway, 4 when it has more
-// (64 KB of V tiles instead of 128: two workgroups share a CU and one's selection overlaps the other's loads).
-// PICKED: dec_pick_kernel has written the lists to a.idx; otherwise every workgroup selects for itself.
-template <int NW, bool PICKED>
+// NW waves (= blocks) per workgroup: 8 when the launch has at most one workgroup per CU anyway, and every workgroup then
+// selects for itself; 4 when it has more (64 KB of V tiles instead of 128, so that two workgroups share a CU), behind
+// dec_pick_kernel, which has written the lists to a.idx.
+template <int NW>
 __global__ void __launch_bounds__(NW * 64) dec_attn2_kernel(DecArgs a) {
+    constexpr bool PICKED = NW < AW;
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];     // NW V tiles of 16 KB, one per wave
     __shared__ float wm[NW][16], wl[NW][16];
     __shared__ int wave_tot[NW];
@@ -901,7 +902,7 @@ __global__ void __launch_bounds__(NW * 64) dec_attn2_kernel(DecArgs a) {
     // the selection's state lives in the V tiles' memory: it is dead before the first tile is requested
     int *sel = reinterpret_cast<int *>(smem);                // [kSelMax] the top-k blocks (without the forced ones), ascending
     int(*hist)[256] = reinterpret_cast<int(*)[256]>(sel + kSelMax);     // [4][256]
-    static_assert((kSelMax + 4 * 256) * 4 <= NW * TILE_ELEMS * 2, "selection state must fit in the V tiles");
+    static_assert(PICKED || (kSelMax + 4 * 256) * 4 <= NW * TILE_ELEMS * 2, "selection state must fit in the V tiles");
     constexpr int NT = NW * 64;
     const int split = blockIdx.x, pair = blockIdx.y;
     const int b = pair / a.hkv;
@@ -998,9 +999,8 @@ struct DecLayout {
     size_t off_part, off_idx, off_opart, off_ml, total;
     // three-stage form
     bool staged;
-    int aw;                     // waves per attend workgroup
+    int aw;                     // waves per attend workgroup: AW, or AW / 2 behind a selection kernel
     int bpw;                    // blocks per attend workgroup (<= aw)
-    bool picked;                // the selection runs as a kernel of its own in front of the attend kernel
     int fsplit, nslot, pk_cap;
     size_t off_pk;
 };
@@ -1022,7 +1022,11 @@ DecLayout dec_layout(const infllmv2_params *p, int batch, int max_ctx, int dense
     // the three-stage form; a dense sequence attends to all its blocks there either way
     const int listed = d.staged ? p->topk_total - p->n_init - p->n_local : p->topk_total;
     const int entries = listed > dense_blocks ? listed : dense_blocks;
-    // three-stage form: four blocks per workgroup once eight would give more than one workgroup per CU
+    // three-stage form: four blocks per workgroup once eight would give more than one workgroup per CU.
+    // The selection is then a kernel of its own: with several attend workgroups on a CU, selecting again in each of a
+    // pair's dozen workgroups costs more than a launch: batch 128 (256 pairs x 14) attend 124 -> 96 us for a 6.4 us
+    // kernel; batch 20 (40 x 14) 61 -> 58.6 us a step.  With at most one workgroup per CU the launch would cost more
+    // than it saves (selection there: ~4 us).
     d.aw = d.staged && pairs * (size_t)((entries + AW - 1) / AW) > 256 ? AW / 2 : AW;
     d.nsplit = (entries + d.aw - 1) / d.aw;
     if (d.nsplit < 1) d.nsplit = 1;
@@ -1037,10 +1041,6 @@ DecLayout dec_layout(const infllmv2_params *p, int batch, int max_ctx, int dense
             d.bpw = (entries + ns - 1) / ns;
         }
     }
-    // Once an attend workgroup is one of several on its CU, selecting again in each of a pair's dozen workgroups costs more
-    // than a launch: batch 128 (256 pairs x 14) attend 124 -> 96 us for a 6.4 us kernel; batch 20 (40 x 14) 61 -> 58.6 us a
-    // step.  With at most one workgroup per CU the launch would cost more than it saves (selection there: ~4 us).
-    d.picked = d.staged && d.aw != AW;
     d.fsplit = d.staged ? (p->n_init + p->n_local + FW - 1) / FW : 0;
     d.nslot = d.fsplit + d.nsplit;
     d.pk_cap = (int)align_up((size_t)(max_ctx + kBlock - 1) / kBlock + 4, 4);
@@ -1122,18 +1122,19 @@ int launch_decode_mfma(const infllmv2_params *p, const void *q, const void *k, c
     if (d.staged) {
         // Larger-than-default dynamic LDS has to be enabled per kernel; the same fixed limit is set on every call,
         // so nothing has to be remembered between calls.
-        const auto attn = d.picked ? dec_attn2_kernel<AW / 2, true> : d.aw == AW ? dec_attn2_kernel<AW, false> : dec_attn2_kernel<AW / 2, false>;
+        const bool picked = d.aw != AW;
+        const auto attn = picked ? dec_attn2_kernel<AW / 2> : dec_attn2_kernel<AW>;
         const size_t lds = attn_lds / (AW / d.aw);
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(attn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
             hipSuccess)
             return INFLLMV2_ERR_HIP;
         // written by the attend kernel only when the caller wants the list; by the pick kernel always
-        a.idx = idx_out || !d.picked ? idx_out : (int32_t *)(base + d.off_idx);
+        a.idx = idx_out || !picked ? idx_out : (int32_t *)(base + d.off_idx);
         const int groups = ((max_ctx + kBlock - 1) / kBlock + PB - 1) / PB;
         hipLaunchKernelGGL(dec_front_kernel, dim3(d.nchunk + d.fsplit, pairs), dim3(256),
                            (size_t)FW * TILE_ELEMS * sizeof(uint16_t), stream, a);
         hipLaunchKernelGGL(dec_pool_kernel, dim3(groups, pairs), dim3(256), 0, stream, a);
-        if (d.picked) hipLaunchKernelGGL(dec_pick_kernel, dim3(pairs), dim3(AW * 64), 0, stream, a);
+        if (picked) hipLaunchKernelGGL(dec_pick_kernel, dim3(pairs), dim3(AW * 64), 0, stream, a);
         hipLaunchKernelGGL(attn, dim3(d.nsplit, pairs), dim3(d.aw * 64), lds, stream, a);
         hipLaunchKernelGGL(dec_merge_kernel, dim3(pairs), dim3(kMergeThreads), 0, stream, a);
         return hip_status(hipGetLastError());
