@@ -5,7 +5,7 @@ import pytest
 
 import synth
 from helpers import assert_out_close, to_dev, to_np
-from test_gpu_parity import _params, _run_prefill_case, m  # noqa: F401
+from test_gpu_parity import _check_backward, _params, _run_prefill_case, m  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -25,3 +25,13 @@ def test_small_tiles(m, oracle, lens, threshold):  # noqa: F811
     pos = np.unique(np.concatenate([np.arange(0, b - a, 13), [b - a - 1]])).astype(np.int32)
     O, _ = oracle.dense_attn(w["q"][a + pos, :16], pos, w["k"][0, a:b], w["v"][0, a:b], op)
     assert_out_close(to_np(out)[a + pos, :16], O, "bf16", "dense")
+
+
+@pytest.mark.parametrize("n,topk", [(1009, 32), (1024, 12), (2039, 20), (2048, 40)])
+def test_union_lists_long_enough_to_be_paired(m, oracle, n, topk):  # noqa: F811
+    """One KV head, where the small tiles reach 1024 (4 tokens) and 2048 (8): a wavefront then has at least four list entries
+    to pair.  Budgets that every token shares in full, and that neighbouring tokens fill differently."""
+    w = synth.make_prefill(n, 16, 1, 128, seed=1300 + n, dtype="bf16")
+    gp, op = _params(m, oracle, "bf16", 16, 1, 128, n_init=1, n_local=2, topk_total=topk)
+    _run_prefill_case(m, oracle, w, gp, op, "bf16")
+    _check_backward(m, oracle, w, gp, op, "bf16")
