@@ -1,9 +1,24 @@
-// What the kernels of the matrix-core backward (attn_bwd_mfma.hip, attn_bwd_dkv.hip) share.
+// What the files of the backward share: attn_bwd.hip (any shape), attn_bwd_mfma.hip and attn_bwd_dkv.hip (matrix-core path).
 #pragma once
 #include "common.h"
 
 namespace ifv2 {
 
+// is block j in the ascending, -1 padded list e[0 .. n)?
+__device__ inline bool list_has(const int32_t *e, int n, int j) {
+    int lo = 0, hi = n;                      // first position whose entry is >= j (padding counts as +inf)
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        const int x = e[mid];
+        if (x >= 0 && x < j) lo = mid + 1; else hi = mid;
+    }
+    return lo < n && e[lo] == j;
+}
+
+// dk[0 .. n) = dv[0 .. n) = 0 by one launch (attn_bwd_mfma.hip); n % 4 == 0, both 16-byte aligned
+void launch_bwd_zero(float *dk, float *dv, int64_t n, hipStream_t stream);
+
+// the matrix-core path's arguments
 struct BwdM {
     const uint16_t *q, *k, *v, *out, *dout;
     const float *lse;

@@ -19,8 +19,7 @@
 //           the last bits of dK and dV, can differ from run to run).
 // Measured, bf16, 1985 tokens, 8 heads on 2, d 128, 16 blocks: dq 1681 -> 86 us, dkv 5636 -> 107 us (vector arithmetic
 // before; with its atomic adds as the accumulators lie in registers instead of through LDS dkv took 490 us).
-#include <algorithm>
-
+#include "attn_bwd.h"
 #include "gen_unit.h"
 
 namespace ifv2 {
@@ -155,17 +154,6 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
     }
 }
 
-// is block j in the ascending, -1 padded list e[0 .. n)?
-__device__ inline bool list_has(const int32_t *e, int n, int j) {
-    int lo = 0, hi = n;                      // first position whose entry is >= j (padding counts as +inf)
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const int x = e[mid];
-        if (x >= 0 && x < j) lo = mid + 1; else hi = mid;
-    }
-    return lo < n && e[lo] == j;
-}
-
 template <typename T, int D>
 __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chunk) {
     constexpr int N = D / 16;
@@ -298,12 +286,6 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
     }
 }
 
-__global__ void __launch_bounds__(256) bwd_zero_kernel(float4 *dk, float4 *dv, int64_t n4) {
-    float4 *p = blockIdx.y ? dv : dk;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256)
-        p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-
 template <typename T, int D>
 int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     const int64_t rows = L.map.total_rows;
@@ -315,9 +297,7 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     void *ws = L.ws;         // <dO, O> per (row, head)
     if (ws == nullptr || L.ws_bytes < (size_t)rows * a.hq * sizeof(float)) return INFLLMV2_ERR_WORKSPACE_TOO_SMALL;
     a.delta = (float *)ws;
-    const int64_t n4 = rows * hkv * D / 4;
-    hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 4096), 2), dim3(256), 0, L.stream,
-                       (float4 *)a.dk, (float4 *)a.dv, n4);
+    launch_bwd_zero(a.dk, a.dv, rows * hkv * D, L.stream);
     hipLaunchKernelGGL((bwd_delta_kernel<T, D>), dim3((unsigned)((rows * a.hq + 3) / 4)), dim3(256), 0, L.stream, a);
     // at most this many tiles (every sequence may end with a partial one)
     const int tokens = tile_tokens(L.map, a.hq / hkv);

@@ -22,7 +22,7 @@
 // this one replaced (four wavefronts of 16 keys, two tokens per barrier) took 6.2 ms with the order of chunks above.  Four
 // wavefronts sharing a block and adding up in LDS: 5.4 ms; without the copies 3.7 ms; all rows L2 hits 4.6 ms; copies
 // spread over the products instead of early: 5.8 ms; chunks of 512 / 256 tokens: 5.1 / 5.3 ms.
-#include "attn_bwd_mfma.h"
+#include "attn_bwd.h"
 #include "attn_unit.h"
 
 namespace ifv2 {
@@ -60,17 +60,6 @@ __device__ inline int swz(int n) { return 4 * (n & 3) + (n >> 2); }
 // 4 bytes per lane, global -> LDS (lane l's word at lds + 4 l)
 __device__ inline void async_copy4(const float *src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
-}
-
-// is block j in the ascending, -1 padded list e[0 .. n)?
-__device__ inline bool list_has(const int32_t *e, int n, int j) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const int x = e[mid];
-        if (x >= 0 && x < j) lo = mid + 1; else hi = mid;
-    }
-    return lo < n && e[lo] == j;
 }
 
 // elements e and e + 1 of a half's 16: probabilities and dZ, packed.  s holds (q k - lse / scale) and dp holds (dO v - Delta)

@@ -13,7 +13,7 @@
 // transposed copy of K staged through registers.
 #include <algorithm>
 
-#include "attn_bwd_mfma.h"
+#include "attn_bwd.h"
 
 namespace ifv2 {
 
@@ -82,13 +82,18 @@ __global__ void __launch_bounds__(256) bwd_sel_bits_kernel(BwdM a) {
             rows[(int64_t)(i / BITS_WORDS) * words + (i & (BITS_WORDS - 1))] = bits[i];
 }
 
-__global__ void __launch_bounds__(256) bwd_fill_zero_kernel(float4 *p0, float4 *p1, int64_t n4) {
-    float4 *p = blockIdx.y ? p1 : p0;
+__global__ void __launch_bounds__(256) bwd_zero_kernel(float4 *dk, float4 *dv, int64_t n4) {
+    float4 *p = blockIdx.y ? dv : dk;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256)
         p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 }  // namespace
+
+void launch_bwd_zero(float *dk, float *dv, int64_t n, hipStream_t stream) {
+    const unsigned groups = (unsigned)std::min<int64_t>((n / 4 + 255) / 256, 8192);
+    hipLaunchKernelGGL(bwd_zero_kernel, dim3(groups, 2), dim3(256), 0, stream, (float4 *)dk, (float4 *)dv, n / 4);
+}
 
 bool bwd_mfma_params(const infllmv2_params *p) {
     return p->dtype == INFLLMV2_BF16 && p->head_dim == D && p->num_q_heads / p->num_kv_heads == G;
@@ -156,9 +161,7 @@ int launch_attn_bwd_mfma(const Launch &L, const void *q, const void *k, const vo
     a.dq = (uint16_t *)dq;
     a.dk = dk;
     a.dv = dv;
-    const int64_t n4 = rows * hkv * D / 4;
-    const unsigned zg = (unsigned)std::min<int64_t>((n4 + 255) / 256, 8192);
-    hipLaunchKernelGGL(bwd_fill_zero_kernel, dim3(zg, 2), dim3(256), 0, L.stream, (float4 *)dk, (float4 *)dv, n4);
+    launch_bwd_zero(dk, dv, rows * hkv * D, L.stream);
     if (use_bits) {
         const size_t lds = (size_t)((L.max_len + kBlock - 1) / kBlock) * BITS_WORDS * sizeof(uint32_t);     // <= 128 KB
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(bwd_sel_bits_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -34,7 +34,7 @@
 // ATTN_TIMING_DROP_PRIVATE=C leaves the union entries with at most C consumers out of the walk (what do they cost?).
 #include <type_traits>
 
-#include "attn_bwd_mfma.h"
+#include "attn_bwd.h"
 #include "attn_unit.h"
 #include "pair_entries.h"
 
@@ -589,7 +589,7 @@ int launch_attn_mfma(const Launch &L, const void *q, const void *k, const void *
     return rc;
 }
 
-// dQ of the backward (declared in attn_bwd_mfma.h)
+// dQ of the backward (declared in attn_bwd.h)
 int launch_bwd_dq(const Launch &L, const BwdM &b, const int32_t *cu_h) {
     AttnArgs a{};
     a.q = b.q;
