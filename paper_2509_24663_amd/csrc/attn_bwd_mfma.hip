@@ -122,8 +122,9 @@ int launch_attn_bwd_mfma(const Launch &L, const void *q, const void *k, const vo
     for (int s = 0; s < L.map.batch; ++s) nblocks += (cu_h[s + 1] - cu_h[s] + kBlock - 1) / kBlock;
     const int hkv = p->num_kv_heads, hq = p->num_q_heads;
     if (nblocks > 65535 || hkv > 65535 || rows > 0x7fffffff / 4) return INFLLMV2_ERR_UNSUPPORTED;
-    // (the tile kernel's limits; longer sequences and strides past them take the vector path)
-    if (L.max_len > 262144 || L.map.kv_tok_stride >= (1 << 24)) return INFLLMV2_ERR_UNSUPPORTED;
+    // What follows is for sequences whose bitmap rows fit LDS and for token strides of which three, in bytes, fit 32 bits (a
+    // card holds 500 tokens of the others); the rest takes the generic kernels.
+    if (L.max_len > 262144 || L.map.kv_tok_stride >= (1 << 28)) return INFLLMV2_ERR_UNSUPPORTED;
     const size_t b_f = align256((size_t)rows * hq * sizeof(float));
     // selection bitmap (block-major): only when block lists exist and it stays moderate (it grows with len^2 / 2048
     // bytes per sequence and KV head: 32 MB at 128K tokens); otherwise the dK/dV kernel searches the lists

@@ -61,8 +61,9 @@ struct AttnArgs {
 };
 
 // NW waves with one token each, SLOTS union entries per barrier interval.  BWD: the backward's dQ for the same tiles and
-// walk: the second tile of a stage is the block's V rows instead of V^T, and the unit is unit_bwd.
-template <int NW, int SLOTS, bool BWD = false>
+// walk: the second tile of a stage is the block's V rows instead of V^T, and the unit is unit_bwd.  WIDE: byte distances of
+// a block in 64 bits, for token strides from 2^24 elements on (see kWideStride).
+template <int NW, int SLOTS, bool BWD = false, bool WIDE = false>
 struct TileKernel {
     static constexpr int T = NW;
     static constexpr int NTHR = NW * 64;
@@ -71,6 +72,7 @@ struct TileKernel {
     static constexpr int NONE = 0xffff;            // no block (block numbers are kept in 16 bits)
     static_assert(16 % NW == 0, "sixteen one-KB pieces per tile are dealt round-robin to the waves");
     static_assert(SLOTS == 1 || SLOTS == 2, "one or two entries per interval");
+    static_assert(!WIDE || (BWD && NW == 16), "built for the backward only");
 
     __device__ static inline void piece_src(int q, int lane, int &row, int &chunk) {
         if (BWD) bwd_piece_src(q, lane, row, chunk);
@@ -223,19 +225,20 @@ struct TileKernel {
         static_assert(NW == 16 || NW == 8 || NW == 4, "pieces 2 NW (K) and NW (V^T) apart have the same swizzle");
         constexpr int KOFF = NW == 4 ? 2 : 1;
         constexpr uint32_t kTileBytes = TILE_ELEMS * 2, kStageBytes = STAGE_ELEMS * 2, kPieceStep = NW * 1024u;
-        const uint32_t blk_bytes = (uint32_t)a.map.kv_tok_stride * (uint32_t)(kBlock * sizeof(uint16_t));   // < 2^31: the stride is < 2^24
+        typedef typename std::conditional<WIDE, uint64_t, uint32_t>::type Step;
+        const Step blk_bytes = (Step)a.map.kv_tok_stride * (Step)(kBlock * sizeof(uint16_t));   // (32 bits: < 2^31, the stride is < 2^24)
         const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(stages));
         uint32_t off_k_w[KOFF];
 #pragma unroll
         for (int u = 0; u < KOFF; ++u) {
             int row, chunk;
             piece_src(w + u * NW, lane, row, chunk);
-            off_k_w[u] = (uint32_t)((row - 4 * (w + u * NW)) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
+            off_k_w[u] = (uint32_t)((row - 4 * (w + u * NW)) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;     // (rows 0 .. 3)
         }
         const uint32_t off_v_w = vt_piece_src_bytes(w, lane) - (uint32_t)w * 1024u;
-        const uint32_t k_step = blk_bytes / PPW;          // K bytes between a wave's pieces of a block
-        const char *kb_w = reinterpret_cast<const char *>(kb) + (uint64_t)w * (blk_bytes / 16u);
-        const char *vtb_w = reinterpret_cast<const char *>(vtb) + (BWD ? (uint64_t)w * (blk_bytes / 16u) : (uint64_t)w * 1024u);
+        const Step k_step = blk_bytes / PPW;              // K bytes between a wave's pieces of a block
+        const char *kb_w = reinterpret_cast<const char *>(kb) + (uint64_t)w * (blk_bytes / 16);
+        const char *vtb_w = reinterpret_cast<const char *>(vtb) + (BWD ? (uint64_t)w * (blk_bytes / 16) : (uint64_t)w * 1024u);
         auto copy_v = [&](uint32_t j, int u, uint32_t dst) {
             if (BWD) async_copy16(vtb_w + (uint64_t)j * blk_bytes + u * k_step, off_k_w[u % KOFF], dst);
             else async_copy16(vtb_w + (j << 14) + u * kPieceStep, off_v_w, dst);
@@ -280,9 +283,12 @@ struct TileKernel {
             for (int u = 0; u < PPW; ++u) {
                 int row, chunk;
                 piece_src(w + u * NW, lane, row, chunk);
-                const uint32_t off = (uint32_t)(min(row, last_row) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
-                async_copy16(reinterpret_cast<const char *>(kb) + (uint64_t)j * blk_bytes, off, dst + u * kPieceStep);
-                if (BWD) async_copy16(reinterpret_cast<const char *>(vtb) + (uint64_t)j * blk_bytes, off, dst + kTileBytes + u * kPieceStep);
+                // (WIDE: rows counted from the piece's first, so that a lane's offset fits 32 bits)
+                const int first = WIDE ? min(4 * (w + u * NW), last_row) : 0;
+                const uint32_t off = (uint32_t)((min(row, last_row) - first) * (int)a.map.kv_tok_stride + chunk * 8) * 2u;
+                const uint64_t at = (uint64_t)j * blk_bytes + (uint64_t)first * (blk_bytes / kBlock);
+                async_copy16(reinterpret_cast<const char *>(kb) + at, off, dst + u * kPieceStep);
+                if (BWD) async_copy16(reinterpret_cast<const char *>(vtb) + at, off, dst + kTileBytes + u * kPieceStep);
                 else async_copy16(vtb_w + (j << 14) + u * kPieceStep, off_v_w, dst + kTileBytes + u * kPieceStep);
             }
         };
@@ -487,12 +493,12 @@ template <int NW, int SLOTS>
 __global__ void __launch_bounds__(NW * 64) attn_tile_kernel(AttnArgs a, int num_tiles) {
     TileKernel<NW, SLOTS>::run(a, num_tiles);
 }
-template <int NW, int SLOTS>
+template <int NW, int SLOTS, bool WIDE>
 __global__ void __launch_bounds__(NW * 64) bwd_dq_mfma_kernel(AttnArgs a, int num_tiles) {
-    TileKernel<NW, SLOTS, true>::run(a, num_tiles);
+    TileKernel<NW, SLOTS, true, WIDE>::run(a, num_tiles);
 }
 
-template <int NW, int SLOTS, bool BWD = false>
+template <int NW, int SLOTS, bool BWD = false, bool WIDE = false>
 int launch_tile(const Launch &L, const AttnArgs &a0, const int32_t *cu_h) {
     constexpr int T = NW;
     AttnArgs a = a0;
@@ -507,7 +513,9 @@ int launch_tile(const Launch &L, const AttnArgs &a0, const int32_t *cu_h) {
                        (size_t)a.nb_cap * 4 + (size_t)a.list_cap * 8;
     if (lds > 160 * 1024 - 256 || nb_max >= 0xffff) return INFLLMV2_ERR_UNSUPPORTED;     // does not fit: the caller pairs nothing
     if (SLOTS == 2 && a.list_cap / 2 + 1 > NW * 64) return INFLLMV2_ERR_UNSUPPORTED;      // one thread packs one interval record
-    auto kern = BWD ? bwd_dq_mfma_kernel<NW, SLOTS> : attn_tile_kernel<NW, SLOTS>;
+    void (*kern)(AttnArgs, int);
+    if constexpr (BWD) kern = bwd_dq_mfma_kernel<NW, SLOTS, WIDE>;
+    else kern = attn_tile_kernel<NW, SLOTS>;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -517,6 +525,10 @@ int launch_tile(const Launch &L, const AttnArgs &a0, const int32_t *cu_h) {
     hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, L.stream, a, (int)tiles);
     return hip_status(hipGetLastError());
 }
+
+// Token strides from here on (elements) put a block's rows more than 2^31 bytes apart, which the 32-bit distances cannot hold.
+// The forward leaves them to the generic kernels; dQ has an instance for them.
+constexpr int64_t kWideStride = 1 << 24;
 
 template <bool BWD>
 int launch_tiles(const Launch &L, const AttnArgs &a, const int32_t *cu_h) {
@@ -533,6 +545,11 @@ int launch_tiles(const Launch &L, const AttnArgs &a, const int32_t *cu_h) {
         tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
     }
     int rc = INFLLMV2_ERR_UNSUPPORTED;
+    if constexpr (BWD)
+        if (L.map.kv_tok_stride >= kWideStride) {
+            rc = launch_tile<16, 2, true, true>(L, a, cu_h);
+            return rc == INFLLMV2_ERR_UNSUPPORTED ? launch_tile<16, 1, true, true>(L, a, cu_h) : rc;
+        }
     if (tiles4 <= most) rc = launch_tile<4, 2, BWD>(L, a, cu_h);
     else if (tiles8 <= most) rc = launch_tile<8, 2, BWD>(L, a, cu_h);
     if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 2, BWD>(L, a, cu_h);
@@ -557,7 +574,7 @@ int launch_attn_mfma(const Launch &L, const void *q, const void *k, const void *
     // 16-byte vector loads need 8-element aligned strides
     if (L.map.kv_tok_stride % 8 != 0 || L.map.kv_head_stride % 8 != 0) return INFLLMV2_ERR_UNSUPPORTED;
     // per-lane load offsets inside one block are kept in 32 bits
-    if (L.map.kv_tok_stride <= 0 || L.map.kv_tok_stride >= (1 << 24)) return INFLLMV2_ERR_UNSUPPORTED;
+    if (L.map.kv_tok_stride <= 0 || L.map.kv_tok_stride >= kWideStride) return INFLLMV2_ERR_UNSUPPORTED;
     AttnArgs a;
     a.q = (const uint16_t *)q;
     a.k = (const uint16_t *)k;

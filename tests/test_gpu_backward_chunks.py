@@ -44,3 +44,23 @@ def test_dq_with_one_entry_per_interval(m, oracle):  # noqa: F811
     rows_d = torch.from_numpy(rows).cuda()
     dQ, _, _ = oracle.attn_bwd(w["q"][rows], rows.astype(np.int32), w["k"][0], w["v"][0], idx[0, rows], to_np(dout[rows_d]), op)
     assert np.abs(to_np(dq[rows_d]) - dQ).max() <= 2e-2 * max(np.abs(dQ).max(), 0.1)
+
+
+@pytest.mark.parametrize("dense", [True, False])
+def test_token_strides_past_32_bits_per_block(m, oracle, dense):  # noqa: F811
+    """K and V rows 2^24 elements apart (a block then spans 2^31 bytes), a partial last block: the same gradients as from
+    contiguous rows, up to the order of fp32 additions and, in dQ, one step of its bf16 rounding."""
+    n, S = 333, 1 << 24
+    w = synth.make_prefill(n, 32, 2, 128, seed=720, dtype="bf16")
+    gp, _ = _params(m, oracle, "bf16", 32, 2, 128, n_init=1, n_local=1, topk_total=3)
+    q, k, v = (to_dev(w[x], "bf16") for x in ("q", "k", "v"))
+    buf = torch.empty(n * S, dtype=torch.bfloat16, device="cuda")
+    kw, vw = (buf.as_strided(k.shape, (128, S, 1), at).copy_(x) for x, at in ((k, 0), (v, 4096)))
+    idx = None if dense else m.sparse_prefill(gp, q, k, v, [0, n])["block_idx"]
+    out, lse = m.dense_attn_fwd(gp, q, k, v, [0, n]) if dense else m.sparse_attn_fwd(gp, q, k, v, idx, [0, n])
+    dout = torch.randn(q.shape, generator=torch.Generator("cuda").manual_seed(5), device="cuda").bfloat16()
+    want = m.sparse_attn_bwd(gp, q, k, v, idx, out, lse, dout, [0, n])
+    got = m.sparse_attn_bwd(gp, q, kw, vw, idx, out, lse, dout, [0, n])
+    for name, a, b, rtol in zip(("dq", "dk", "dv"), got, want, (2.0 ** -7, 0.0, 0.0)):
+        a, b = to_np(a), to_np(b)
+        assert (np.abs(a - b) <= rtol * np.abs(b) + 1e-5 * np.abs(b).max()).all(), name
