@@ -214,13 +214,12 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
     // ---- tokens of the chunk that selected the block, in token order
     int total = 0;
     if (!dense && a.sel_bits != nullptr) {
-        // from the selection bitmap: lane l expands the chunk's bits [l n, (l + 1) n), n = chunk / 64
-        const int words = (len + 31) / 32, n = chunk / 64;
-        const uint32_t *row = a.sel_bits + (int64_t)h * a.sel_words + sel_base(a.map, seq) + (int64_t)j * words + (c0 >> 5);
-        const int wd = (lane * n) >> 5;
+        // from the selection bitmap: lane l expands the chunk's bits [l n, (l + 1) n), n = chunk / 64 (at least 1)
+        const int words = (len + 31) / 32, n = max(chunk / 64, 1), first = c0 + lane * n;
+        const uint32_t *row = a.sel_bits + (int64_t)h * a.sel_words + sel_base(a.map, seq) + (int64_t)j * words;
         // (words of tokens in front of the block are not written)
-        const uint32_t word = wd < ((c1 - c0 + 31) >> 5) && c0 + 32 * wd >= j * kBlock ? row[wd] : 0u;
-        const uint32_t bits = (word >> ((lane * n) & 31)) & ((1u << n) - 1u);
+        const uint32_t word = first < c1 && (first & ~31) >= j * kBlock ? row[first >> 5] : 0u;
+        const uint32_t bits = (word >> (first & 31)) & ((1u << n) - 1u);
         const int cnt = __popc(bits);
         int incl = cnt;                                        // inclusive prefix
 #pragma unroll
@@ -358,9 +357,15 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
 }  // namespace
 
 int launch_bwd_dkv(const BwdM &a, int32_t max_len, hipStream_t stream) {
-    // Tokens per workgroup: 1024, fewer while that leaves SIMDs without work (half of the pairs of a causal sequence are empty)
+    // Tokens per workgroup: 1024, fewer while that leaves SIMDs without work (half of the pairs of a causal sequence are empty).
+    // A workgroup takes 2 us per pair of tokens, so with little to share out the longest list is the time: 500 tokens on 2 KV
+    // heads, whole training step, 509 us with chunks of 1024, 299 with 256, 135 with 64; 8000 tokens 2.30 / 2.02 / 2.10 ms.
+    // Every chunk of a block adds to the same rows, so the last halving pays only while there are few of them: 64 tokens
+    // 104 -> 75 us, 1000 tokens 177 -> 170, but 1300 tokens 239 -> 248.
     int chunk = MAX_CHUNK;
-    while (chunk > 64 && a.nblocks * ((max_len + chunk - 1) / chunk) * a.map.num_kv_heads < 4096) chunk /= 2;
+    auto workgroups = [&](int c) { return a.nblocks * ((max_len + c - 1) / c) * a.map.num_kv_heads; };
+    while (chunk > 64 && workgroups(chunk) < 4096) chunk /= 2;
+    if (chunk == 64 && max_len <= 1024 && workgroups(chunk) < 4096) chunk = 32;
     const int groups = (max_len + chunk - 1) / chunk * a.map.num_kv_heads;
     const int64_t wgs = 8ll * ((groups + 7) / 8) * a.nblocks;
     if (wgs > 0xffffffffll / 64) return INFLLMV2_ERR_UNSUPPORTED;       // (a launch has fewer than 2^32 threads in x)
