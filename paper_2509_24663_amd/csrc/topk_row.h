@@ -124,11 +124,26 @@ __device__ inline void topk_row(const float *srow, int t, const TopkArgs &a, int
                 keys[c] = dead ? 0u : __float_as_uint(m);
             }
         }
+    } else if (NCH > 0 && NCH <= 4 && MODE == TOPK_POOLED) {
+        // short rows: all loads first, addresses clamped into the row (entry bt always exists); undefined, forced and
+        // out-of-range entries are masked afterwards
+        float x[NCH > 0 ? NCH : 1];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) x[c] = srow[min(c * 64 + lane, bt)];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int j = c * 64 + lane;
+            const bool dead = j >= nblk || j < f_init || j >= f_lo || !(max(a.pool_stride * j - a.pool_pad, 0) < v);
+            keys[c] = dead ? 0u : __float_as_uint(x[c]);
+        }
     } else if (NCH > 0 && MODE == TOPK_POOLED) {
         // Live are the blocks [f_init, j_end): not forced and with a visible key in their window.  The row is read through a
         // buffer descriptor that ends at j_end, so everything from there on (past the row, too) arrives as 0 without an
         // address or a mask being computed for it; the initial blocks are masked in the chunks that hold any.
-        const int j_end = v > 0 ? (int)min((int64_t)f_lo, ((int64_t)v + a.pool_pad + a.pool_stride - 1) / a.pool_stride) : 0;
+        // (nearly always all up to f_lo, which takes no division; v + pad < 2^32)
+        int j_end = f_lo;
+        if (max((int64_t)a.pool_stride * (f_lo - 1) - a.pool_pad, (int64_t)0) >= v)
+            j_end = v > 0 ? (int)(((uint32_t)v + (uint32_t)a.pool_pad - 1u) / (uint32_t)a.pool_stride + 1u) : 0;
         const __amdgpu_buffer_rsrc_t row =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(srow), 0, j_end * (int)sizeof(float), 0x00020000);
 #pragma unroll

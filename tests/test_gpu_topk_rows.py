@@ -19,7 +19,7 @@ def _expected(row, pos, p):
 
 
 @pytest.mark.parametrize("blocks,n_init,topk,pad,cmp", [
-    (300, 1, 64, 0, (32, 16)), (512, 0, 20, 1, (32, 16)), (700, 70, 140, 0, (32, 16)), (1024, 2, 96, 0, (64, 16)),
+    (70, 1, 9, 0, (32, 16)), (130, 1, 20, 1, (64, 16)), (256, 30, 64, 3, (32, 16)), (300, 1, 64, 0, (32, 16)), (512, 0, 20, 1, (32, 16)), (700, 70, 140, 0, (32, 16)), (1024, 2, 96, 0, (64, 16)),
     (1500, 1, 16, 3, (32, 16)), (2048, 1, 64, 0, (32, 16))])
 def test_pooled_rows_of_every_length_class(blocks, n_init, topk, pad, cmp):
     import paper_2509_24663_amd as m
@@ -30,7 +30,7 @@ def test_pooled_rows_of_every_length_class(blocks, n_init, topk, pad, cmp):
     s = torch.where(s < 0.3, (s * 40).floor() / 40, s)                   # ties among a part of them
     idx = m.topk_pooled(p, s, [0, n])[0]
     chunks = (blocks + 63) // 64
-    cap = 8 if chunks <= 8 else 16 if chunks <= 16 else 32
+    cap = 4 if chunks <= 4 else 8 if chunks <= 8 else 16 if chunks <= 16 else 32
     edges = [e for q in range(1, 5) for e in (q * cap // 4 * 4096 + d for d in (-65, -64, -1, 0, 1, 63, 64))]
     rows = sorted({r for r in edges + [0, 31, 64 * topk, n - 1, n // 3, n // 2 + 17] if 0 <= r < n})
     got, sc = idx[rows].cpu().numpy(), s[0, rows].cpu().numpy()
