@@ -46,6 +46,15 @@ def test_dq_with_one_entry_per_interval(m, oracle):  # noqa: F811
     assert np.abs(to_np(dq[rows_d]) - dQ).max() <= 2e-2 * max(np.abs(dQ).max(), 0.1)
 
 
+@pytest.mark.parametrize("heads", [(16, 1), (32, 2)])
+def test_more_sequences_than_xcds(m, oracle, heads):  # noqa: F811
+    """Eleven sequences: the (chunk, head) groups move on by one of the eight XCDs with every sequence."""
+    lens = [70, 129, 1, 64, 200, 33, 65, 130, 40, 300, 90]
+    w = synth.make_varlen(lens, *heads, 128, seed=730, dtype="bf16")
+    gp, op = _params(m, oracle, "bf16", *heads, 128, n_init=1, n_local=1, topk_total=3, dense_threshold=80)
+    _check_backward(m, oracle, w, gp, op, "bf16")
+
+
 @pytest.mark.parametrize("dense", [True, False])
 def test_token_strides_past_32_bits_per_block(m, oracle, dense):  # noqa: F811
     """K and V rows 2^24 elements apart (a block then spans 2^31 bytes), a partial last block: the same gradients as from
