@@ -420,7 +420,8 @@ __global__ void __launch_bounds__(SEL_THREADS) dec_select_kernel(DecArgs a, int 
         const uint32_t key = in ? pk[j] : 0u;
         int eq_tot, sel_tot;
         const int eq_rank = eq_seen + wg_prefix_count(lv && key == thr, wave_tot, tid, eq_tot);
-        const bool sel = forced || (lv && key > thr) || (lv && key == thr && eq_rank < need);
+        // (kr == 0: the radix select found nothing, and only the forced blocks have room in the list)
+        const bool sel = forced || (lv && kr > 0 && (key > thr || (key == thr && eq_rank < need)));
         const int pos = written + wg_prefix_count(sel, wave_tot, tid, sel_tot);
         if (sel) out[pos] = j;
         written += sel_tot;
