@@ -645,6 +645,12 @@ struct ScoreKernel {
         unsigned carry[TPW];                 // bit patterns of non-negative floats
 #pragma unroll
         for (int i = 0; i < TPW; ++i) carry[i] = 0u;
+        // The tile's own block is the last that is written.  (Said only where windows are shifted by one: with compressed
+        // windows of one stride the last key of a block is visible to the block's last token, and the next block's window
+        // starts there.)
+        static_assert(kBlock % T == 0, "a tile's tokens lie in one block");
+        const int bt = __builtin_amdgcn_readfirstlane(t0) / kBlock;
+        auto written = [&](int jb, int visible) -> bool { return max(4 * jb - POOL, 0) < visible && (POOL <= 0 || jb <= bt); };
         float *const out_w = a.out + ((int64_t)h * a.map.total_rows + row0 + w * TPW) * a.row_stride;
         auto vec2_body = [&](int kt, auto edge_c) {
             constexpr bool edge_tile = decltype(edge_c)::value;   // the tile reaches past some token's visible keys
@@ -675,7 +681,7 @@ struct ScoreKernel {
                     unsigned below = dpp_move<DPP_WAVE_SHR1>(shifted_src);
                     if (lane == 0) below = carry[i];
                     carry[i] = __builtin_amdgcn_readlane(shifted_src, 63);
-                    const bool has_visible_key = !edge_tile || max(4 * jb - POOL, 0) < vis[i];
+                    const bool has_visible_key = !edge_tile || written(jb, vis[i]);
                     if (writer && has_visible_key) out_w[i * a.row_stride + jb] = __uint_as_float(max(below, own));
                 }
             }
@@ -691,7 +697,7 @@ struct ScoreKernel {
             const int jb = nkt * (kBlock / 4) - (POOL ? 0 : 1);
 #pragma unroll
             for (int i = 0; i < TPW; ++i)
-                if (lane == 0 && max(4 * jb - POOL, 0) < vis[i]) out_w[i * a.row_stride + jb] = __uint_as_float(carry[i]);
+                if (lane == 0 && written(jb, vis[i])) out_w[i * a.row_stride + jb] = __uint_as_float(carry[i]);
         };
         TilePre pf = load_tile(kt_fine, 0, tid);
         stage_tile(smem, tid, pf);
