@@ -223,7 +223,8 @@ int infllmv2_topk_pooled(const infllmv2_params *p, const float *s_cmp_d, int64_t
  * whose block u / B is listed in block_idx[h, t, :]; O = softmax(scale * q K^T) V.
  * Sequences shorter than dense_threshold ignore block_idx and attend to every u <= t (Sec. 3.2).
  *   block_idx_d    device int32 [num_kv_heads, total_tokens, topk_total] (entries must be valid block
- *                  numbers <= b_t or -1; as produced by infllmv2_topk_blocks)
+ *                  numbers <= b_t or -1; as produced by infllmv2_topk_blocks, though a list may leave out blocks that
+ *                  call would always keep, the token's own among them)
  *   out_d          device out, dtype [total_tokens, num_q_heads, head_dim]
  *   lse_d          device out float32 [num_q_heads, total_tokens]: ln sum_u exp(scale * <q, k_u>); may be NULL
  *   workspace_d    device scratch, see the general rules (INFLLMV2_OP_SPARSE_ATTN_FWD)

@@ -302,8 +302,9 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     // at most this many tiles (every sequence may end with a partial one)
     const int tokens = tile_tokens(L.map, a.hq / hkv);
     hipLaunchKernelGGL((bwd_dq_kernel<T, D>), dim3((unsigned)(rows / tokens + L.map.batch), hkv), dim3(NW * 64), 0, L.stream, a);
-    // Tokens per dkv workgroup: 256, or down to 64 while the launch would leave CUs without a second workgroup (half of the
-    // (block, chunk) pairs of a causal sequence are empty)
+    // Tokens per dkv workgroup: 256, or down to 64 while the launch would leave CUs without several workgroups (half of the
+    // (block, chunk) pairs of a causal sequence are empty).  Training step with 256 / 128 / 64, 8 heads on 2, bf16: 500
+    // tokens 128 / 85 / 64 us, 4000 tokens 545 / 537 / 632, 8000 tokens 1180 / 1218 / 1340.
     int chunk = BWD_CHUNK;
     while (chunk > 64 && nblocks * ((L.max_len + chunk - 1) / chunk) * hkv < 2048) chunk /= 2;
     const unsigned chunks = (unsigned)((L.max_len + chunk - 1) / chunk);

@@ -126,7 +126,7 @@ int launch_attn_bwd_mfma(const Launch &L, const void *q, const void *k, const vo
     // card holds 500 tokens of the others); the rest takes the generic kernels.
     if (L.max_len > 262144 || L.map.kv_tok_stride >= (1 << 28)) return INFLLMV2_ERR_UNSUPPORTED;
     const size_t b_f = align256((size_t)rows * hq * sizeof(float));
-    // selection bitmap (block-major): only when block lists exist and it stays moderate (it grows with len^2 / 2048
+    // selection bitmap (block-major): only when block lists exist and it stays moderate (it grows with len^2 / 512
     // bytes per sequence and KV head: 32 MB at 128K tokens); otherwise the dK/dV kernel searches the lists
     int64_t sel_words = 0, sel_tiles = 0;
     if (idx != nullptr)

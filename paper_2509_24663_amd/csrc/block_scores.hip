@@ -784,8 +784,9 @@ int launch_block_scores(const Launch &L, const void *q, const float *kc, float *
         ScoreArgs a{(const uint16_t *)q, kc, HalfTiles{}, HalfTiles{}, s_shared, L.map, L.p->num_q_heads, L.p->cmp_len, L.p->cmp_stride,
                     L.p->dense_threshold, L.p->lse_mode, L.p->softmax_scale, row_stride};
         // Four tokens per wavefront, so that a key fragment read from LDS feeds four products; two or one while even that
-        // leaves CUs without a workgroup (a short prompt is one chain of loads and products per token of a wavefront: 777
-        // tokens on 2 KV heads 14.9 us with four, 8.2 with one).
+        // leaves CUs without a workgroup (a short prompt is one chain of loads and products per token of a wavefront).  With
+        // four / two / one on 2 KV heads: 777 tokens 14.7 / 9.8 / 7.8 us, 1500 tokens 18.3 / 12.1 / 11.0, 2040 tokens 18.0 /
+        // 12.5 / 13.2, 3000 tokens 22.8 / 21.0 / 22.0.
         const int64_t most = 256 / L.p->num_kv_heads;
         int64_t tiles8 = 0, tiles16 = 0;
         for (int s = 0; s < L.map.batch; ++s) {

@@ -79,7 +79,8 @@ compress_k_kernel(const T *__restrict__ k, RowMap map, int lc, int sc, float *__
 
 template <typename T, int D>
 int launch_t(const Launch &L, const void *k, float *kc, int32_t *cu_c, const int32_t *cu_h) {
-    // 256 threads per workgroup, or 64 while that leaves most CUs without one
+    // 256 threads per workgroup, or 64 while that leaves CUs without one (64 / 256 threads on 2 KV heads: 777 tokens 4.9 / 5.1
+    // us, 8000 tokens 5.0 / 5.4, 65000 tokens 12.8 / 11.9)
     const int lc = L.p->cmp_len, sc = L.p->cmp_stride;
     int threads = 256;
     int64_t tiles = 0;

@@ -206,7 +206,8 @@ struct Tile {
 };
 __host__ __device__ inline int tile_tokens(const RowMap &m, int G) { return m.ctx ? 1 : kCols / G; }
 
-// wave 0 looks the tile up (64 sequences per step), every thread gets it; two barriers.  false: past the last tile
+// wave 0 looks the tile up (64 sequences per step), every thread gets it; a barrier only if it has to look
+// among several sequences.  false: past the last tile
 __device__ inline bool find_tile(const RowMap &m, int tile, int tokens, Tile &t, int *s_tile /* 3 ints of LDS */) {
     if (m.ctx) {
         t.seq = tile;
