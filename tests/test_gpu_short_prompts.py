@@ -10,7 +10,8 @@ from test_gpu_parity import _check_backward, _params, _run_prefill_case, m  # no
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("lens,threshold", [([511], 0), ([512], 0), ([513], 0), ([1021], 0), ([1025], 0), ([2049], 0),
+@pytest.mark.parametrize("lens,threshold", [([511], 0), ([512], 0), ([513], 0), ([1021], 0), ([1024], 0), ([1025], 0), ([2048], 0),
+                                            ([2049], 0),
                                             ([3, 130, 1, 250], 100), ([65, 301, 70, 480], 128)])
 def test_small_tiles(m, oracle, lens, threshold):  # noqa: F811
     w = synth.make_varlen(lens, 32, 2, 128, seed=1200 + len(lens) + lens[0], dtype="bf16")
