@@ -221,6 +221,12 @@ static int launch_generic(const Launch &L, const void *q, const float *kc, float
 // (never the case for real activations) is re-staged with its own shift; both are undone by a multiply on the
 // accumulator, on a slower path.  Both passes see the same logits.
 //
+// What a workgroup does before its first product and between its passes is paid once per 32 tokens, which at 10000 tokens is
+// a third of the kernel: counts by shift instead of division, the Q rows and the first key tile requested together, lane
+// maxima by lane moves, no reference in the merge of a pass that had none.  Kernel at 5000 tokens 35.2 -> 33.1 us, LSE
+// Approximation at 20011 tokens 199 -> 186, 65536 tokens 1.2 % less.  (One resident workgroup per CU that goes through the
+// tiles gains nothing more: 102.3 against 102.8 us for the call at 10000 tokens, 2084 against 2078 at 65536.)
+//
 // Vector-instruction budget.  MFMA and vector instructions share one issue port, and a (token, key tile) pair
 // has 16 MFMAs against 16 exponentials plus their sums, so every other vector instruction per logit shows up
 // in the run time.  Two are avoided: softmax_scale * log2(e) is multiplied into K^{C1} when a tile is converted
@@ -258,6 +264,7 @@ struct ScoreArgs {
     int hq, lc, sc, dense_below, lse_mode;
     float scale;
     int64_t row_stride;
+    int sc_shift;             // log2(sc) where sc is a power of two, else -1
 };
 
 __device__ inline float s_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -276,6 +283,19 @@ __device__ inline float row16_all(float x) {
     x = step(x, __uint_as_float(dpp_move<0x4E>(__float_as_uint(x))));       // quad_perm [2,3,0,1]
     x = step(x, __uint_as_float(dpp_move<0x141>(__float_as_uint(x))));      // row_half_mirror
     return step(x, __uint_as_float(dpp_move<0x140>(__float_as_uint(x))));   // row_mirror
+}
+// max over the wave, result in every lane
+__device__ inline float wave64_max(float x) {
+    x = row16_all<true>(x);
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float y = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+// element e of eight bf16 values
+__device__ inline float bf16_at(const uint4 &v, int e) {
+    const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+    return __uint_as_float(e & 1 ? u[e >> 1] & 0xffff0000u : u[e >> 1] << 16);
 }
 constexpr int DPP_QUAD_SWAP1 = 0xB1;   // quad_perm [1,0,3,2]
 constexpr int DPP_QUAD_SWAP2 = 0x4E;   // quad_perm [2,3,0,1]
@@ -368,6 +388,28 @@ __device__ inline float swap_add(float x, float y) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// num_cmp with a shift where the stride is a power of two: a division is some forty scalar instructions, and a workgroup needs
+// four of these counts before it can request its first byte
+struct CmpCount {
+    int lc, sc, shift;         // shift < 0: sc is no power of two
+    __device__ inline int operator()(int n) const {
+        const int d = n - lc;
+        return d < 0 ? 0 : (shift >= 0 ? d >> shift : d / sc) + 1;
+    }
+};
+// visible_cmp of consecutive tokens, from the first one on: one division for all of them
+struct VisibleCount {
+    int v, left, sc;           // keys the next token sees; tokens until it is one more
+    __device__ inline VisibleCount(int t, const CmpCount &c) : v(c(t + 1)), sc(c.sc) {
+        left = v == 0 ? c.lc - 1 - t : v * sc - (t - (c.lc - 1));      // key v completes at token v sc + lc - 1
+    }
+    __device__ inline int next() {
+        const int now = v;
+        if (--left == 0) { ++v; left = sc; }
+        return now;
+    }
+};
+
 template <int NW, int TPW>
 struct ScoreKernel {
     static constexpr int T = NW * TPW;
@@ -421,40 +463,47 @@ struct ScoreKernel {
     template <int POOL>
     __device__ static void run(const ScoreArgs &a, int num_tiles) {
         extern __shared__ __attribute__((aligned(16))) _Float16 smem[];     // two tiles (double buffer)
-        __shared__ int s_seq, s_tile, s_tbase[2];
-        const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+        __shared__ int s_where[4];
+        const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int h = blockIdx.y;
         const int tile_id = num_tiles - 1 - (int)blockIdx.x;     // longest rows first
-        if (tid == 0) {
-            int rem = tile_id, s = 0, tb_fine = 0, tb_coarse = 0;      // first key tile of the sequence
-            for (; s < a.map.batch; ++s) {
-                const int slen = a.map.cu[s + 1] - a.map.cu[s];
-                const int nt = (slen + T - 1) / T;
-                if (rem < nt) break;
-                rem -= nt;
-                tb_fine += (num_cmp(slen, a.lc, a.sc) + kBlock - 1) / kBlock;
-                tb_coarse += (num_cmp(slen, 4 * a.lc, 4 * a.sc) + kBlock - 1) / kBlock;
+        int seq = 0, tile_in_seq = tile_id, tb_fine = 0, tb_coarse = 0;    // tb: first key tile of the sequence
+        if (a.map.batch > 1) {                                   // (one sequence needs no walk: two trips to memory less)
+            if (tid == 0) {
+                int s = 0;
+                for (; s < a.map.batch; ++s) {
+                    const int slen = a.map.cu[s + 1] - a.map.cu[s];
+                    const int nt = (slen + T - 1) / T;
+                    if (tile_in_seq < nt) break;
+                    tile_in_seq -= nt;
+                    tb_fine += (num_cmp(slen, a.lc, a.sc) + kBlock - 1) / kBlock;
+                    tb_coarse += (num_cmp(slen, 4 * a.lc, 4 * a.sc) + kBlock - 1) / kBlock;
+                }
+                s_where[0] = s;
+                s_where[1] = tile_in_seq;
+                s_where[2] = tb_fine;
+                s_where[3] = tb_coarse;
             }
-            s_seq = s;
-            s_tile = rem;
-            s_tbase[0] = tb_fine;
-            s_tbase[1] = tb_coarse;
+            __syncthreads();
+            seq = __builtin_amdgcn_readfirstlane(s_where[0]);
+            tile_in_seq = __builtin_amdgcn_readfirstlane(s_where[1]);
+            tb_fine = __builtin_amdgcn_readfirstlane(s_where[2]);
+            tb_coarse = __builtin_amdgcn_readfirstlane(s_where[3]);
         }
-        __syncthreads();
-        const int seq = s_seq;
         if (seq >= a.map.batch) return;
         const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;
         if (len < a.dense_below) return;
-        const int t0 = s_tile * T;
+        const int t0 = tile_in_seq * T;
+        if (t0 >= len) return;                                   // (grid: every tile exists; one sequence is not searched)
         const int ntok = min(T, len - t0);
-        const int nc = num_cmp(len, a.lc, a.sc);
-        const int vis_last = min(visible_cmp(t0 + ntok - 1, a.lc, a.sc), nc);
+        const CmpCount fine_count{a.lc, a.sc, a.sc_shift};
+        const CmpCount coarse_count{4 * a.lc, 4 * a.sc, a.sc_shift < 0 ? -1 : a.sc_shift + 2};
+        const int nc = fine_count(len);
+        const int vis_last = min(fine_count(t0 + ntok), nc);
         if (vis_last == 0) return;
         const int nkt = (vis_last + kBlock - 1) / kBlock;
         const int row0 = tok0 + t0;
         // this sequence's key tiles and their shifts (wave-uniform addresses)
-        const int tb_fine = __builtin_amdgcn_readfirstlane(s_tbase[0]);
-        const int tb_coarse = __builtin_amdgcn_readfirstlane(s_tbase[1]);
         const _Float16 *kt_fine = a.fine.data + ((int64_t)h * a.fine.tiles + tb_fine) * (kBlock * SD);
         const int32_t *sh_fine = a.fine.shift + (int64_t)h * a.fine.tiles + tb_fine;
         const _Float16 *kt_coarse = a.lse_mode ? a.coarse.data + ((int64_t)h * a.coarse.tiles + tb_coarse) * (kBlock * SD) : kt_fine;
@@ -468,37 +517,44 @@ struct ScoreKernel {
         // takes the slower path that multiplies the accumulator by the difference.
         int ce;
         (void)frexpf(a.scale * S_LOG2E, &ce);
+        ce = __builtin_amdgcn_readfirstlane(ce);
         half8 qf[TPW][4];
         int vis[TPW];
         // keys of pass 1: the fine ones, or with the LSE Approximation the coarse ones (Eq. 7)
-        const int nc2 = num_cmp(len, 4 * a.lc, 4 * a.sc);
+        const int nc2 = a.lse_mode ? coarse_count(len) : 0;
         int vis1[TPW];
         int vis1_min = 1 << 30;
         float cq[TPW];                   // 2^(ce - token's exponent): multiplies the accumulator (normally 1)
         bool q_plain = true;
         int vis_min = 1 << 30;
+        // every row of the wave is requested before the first is looked at, and with them the first key tile of pass 1: one
+        // trip to memory (rows past the sequence's end repeat its last token and see no key)
+        uint4 raw[TPW][4];
+        VisibleCount fine_keys(t0 + w * TPW, fine_count), coarse_keys(t0 + w * TPW, coarse_count);
 #pragma unroll
         for (int i = 0; i < TPW; ++i) {
             const int ti = w * TPW + i;
-            vis[i] = ti < ntok ? min(visible_cmp(t0 + ti, a.lc, a.sc), nc) : 0;
+            vis[i] = ti < ntok ? min(fine_keys.next(), nc) : 0;
             vis_min = min(vis_min, vis[i]);
-            vis1[i] = a.lse_mode == 0 ? vis[i] : (ti < ntok ? min(visible_cmp(t0 + ti, 4 * a.lc, 4 * a.sc), nc2) : 0);
+            vis1[i] = a.lse_mode == 0 ? vis[i] : (ti < ntok ? min(coarse_keys.next(), nc2) : 0);
             vis1_min = min(vis1_min, vis1[i]);
-            const uint16_t *qp = a.q + ((int64_t)(row0 + ti) * a.hq + h * SG + n16) * SD + g * 8;
-            float x[4][8];
+            const uint16_t *qp = a.q + ((int64_t)(row0 + min(ti, ntok - 1)) * a.hq + h * SG + n16) * SD + g * 8;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) raw[i][ks] = *reinterpret_cast<const uint4 *>(qp + ks * 32);
+        }
+        const int vis1_last = a.lse_mode == 0 ? vis_last : min(coarse_count(t0 + ntok), nc2);
+        const int nkt1 = (vis1_last + kBlock - 1) / kBlock;
+        TilePre first = {};
+        if (nkt1 > 0) first = load_tile(kt_coarse, 0, tid);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
             float amax = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const uint4 raw = ti < ntok ? *reinterpret_cast<const uint4 *>(qp + ks * 32) : make_uint4(0, 0, 0, 0);
-                const uint32_t u[4] = {raw.x, raw.y, raw.z, raw.w};
+            for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    x[ks][2 * e] = __uint_as_float(u[e] << 16);
-                    x[ks][2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
-                    amax = fmaxf(amax, fmaxf(fabsf(x[ks][2 * e]), fabsf(x[ks][2 * e + 1])));
-                }
-            }
-            amax = wave_max(amax);
+                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(bf16_at(raw[i][ks], e)));
+            amax = wave64_max(amax);
             if (!(amax < 3.0e38f)) amax = 3.0e38f;     // Inf / NaN inputs: keep going, results are Inf / NaN anyway
             int exq = 0;
             if (amax > 0.f) (void)frexpf(amax, &exq);  // amax = f * 2^exq, 0.5 <= f < 1
@@ -511,7 +567,7 @@ struct ScoreKernel {
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) qf[i][ks][e] = (_Float16)(x[ks][e] * sc);
+                for (int e = 0; e < 8; ++e) qf[i][ks][e] = (_Float16)(bf16_at(raw[i][ks], e) * sc);
         }
         f32x4 acc[TPW][4];
         f32x4 nm[TPW];                   // per lane and head row: minus the reference (log2 domain)
@@ -588,18 +644,17 @@ struct ScoreKernel {
                 }
             }
         };
-        const int vis1_last = a.lse_mode == 0 ? vis_last : min(visible_cmp(t0 + ntok - 1, 4 * a.lc, 4 * a.sc), nc2);
-        const int nkt1 = (vis1_last + kBlock - 1) / kBlock;
         float lse2[TPW][4];
         auto pass1 = [&](auto tracked_c) -> bool {       // returns true if some row's sum cannot be trusted
+            constexpr bool tracked = decltype(tracked_c)::value;
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
                 nm[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int r = 0; r < 4; ++r) l[i][r] = 0.f;
             }
-            TilePre pf = {};
-            if (nkt1 > 0) stage_tile(smem, tid, load_tile(kt_coarse, 0, tid));
+            TilePre pf = first;
+            if (nkt1 > 0) stage_tile(smem, tid, tracked ? load_tile(kt_coarse, 0, tid) : first);
             for (int kt = 0; kt < nkt1; ++kt) {
                 if (kt + 1 < nkt1) pf = load_tile(kt_coarse, kt + 1, tid);
                 if (late && kt > 0) vec1(kt - 1, tracked_c);
@@ -616,10 +671,14 @@ struct ScoreKernel {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     // (lane moves inside the 16-lane row: no LDS round trips)
-                    float mm = -nm[i][r], ll = l[i][r];
-                    const float mrow = row16_all<true>(mm);
-                    ll = row16_all<false>(ll * s_exp2(mm - mrow));
-                    mm = mrow;
+                    float mm = 0.f, ll = l[i][r];
+                    if (tracked) {                       // (untracked references are all zero)
+                        mm = -nm[i][r];
+                        const float mrow = row16_all<true>(mm);
+                        ll *= s_exp2(mm - mrow);
+                        mm = mrow;
+                    }
+                    ll = row16_all<false>(ll);
                     // a row that saw no key at all (possible with the coarse keys of the LSE Approximation while
                     // fine keys are already visible) normalises everything to zero
                     lse2[i][r] = ll > 0.f ? mm + __log2f(ll) : INFINITY;
@@ -782,19 +841,19 @@ int launch_block_scores(const Launch &L, const void *q, const float *kc, float *
     if (cu_h != nullptr && L.map.ctx == nullptr && scores_mfma_params(L.p, pooled) &&
         (((uintptr_t)q | (uintptr_t)kc) & 15) == 0) {
         ScoreArgs a{(const uint16_t *)q, kc, HalfTiles{}, HalfTiles{}, s_shared, L.map, L.p->num_q_heads, L.p->cmp_len, L.p->cmp_stride,
-                    L.p->dense_threshold, L.p->lse_mode, L.p->softmax_scale, row_stride};
-        // Four tokens per wavefront, so that a key fragment read from LDS feeds four products; two or one while even that
-        // leaves CUs without a workgroup (a short prompt is one chain of loads and products per token of a wavefront).  With
-        // four / two / one on 2 KV heads: 777 tokens 14.7 / 9.8 / 7.8 us, 1500 tokens 18.3 / 12.1 / 11.0, 2040 tokens 18.0 /
-        // 12.5 / 13.2, 3000 tokens 22.8 / 21.0 / 22.0.
-        const int64_t most = 256 / L.p->num_kv_heads;
+                    L.p->dense_threshold, L.p->lse_mode, L.p->softmax_scale, row_stride,
+                    (L.p->cmp_stride & (L.p->cmp_stride - 1)) == 0 ? __builtin_ctz(L.p->cmp_stride) : -1};
+        // Four tokens per wavefront, so that a key fragment read from LDS feeds four products; fewer for short prompts, whose
+        // time is what one workgroup takes from its first load to its last store.  Kernel with one / two / four on 2 KV
+        // heads: 777 tokens 7.2 / 9.0 / 13.1 us, 1500 tokens 9.9 / 11.2 / 16.6, 2000 tokens 12.2 / 11.8 / 17.2, 3000 tokens
+        // 19.9 / 19.8 / 21.3, 4000 tokens 28.2 / 24.8 / 26.0, 4500 tokens 31.8 / 34.1 / 31.5.
         int64_t tiles8 = 0, tiles16 = 0;
         for (int s = 0; s < L.map.batch; ++s) {
             tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
             tiles16 += (cu_h[s + 1] - cu_h[s] + 15) / 16;
         }
-        if (tiles8 <= most) return launch_scores_pool<8, 1>(L, a, cu_h, pooled ? pool.pad : -1);
-        if (tiles16 <= most) return launch_scores_pool<8, 2>(L, a, cu_h, pooled ? pool.pad : -1);
+        if (tiles8 * L.p->num_kv_heads <= 384) return launch_scores_pool<8, 1>(L, a, cu_h, pooled ? pool.pad : -1);
+        if (tiles16 * L.p->num_kv_heads <= 512) return launch_scores_pool<8, 2>(L, a, cu_h, pooled ? pool.pad : -1);
         return launch_scores_pool<8, 4>(L, a, cu_h, pooled ? pool.pad : -1);
     }
     if (L.p->head_dim == 128)
