@@ -119,12 +119,15 @@ def _check(st: int, where: str):
         raise InfllmV2Error(st, where)
 
 
+# Addresses and the stream go over as plain integers: the signatures convert them, and a wrapper object per argument, or a
+# torch.cuda.Stream per call (2.9 us of the 8 to 13 that a call took on the host; its number alone 0.1), is what short
+# prompts and small decode steps wait for.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 # `op` of infllmv2_workspace_bytes (enum infllmv2_op)
@@ -137,17 +140,16 @@ def workspace_bytes(op: int, p: Params, batch: int, total_tokens: int, max_seqle
     return int(lib().infllmv2_workspace_bytes(int(op), ctypes.byref(p), int(batch), int(total_tokens), int(max_seqlen)))
 
 
-def _workspace(op: int, p: Params, cu_h: torch.Tensor, device, given: Optional[torch.Tensor]):
+def _workspace(op: int, p: Params, si: "SeqInfo", device, given: Optional[torch.Tensor]):
     """The caller's scratch tensor, or a new one of the size the library asks for (None when it asks for none)."""
     if given is not None:
         return given
-    batch = cu_h.numel() - 1
-    need = workspace_bytes(op, p, batch, int(cu_h[-1]), _max_len(cu_h))
+    need = workspace_bytes(op, p, si.batch, si.total, si.max_len)
     return torch.empty(need, dtype=torch.uint8, device=device) if need else None
 
 
 def _ws_args(ws: Optional[torch.Tensor]):
-    return (None, 0) if ws is None else (ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size())
+    return (None, 0) if ws is None else (ws.data_ptr(), ws.numel() * ws.element_size())
 
 
 class SeqInfo:
@@ -163,15 +165,9 @@ class SeqInfo:
         self.total = int(self.cu_h[-1])
 
 
-def _cu_pair(cu_seqlens):
-    """host int32 tensor + device copy (pass a SeqInfo to avoid the copy on every call)"""
-    si = cu_seqlens if isinstance(cu_seqlens, SeqInfo) else SeqInfo(cu_seqlens)
-    return si.cu_h, si.cu_d
-
-
-def _max_len(cu_h: torch.Tensor) -> int:
-    """Longest sequence; only where a buffer is made here (a few microseconds of tensor arithmetic)."""
-    return int((cu_h[1:] - cu_h[:-1]).max()) if cu_h.numel() > 1 else 0
+def _seq_info(cu_seqlens) -> SeqInfo:
+    """pass a SeqInfo to avoid the copy to the device on every call"""
+    return cu_seqlens if isinstance(cu_seqlens, SeqInfo) else SeqInfo(cu_seqlens)
 
 
 def _kv_strides(k: torch.Tensor):
@@ -184,11 +180,10 @@ def _kv_strides(k: torch.Tensor):
 def compress_k(p: Params, k: torch.Tensor, cu_seqlens, out=None):
     """Stage 1.  k [hkv, T, d] (device).  Returns kc [hkv, total_c, d] fp32, cu_seqlens_c (device int32).
     out: optional (kc, cu_seqlens_c) buffers to reuse."""
-    cu_h, cu_d = _cu_pair(cu_seqlens)
-    batch = cu_h.numel() - 1
+    si = _seq_info(cu_seqlens)
+    cu_h, cu_d, batch = si.cu_h, si.cu_d, si.batch
     if out is None:
-        lens = (cu_h[1:] - cu_h[:-1]).tolist()
-        total_c = sum(num_cmp(p, n) for n in lens)
+        total_c = sum(num_cmp(p, n) for n in si.lens)
         kc = torch.empty((p.num_kv_heads, max(total_c, 1), p.head_dim), dtype=torch.float32, device=k.device)
         cu_c = torch.empty(batch + 1, dtype=torch.int32, device=k.device)
     else:
@@ -218,12 +213,12 @@ def block_scores(p: Params, q: torch.Tensor, kc: torch.Tensor, cu_seqlens, cu_se
     """Stage 2.  q [T, hq, d]; returns S^shared [hkv, T, row_stride] fp32 (entries beyond v(t) unspecified).
     workspace: a uint8 device tensor of workspace_bytes(OP_BLOCK_SCORES, ...) bytes to reuse (else made here)."""
     assert q.is_contiguous() and kc.is_contiguous()
-    cu_h, cu_d = _cu_pair(cu_seqlens)
-    batch = cu_h.numel() - 1
+    si = _seq_info(cu_seqlens)
+    cu_h, cu_d, batch = si.cu_h, si.cu_d, si.batch
     if out is None:
-        rs = max(4, (num_cmp(p, _max_len(cu_h)) + 3) // 4 * 4)
+        rs = max(4, (num_cmp(p, si.max_len) + 3) // 4 * 4)
         out = torch.empty((p.num_kv_heads, q.shape[0], rs), dtype=torch.float32, device=q.device)
-    ws = _workspace(OP_BLOCK_SCORES, p, cu_h, q.device, workspace)
+    ws = _workspace(OP_BLOCK_SCORES, p, si, q.device, workspace)
     st = lib().infllmv2_block_scores(ctypes.byref(p), _ptr(q), _ptr(kc), kc.shape[1], _ptr(cu_h), _ptr(cu_d),
                                      _ptr(cu_seqlens_c), batch, _ptr(out), out.shape[2], *_ws_args(ws), _stream())
     _check(st, "infllmv2_block_scores")
@@ -232,8 +227,8 @@ def block_scores(p: Params, q: torch.Tensor, kc: torch.Tensor, cu_seqlens, cu_se
 
 def topk_blocks(p: Params, s_shared: torch.Tensor, cu_seqlens, out: Optional[torch.Tensor] = None):
     """Stage 3.  s_shared [hkv, T, row_stride] -> block_idx [hkv, T, topk_total] int32."""
-    cu_h, cu_d = _cu_pair(cu_seqlens)
-    batch = cu_h.numel() - 1
+    si = _seq_info(cu_seqlens)
+    cu_h, cu_d, batch = si.cu_h, si.cu_d, si.batch
     if out is None:
         out = torch.empty((p.num_kv_heads, s_shared.shape[1], p.topk_total), dtype=torch.int32, device=s_shared.device)
     st = lib().infllmv2_topk_blocks(ctypes.byref(p), _ptr(s_shared), s_shared.shape[2], _ptr(cu_h), _ptr(cu_d), batch,
@@ -246,13 +241,13 @@ def block_scores_pooled(p: Params, q: torch.Tensor, kc: torch.Tensor, cu_seqlens
                         out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None):
     """Stages 2 with the max-pooling fused.  Returns S^cmp [hkv, T, row_stride >= ceil(max len / 64)] fp32; entry j of
     a row is written iff the block's pooling window holds a visible key."""
-    cu_h, cu_d = _cu_pair(cu_seqlens)
-    batch = cu_h.numel() - 1
+    si = _seq_info(cu_seqlens)
+    cu_h, cu_d, batch = si.cu_h, si.cu_d, si.batch
     if out is None:
-        rs = max(1, (_max_len(cu_h) + p.block_size - 1) // p.block_size)
+        rs = max(1, (si.max_len + p.block_size - 1) // p.block_size)
         out = torch.empty((p.num_kv_heads, q.shape[0], rs), dtype=torch.float32, device=q.device)
     assert q.is_contiguous() and kc.is_contiguous()
-    ws = _workspace(OP_BLOCK_SCORES_POOLED, p, cu_h, q.device, workspace)
+    ws = _workspace(OP_BLOCK_SCORES_POOLED, p, si, q.device, workspace)
     st = lib().infllmv2_block_scores_pooled(ctypes.byref(p), _ptr(q), _ptr(kc), kc.shape[1], _ptr(cu_h), _ptr(cu_d),
                                             _ptr(cu_seqlens_c), batch, _ptr(out), out.shape[2], *_ws_args(ws),
                                             _stream())
@@ -262,8 +257,8 @@ def block_scores_pooled(p: Params, q: torch.Tensor, kc: torch.Tensor, cu_seqlens
 
 def topk_pooled(p: Params, s_cmp: torch.Tensor, cu_seqlens, out: Optional[torch.Tensor] = None):
     """Stage 3 on pooled scores.  s_cmp [hkv, T, row_stride] -> block_idx [hkv, T, topk_total] int32."""
-    cu_h, cu_d = _cu_pair(cu_seqlens)
-    batch = cu_h.numel() - 1
+    si = _seq_info(cu_seqlens)
+    cu_h, cu_d, batch = si.cu_h, si.cu_d, si.batch
     if out is None:
         out = torch.empty((p.num_kv_heads, s_cmp.shape[1], p.topk_total), dtype=torch.int32, device=s_cmp.device)
     st = lib().infllmv2_topk_pooled(ctypes.byref(p), _ptr(s_cmp), s_cmp.shape[2], _ptr(cu_h), _ptr(cu_d), batch,
@@ -274,14 +269,14 @@ def topk_pooled(p: Params, s_cmp: torch.Tensor, cu_seqlens, out: Optional[torch.
 
 def sparse_attn_fwd(p: Params, q, k, v, block_idx, cu_seqlens, out=None, lse=None, workspace=None):
     """Stage 4.  Returns (out [T, hq, d], lse [hq, T]).  workspace: scratch tensor to reuse (else made here)."""
-    cu_h, cu_d = _cu_pair(cu_seqlens)
-    batch = cu_h.numel() - 1
+    si = _seq_info(cu_seqlens)
+    cu_h, cu_d, batch = si.cu_h, si.cu_d, si.batch
     out = torch.empty_like(q) if out is None else out
     lse = torch.empty((p.num_q_heads, q.shape[0]), dtype=torch.float32, device=q.device) if lse is None else lse
     ts, hs = _kv_strides(k)
     assert _kv_strides(v) == (ts, hs)
     assert q.is_contiguous() and out.is_contiguous() and lse.is_contiguous() and block_idx.is_contiguous()
-    ws = _workspace(OP_SPARSE_ATTN_FWD, p, cu_h, q.device, workspace)
+    ws = _workspace(OP_SPARSE_ATTN_FWD, p, si, q.device, workspace)
     st = lib().infllmv2_sparse_attn_fwd(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), ts, hs, _ptr(block_idx),
                                         _ptr(cu_h), _ptr(cu_d), batch, _ptr(out), _ptr(lse), *_ws_args(ws), _stream())
     _check(st, "infllmv2_sparse_attn_fwd")
@@ -290,14 +285,14 @@ def sparse_attn_fwd(p: Params, q, k, v, block_idx, cu_seqlens, out=None, lse=Non
 
 def dense_attn_fwd(p: Params, q, k, v, cu_seqlens, out=None, lse=None, workspace=None):
     """Dense causal GQA attention.  Returns (out [T, hq, d], lse [hq, T])."""
-    cu_h, cu_d = _cu_pair(cu_seqlens)
-    batch = cu_h.numel() - 1
+    si = _seq_info(cu_seqlens)
+    cu_h, cu_d, batch = si.cu_h, si.cu_d, si.batch
     out = torch.empty_like(q) if out is None else out
     lse = torch.empty((p.num_q_heads, q.shape[0]), dtype=torch.float32, device=q.device) if lse is None else lse
     ts, hs = _kv_strides(k)
     assert _kv_strides(v) == (ts, hs)
     assert q.is_contiguous() and out.is_contiguous() and lse.is_contiguous()
-    ws = _workspace(OP_DENSE_ATTN_FWD, p, cu_h, q.device, workspace)
+    ws = _workspace(OP_DENSE_ATTN_FWD, p, si, q.device, workspace)
     st = lib().infllmv2_dense_attn_fwd(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), ts, hs, _ptr(cu_h), _ptr(cu_d),
                                        batch, _ptr(out), _ptr(lse), *_ws_args(ws), _stream())
     _check(st, "infllmv2_dense_attn_fwd")
@@ -309,8 +304,8 @@ def sparse_attn_bwd(p: Params, q, k, v, block_idx, out, lse, dout, cu_seqlens, d
     """Gradients of stage 4 for a given selection (block_idx None: dense).  Returns (dq like q, dk, dv float32
     [hkv, T, d]).  workspace: scratch tensor to reuse; when it is made here it includes room for the selection
     bitmap unless that would take more than sel_bitmap_max_bytes (0: never)."""
-    cu_h, cu_d = _cu_pair(cu_seqlens)
-    batch = cu_h.numel() - 1
+    si = _seq_info(cu_seqlens)
+    cu_h, cu_d, batch = si.cu_h, si.cu_d, si.batch
     ts, hs = _kv_strides(k)
     assert _kv_strides(v) == (ts, hs)
     T = q.shape[0]
@@ -320,9 +315,8 @@ def sparse_attn_bwd(p: Params, q, k, v, block_idx, out, lse, dout, cu_seqlens, d
     assert dout.is_contiguous() and out.is_contiguous() and dq.is_contiguous() and dk.is_contiguous() and dv.is_contiguous()
     assert q.is_contiguous() and lse.is_contiguous()
     if workspace is None:
-        max_len = _max_len(cu_h)
-        full = workspace_bytes(OP_SPARSE_ATTN_BWD, p, batch, T, max_len)
-        least = workspace_bytes(OP_SPARSE_ATTN_BWD_MIN, p, batch, T, max_len)
+        full = workspace_bytes(OP_SPARSE_ATTN_BWD, p, batch, T, si.max_len)
+        least = workspace_bytes(OP_SPARSE_ATTN_BWD_MIN, p, batch, T, si.max_len)
         need = full if block_idx is not None and full - least <= sel_bitmap_max_bytes else least
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device) if need else None
     st = lib().infllmv2_sparse_attn_bwd(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), ts, hs, _ptr(block_idx), _ptr(out),
@@ -393,11 +387,11 @@ def sparse_prefill(p: Params, q, k, v, cu_seqlens, buffers: Optional[dict] = Non
     fused_pool: stages 2 and 3 through the pooled entry points (s_cmp instead of s_shared in the result).
     Returns dict(out, lse, block_idx, s_shared | s_cmp, kc, cu_seqlens_c)."""
     b = buffers or {}
-    si = cu_seqlens if isinstance(cu_seqlens, SeqInfo) else SeqInfo(cu_seqlens)
+    si = _seq_info(cu_seqlens)
     kc, cu_c = compress_k(p, k, si, out=(b["kc"], b["cu_seqlens_c"]) if b else None)
     ws_scores = b.get("ws_scores")
     if ws_scores is None:
-        ws_scores = _workspace(OP_BLOCK_SCORES_POOLED if fused_pool else OP_BLOCK_SCORES, p, si.cu_h, q.device, None)
+        ws_scores = _workspace(OP_BLOCK_SCORES_POOLED if fused_pool else OP_BLOCK_SCORES, p, si, q.device, None)
     if fused_pool:
         sc = block_scores_pooled(p, q, kc, si, cu_c, out=b.get("s_cmp"), workspace=ws_scores)
         idx = topk_pooled(p, sc, si, out=b.get("block_idx"))
@@ -408,7 +402,7 @@ def sparse_prefill(p: Params, q, k, v, cu_seqlens, buffers: Optional[dict] = Non
         scores = dict(s_shared=sh)
     ws_attn = b.get("ws_attn")
     if ws_attn is None:
-        ws_attn = _workspace(OP_SPARSE_ATTN_FWD, p, si.cu_h, q.device, None)
+        ws_attn = _workspace(OP_SPARSE_ATTN_FWD, p, si, q.device, None)
     out, lse = sparse_attn_fwd(p, q, k, v, idx, si, out=b.get("out"), lse=b.get("lse"), workspace=ws_attn)
     return dict(out=out, lse=lse, block_idx=idx, kc=kc, cu_seqlens_c=cu_c, ws_attn=ws_attn, ws_scores=ws_scores,
                 **scores)
