@@ -293,7 +293,8 @@ int infllmv2_sparse_decode(const infllmv2_params *p, const void *q_d, const void
                            int32_t *block_idx_out_d, void *out_d, float *lse_d,
                            void *workspace_d, size_t workspace_bytes, void *stream);
 
-/* Bytes of scratch infllmv2_sparse_decode needs for `batch` sequences of at most max_ctx_len tokens
+/* Bytes of scratch infllmv2_sparse_decode makes use of for `batch` sequences of at most max_ctx_len tokens; with few
+ * sequences it also accepts somewhat less and then splits the work more coarsely
  * (= infllmv2_workspace_bytes(INFLLMV2_OP_SPARSE_DECODE, p, batch, 0, max_ctx_len)). */
 size_t infllmv2_decode_workspace_bytes(const infllmv2_params *p, int32_t batch, int32_t max_ctx_len);
 

@@ -12,11 +12,11 @@ int launch_attn_mfma(const Launch &L, const void *q, const void *k, const void *
                      int dense_below, void *out, float *lse, const int32_t *cu_h);
 bool attn_mfma_supported(const infllmv2_params *p);
 bool decode_mfma_supported(const infllmv2_params *p);
-size_t decode_mfma_workspace(const infllmv2_params *p, int batch, int max_ctx);
+size_t decode_mfma_workspace(const infllmv2_params *p, int batch, int max_ctx, bool fine);
 int launch_decode_mfma(const infllmv2_params *p, const void *q, const void *k, const void *v, int64_t kv_batch_stride,
                        int64_t kv_head_stride, int64_t kv_tok_stride, const float *kc, int64_t kc_head_stride,
                        const int32_t *ctx_h, const int32_t *ctx_d, int batch, int32_t *idx_out, void *out, float *lse,
-                       void *ws, hipStream_t stream);
+                       void *ws, size_t ws_bytes, hipStream_t stream);
 }  // namespace ifv2
 
 static int check_params(const infllmv2_params *p) {
@@ -310,12 +310,7 @@ size_t infllmv2_workspace_bytes(int op, const infllmv2_params *p, int32_t batch,
 }
 
 size_t infllmv2_decode_workspace_bytes(const infllmv2_params *p, int32_t batch, int32_t max_ctx_len) {
-    if (check_params(p) != INFLLMV2_OK || batch < 0 || max_ctx_len < 0) return 0;
-    const size_t rs = align_up((size_t)num_cmp(max_ctx_len, p->cmp_len, p->cmp_stride) + 4, 4);
-    const size_t rows = (size_t)batch * p->num_kv_heads;
-    const size_t generic = align_up(rows * rs * sizeof(float), 256) + align_up(rows * p->topk_total * sizeof(int32_t), 256) + 256;
-    const size_t fast = decode_mfma_supported(p) ? decode_mfma_workspace(p, batch, max_ctx_len) : 0;
-    return generic > fast ? generic : fast;
+    return check_params(p) != INFLLMV2_OK || batch < 0 || max_ctx_len < 0 ? 0 : ifv2::decode_scratch_bytes(p, batch, max_ctx_len, true);
 }
 
 int infllmv2_sparse_decode(const infllmv2_params *p, const void *q_d, const void *k_cache_d, const void *v_cache_d,
@@ -339,7 +334,7 @@ int infllmv2_sparse_decode(const infllmv2_params *p, const void *q_d, const void
     if (kc_head_stride < (int64_t)num_cmp(max_ctx, p->cmp_len, p->cmp_stride) * p->head_dim)
         return INFLLMV2_ERR_INVALID_ARGUMENT;
     if (batch == 0) return INFLLMV2_OK;
-    const size_t need = infllmv2_decode_workspace_bytes(p, batch, max_ctx);
+    const size_t need = ifv2::decode_scratch_bytes(p, batch, max_ctx, false);
     if (workspace_d == nullptr || ((uintptr_t)workspace_d & 255) != 0) return INFLLMV2_ERR_INVALID_ARGUMENT;
     if (workspace_bytes < need) return INFLLMV2_ERR_WORKSPACE_TOO_SMALL;
 
@@ -350,7 +345,7 @@ int infllmv2_sparse_decode(const infllmv2_params *p, const void *q_d, const void
     if (decode_mfma_supported(p) && aligned) {
         const int rc = launch_decode_mfma(p, q_d, k_cache_d, v_cache_d, kv_batch_stride, kv_head_stride, kv_tok_stride,
                                           kc_cache_d, kc_head_stride, ctx_lens_h, ctx_lens_d, batch, block_idx_out_d,
-                                          out_d, lse_d, workspace_d, (hipStream_t)stream);
+                                          out_d, lse_d, workspace_d, workspace_bytes, (hipStream_t)stream);
         if (rc != INFLLMV2_ERR_UNSUPPORTED) return rc;
     }
 
@@ -406,6 +401,14 @@ BatchTotals bound_totals(const infllmv2_params *p, int batch, int64_t total_toke
     t.kt_coarse = total_tokens / ((int64_t)4 * p->cmp_stride * kBlock) + batch;
     t.sel_words = t.blocks * ((int64_t)max_seqlen / 32 + 1);
     return t;
+}
+
+size_t decode_scratch_bytes(const infllmv2_params *p, int batch, int max_ctx, bool most) {
+    const size_t rs = align_up((size_t)num_cmp(max_ctx, p->cmp_len, p->cmp_stride) + 4, 4);
+    const size_t rows = (size_t)batch * p->num_kv_heads;
+    const size_t generic = align_up(rows * rs * sizeof(float), 256) + align_up(rows * p->topk_total * sizeof(int32_t), 256) + 256;
+    const size_t fast = decode_mfma_supported(p) ? decode_mfma_workspace(p, batch, max_ctx, most) : 0;
+    return generic > fast ? generic : fast;
 }
 
 int launch_attn(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx,

@@ -222,5 +222,8 @@ size_t scores_ws_bytes(const infllmv2_params *p, const BatchTotals &t, bool pool
 size_t attn_fwd_ws_bytes(const infllmv2_params *p, const BatchTotals &t);
 // with_bitmap: including the block-major selection bitmap that speeds up dK/dV when block lists are given
 size_t attn_bwd_ws_bytes(const infllmv2_params *p, const BatchTotals &t, bool with_bitmap);
+// scratch of a decode step (params already checked): what it can use at most (the size the query reports), or the least
+// that it accepts
+size_t decode_scratch_bytes(const infllmv2_params *p, int batch, int max_ctx, bool most);
 
 }  // namespace ifv2

@@ -487,7 +487,7 @@ __device__ inline void attend_partial(const DecArgs &a, int pair, int L, int slo
         st.l += __shfl_xor(st.l, 16);
         st.l += __shfl_xor(st.l, 32);
     }
-    if (w < NWV && g == 0) { wm[w][m16] = st.m; wl[w][m16] = st.l; }
+    if (w < NWV && g == 0) wm[w][m16] = st.m;
     __syncthreads();                                  // every wave is done with its V tile: reuse as scratch
     // Each wave scales its partial to the workgroup's reference of its lane's head and lays it down as it sits in
     // registers (slot dt * 64 + lane holds dims 16 dt + 4 (lane / 16) .. + 3 of head lane % 16); the threads then
@@ -497,6 +497,7 @@ __device__ inline void attend_partial(const DecArgs &a, int pair, int L, int slo
 #pragma unroll
         for (int k = 1; k < NWV; ++k) mm = fmaxf(mm, wm[k][m16]);
         const float wgt = st.m == -INFINITY ? 0.f : fast_exp2((st.m - mm) * c);
+        if (g == 0) wl[w][m16] = st.l * wgt;
         float4 *scr4 = reinterpret_cast<float4 *>(smem);           // [NWV waves][512 slots]
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt)
@@ -517,11 +518,12 @@ __device__ inline void attend_partial(const DecArgs &a, int pair, int L, int slo
         }
     }
     if (tid < 16) {
-        float mm = -INFINITY;
-        for (int k = 0; k < NWV; ++k) mm = fmaxf(mm, wm[k][tid]);
-        float ll = 0.f;
-        for (int k = 0; k < NWV; ++k)
-            if (wm[k][tid] != -INFINITY) ll += wl[k][tid] * fast_exp2((wm[k][tid] - mm) * c);
+        float mm = -INFINITY, ll = 0.f;
+#pragma unroll
+        for (int k = 0; k < NWV; ++k) {
+            mm = fmaxf(mm, wm[k][tid]);
+            ll += wl[k][tid];
+        }
         float *ml = a.mlpart + ((int64_t)pair * a.nslot + slot) * 32;
         ml[tid * 2] = mm;
         ml[tid * 2 + 1] = ll;
@@ -754,7 +756,7 @@ __device__ inline void pick_blocks(const DecArgs &a, int pair, const Forced &fo,
             for (int u = 0; u < 4; ++u) c[u] = hist[pass][255 - 4 * lane - u];
             const int mine = c[0] + c[1] + c[2] + c[3];
             int above = wave_inclusive_sum(mine) - mine;
-            int digit = 0, knew = 0;
+            int digit = 0, knew = 0, all_taken = 0;
             bool found = false;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -762,15 +764,21 @@ __device__ inline void pick_blocks(const DecArgs &a, int pair, const Forced &fo,
                     found = true;
                     digit = 255 - 4 * lane - u;
                     knew = k - above;
+                    all_taken = k == above + c[u];
                 }
                 above += c[u];
             }
             const int src = max(__ffsll((long long)__ballot(found)) - 1, 0);     // exactly one lane (kr >= 1 keys exist)
             prefix = (prefix << 8) | (uint32_t)__builtin_amdgcn_readlane(digit, src);
             k = __builtin_amdgcn_readlane(knew, src);
+            if (__builtin_amdgcn_readlane(all_taken, src)) {         // every key of the bucket: its lower digits do not matter
+                prefix = (prefix << (8 * pass)) - 1u;                // (not 0: then every key would be taken)
+                k = 0;
+                break;
+            }
         }
         const uint32_t thr = prefix;                     // the kr-th largest key; `need` of the keys equal to it are taken
-        const int need = k;
+        const int need = k;                              // (or everything above thr)
         // emission in ascending block order: one prefix count over the threads for (keys above, keys equal)
         int ca = 0, cb = 0;
 #pragma unroll
@@ -1011,7 +1019,11 @@ bool staged_params(const infllmv2_params *p) {
     return p->lse_mode == 0 && (int64_t)p->pool_stride * PB + p->pool_len <= kPoolKeysMax;
 }
 
-DecLayout dec_layout(const infllmv2_params *p, int batch, int max_ctx, int dense_blocks) {
+// fine: with few pairs, as many splits as the merge takes in one round, which pull fewer blocks each (one sequence on 2 KV
+// heads at 32776 tokens: 11 splits of 5 blocks instead of 7 of 8, step 27.0 -> 25.5 us; 19, 27 and 43 splits, merged in
+// two and three rounds, 26.5, 26.7 and 28.3).  The partials take more scratch; a caller whose scratch holds only the others
+// gets those.
+DecLayout dec_layout(const infllmv2_params *p, int batch, int max_ctx, int dense_blocks, bool fine) {
     DecLayout d;
     const size_t pairs = (size_t)batch * p->num_kv_heads;
     const int max_nc = num_cmp(max_ctx, p->cmp_len, p->cmp_stride);
@@ -1036,8 +1048,10 @@ DecLayout dec_layout(const infllmv2_params *p, int batch, int max_ctx, int dense
         // one workgroup per CU at most: as many splits as fill the 256 CUs, each with fewer blocks (C4: 32 pairs x 8
         // splits of 7 blocks instead of 7 splits of 8 -- every CU then pulls 7/8 of the bytes)
         const int fit = (int)(256 / (pairs ? pairs : 1));
-        const int ns = fit < entries ? fit : entries;
-        if (ns > d.nsplit && ns <= 16 - ((p->n_init + p->n_local + FW - 1) / FW)) {
+        const int slots = 16 - (p->n_init + p->n_local + FW - 1) / FW;      // partials the merge takes in one round
+        int ns = fit < entries ? fit : entries;
+        if (ns > slots) ns = fine ? slots : 0;
+        if (ns > d.nsplit) {
             d.nsplit = ns;
             d.bpw = (entries + ns - 1) / ns;
         }
@@ -1067,15 +1081,15 @@ bool decode_mfma_supported(const infllmv2_params *p) {
 }
 
 // worst case over the dense fallback: a sequence just below the threshold attends to all its blocks
-size_t decode_mfma_workspace(const infllmv2_params *p, int batch, int max_ctx) {
+size_t decode_mfma_workspace(const infllmv2_params *p, int batch, int max_ctx, bool fine) {
     const int dense_tokens = p->dense_threshold > 0 ? (p->dense_threshold - 1 < max_ctx ? p->dense_threshold - 1 : max_ctx) : 0;
-    return dec_layout(p, batch, max_ctx, (dense_tokens + kBlock - 1) / kBlock).total;
+    return dec_layout(p, batch, max_ctx, (dense_tokens + kBlock - 1) / kBlock, fine).total;
 }
 
 int launch_decode_mfma(const infllmv2_params *p, const void *q, const void *k, const void *v, int64_t kv_batch_stride,
                        int64_t kv_head_stride, int64_t kv_tok_stride, const float *kc, int64_t kc_head_stride,
                        const int32_t *ctx_h, const int32_t *ctx_d, int batch, int32_t *idx_out, void *out, float *lse,
-                       void *ws, hipStream_t stream) {
+                       void *ws, size_t ws_bytes, hipStream_t stream) {
     int max_ctx = 0, dense_blocks = 0;
     for (int b = 0; b < batch; ++b) {
         if (ctx_h[b] > max_ctx) max_ctx = ctx_h[b];
@@ -1084,7 +1098,8 @@ int launch_decode_mfma(const infllmv2_params *p, const void *q, const void *k, c
             if (nb > dense_blocks) dense_blocks = nb;
         }
     }
-    const DecLayout d = dec_layout(p, batch, max_ctx, dense_blocks);
+    DecLayout d = dec_layout(p, batch, max_ctx, dense_blocks, true);
+    if (d.total > ws_bytes) d = dec_layout(p, batch, max_ctx, dense_blocks, false);
     const int pairs = batch * p->num_kv_heads;
     DecArgs a;
     a.q = (const uint16_t *)q;

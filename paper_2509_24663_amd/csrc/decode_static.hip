@@ -48,7 +48,8 @@ int infllmv2_sparse_decode_static(const infllmv2_params *p, const void *q_d, con
         if (ctx_lens_h[b] > max_ctx) max_ctx = ctx_lens_h[b];
     }
     // the step must fit the fixed array: decided on the host, before the device is touched
-    const size_t need = infllmv2_decode_workspace_bytes(p, batch, max_ctx);
+    const size_t most = infllmv2_decode_workspace_bytes(p, batch, max_ctx);             // 0: parameters refused below
+    const size_t need = most ? ifv2::decode_scratch_bytes(p, batch, max_ctx, false) : 0;
     if (need > kScratchBytes) return INFLLMV2_ERR_WORKSPACE_TOO_SMALL;
     void *ptr = nullptr;
     if (batch > 0 && need > 0) {
