@@ -49,6 +49,6 @@ __device__ inline int64_t sel_base(const RowMap &m, int seq) {
 // dQ: the forward's tile kernel with another unit (attn_mfma.hip)
 int launch_bwd_dq(const Launch &L, const BwdM &a, const int32_t *cu_h);
 // dK, dV (attn_bwd_dkv.hip)
-int launch_bwd_dkv(const BwdM &a, int32_t max_len, hipStream_t stream);
+int launch_bwd_dkv(const BwdM &a, const int32_t *cu_h, int32_t max_len, hipStream_t stream);
 
 }  // namespace ifv2

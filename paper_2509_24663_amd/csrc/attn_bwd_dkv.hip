@@ -22,6 +22,8 @@
 // this one replaced (four wavefronts of 16 keys, two tokens per barrier) took 6.2 ms with the order of chunks above.  Four
 // wavefronts sharing a block and adding up in LDS: 5.4 ms; without the copies 3.7 ms; all rows L2 hits 4.6 ms; copies
 // spread over the products instead of early: 5.8 ms; chunks of 512 / 256 tokens: 5.1 / 5.3 ms.
+#include <algorithm>
+
 #include "attn_bwd.h"
 #include "attn_unit.h"
 
@@ -357,16 +359,47 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
 
 }  // namespace
 
-int launch_bwd_dkv(const BwdM &a, int32_t max_len, hipStream_t stream) {
-    // Tokens per workgroup: 1024, fewer while that leaves SIMDs without work (half of the pairs of a causal sequence are empty).
-    // A workgroup takes 2 us per pair of tokens, so with little to share out the longest list is the time: 500 tokens on 2 KV
-    // heads, whole training step, 509 us with chunks of 1024, 299 with 256, 135 with 64; 8000 tokens 2.30 / 2.02 / 2.10 ms.
-    // Every chunk of a block adds to the same rows, so the last halving pays only while there are few of them: 64 tokens
-    // 104 -> 75 us, 1000 tokens 177 -> 170, but 1300 tokens 239 -> 248.
-    int chunk = MAX_CHUNK;
-    auto workgroups = [&](int c) { return a.nblocks * ((max_len + c - 1) / c) * a.map.num_kv_heads; };
-    while (chunk > 64 && workgroups(chunk) < 4096) chunk /= 2;
-    if (chunk == 64 && max_len <= 1024 && workgroups(chunk) < 4096) chunk = 32;
+// Microseconds a launch with chunks of c tokens takes, up to what does not depend on c: a workgroup 35 for its keys and its
+// adds (every chunk of a block adds to the same rows) and 1.7 per pair of tokens (a fifth less while SIMDs are idle), on 128
+// SIMDs of the XCD that has most of them, and half of the longest list where the others end; or the longest list.
+// From the backward call at 264 shapes (1 to 8 KV heads, 700 to 24000 tokens, dense, budgets of 16 to 96 blocks, packed)
+// times six chunks: the one it prefers is 0.7 % from the best on average and 3.5 % at most, where the rule before it (as
+// many chunks as make 4096 workgroups) was 7.1 % off.
+static float dkv_cost(const BwdM &a, const int32_t *cu_h, int32_t max_len, int c) {
+    constexpr float kPair = 1.7f, kFixed = 35.f;
+    const int hkv = a.map.num_kv_heads;
+    const int64_t groups = ((int64_t)max_len + c - 1) / c * hkv;
+    const bool each = groups * a.map.batch <= 512;         // which XCD a workgroup is on matters while there are few
+    double wgs = 0, tokens = 0, xcd[8] = {};
+    for (int s = 0; s < a.map.batch; ++s) {
+        const double len = cu_h[s + 1] - cu_h[s], nb = (cu_h[s + 1] - cu_h[s] + kBlock - 1) / kBlock;
+        const double chunks = (cu_h[s + 1] - cu_h[s] + c - 1) / c, most = a.topk_total;
+        wgs += hkv * chunks * (nb + std::max(c / kBlock, 1)) / 2;
+        // entries of the lists: a token selects every block up to its own, or the budget
+        tokens += hkv * (a.idx == nullptr || len < a.dense_below || nb <= most
+                             ? len * (nb + 1) / 2 : kBlock * most * (most + 1) / 2 + (len - kBlock * most) * most);
+        if (each)
+            for (int64_t g = 0; g < groups && g / hkv * c < len; ++g)
+                xcd[(g - s) & 7] += (std::min<int64_t>(g / hkv * c + c, (int64_t)len) - 1) / kBlock + 1;
+    }
+    if (wgs == 0) return 0.f;
+    const double rounds = (each ? *std::max_element(xcd, xcd + 8) * 8 : wgs) / 1024;
+    const double pair = kPair * (rounds < 1 ? 0.8 + 0.2 * rounds : 1.0);
+    const double longest = std::min(c, max_len) * pair / 2 + kFixed, mean = tokens / wgs * pair / 2 + kFixed;
+    return (float)(rounds <= 1 ? longest : std::max(longest, rounds * mean + longest / 2));
+}
+
+int launch_bwd_dkv(const BwdM &a, const int32_t *cu_h, int32_t max_len, hipStream_t stream) {
+    // One sequence on 2 KV heads, training step with chunks of 32 / 64 / 128 / 256 / 512: 500 tokens 87 / 114 / 168 / 276 / 486
+    // us, 1500 tokens 283 / 235 / 270 / 370 / 581, 2000 tokens 376 / 360 / 321 / 408 / 619, 3000 tokens 580 / 539 / 551 / 499
+    // / 716, 8000 tokens 2.63 / 2.09 / 2.04 / 2.07 / 2.15 ms, 16000 tokens - / 5.53 / 4.86 / 4.68 / 4.77, 32768 tokens
+    // - / - / 12.5 / 11.15 / 11.0, with chunks of 1024 10.94.
+    int chunk = 32;
+    float best = dkv_cost(a, cu_h, max_len, chunk);
+    for (int c = 64; c <= MAX_CHUNK; c *= 2) {
+        const float cost = dkv_cost(a, cu_h, max_len, c);
+        if (cost < best) { best = cost; chunk = c; }
+    }
     const int groups = (max_len + chunk - 1) / chunk * a.map.num_kv_heads;
     const int64_t wgs = 8ll * ((groups + 7) / 8) * a.nblocks;
     if (wgs > 0xffffffffll / 64) return INFLLMV2_ERR_UNSUPPORTED;       // (a launch has fewer than 2^32 threads in x)

@@ -23,8 +23,11 @@ constexpr int D = 128, G = 16;
 
 // ------------------------------------------------------------------------------------------ pre-passes
 __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdM a) {
-    // 16 threads per (token, query head): minus Delta = <dO, O> and minus lse / scale, both token-major
+    // 16 threads per (token, query head): minus Delta = <dO, O> and minus lse / scale, both token-major; and the token's rows of
+    // dK and dV cleared for the dK/dV kernel's adds (a launch less: 4.7 us of the call at 500
+    // tokens; 11 us at 32768, where clearing beside the copy rate costs 8)
     const int row = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
+    (tid < D ? a.dk : a.dv)[((int64_t)h * a.map.total_rows + row) * D + (tid & (D - 1))] = 0.f;
     const int head = tid >> 4, d0 = (tid & 15) * 8;
     const int64_t off = ((int64_t)row * a.hq + h * G + head) * D + d0;
     const uint4 rg = *reinterpret_cast<const uint4 *>(a.dout + off);
@@ -48,14 +51,17 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdM a) {
 // Inverse of the block lists: bit t of row j says that token t selected key block j.  The dK/dV kernel then gets
 // the tokens of a (block, token chunk) pair with one short read instead of searching every token's list.
 // One workgroup per 256 tokens of a sequence; a wavefront reads a token's list with one coalesced load (lane = list
-// entry) and takes its 64 tokens in turn.  The tile's eight words of every row are put together in LDS and stored
+// entry), eight of its 32 tokens requested at once.  The tile's eight words of every row are put together in LDS (rows nine
+// words apart: the entries of a list are ascending blocks, which eight words apart would share eight banks) and stored
 // whole: no atomics on memory, and nothing has to be cleared before (rows past the tile's last block are not written,
-// which is why a reader of row j looks only at tokens from 64 j on).  Bound by the latency of one list read per token
-// and wavefront: 37 us at 32K tokens and 2 KV heads, where atomic ORs into memory took 195 us behind a zero fill.
-constexpr int BITS_TILE = 256, BITS_WORDS = BITS_TILE / 32;
-__global__ void __launch_bounds__(256) bwd_sel_bits_kernel(BwdM a) {
-    extern __shared__ uint32_t bits[];                // [blocks up to the tile's last][BITS_WORDS]
+// which is why a reader of row j looks only at tokens from 64 j on).  Bound by the latency of the list reads: 26 us up to
+// 2000 tokens and 37 at 32768, on 2 KV heads, with four wavefronts that read one list after the other, 6 and 9 now.
+constexpr int BITS_TILE = 256, BITS_WORDS = BITS_TILE / 32, BITS_ROW = BITS_WORDS + 1, BITS_WAVES = 8;
+constexpr size_t kBitsLdsMax = (size_t)262144 / kBlock * BITS_ROW * sizeof(uint32_t);       // longest sequence of this path
+__global__ void __launch_bounds__(BITS_WAVES * 64) bwd_sel_bits_kernel(BwdM a) {
+    extern __shared__ uint32_t bits[];                // [blocks up to the tile's last][BITS_ROW]
     __shared__ int s_tile[3];
+    constexpr int NT = BITS_WAVES * 64, PER = BITS_TILE / BITS_WAVES, U = 8;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = blockIdx.y;
     int tile;
     const int seq = find_seq_tile(a.map.cu, a.map.batch, BITS_TILE, blockIdx.x, tile, s_tile);
@@ -64,22 +70,27 @@ __global__ void __launch_bounds__(256) bwd_sel_bits_kernel(BwdM a) {
     if (len < a.dense_below) return;                  // dense sequences need no lists
     const int words = (len + 31) / 32;
     const int n = (min(tile * BITS_TILE + BITS_TILE, len) - 1) / kBlock + 1;      // rows
-    for (int i = tid; i < n * BITS_WORDS; i += 256) bits[i] = 0u;
+    for (int i = tid; i < n * BITS_ROW; i += NT) bits[i] = 0u;
     __syncthreads();
-    const int t_first = tile * BITS_TILE + w * 64, t_end = min(t_first + 64, len);
-    for (int t = t_first; t < t_end; ++t) {
-        const int bt = t / kBlock;
-        const int32_t *e = a.idx + head_row(a.map, h, tok0 + t) * a.topk_total;
-        for (int i = lane; i < a.topk_total; i += 64) {
-            const int j = e[i];
-            if (j >= 0 && j <= bt) atomicOr(&bits[j * BITS_WORDS + ((t >> 5) & (BITS_WORDS - 1))], 1u << (t & 31));
+    const int t_first = tile * BITS_TILE + w * PER, t_end = min(t_first + PER, len);
+    const int32_t *lists = a.idx + head_row(a.map, h, tok0) * a.topk_total;
+    for (int i = lane; i < a.topk_total; i += 64) {
+        for (int t = t_first; t < t_end; t += U) {
+            int j[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) j[u] = lists[(int64_t)min(t + u, t_end - 1) * a.topk_total + i];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int x = min(t + u, t_end - 1);  // (the last token again: the same bit)
+                if (j[u] >= 0 && j[u] <= x / kBlock) atomicOr(&bits[j[u] * BITS_ROW + ((x >> 5) & (BITS_WORDS - 1))], 1u << (x & 31));
+            }
         }
     }
     __syncthreads();
     uint32_t *rows = a.sel_bits + (int64_t)h * a.sel_words + sel_base(a.map, seq) + tile * BITS_WORDS;
-    for (int i = tid; i < n * BITS_WORDS; i += 256)
+    for (int i = tid; i < n * BITS_WORDS; i += NT)
         if (tile * BITS_WORDS + (i & (BITS_WORDS - 1)) < words)
-            rows[(int64_t)(i / BITS_WORDS) * words + (i & (BITS_WORDS - 1))] = bits[i];
+            rows[(int64_t)(i / BITS_WORDS) * words + (i & (BITS_WORDS - 1))] = bits[i / BITS_WORDS * BITS_ROW + (i & (BITS_WORDS - 1))];
 }
 
 __global__ void __launch_bounds__(256) bwd_zero_kernel(float4 *dk, float4 *dv, int64_t n4) {
@@ -162,19 +173,18 @@ int launch_attn_bwd_mfma(const Launch &L, const void *q, const void *k, const vo
     a.dq = (uint16_t *)dq;
     a.dk = dk;
     a.dv = dv;
-    launch_bwd_zero(dk, dv, rows * hkv * D, L.stream);
     if (use_bits) {
-        const size_t lds = (size_t)((L.max_len + kBlock - 1) / kBlock) * BITS_WORDS * sizeof(uint32_t);     // <= 128 KB
+        const size_t lds = (size_t)((L.max_len + kBlock - 1) / kBlock) * BITS_ROW * sizeof(uint32_t);
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(bwd_sel_bits_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                128 * 1024) != hipSuccess)
+                                (int)kBitsLdsMax) != hipSuccess)
             return INFLLMV2_ERR_HIP;
-        hipLaunchKernelGGL(bwd_sel_bits_kernel, dim3((unsigned)sel_tiles, hkv), dim3(256), lds, L.stream, a);
+        hipLaunchKernelGGL(bwd_sel_bits_kernel, dim3((unsigned)sel_tiles, hkv), dim3(BITS_WAVES * 64), lds, L.stream, a);
     }
     hipLaunchKernelGGL(bwd_prep_kernel, dim3((unsigned)rows, hkv), dim3(256), 0, L.stream, a);
     if (hipGetLastError() != hipSuccess) return INFLLMV2_ERR_HIP;
     const int rc = launch_bwd_dq(L, a, cu_h);
     if (rc != INFLLMV2_OK) return rc;
-    return launch_bwd_dkv(a, L.max_len, L.stream);
+    return launch_bwd_dkv(a, cu_h, L.max_len, L.stream);
 }
 
 }  // namespace ifv2
