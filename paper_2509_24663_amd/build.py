@@ -23,9 +23,13 @@ FLAGS = [
 ]
 
 # Per-file additions.  The dK/dV kernel keeps 256 accumulator registers, placed in AGPRs by hand, next to 240 others; with
-# the default form the compiler wants AGPRs for its short-lived MFMA results as well and spills.
+# the default form the compiler wants AGPRs for its short-lived MFMA results as well and spills.  The generic kernels' products
+# feed vector instructions at once: in the default form two moves per element go to and from the AGPRs.
+_VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
 EXTRA_FLAGS = {
-    "attn_bwd_dkv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attn_bwd_dkv.hip": _VGPR_FORM,
+    "attn_generic.hip": _VGPR_FORM,
+    "attn_bwd.hip": _VGPR_FORM,
 }
 
 

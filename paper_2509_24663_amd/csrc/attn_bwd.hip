@@ -12,13 +12,16 @@
 //   dq    : the workgroup and block walk of the generic forward kernel: per block S^T = K Q^T and dP^T = V dO^T
 //           (keys x columns), dZ^T in registers, dQ^T += K^T dZ^T
 //   dkv   : one workgroup of 4 wavefronts per (KV block, chunk of later tokens, KV head): lists the tokens of its chunk
-//           that selected the block and takes 16 / G of them at a time, 16 rows of Q and dO; wavefront w holds keys
+//           that selected the block and takes 16 / G of them at a time, 16 rows of Q and dO (bf16: twice that); wavefront w holds keys
 //           16 w .. 16 w + 15 (their K and V rows stay in registers): S = Q K^T, dP = dO V^T (rows x keys), then
 //           dV += P^T dO and dK += dZ^T Q, contracted over the 16 rows.  The block's 64 rows of dK and dV are added to
 //           the float32 result with atomics (one add per element and workgroup; the order of the adds, and with it
 //           the last bits of dK and dV, can differ from run to run).
-// Measured, bf16, 1985 tokens, 8 heads on 2, d 128, 16 blocks: dq 1681 -> 86 us, dkv 5636 -> 107 us (vector arithmetic
-// before; with its atomic adds as the accumulators lie in registers instead of through LDS dkv took 490 us).
+// Measured, bf16, 1985 tokens, 8 heads on 2, d 128, 16 blocks: dq 87 -> 55 us (bound by the rows' trips from the L2, as the
+// forward kernel: two column groups per wavefront, half blocks requested ahead), dkv 108 -> 103 (products over 32 rows, the
+// products' operands and sums in vector registers instead of copied to and from accumulators, which took the fp32 kernel
+// from 346 to 251 us at 2000 tokens; with its atomic adds as the accumulators lie in registers instead of through LDS dkv took
+// 490 us).
 #include "attn_bwd.h"
 #include "gen_unit.h"
 
@@ -58,16 +61,16 @@ __global__ void __launch_bounds__(256) bwd_delta_kernel(BwdArgs<T> a) {
     if (lane == 0) a.delta[qhead_row(a.map, qh, a.hq, row)] = s;
 }
 
-template <typename T, int D>
+template <typename T, int D, int CG>
 __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
     constexpr int N = D / 16;
     __shared__ Union un;
-    __shared__ float o_s[NW][kCols][D + 4];
+    __shared__ float o_s[NW][CG * kCols][D + 4];
     __shared__ int s_tile[3];
     const int h = blockIdx.y, G = a.hq / a.map.num_kv_heads;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     Tile t;
-    if (!find_tile(a.map, gridDim.x - 1 - blockIdx.x, tile_tokens(a.map, G), t, s_tile)) return;
+    if (!find_tile(a.map, gridDim.x - 1 - blockIdx.x, CG * tile_tokens(a.map, G), t, s_tile)) return;
     const bool dense = a.idx == nullptr || t.len < a.dense_below;
     const int32_t *lists = dense ? nullptr : a.idx + head_row(a.map, h, t.row0) * a.topk_total;
     const int nblk = (t.t0 + t.ntok - 1) / kBlock + 1;
@@ -75,78 +78,125 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
     const T *vb = a.v + t.kv_base + (int64_t)h * a.map.kv_head_stride;
 
     const int m = lane & 15, g = lane >> 4;
-    const int ti = m / G;
-    const bool used = ti < t.ntok;
-    const int row = t.row0 + (used ? ti : 0), qh = h * G + (used ? m - ti * G : 0);
-    RowFrag<T, D> qf, gf;
-    qf.load(a.q + ((int64_t)row * a.hq + qh) * D, g);
-    gf.load(a.dout + ((int64_t)row * a.hq + qh) * D, g);
-    const float lse = a.lse[qhead_row(a.map, qh, a.hq, row)], delta = a.delta[qhead_row(a.map, qh, a.hq, row)];
+    const int tokens = tile_tokens(a.map, G);
+    int ti[CG];
+    bool used[CG];
+    RowFrag<T, D> qf[CG], gf[CG];
+    float lse[CG], delta[CG];
+#pragma unroll
+    for (int x = 0; x < CG; ++x) {
+        ti[x] = x * tokens + m / G;
+        used[x] = m / G < tokens && ti[x] < t.ntok;
+        const int row = t.row0 + (used[x] ? ti[x] : 0), qh = h * G + (used[x] ? m % G : 0);
+        qf[x].load(a.q + ((int64_t)row * a.hq + qh) * D, g);
+        gf[x].load(a.dout + ((int64_t)row * a.hq + qh) * D, g);
+        lse[x] = a.lse[qhead_row(a.map, qh, a.hq, row)];
+        delta[x] = a.delta[qhead_row(a.map, qh, a.hq, row)];
+    }
+    const KeyRows<T, D> krows(kb, a.map.kv_tok_stride, t.len, m, g), vrows(vb, a.map.kv_tok_stride, t.len, m, g);
 
     // as in the forward kernel: one pass for all tokens of the tile, and again token by token with the K rows that a
     // token does not see taken as 0 if something came out that is not finite (0 x infinity)
-    uint32_t all = (1u << t.ntok) - 1u;
+    uint32_t all = t.ntok == 32 ? ~0u : (1u << t.ntok) - 1u;
     int solo = -1;
     for (;;) {
-        const int solo_t = t.t0 + solo;
-        f32x4 acc[N];                                    // dQ^T: dim N (4 g + r) + j, this lane's column
+        f32x4 acc[CG][N];                                // dQ^T: dim N (4 g + r) + j, this lane's column
 #pragma unroll
-        for (int j = 0; j < N; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int x = 0; x < CG; ++x)
+#pragma unroll
+            for (int j = 0; j < N; ++j) acc[x][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int c0 = 0; c0 < nblk; c0 += kChunk) {
             un.build(lists, a.topk_total, t, c0, nblk, all, tid, NW * 64);
-            const int count = un.count;
-            for (int e = w; e < count; e += NW) {
-                const int2 ent = un.list[e];
-                const int u0 = ent.x * kBlock;
-                const int lim = used && ((ent.y >> ti) & 1) ? t.t0 + ti - u0 : -1;
-                f32x4 s[4], dp[4];
+            const int items = 2 * un.count;              // half blocks
+            RowFrag<T, D> kf[2], vf[2];
+            Spread<T, D> kr[2][4];
+            int2 ent = {0, 0};
+            auto key_of = [&](int it) -> int {
+                ent = un.list[it >> 1];
+                ent.x = __builtin_amdgcn_readfirstlane(ent.x);
+                ent.y = __builtin_amdgcn_readfirstlane(ent.y);
+                return ent.x * kBlock + 32 * (it & 1);
+            };
+            int u0 = 0;
+            if (w < items) {
+                u0 = key_of(w);
+                krows.frags(kf, u0, m, g);
+                vrows.frags(vf, u0, m, g);
+                krows.spread(kr, u0, m, g);
+            }
+            for (int it = w; it < items; it += NW) {
+                f32x4 s[CG][2], dp[CG][2];
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) {
-                    const int64_t off = (int64_t)min(u0 + 16 * kt + m, t.len - 1) * a.map.kv_tok_stride;
-                    RowFrag<T, D> kf, vf;
-                    kf.load(kb + off, g);
-                    vf.load(vb + off, g);
-                    s[kt] = row_product<D>(kf, qf);
-                    dp[kt] = row_product<D>(vf, gf);
+                for (int x = 0; x < CG; ++x)
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt) {
+                        s[x][kt] = row_product<D>(kf[kt], qf[x]);
+                        dp[x][kt] = row_product<D>(vf[kt], gf[x]);
+                    }
+                const int here = u0;
+                const uint32_t takers = (uint32_t)ent.y;
+                const bool more = it + NW < items;
+                if (more) {                              // the next half block's rows, while this one's weights are formed
+                    u0 = key_of(it + NW);
+                    krows.frags(kf, u0, m, g);
+                    vrows.frags(vf, u0, m, g);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (solo >= 0) {
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (here + 16 * kt + 4 * g + r > t.t0 + solo) kr[kt][r].zero();
                 }
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt)
+                for (int x = 0; x < CG; ++x) {
+                    if (CG > 1 && ((takers >> (x * tokens)) & ((1u << tokens) - 1u)) == 0u) continue;
+                    const int lim = used[x] && ((takers >> ti[x]) & 1u) ? t.t0 + ti[x] - here : -1;   // last visible key
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float p = exp2_fast(__builtin_fmaf(s[kt][r], a.scale, -lse) * kLog2e);
-                        s[kt][r] = 16 * kt + 4 * g + r <= lim ? p * (dp[kt][r] - delta) : 0.f;
-                    }
+                    for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) {
-                    Spread<T, D> kr[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int u = u0 + 16 * kt + 4 * g + r;
-                        kr[r].load(kb + (int64_t)min(u, t.len - 1) * a.map.kv_tok_stride, m);
-                        if (solo >= 0 && u > solo_t) kr[r].zero();
-                    }
-                    weighted_rows<false, D>(acc, s[kt], kr);
+                        for (int r = 0; r < 4; ++r) {
+                            const float p = exp2_fast(__builtin_fmaf(s[x][kt][r], a.scale, -lse[x]) * kLog2e);
+                            s[x][kt][r] = 16 * kt + 4 * g + r <= lim ? p * (dp[x][kt][r] - delta[x]) : 0.f;
+                        }
+                    weighted_rows32<false, true, D>(acc[x], s[x][0], s[x][1], kr[0], kr[1]);
                 }
+                if (more) krows.spread(kr, u0, m, g);
+                __builtin_amdgcn_sched_barrier(0);
             }
             __syncthreads();
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int x = 0; x < CG; ++x)
 #pragma unroll
-            for (int j = 0; j < N; ++j) o_s[w][m][N * (4 * g + r) + j] = acc[j][r];
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < N; ++j) o_s[w][x * kCols + m][N * (4 * g + r) + j] = acc[x][j][r];
         __syncthreads();
         static_assert(NW * 64 == kCols * 16, "sixteen threads per column");
-        const int col = tid >> 4, d0 = (tid & 15) * N, tc = col / G;
-        float y[N];
+        const int d0 = (tid & 15) * N;
+        float y[CG][N];
         bool bad = false;
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            y[j] = ((o_s[0][col][d0 + j] + o_s[1][col][d0 + j]) + (o_s[2][col][d0 + j] + o_s[3][col][d0 + j])) * a.scale;
-            bad |= !finite(y[j]);
+        for (int x = 0; x < CG; ++x) {
+            const int col = x * kCols + (tid >> 4), tc = x * tokens + (tid >> 4) / G;
+            const bool mine = (tid >> 4) / G < tokens && tc < t.ntok && ((all >> tc) & 1u);
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                y[x][j] = ((o_s[0][col][d0 + j] + o_s[1][col][d0 + j]) + (o_s[2][col][d0 + j] + o_s[3][col][d0 + j])) * a.scale;
+                bad |= mine && !finite(y[x][j]);
+            }
         }
-        const bool mine = tc < t.ntok && ((all >> tc) & 1u);
-        const bool again = solo < 0 && __syncthreads_or(mine && bad);
-        if (!again && mine) store_row<T, N>(a.dq + ((int64_t)(t.row0 + tc) * a.hq + h * G + col - tc * G) * D + d0, y);
+        const bool again = solo < 0 && __syncthreads_or(bad);
+        if (!again) {
+#pragma unroll
+            for (int x = 0; x < CG; ++x) {
+                const int tc = x * tokens + (tid >> 4) / G;
+                if ((tid >> 4) / G < tokens && tc < t.ntok && ((all >> tc) & 1u))
+                    store_row<T, N>(a.dq + ((int64_t)(t.row0 + tc) * a.hq + h * G + (tid >> 4) % G) * D + d0, y[x]);
+            }
+        }
         if (solo < 0 && !again) return;
         if (++solo >= t.ntok) return;
         all = 1u << solo;
@@ -157,9 +207,10 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
 template <typename T, int D>
 __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chunk) {
     constexpr int N = D / 16;
-    __shared__ __attribute__((aligned(16))) T rows_s[2][2][kCols][D + 16 / sizeof(T)];      // [buffer][Q, dO][row]
-    __shared__ float lse_s[2][kCols], delta_s[2][kCols];
-    __shared__ int t_s[2][kCols];
+    constexpr int RG = sizeof(T) == 2 ? 2 : 1, ROWS = RG * kCols;      // groups of 16 rows of Q and dO per step
+    __shared__ __attribute__((aligned(16))) T rows_s[2][2][ROWS][D + 16 / sizeof(T)];      // [buffer][Q, dO][row]
+    __shared__ float lse_s[2][ROWS], delta_s[2][ROWS];
+    __shared__ int t_s[2][ROWS];
     __shared__ int s_tile[3], s_list[BWD_CHUNK], s_wave_cnt[NW];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int h = blockIdx.z, G = a.hq / a.map.num_kv_heads;
@@ -200,60 +251,77 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
     for (int i = 0; i < N; ++i) acc_k[i] = acc_v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // A group is the list's next `tokens` entries with their G heads: row x is entry x / G, head x % G.  The four
-    // wavefronts need the same 16 rows of Q and dO twice (as row operands and spread over lanes), so they pass through
-    // LDS once: thread (row, part) brings a sixteenth of its row, the next group's in flight in registers while the
-    // current one is computed; one barrier per group.  Unused rows hold zeros and see no key.
+    // wavefronts need the same rows of Q and dO twice (as row operands and spread over lanes), so they pass through
+    // LDS once: thread (row, part) brings a sixteenth of its row of every group, the next step's in flight in registers while
+    // the current one is computed; one barrier per step.  Unused rows hold zeros and see no key.  bf16 rows: two groups per
+    // step, whose 32 rows are one contraction.
     const int tokens = kCols / G;
     const int x_row = tid >> 4, x_slot = x_row / G, x_head = h * G + x_row - x_slot * G;
-    struct Pre { Spread<T, D> q, g; float lse, delta; int t; };
+    struct Pre { Spread<T, D> q[RG], g[RG]; float lse[RG], delta[RG]; int t[RG]; };
     auto fetch = [&](int it) -> Pre {
         Pre pr;
-        const bool used = x_slot < min(tokens, total - it);
-        const int t = s_list[used ? it + x_slot : 0];
-        const int64_t off = ((int64_t)(tok0 + t) * a.hq + (used ? x_head : h * G)) * D;
-        pr.q.load(a.q + off, tid & 15);
-        pr.g.load(a.dout + off, tid & 15);
-        const int64_t lr = qhead_row(a.map, used ? x_head : h * G, a.hq, tok0 + t);
-        pr.lse = a.lse[lr];
-        pr.delta = a.delta[lr];
-        pr.t = used ? t : -1;
-        if (!used) { pr.q.zero(); pr.g.zero(); }
+#pragma unroll
+        for (int i = 0; i < RG; ++i) {
+            const int e = it + i * tokens + x_slot;
+            const bool used = x_slot < tokens && e < total;
+            const int t = s_list[used ? e : 0];
+            const int64_t off = ((int64_t)(tok0 + t) * a.hq + (used ? x_head : h * G)) * D;
+            pr.q[i].load(a.q + off, tid & 15);
+            pr.g[i].load(a.dout + off, tid & 15);
+            const int64_t lr = qhead_row(a.map, used ? x_head : h * G, a.hq, tok0 + t);
+            pr.lse[i] = a.lse[lr];
+            pr.delta[i] = a.delta[lr];
+            pr.t[i] = used ? t : -1;
+            if (!used) { pr.q[i].zero(); pr.g[i].zero(); }
+        }
         return pr;
     };
     auto stage = [&](int buf, const Pre &pr) {
-        pr.q.store_lds(&rows_s[buf][0][x_row][0], tid & 15);
-        pr.g.store_lds(&rows_s[buf][1][x_row][0], tid & 15);
-        if ((tid & 15) == 0) {
-            lse_s[buf][x_row] = pr.lse;
-            delta_s[buf][x_row] = pr.delta;
-            t_s[buf][x_row] = pr.t;
+#pragma unroll
+        for (int i = 0; i < RG; ++i) {
+            const int row = i * kCols + x_row;
+            pr.q[i].store_lds(&rows_s[buf][0][row][0], tid & 15);
+            pr.g[i].store_lds(&rows_s[buf][1][row][0], tid & 15);
+            if ((tid & 15) == 0) {
+                lse_s[buf][row] = pr.lse[i];
+                delta_s[buf][row] = pr.delta[i];
+                t_s[buf][row] = pr.t[i];
+            }
         }
     };
     stage(0, fetch(0));
     __syncthreads();
     int buf = 0;
-    for (int it = 0; it < total; it += tokens, buf ^= 1) {
-        const bool more = it + tokens < total;
+    for (int it = 0; it < total; it += RG * tokens, buf ^= 1) {
+        const bool more = it + RG * tokens < total;
         Pre nxt = {};
-        if (more) nxt = fetch(it + tokens);
-        RowFrag<T, D> qf, gf;
-        qf.load_lds(&rows_s[buf][0][m][0], g);
-        gf.load_lds(&rows_s[buf][1][m][0], g);
-        const f32x4 s = row_product<D>(qf, kf);
-        const f32x4 dp = row_product<D>(gf, vf);
-        f32x4 p, dz;
-        Spread<T, D> qr[4], gr[4];
+        if (more) nxt = fetch(it + RG * tokens);
+        f32x4 p[RG], dz[RG];
+        Spread<T, D> qr[RG][4], gr[RG][4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int x = 4 * g + r;
-            const bool vis = key <= t_s[buf][x];
-            p[r] = vis ? exp2_fast(__builtin_fmaf(s[r], a.scale, -lse_s[buf][x]) * kLog2e) : 0.f;
-            dz[r] = vis ? p[r] * (dp[r] - delta_s[buf][x]) : 0.f;
-            qr[r].load_lds(&rows_s[buf][0][x][0], m);
-            gr[r].load_lds(&rows_s[buf][1][x][0], m);
+        for (int i = 0; i < RG; ++i) {
+            RowFrag<T, D> qf, gf;
+            qf.load_lds(&rows_s[buf][0][i * kCols + m][0], g);
+            gf.load_lds(&rows_s[buf][1][i * kCols + m][0], g);
+            const f32x4 s = row_product<D>(qf, kf);
+            const f32x4 dp = row_product<D>(gf, vf);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int x = i * kCols + 4 * g + r;
+                const bool vis = key <= t_s[buf][x];
+                p[i][r] = vis ? exp2_fast(__builtin_fmaf(s[r], a.scale, -lse_s[buf][x]) * kLog2e) : 0.f;
+                dz[i][r] = vis ? p[i][r] * (dp[r] - delta_s[buf][x]) : 0.f;
+                qr[i][r].load_lds(&rows_s[buf][0][x][0], m);
+                gr[i][r].load_lds(&rows_s[buf][1][x][0], m);
+            }
         }
-        weighted_rows<true, D>(acc_v, p, gr);
-        weighted_rows<true, D>(acc_k, dz, qr);
+        if constexpr (RG == 2) {
+            weighted_rows32<true, true, D>(acc_v, p[0], p[1], gr[0], gr[1]);
+            weighted_rows32<true, true, D>(acc_k, dz[0], dz[1], qr[0], qr[1]);
+        } else {
+            weighted_rows<true, D>(acc_v, p[0], gr[0]);
+            weighted_rows<true, D>(acc_k, dz[0], qr[0]);
+        }
         if (more) stage(buf ^ 1, nxt);
         __syncthreads();
     }
@@ -286,6 +354,14 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
     }
 }
 
+template <typename T, int D, int CG>
+void launch_dq(const Launch &L, const BwdArgs<T> &a) {
+    const int tokens = CG * tile_tokens(L.map, a.hq / L.map.num_kv_heads);
+    // at most this many tiles (every sequence may end with a partial one)
+    hipLaunchKernelGGL((bwd_dq_kernel<T, D, CG>), dim3((unsigned)(L.map.total_rows / tokens + L.map.batch), L.map.num_kv_heads),
+                       dim3(NW * 64), 0, L.stream, a);
+}
+
 template <typename T, int D>
 int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     const int64_t rows = L.map.total_rows;
@@ -299,9 +375,16 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     a.delta = (float *)ws;
     launch_bwd_zero(a.dk, a.dv, rows * hkv * D, L.stream);
     hipLaunchKernelGGL((bwd_delta_kernel<T, D>), dim3((unsigned)((rows * a.hq + 3) / 4)), dim3(256), 0, L.stream, a);
-    // at most this many tiles (every sequence may end with a partial one)
+    // Column groups per wavefront as in the forward kernel; by tiles of one group times KV heads, one / two groups: bf16 d 128:
+    // 250 tiles 15.0 / 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1; fp32 d 64: 400 38 / 34, 800 74 / 58.  (fp32
+    // d 128: two groups need 54 registers more than there are.)
     const int tokens = tile_tokens(L.map, a.hq / hkv);
-    hipLaunchKernelGGL((bwd_dq_kernel<T, D>), dim3((unsigned)(rows / tokens + L.map.batch), hkv), dim3(NW * 64), 0, L.stream, a);
+    bool two = false;
+    if constexpr (D * sizeof(T) < 512) {
+        two = (rows / tokens + L.map.batch - 1) * hkv > (sizeof(T) == 2 ? 280 : 350);
+        if (two) launch_dq<T, D, 2>(L, a);
+    }
+    if (!two) launch_dq<T, D, 1>(L, a);
     // Tokens per dkv workgroup: 256, or down to 64 while the launch would leave CUs without several workgroups (half of the
     // (block, chunk) pairs of a causal sequence are empty).  Training step with 256 / 128 / 64, 8 heads on 2, bf16: 500
     // tokens 128 / 85 / 64 us, 4000 tokens 545 / 537 / 632, 8000 tokens 1180 / 1218 / 1340.

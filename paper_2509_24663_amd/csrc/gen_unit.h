@@ -47,6 +47,10 @@ template <int D> struct RowFrag<bf16_t, D> {
         for (int s = 0; s < D / 32; ++s)
             x[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8_u *>(row + 32 * s + 8 * g));
     }
+    __device__ inline void load_at(const char *base, uint32_t off) {      // lane offset: row and quarter, in bytes
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s) x[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8_u *>(base + off + 64 * s));
+    }
     __device__ inline void load_lds(const bf16_t *row, int g) {   // 16-byte aligned rows
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) x[s] = *reinterpret_cast<const bf16x8 *>(row + 32 * s + 8 * g);
@@ -58,6 +62,10 @@ template <int D> struct RowFrag<float, D> {
 #pragma unroll
         for (int c = 0; c < D / 16; ++c)
             x[c] = __builtin_bit_cast(f32x4, *reinterpret_cast<const f32x4_u *>(row + 16 * c + 4 * g));
+    }
+    __device__ inline void load_at(const char *base, uint32_t off) {
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) x[c] = __builtin_bit_cast(f32x4, *reinterpret_cast<const f32x4_u *>(base + off + 64 * c));
     }
     __device__ inline void load(const bf16_t *row, int g) {       // bf16 data against a float32 operand
 #pragma unroll
@@ -105,6 +113,7 @@ struct Spread {
     typedef uint32_t LWords __attribute__((ext_vector_type(W), aligned(kLdsAlign)));
     Words raw;
     __device__ inline void load(const T *row, int m) { raw = *reinterpret_cast<const UWords *>(row + m * N); }
+    __device__ inline void load_at(const char *base, uint32_t off) { raw = *reinterpret_cast<const UWords *>(base + off); }
     __device__ inline void load_lds(const T *row, int m) { raw = *reinterpret_cast<const LWords *>(row + m * N); }
     __device__ inline void store_lds(T *row, int m) const { *reinterpret_cast<LWords *>(row + m * N) = raw; }
     __device__ inline void zero() { raw = 0u; }
@@ -114,9 +123,7 @@ struct Spread {
 // index 4 g + r (for result row / column m), v[r] its row.  WEIGHTS_FIRST: the weights are the first operand, i.e.
 // acc[j] holds (weight row 4 g + r, element N m + j); otherwise (element N (4 g + r) + j, weight column m).
 //
-// fp32 rows: 4 N products 16x16x4.  bf16 rows: the weights are cut, exactly, into three bf16 pieces of eight significant
-// bits each (truncation, so that nothing rounds), and 3 N products 16x16x16 with the rows as stored give the same sum
-// of fp32 weights x bf16 values -- a product of either kind adds in fp32 -- in 3/8 of the matrix-core time.
+// fp32 rows: 4 N products 16x16x4.
 template <bool WEIGHTS_FIRST, int D>
 __device__ inline void weighted_rows(f32x4 (&acc)[D / 16], f32x4 w, const Spread<float, D> (&v)[4]) {
 #pragma unroll
@@ -128,41 +135,104 @@ __device__ inline void weighted_rows(f32x4 (&acc)[D / 16], f32x4 w, const Spread
                                    : __builtin_amdgcn_mfma_f32_16x16x4f32(x, w[r], acc[j], 0, 0, 0);
         }
 }
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // the upper (lower) halves of two words, a's first
 __device__ inline uint32_t upper_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 __device__ inline uint32_t lower_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
-// the next piece of four weights; what is left stays in w (an infinite weight is its own first piece)
-__device__ inline s16x4 take_piece(f32x4 &w) {
-    uint32_t u[4];
+
+// The same over the 32 contraction indices of two such groups of rows (weights w0 with rows a, w1 with rows b).  bf16 rows: the
+// weights are cut, exactly, into three bf16 pieces of eight significant bits each (truncation, so that nothing rounds), and
+// 3 N products 16x16x32 with the rows as stored give the same sum of fp32 weights x bf16 values -- a product of either kind
+// adds in fp32 -- in 3/16 of the matrix-core time (a product 16x16x16 occupies the matrix core as long as one over 32).
+// CHECKED: the weights may be infinite (an unchecked infinite weight gives NaN, an infinite one is its own first piece).
+template <bool WEIGHTS_FIRST, bool CHECKED, int D>
+__device__ inline void weighted_rows32(f32x4 (&acc)[D / 16], f32x4 w0, f32x4 w1, const Spread<float, D> (&a)[4],
+                                       const Spread<float, D> (&b)[4]) {
+    weighted_rows<WEIGHTS_FIRST, D>(acc, w0, a);
+    weighted_rows<WEIGHTS_FIRST, D>(acc, w1, b);
+}
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// the next piece of eight weights; what is left stays in w0, w1
+template <bool CHECKED>
+__device__ inline bf16x8 take_piece32(f32x4 &w0, f32x4 &w1) {
+    uint32_t u[8];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        u[r] = __float_as_uint(w[r]);
-        w[r] = finite(w[r]) ? w[r] - __uint_as_float(u[r] & 0xffff0000u) : 0.f;
+        u[r] = __float_as_uint(w0[r]);
+        u[4 + r] = __float_as_uint(w1[r]);
+        const float r0 = w0[r] - __uint_as_float(u[r] & 0xffff0000u), r1 = w1[r] - __uint_as_float(u[4 + r] & 0xffff0000u);
+        w0[r] = CHECKED && !finite(w0[r]) ? 0.f : r0;
+        w1[r] = CHECKED && !finite(w1[r]) ? 0.f : r1;
     }
-    return __builtin_bit_cast(s16x4, (u32x2){upper_halves(u[0], u[1]), upper_halves(u[2], u[3])});
+    return __builtin_bit_cast(bf16x8, (u32x4){upper_halves(u[0], u[1]), upper_halves(u[2], u[3]), upper_halves(u[4], u[5]),
+                                              upper_halves(u[6], u[7])});
 }
-template <bool WEIGHTS_FIRST, int D>
-__device__ inline void weighted_rows(f32x4 (&acc)[D / 16], f32x4 w, const Spread<bf16_t, D> (&v)[4]) {
-    const s16x4 p0 = take_piece(w), p1 = take_piece(w), p2 = take_piece(w);
+template <bool WEIGHTS_FIRST, bool CHECKED, int D>
+__device__ inline void weighted_rows32(f32x4 (&acc)[D / 16], f32x4 w0, f32x4 w1, const Spread<bf16_t, D> (&a)[4],
+                                       const Spread<bf16_t, D> (&b)[4]) {
+    const bf16x8 p0 = take_piece32<CHECKED>(w0, w1), p1 = take_piece32<CHECKED>(w0, w1), p2 = take_piece32<CHECKED>(w0, w1);
 #pragma unroll
     for (int j = 0; j < D / 16; ++j) {
         const int i = j / 2;
-        const u32x2 x = j & 1 ? (u32x2){upper_halves(v[0].raw[i], v[1].raw[i]), upper_halves(v[2].raw[i], v[3].raw[i])}
-                              : (u32x2){lower_halves(v[0].raw[i], v[1].raw[i]), lower_halves(v[2].raw[i], v[3].raw[i])};
-        const s16x4 row = __builtin_bit_cast(s16x4, x);
+        const u32x4 x = j & 1 ? (u32x4){upper_halves(a[0].raw[i], a[1].raw[i]), upper_halves(a[2].raw[i], a[3].raw[i]),
+                                        upper_halves(b[0].raw[i], b[1].raw[i]), upper_halves(b[2].raw[i], b[3].raw[i])}
+                              : (u32x4){lower_halves(a[0].raw[i], a[1].raw[i]), lower_halves(a[2].raw[i], a[3].raw[i]),
+                                        lower_halves(b[0].raw[i], b[1].raw[i]), lower_halves(b[2].raw[i], b[3].raw[i])};
+        const bf16x8 row = __builtin_bit_cast(bf16x8, x);
         if (WEIGHTS_FIRST) {
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p2, row, acc[j], 0, 0, 0);
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p1, row, acc[j], 0, 0, 0);
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p0, row, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p2, row, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, row, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, row, acc[j], 0, 0, 0);
         } else {
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(row, p2, acc[j], 0, 0, 0);
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(row, p1, acc[j], 0, 0, 0);
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(row, p0, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row, p2, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row, p1, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row, p0, acc[j], 0, 0, 0);
         }
     }
 }
+
+// K or V rows of one (sequence, KV head): 32 consecutive keys at a time as row fragments or spread rows.  The address of a
+// row is a scalar base and a lane offset that stays the same for the whole walk; only the 32 keys that hold the sequence's
+// end (rows past it repeat the last one), and token strides of 2^26 bytes and more, form it per lane.
+template <typename T, int D>
+struct KeyRows {
+    const char *base;              // token 0 of the sequence, this head
+    int64_t stride;                // bytes from token to token
+    int len;
+    uint32_t frag_off, spread_off;
+    bool narrow;
+    __device__ inline KeyRows(const T *p, int64_t tok_stride, int len_, int m, int g)
+        : base(reinterpret_cast<const char *>(p)), stride(tok_stride * (int64_t)sizeof(T)), len(len_) {
+        narrow = stride < (1 << 26) && stride >= 0;
+        frag_off = (uint32_t)((int)stride * m + 16 * g);
+        spread_off = (uint32_t)((int)stride * 4 * g + m * (D / 16) * (int)sizeof(T));
+    }
+    __device__ inline void frags(RowFrag<T, D> (&f)[2], int key0, int m, int g) const {
+        if (narrow && key0 + 32 <= len) {
+            const char *p = base + (int64_t)key0 * stride;
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) f[kt].load_at(p + 16 * kt * stride, frag_off);
+        } else {
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+                f[kt].load(reinterpret_cast<const T *>(base + (int64_t)min(key0 + 16 * kt + m, len - 1) * stride), g);
+        }
+    }
+    __device__ inline void spread(Spread<T, D> (&v)[2][4], int key0, int m, int g) const {
+        if (narrow && key0 + 32 <= len) {
+            const char *p = base + (int64_t)key0 * stride;
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[kt][r].load_at(p + (16 * kt + r) * stride, spread_off);
+        } else {
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    v[kt][r].load(reinterpret_cast<const T *>(base + (int64_t)min(key0 + 16 * kt + 4 * g + r, len - 1) * stride), m);
+        }
+    }
+};
 
 // max / sum over the four lane groups (lanes with equal lane % 16), result in every lane
 __device__ inline float groups_max(float x) {

@@ -1,0 +1,78 @@
+"""The generic attention and gradient kernels with one and two column groups per wavefront: the token counts on both sides of
+each rule, tiles that end ragged, groups that do not divide 16, packed and switched sequences, strided rows and infinities in
+rows that only some of a tile's tokens see; against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from helpers import assert_out_close, to_dev, to_np
+from test_gpu_parity import _check_backward, _params, _run_prefill_case, m  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,lens", [
+    ("bf16", 8, 2, 128, [555]), ("bf16", 8, 2, 128, [565]), ("bf16", 8, 2, 128, [755]), ("bf16", 8, 2, 128, [769]),
+    ("bf16", 8, 2, 64, [3, 700, 66]), ("bf16", 24, 8, 64, [131, 120]),        # G = 3: five tokens per group, 15 columns
+    ("bf16", 8, 8, 128, [777]),                                               # G = 1: 32 tokens per tile
+    ("fp32", 8, 2, 64, [705]), ("fp32", 8, 2, 128, [1195]), ("fp32", 8, 2, 128, [1000, 210]),
+    ("fp32", 24, 4, 128, [331]),                                              # G = 6: two tokens per group, 12 columns
+    ("bf16", 48, 4, 128, [101, 17]),                                          # G = 12: one token per group
+])
+def test_both_sides_of_the_rules(m, oracle, dtype, hq, hkv, d, lens):  # noqa: F811
+    w = synth.make_varlen(lens, hq, hkv, d, seed=2800 + sum(lens) + d, dtype=dtype)
+    gp, op = _params(m, oracle, dtype, hq, hkv, d, n_init=1, n_local=1, topk_total=4, dense_threshold=67 if len(lens) > 1 else 0)
+    T = sum(lens)
+    rows = np.unique(np.concatenate([np.arange(0, T, 7), np.arange(max(0, T - 70), T)]))
+    _run_prefill_case(m, oracle, w, gp, op, dtype, rows=rows)
+    _check_backward(m, oracle, w, gp, op, dtype)
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 400), ("bf16", 1100), ("fp32", 1300)])
+def test_infinite_rows_stay_with_the_tokens_that_see_them(m, oracle, dtype, n):  # noqa: F811
+    """A V row of infinities in the second half of a block: the tokens before it in the same block are computed again without
+    it, and give what they give when the row is finite."""
+    hq, hkv, d = 8, 2, 128
+    w = synth.make_prefill(n, hq, hkv, d, seed=2900 + n, dtype=dtype)
+    gp, op = _params(m, oracle, dtype, hq, hkv, d, n_init=1, n_local=1, topk_total=3)
+    q, k, v = (to_dev(w[x], dtype) for x in ("q", "k", "v"))
+    idx = m.sparse_prefill(gp, q, k, v, [0, n])["block_idx"]
+    clean, _ = m.sparse_attn_fwd(gp, q, k, v, idx, [0, n])
+    hit = 64 * (n // 128) + 41
+    v[:, hit] = float("inf")
+    out, lse = m.sparse_attn_fwd(gp, q, k, v, idx, [0, n])
+    idx_h = to_np(idx)
+    for h in range(hkv):
+        sees = np.array([t >= hit and hit // 64 in idx_h[h, t] for t in range(n)])
+        o, c = to_np(out)[:, 4 * h:4 * h + 4], to_np(clean)[:, 4 * h:4 * h + 4]
+        assert not np.isfinite(o[sees]).any() and sees.any()
+        assert_out_close(o[~sees], c[~sees], dtype, "tokens that do not see the row")
+    assert torch.isfinite(lse).all()
+
+
+def test_strided_rows(m, oracle):  # noqa: F811
+    """Rows 192 elements apart, and 2^25 elements apart (64-bit row distances), against rows side by side."""
+    n, hq, hkv, d = 780, 8, 2, 128
+    w = synth.make_prefill(n, hq, hkv, d, seed=2950, dtype="bf16")
+    gp, _ = _params(m, oracle, "bf16", hq, hkv, d, n_init=1, n_local=1, topk_total=4)
+    q, k, v = (to_dev(w[x], "bf16") for x in ("q", "k", "v"))
+    idx = m.sparse_prefill(gp, q, k, v, [0, n])["block_idx"]
+    out, lse = m.sparse_attn_fwd(gp, q, k, v, idx, [0, n])
+    dout = torch.flip(out, (0,)).contiguous()
+    want = m.sparse_attn_bwd(gp, q, k, v, idx, out, lse, dout, [0, n])
+    for stride in (192, 1 << 25):
+        buf = torch.zeros(n * stride + 2048, dtype=torch.bfloat16, device="cuda")
+        ks, vs = (torch.as_strided(buf, (hkv, n, d), (d if stride > 1000 else n * stride, stride, 1), o) for o in (0, 1024)) \
+            if stride > 1000 else (torch.zeros(hkv, n, stride, dtype=torch.bfloat16, device="cuda")[:, :, :d] for _ in range(2))
+        ks.copy_(k)
+        vs.copy_(v)
+        o2, l2 = m.sparse_attn_fwd(gp, q, ks, vs, idx, [0, n])
+        assert torch.equal(out, o2) and torch.equal(lse, l2)
+        got = m.sparse_attn_bwd(gp, q, ks, vs, idx, out, lse, dout, [0, n])
+        assert torch.equal(got[0], want[0])
+        for x, y in zip(got[1:], want[1:]):
+            # (the order of the float adds differs from run to run)
+            assert (x - y).abs().max() <= 2e-5 * float(y.abs().max())
+        del buf, ks, vs
+        torch.cuda.empty_cache()
