@@ -410,21 +410,33 @@ struct VisibleCount {
     }
 };
 
-template <int NW, int TPW>
+// DIRECT: the key tiles are converted from K^{C1} as they are staged, with no pre-pass (see launch_block_scores).
+template <int NW, int TPW, bool DIRECT>
 struct ScoreKernel {
     static constexpr int T = NW * TPW;
     static constexpr int NTHR = NW * 64;
     static constexpr int NCH = 1024 / NTHR;        // 16-byte chunks of a 64 x 128 fp16 tile per thread
 
-    // one thread's share of a tile in flight; passed and returned by value so that it stays in registers
+    // one thread's share of a tile in flight, NCH times eight elements; passed and returned by value so that it stays in
+    // registers
     struct TilePre {
-        uint4 c[NCH];
+        uint4 c[DIRECT ? 2 * NCH : NCH];
     };
-    __device__ static inline TilePre load_tile(const _Float16 *tiles, int kt, int tid) {
-        const uint4 *src = reinterpret_cast<const uint4 *>(tiles) + (int64_t)kt * 1024;
+    // tile kt of a sequence's fp16 tiles, or of its nc rows of K^{C1}
+    __device__ static inline TilePre load_tile(const void *keys, int kt, int nc, int tid) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(keys) + (int64_t)kt * (DIRECT ? 2048 : 1024);
         TilePre pf;
 #pragma unroll
-        for (int r = 0; r < NCH; ++r) pf.c[r] = src[tid + r * NTHR];
+        for (int r = 0; r < NCH; ++r) {
+            const int c = tid + r * NTHR;
+            if (DIRECT) {
+                const bool in = kt * kBlock + (c >> 4) < nc;
+                pf.c[2 * r] = in ? src[2 * c] : make_uint4(0, 0, 0, 0);
+                pf.c[2 * r + 1] = in ? src[2 * c + 1] : make_uint4(0, 0, 0, 0);
+            } else {
+                pf.c[r] = src[c];
+            }
+        }
         return pf;
     }
     // registers -> LDS (padded rows), then a workgroup barrier: every thread calls it
@@ -435,6 +447,48 @@ struct ScoreKernel {
             *reinterpret_cast<uint4 *>(tile + (c >> 4) * SKS + (c & 15) * 8) = pf.c[r];
         }
         __syncthreads();
+    }
+    // The same with the conversion of kc_half_kernel on the way.  Returns the tile's shift, 0 unless a magnitude reaches 2^15:
+    // each wavefront says whether it holds one (flags), and only then the tile's largest is looked for and the tile staged again.
+    __device__ static inline int stage_direct(_Float16 *tile, int tid, const TilePre pf, float cm, int *flags, float *tops) {
+        const int lane = tid & 63, w = tid >> 6;
+        auto element = [&](int i) -> float {
+            const uint32_t u[4] = {pf.c[i >> 2].x, pf.c[i >> 2].y, pf.c[i >> 2].z, pf.c[i >> 2].w};
+            return __uint_as_float(u[i & 3]);
+        };
+        auto put = [&](float f) {
+#pragma unroll
+            for (int r = 0; r < NCH; ++r) {
+                const int c = tid + r * NTHR;
+                half8 hv;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) hv[e] = (_Float16)(element(8 * r + e) * f);
+                *reinterpret_cast<half8 *>(tile + (c >> 4) * SKS + (c & 15) * 8) = hv;
+            }
+        };
+        put(cm);
+        float top = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8 * NCH; ++i) top = fmaxf(top, fabsf(element(i)));
+        const bool large = __any(!(top < S_FP16_SAFE));
+        if (lane == 0) flags[w] = large;
+        __syncthreads();
+        int any = 0;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) any |= flags[k];
+        if (__builtin_amdgcn_readfirstlane(any) == 0) return 0;
+        top = wave64_max(top);
+        if (lane == 0) tops[w] = top;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NW; ++k) top = fmaxf(top, tops[k]);
+        if (!(top < 3.0e38f)) top = 3.0e38f;              // as in kc_half_kernel
+        int ek = 0;
+        (void)frexpf(top, &ek);
+        const int shift = __builtin_amdgcn_readfirstlane(max(0, ek - 15));
+        put(__builtin_ldexpf(cm, -shift));
+        __syncthreads();
+        return shift;
     }
 
     template <bool SEEDED>
@@ -463,7 +517,8 @@ struct ScoreKernel {
     template <int POOL>
     __device__ static void run(const ScoreArgs &a, int num_tiles) {
         extern __shared__ __attribute__((aligned(16))) _Float16 smem[];     // two tiles (double buffer)
-        __shared__ int s_where[4];
+        __shared__ int s_where[4], s_flags[2][NW];
+        __shared__ float s_tops[NW];
         const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int h = blockIdx.y;
         const int tile_id = num_tiles - 1 - (int)blockIdx.x;     // longest rows first
@@ -504,10 +559,11 @@ struct ScoreKernel {
         const int nkt = (vis_last + kBlock - 1) / kBlock;
         const int row0 = tok0 + t0;
         // this sequence's key tiles and their shifts (wave-uniform addresses)
-        const _Float16 *kt_fine = a.fine.data + ((int64_t)h * a.fine.tiles + tb_fine) * (kBlock * SD);
+        const void *kt_fine = a.fine.data + ((int64_t)h * a.fine.tiles + tb_fine) * (kBlock * SD);
         const int32_t *sh_fine = a.fine.shift + (int64_t)h * a.fine.tiles + tb_fine;
-        const _Float16 *kt_coarse = a.lse_mode ? a.coarse.data + ((int64_t)h * a.coarse.tiles + tb_coarse) * (kBlock * SD) : kt_fine;
+        const void *kt_coarse = a.lse_mode ? a.coarse.data + ((int64_t)h * a.coarse.tiles + tb_coarse) * (kBlock * SD) : kt_fine;
         const int32_t *sh_coarse = a.lse_mode ? a.coarse.shift + (int64_t)h * a.coarse.tiles + tb_coarse : sh_fine;
+        if (DIRECT) kt_fine = kt_coarse = a.kc + ((int64_t)h * a.map.kc_total_c + a.map.cu_c[seq]) * SD;      // (lse_mode 0)
         const int n16 = lane & 15, g = lane >> 4;
 
         // ---- Q rows of this wave's tokens: bf16 -> fp16, times a power of two (exact).  With
@@ -516,7 +572,7 @@ struct ScoreKernel {
         // A token whose magnitudes would leave fp16's comfortable range that way gets its own exponent instead and
         // takes the slower path that multiplies the accumulator by the difference.
         int ce;
-        (void)frexpf(a.scale * S_LOG2E, &ce);
+        const float cm = frexpf(a.scale * S_LOG2E, &ce);
         ce = __builtin_amdgcn_readfirstlane(ce);
         half8 qf[TPW][4];
         int vis[TPW];
@@ -545,7 +601,7 @@ struct ScoreKernel {
         const int vis1_last = a.lse_mode == 0 ? vis_last : min(coarse_count(t0 + ntok), nc2);
         const int nkt1 = (vis1_last + kBlock - 1) / kBlock;
         TilePre first = {};
-        if (nkt1 > 0) first = load_tile(kt_coarse, 0, tid);
+        if (nkt1 > 0) first = load_tile(kt_coarse, 0, nc, tid);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < TPW; ++i) {
@@ -580,9 +636,14 @@ struct ScoreKernel {
         }
 
         // Matrix-core step of either pass: acc = y - seed for tile kt (y = the logit in the log2 domain)
+        int direct_shift = 0;                          // DIRECT: of the tile staged last
+        auto stage = [&](int kt, const TilePre pf) {
+            if constexpr (DIRECT) direct_shift = stage_direct(smem + (kt & 1) * S_TILE, tid, pf, cm, s_flags[kt & 1], s_tops);
+            else stage_tile(smem + (kt & 1) * S_TILE, tid, pf);
+        };
         auto mma = [&](int kt, const int32_t *shifts, const f32x4 (&seed)[TPW]) {
             const _Float16 *tile = smem + (kt & 1) * S_TILE;
-            const int tshift = shifts[kt];
+            const int tshift = DIRECT ? direct_shift : shifts[kt];
             if (q_plain && tshift == 0) {
                 tile_mma<true>(qf, tile, lane, acc, seed);
             } else {
@@ -654,13 +715,13 @@ struct ScoreKernel {
                 for (int r = 0; r < 4; ++r) l[i][r] = 0.f;
             }
             TilePre pf = first;
-            if (nkt1 > 0) stage_tile(smem, tid, tracked ? load_tile(kt_coarse, 0, tid) : first);
+            if (nkt1 > 0) stage(0, tracked ? load_tile(kt_coarse, 0, nc, tid) : first);
             for (int kt = 0; kt < nkt1; ++kt) {
-                if (kt + 1 < nkt1) pf = load_tile(kt_coarse, kt + 1, tid);
+                if (kt + 1 < nkt1) pf = load_tile(kt_coarse, kt + 1, nc, tid);
                 if (late && kt > 0) vec1(kt - 1, tracked_c);
                 mma(kt, sh_coarse, nm);
                 if (!late) vec1(kt, tracked_c);
-                if (kt + 1 < nkt1) stage_tile(smem + ((kt + 1) & 1) * S_TILE, tid, pf);
+                if (kt + 1 < nkt1) stage(kt + 1, pf);
                 else __syncthreads();
             }
             if (late && nkt1 > 0) vec1(nkt1 - 1, tracked_c);
@@ -758,14 +819,14 @@ struct ScoreKernel {
             for (int i = 0; i < TPW; ++i)
                 if (lane == 0 && written(jb, vis[i])) out_w[i * a.row_stride + jb] = __uint_as_float(carry[i]);
         };
-        TilePre pf = load_tile(kt_fine, 0, tid);
-        stage_tile(smem, tid, pf);
+        TilePre pf = load_tile(kt_fine, 0, nc, tid);
+        stage(0, pf);
         for (int kt = 0; kt < nkt; ++kt) {
-            if (kt + 1 < nkt) pf = load_tile(kt_fine, kt + 1, tid);
+            if (kt + 1 < nkt) pf = load_tile(kt_fine, kt + 1, nc, tid);
             if (late && kt > 0) vec2(kt - 1);
             mma(kt, sh_fine, nlse);
             if (!late) vec2(kt);
-            if (kt + 1 < nkt) stage_tile(smem + ((kt + 1) & 1) * S_TILE, tid, pf);
+            if (kt + 1 < nkt) stage(kt + 1, pf);
             else __syncthreads();
         }
         if (late) vec2(nkt - 1);
@@ -773,12 +834,12 @@ struct ScoreKernel {
     }
 };
 
-template <int NW, int TPW, int POOL>
+template <int NW, int TPW, int POOL, bool DIRECT>
 __global__ void __launch_bounds__(NW * 64) block_scores_mfma_kernel(ScoreArgs a, int num_tiles) {
-    ScoreKernel<NW, TPW>::template run<POOL>(a, num_tiles);
+    ScoreKernel<NW, TPW, DIRECT>::template run<POOL>(a, num_tiles);
 }
 
-template <int NW, int TPW, int POOL>
+template <int NW, int TPW, int POOL, bool DIRECT>
 int launch_scores_mfma(const Launch &L, ScoreArgs a, const int32_t *cu_h) {
     constexpr int T = NW * TPW;
     int64_t tiles = 0, kt_fine = 0, kt_coarse = 0;
@@ -801,20 +862,21 @@ int launch_scores_mfma(const Launch &L, ScoreArgs a, const int32_t *cu_h) {
     int32_t *sh_fine = (int32_t *)((char *)ws + data_bytes), *sh_coarse = sh_fine + (size_t)hkv * kt_fine;
     int ce;
     const float cm = frexpf(a.scale * S_LOG2E, &ce);
-    hipLaunchKernelGGL(kc_half_kernel, dim3((unsigned)(kt_fine + kt_coarse), hkv), dim3(256), 0, L.stream, a.kc, L.map,
+    if (!DIRECT)
+        hipLaunchKernelGGL(kc_half_kernel, dim3((unsigned)(kt_fine + kt_coarse), hkv), dim3(256), 0, L.stream, a.kc, L.map,
                        a.lc, a.sc, a.dense_below, cm, fine, sh_fine, (int)kt_fine, coarse, sh_coarse, (int)kt_coarse);
     a.fine = HalfTiles{fine, sh_fine, (int32_t)kt_fine};
     a.coarse = HalfTiles{coarse, sh_coarse, (int32_t)kt_coarse};
     const size_t lds = (size_t)2 * S_TILE * sizeof(_Float16);
     dim3 grid((unsigned)tiles, hkv);
-    hipLaunchKernelGGL((block_scores_mfma_kernel<NW, TPW, POOL>), grid, dim3(NW * 64), lds, L.stream, a, (int)tiles);
+    hipLaunchKernelGGL((block_scores_mfma_kernel<NW, TPW, POOL, DIRECT>), grid, dim3(NW * 64), lds, L.stream, a, (int)tiles);
     return hip_status(hipGetLastError());
 }
 
-template <int NW, int TPW>
+template <int NW, int TPW, bool DIRECT = false>
 int launch_scores_pool(const Launch &L, const ScoreArgs &a, const int32_t *cu_h, int pool) {
-    if (pool < 0) return launch_scores_mfma<NW, TPW, -1>(L, a, cu_h);
-    return pool == 0 ? launch_scores_mfma<NW, TPW, 0>(L, a, cu_h) : launch_scores_mfma<NW, TPW, 1>(L, a, cu_h);
+    if (pool < 0) return launch_scores_mfma<NW, TPW, -1, DIRECT>(L, a, cu_h);
+    return pool == 0 ? launch_scores_mfma<NW, TPW, 0, DIRECT>(L, a, cu_h) : launch_scores_mfma<NW, TPW, 1, DIRECT>(L, a, cu_h);
 }
 
 bool scores_mfma_params(const infllmv2_params *p, bool pooled) {
@@ -846,14 +908,22 @@ int launch_block_scores(const Launch &L, const void *q, const float *kc, float *
         // Four tokens per wavefront, so that a key fragment read from LDS feeds four products; fewer for short prompts, whose
         // time is what one workgroup takes from its first load to its last store.  Kernel with one / two / four on 2 KV
         // heads: 777 tokens 7.2 / 9.0 / 13.1 us, 1500 tokens 9.9 / 11.2 / 16.6, 2000 tokens 12.2 / 11.8 / 17.2, 3000 tokens
-        // 19.9 / 19.8 / 21.3, 4000 tokens 28.2 / 24.8 / 26.0, 4500 tokens 31.8 / 34.1 / 31.5.
+        // 19.9 / 19.8 / 21.3, 4000 tokens 28.2 / 24.8 / 26.0, 4500 tokens 31.8 / 34.1 / 31.5.  With one and two (and the exact
+        // normalisation) a workgroup also converts the few key tiles it needs: the kernel then takes as long (777 tokens 7.8 ->
+        // 8.0 us, 2000 tokens 12.2 -> 13.4, 4000 tokens 25 -> 29), and a pre-pass of 3.9 to 4.9 us and its launch are gone.
         int64_t tiles8 = 0, tiles16 = 0;
         for (int s = 0; s < L.map.batch; ++s) {
             tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
             tiles16 += (cu_h[s + 1] - cu_h[s] + 15) / 16;
         }
-        if (tiles8 * L.p->num_kv_heads <= 384) return launch_scores_pool<8, 1>(L, a, cu_h, pooled ? pool.pad : -1);
-        if (tiles16 * L.p->num_kv_heads <= 512) return launch_scores_pool<8, 2>(L, a, cu_h, pooled ? pool.pad : -1);
+        if (tiles8 * L.p->num_kv_heads <= 384) {
+            if (a.lse_mode == 0) return launch_scores_pool<8, 1, true>(L, a, cu_h, pooled ? pool.pad : -1);
+            return launch_scores_pool<8, 1>(L, a, cu_h, pooled ? pool.pad : -1);
+        }
+        if (tiles16 * L.p->num_kv_heads <= 512) {
+            if (a.lse_mode == 0) return launch_scores_pool<8, 2, true>(L, a, cu_h, pooled ? pool.pad : -1);
+            return launch_scores_pool<8, 2>(L, a, cu_h, pooled ? pool.pad : -1);
+        }
         return launch_scores_pool<8, 4>(L, a, cu_h, pooled ? pool.pad : -1);
     }
     if (L.p->head_dim == 128)
