@@ -15,9 +15,6 @@ __device__ inline bool list_has(const int32_t *e, int n, int j) {
     return lo < n && e[lo] == j;
 }
 
-// dk[0 .. n) = dv[0 .. n) = 0 by one launch (attn_bwd_mfma.hip); n % 4 == 0, both 16-byte aligned
-void launch_bwd_zero(float *dk, float *dv, int64_t n, hipStream_t stream);
-
 // the matrix-core path's arguments
 struct BwdM {
     const uint16_t *q, *k, *v, *out, *dout;

@@ -22,6 +22,8 @@
 // products' operands and sums in vector registers instead of copied to and from accumulators, which took the fp32 kernel
 // from 346 to 251 us at 2000 tokens; with its atomic adds as the accumulators lie in registers instead of through LDS dkv took
 // 490 us).
+#include <algorithm>
+
 #include "attn_bwd.h"
 #include "gen_unit.h"
 
@@ -354,6 +356,13 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
     }
 }
 
+// dk[0 .. n) = dv[0 .. n) = 0 by one launch; n % 4 == 0, both 16-byte aligned
+__global__ void __launch_bounds__(256) bwd_zero_kernel(float4 *dk, float4 *dv, int64_t n4) {
+    float4 *p = blockIdx.y ? dv : dk;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256)
+        p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
 template <typename T, int D, int CG>
 void launch_dq(const Launch &L, const BwdArgs<T> &a) {
     const int tokens = CG * tile_tokens(L.map, a.hq / L.map.num_kv_heads);
@@ -373,7 +382,9 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     void *ws = L.ws;         // <dO, O> per (row, head)
     if (ws == nullptr || L.ws_bytes < (size_t)rows * a.hq * sizeof(float)) return INFLLMV2_ERR_WORKSPACE_TOO_SMALL;
     a.delta = (float *)ws;
-    launch_bwd_zero(a.dk, a.dv, rows * hkv * D, L.stream);
+    const int64_t n4 = rows * hkv * D / 4;
+    hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 8192), 2), dim3(256), 0, L.stream,
+                       (float4 *)a.dk, (float4 *)a.dv, n4);
     hipLaunchKernelGGL((bwd_delta_kernel<T, D>), dim3((unsigned)((rows * a.hq + 3) / 4)), dim3(256), 0, L.stream, a);
     // Column groups per wavefront as in the forward kernel; by tiles of one group times KV heads, one / two groups: bf16 d 128:
     // 250 tiles 15.0 / 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1; fp32 d 64: 400 38 / 34, 800 74 / 58.  (fp32

@@ -394,16 +394,19 @@ int launch_bwd_dkv(const BwdM &a, const int32_t *cu_h, int32_t max_len, hipStrea
     // us, 1500 tokens 283 / 235 / 270 / 370 / 581, 2000 tokens 376 / 360 / 321 / 408 / 619, 3000 tokens 580 / 539 / 551 / 499
     // / 716, 8000 tokens 2.63 / 2.09 / 2.04 / 2.07 / 2.15 ms, 16000 tokens - / 5.53 / 4.86 / 4.68 / 4.77, 32768 tokens
     // - / - / 12.5 / 11.15 / 11.0, with chunks of 1024 10.94.
-    int chunk = 32;
+    // Every sequence gets the chunks of the longest (those past its end leave at once: 440000 of them beside a sequence of 32768
+    // tokens do not show), and a launch has fewer than 2^32 threads in x, which bounds the chunks from below.
+    auto groups = [&](int c) { return (max_len + c - 1) / c * a.map.num_kv_heads; };
+    auto launched = [&](int c) { return 8ll * ((groups(c) + 7) / 8) * a.nblocks; };
+    constexpr int64_t kMost = 0xffffffffll / 64;
+    if (launched(MAX_CHUNK) > kMost) return INFLLMV2_ERR_UNSUPPORTED;
+    int chunk = MAX_CHUNK;
     float best = dkv_cost(a, cu_h, max_len, chunk);
-    for (int c = 64; c <= MAX_CHUNK; c *= 2) {
+    for (int c = MAX_CHUNK / 2; c >= 32 && launched(c) <= kMost; c /= 2) {
         const float cost = dkv_cost(a, cu_h, max_len, c);
-        if (cost < best) { best = cost; chunk = c; }
+        if (cost <= best) { best = cost; chunk = c; }
     }
-    const int groups = (max_len + chunk - 1) / chunk * a.map.num_kv_heads;
-    const int64_t wgs = 8ll * ((groups + 7) / 8) * a.nblocks;
-    if (wgs > 0xffffffffll / 64) return INFLLMV2_ERR_UNSUPPORTED;       // (a launch has fewer than 2^32 threads in x)
-    hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3((unsigned)wgs), dim3(64), 0, stream, a, chunk, groups);
+    hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3((unsigned)launched(chunk)), dim3(64), 0, stream, a, chunk, groups(chunk));
     return hip_status(hipGetLastError());
 }
 

@@ -93,18 +93,7 @@ __global__ void __launch_bounds__(BITS_WAVES * 64) bwd_sel_bits_kernel(BwdM a) {
             rows[(int64_t)(i / BITS_WORDS) * words + (i & (BITS_WORDS - 1))] = bits[i / BITS_WORDS * BITS_ROW + (i & (BITS_WORDS - 1))];
 }
 
-__global__ void __launch_bounds__(256) bwd_zero_kernel(float4 *dk, float4 *dv, int64_t n4) {
-    float4 *p = blockIdx.y ? dv : dk;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256)
-        p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-
 }  // namespace
-
-void launch_bwd_zero(float *dk, float *dv, int64_t n, hipStream_t stream) {
-    const unsigned groups = (unsigned)std::min<int64_t>((n / 4 + 255) / 256, 8192);
-    hipLaunchKernelGGL(bwd_zero_kernel, dim3(groups, 2), dim3(256), 0, stream, (float4 *)dk, (float4 *)dv, n / 4);
-}
 
 bool bwd_mfma_params(const infllmv2_params *p) {
     return p->dtype == INFLLMV2_BF16 && p->head_dim == D && p->num_q_heads / p->num_kv_heads == G;
