@@ -396,11 +396,29 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
         if (two) launch_dq<T, D, 2>(L, a);
     }
     if (!two) launch_dq<T, D, 1>(L, a);
-    // Tokens per dkv workgroup: 256, or down to 64 while the launch would leave CUs without several workgroups (half of the
-    // (block, chunk) pairs of a causal sequence are empty).  Training step with 256 / 128 / 64, 8 heads on 2, bf16: 500
-    // tokens 128 / 85 / 64 us, 4000 tokens 545 / 537 / 632, 8000 tokens 1180 / 1218 / 1340.
+    // Tokens per dkv workgroup: as many (256 at most) as leave 256 workgroups with work, but not so many that these make little
+    // more than the two rounds of 256 that the chip takes at once.  Training step with 256 / 128 / 64 / 32, 8 heads on 2, bf16:
+    // 300 tokens 106 / 68 / 50 / 41 us, 1000 tokens 133 / 97 / 88 / 100, 1985 tokens 209 / 217 / 237 / 247, 2500 tokens 268 /
+    // 276 / 310 / 367, 3300 tokens (728 workgroups with 256) 428 / 414 / 452 / 553, 4000 tokens 713 / 738 / 719 / 831; fp32, 1000
+    // tokens 282 / 200 / 191 / 201.  The smaller workgroups of d 64 are better shorter: 1400 fp32 tokens 221 / 176 / 154 / 165,
+    // 4000 bf16 tokens 405 / 410 / 375 / 423.
+    // So are lists that leave blocks out, whose workgroups differ more: 1985 bf16 tokens with 16 blocks each 203 with 256, 197 with 64.
+    auto busy = [&](int c) {                     // workgroups whose chunk does not end before their block (causal)
+        int64_t n = 0;
+        for (int s = 0; s < L.map.batch; ++s) {
+            const int64_t len = cu_h[s + 1] - cu_h[s];
+            n += (len + c - 1) / c * ((len + kBlock - 1) / kBlock + std::max(c / kBlock, 1)) / 2 * hkv;
+        }
+        return n;
+    };
     int chunk = BWD_CHUNK;
-    while (chunk > 64 && nblocks * ((L.max_len + chunk - 1) / chunk) * hkv < 2048) chunk /= 2;
+    if (D == 128 && (L.max_len + kBlock - 1) / kBlock <= L.p->topk_total) {
+        while (chunk > 32 && busy(chunk) < 256) chunk /= 2;
+        if (chunk == BWD_CHUNK && busy(chunk) > 512 && busy(chunk) <= 768) chunk /= 2;
+    } else {
+        while (chunk > 64 && nblocks * ((L.max_len + chunk - 1) / chunk) * hkv < 2048) chunk /= 2;
+        if (chunk == 64 && busy(chunk) < 256) chunk = 32;
+    }
     const unsigned chunks = (unsigned)((L.max_len + chunk - 1) / chunk);
     hipLaunchKernelGGL((bwd_dkv_kernel<T, D>), dim3(chunks, (unsigned)nblocks, hkv), dim3(NW * 64), 0, L.stream, a, chunk);
     return hip_status(hipGetLastError());

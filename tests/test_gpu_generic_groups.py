@@ -76,3 +76,14 @@ def test_strided_rows(m, oracle):  # noqa: F811
             assert (x - y).abs().max() <= 2e-5 * float(y.abs().max())
         del buf, ks, vs
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,lens", [
+    ("bf16", 8, 2, 128, [33]), ("bf16", 8, 2, 128, [31, 300, 32, 1]), ("fp32", 8, 2, 128, [289]), ("bf16", 8, 2, 64, [97, 160]),
+    ("fp32", 8, 2, 64, [350]), ("bf16", 8, 8, 128, [500]), ("bf16", 16, 16, 128, [700, 65]),
+])
+def test_token_chunks_of_dkv(m, oracle, dtype, hq, hkv, d, lens):  # noqa: F811
+    """Chunks from 32 to 256 tokens, with ends inside and at the edge of a chunk."""
+    w = synth.make_varlen(lens, hq, hkv, d, seed=2950 + sum(lens) + d, dtype=dtype)
+    gp, op = _params(m, oracle, dtype, hq, hkv, d, n_init=1, n_local=1, topk_total=4)
+    _check_backward(m, oracle, w, gp, op, dtype)
