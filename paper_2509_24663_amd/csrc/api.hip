@@ -7,7 +7,7 @@ using namespace ifv2;
 
 namespace ifv2 {
 int launch_attn_generic(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx,
-                        int dense_below, void *out, float *lse);
+                        int dense_below, void *out, float *lse, const int32_t *cu_h);
 int launch_attn_mfma(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx,
                      int dense_below, void *out, float *lse, const int32_t *cu_h);
 bool attn_mfma_supported(const infllmv2_params *p);
@@ -372,7 +372,7 @@ int infllmv2_sparse_decode(const infllmv2_params *p, const void *q_d, const void
     if (st) return st;
     st = launch_topk(L, scores, (int64_t)rs, idx, false);
     if (st) return st;
-    return launch_attn_generic(L, q_d, k_cache_d, v_cache_d, idx, p->dense_threshold, out_d, lse_d);
+    return launch_attn_generic(L, q_d, k_cache_d, v_cache_d, idx, p->dense_threshold, out_d, lse_d, nullptr);
 }
 
 }  // extern "C"
@@ -419,6 +419,6 @@ int launch_attn(const Launch &L, const void *q, const void *k, const void *v, co
         const int rc = launch_attn_mfma(L, q, k, v, idx, dense_below, out, lse, cu_h);
         if (rc != INFLLMV2_ERR_UNSUPPORTED) return rc;      // strides or sizes outside the tile kernel's limits
     }
-    return launch_attn_generic(L, q, k, v, idx, dense_below, out, lse);
+    return launch_attn_generic(L, q, k, v, idx, dense_below, out, lse, cu_h);
 }
 }  // namespace ifv2

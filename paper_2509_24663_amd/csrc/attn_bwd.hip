@@ -26,6 +26,7 @@
 
 #include "attn_bwd.h"
 #include "gen_unit.h"
+#include "launch_rules.h"
 
 namespace ifv2 {
 
@@ -109,7 +110,7 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
             for (int j = 0; j < N; ++j) acc[x][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int c0 = 0; c0 < nblk; c0 += kChunk) {
             un.build(lists, a.topk_total, t, c0, nblk, all, tid, NW * 64);
-            const int items = 2 * un.count;              // half blocks
+            const int items = un.half_blocks(t);
             RowFrag<T, D> kf[2], vf[2];
             Spread<T, D> kr[2][4];
             int2 ent = {0, 0};
@@ -386,13 +387,10 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 8192), 2), dim3(256), 0, L.stream,
                        (float4 *)a.dk, (float4 *)a.dv, n4);
     hipLaunchKernelGGL((bwd_delta_kernel<T, D>), dim3((unsigned)((rows * a.hq + 3) / 4)), dim3(256), 0, L.stream, a);
-    // Column groups per wavefront as in the forward kernel; by tiles of one group times KV heads, one / two groups: bf16 d 128:
-    // 250 tiles 15.0 / 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1; fp32 d 64: 400 38 / 34, 800 74 / 58.  (fp32
-    // d 128: two groups need 54 registers more than there are.)
-    const int tokens = tile_tokens(L.map, a.hq / hkv);
     bool two = false;
     if constexpr (D * sizeof(T) < 512) {
-        two = (rows / tokens + L.map.batch - 1) * hkv > (sizeof(T) == 2 ? 280 : 350);
+        two = rules::generic_dq_two_groups(sizeof(T) == 2, D, hkv, rules::walks(cu_h, L.map.batch, tile_tokens(L.map, a.hq / hkv),
+                                                                               a.idx != nullptr, a.topk_total, a.dense_below));
         if (two) launch_dq<T, D, 2>(L, a);
     }
     if (!two) launch_dq<T, D, 1>(L, a);

@@ -8,17 +8,18 @@
 // softmax state of its own, and the partial results are merged in LDS at the end.  Operands come straight from global
 // memory: a K row fragment is what the row product wants as it is, a V row is spread over the 16 lanes of a group, so
 // nothing passes through LDS and no barrier stands between blocks.  The rows of the next half block are requested as soon
-// as the registers of this one's are free.
+// as the registers of this one's are free (AHEAD), or, in launches of many workgroups, as late as they are needed: fewer
+// registers, one wavefront more per SIMD (launch_rules.h).
 //
 // What bounds it: bf16, the trips of the rows from the L2 to the CUs (12 TB/s), which is why two column groups share them;
 // fp32, the products (32 clocks each) and how evenly a tile's half blocks fall on its wavefronts.  Half as many vector
 // instructions (rows addressed by a scalar base and a constant lane offset, products over 32 keys, no checks for
 // infinities in the first pass, sums rescaled only when a logit is larger than all before) alone took the bf16 case below
 // from 58 to 47 us.  Measured: fp32, 2048 tokens, 4 heads on 1, d 64, 8 blocks: 34 -> 30 us; bf16, 1985 tokens, 8 heads
-// on 2, d 128, 16 blocks: 58 -> 41 us; fp32, 600 / 2000 tokens, 8 heads on 2, d 128: 36 -> 22, 131 -> 128 us.  Taken back: the
-// wavefronts of two tiles side by side, meeting in the L1 (51 us), three and four wavefronts per SIMD without the rows
-// requested ahead (50 - 55 us).
+// on 2, d 128, 16 blocks: 58 -> 39 us; fp32, 600 / 2000 tokens, 8 heads on 2, d 128: 36 -> 20, 131 -> 113 us; bf16, 4000 tokens,
+// 8 heads on 2, d 128: 153 -> 95 us.  Taken back: the wavefronts of two tiles side by side, meeting in the L1 (51 us).
 #include "gen_unit.h"
+#include "launch_rules.h"
 
 namespace ifv2 {
 
@@ -27,7 +28,7 @@ namespace {
 using namespace gen;
 
 constexpr int NW = 4;             // wavefronts per workgroup
-template <typename T, int D, int CG>
+template <typename T, int D, int CG, bool AHEAD>
 __global__ void __launch_bounds__(NW * 64)
 attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
                     const int32_t *__restrict__ idx, int topk_total, int dense_below, RowMap map, int hq,
@@ -79,7 +80,7 @@ attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *_
         }
         for (int c0 = 0; c0 < nblk; c0 += kChunk) {
             un.build(lists, topk_total, t, c0, nblk, all, tid, NW * 64);
-            const int items = 2 * un.count;              // half blocks
+            const int items = un.half_blocks(t);
             RowFrag<T, D> kf[2];
             Spread<T, D> vr[2][4];
             int2 ent = {0, 0};
@@ -90,12 +91,16 @@ attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *_
                 return ent.x * kBlock + 32 * (it & 1);
             };
             int u0 = 0;
-            if (w < items) {
+            if (AHEAD && w < items) {
                 u0 = key_of(w);
                 krows.frags(kf, u0, m, g);
                 vrows.spread(vr, u0, m, g);
             }
             for (int it = w; it < items; it += NW) {
+                if (!AHEAD) {
+                    u0 = key_of(it);
+                    krows.frags(kf, u0, m, g);
+                }
                 f32x4 s[CG][2];
 #pragma unroll
                 for (int x = 0; x < CG; ++x)
@@ -104,7 +109,8 @@ attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *_
                 // lane: keys 16 kt + 4 g + r of the half block
                 const int here = u0;
                 const uint32_t takers = (uint32_t)ent.y;
-                const bool more = it + NW < items;
+                const bool more = AHEAD && it + NW < items;
+                if (!AHEAD) vrows.spread(vr, u0, m, g);
                 if (more) {                              // the next half block's K rows, while this one's softmax runs
                     u0 = key_of(it + NW);
                     krows.frags(kf, u0, m, g);
@@ -215,13 +221,13 @@ attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *_
     }
 }
 
-template <typename T, int D, int CG>
+template <typename T, int D, int CG, bool AHEAD>
 int launch_cg(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, void *out,
               float *lse) {
     const int tokens = CG * tile_tokens(L.map, L.p->num_q_heads / L.p->num_kv_heads);
     // at most this many tiles (every sequence may end with a partial one)
     const unsigned tiles = L.map.ctx ? L.map.total_rows : L.map.total_rows / tokens + L.map.batch;
-    hipLaunchKernelGGL((attn_generic_kernel<T, D, CG>), dim3(tiles, L.p->num_kv_heads), dim3(NW * 64), 0, L.stream,
+    hipLaunchKernelGGL((attn_generic_kernel<T, D, CG, AHEAD>), dim3(tiles, L.p->num_kv_heads), dim3(NW * 64), 0, L.stream,
                        (const T *)q, (const T *)k, (const T *)v, idx, L.p->topk_total, dense_below, L.map,
                        L.p->num_q_heads, L.p->softmax_scale, (T *)out, lse);
     return hip_status(hipGetLastError());
@@ -229,30 +235,31 @@ int launch_cg(const Launch &L, const void *q, const void *k, const void *v, cons
 
 template <typename T, int D>
 int launch_t(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, void *out,
-             float *lse) {
+             float *lse, const int32_t *cu_h) {
     if (L.map.total_rows == 0) return INFLLMV2_OK;
-    // Two column groups per wavefront: a K or V row read (and a V row spread) serves twice the columns, for half as many
-    // wavefronts.  By tiles of one group times KV heads, one / two groups: bf16 d 128: 300 tiles 12.8 / 13.8 us, 400 18.6 / 16.7,
-    // 994 46.8 / 40.5; d 64: 400 12.8 / 13.3, 600 18.8 / 17.9.  fp32 is bound by its products (d 64, 1200 tiles 84 / 88; d 128: the
-    // registers do not suffice for two groups), and a decode call has one token per tile.
-    if constexpr (sizeof(T) == 2) {
-        const int tokens = tile_tokens(L.map, L.p->num_q_heads / L.p->num_kv_heads);
-        if (L.map.ctx == nullptr && (int64_t)(L.map.total_rows / tokens + L.map.batch - 1) * L.p->num_kv_heads > 380)
-            return launch_cg<T, D, 2>(L, q, k, v, idx, dense_below, out, lse);
-    }
-    return launch_cg<T, D, 1>(L, q, k, v, idx, dense_below, out, lse);
+    if (L.map.ctx != nullptr) return launch_cg<T, D, 1, true>(L, q, k, v, idx, dense_below, out, lse);      // (one token per tile)
+    const int hkv = L.p->num_kv_heads;
+    const rules::Walks x = rules::walks(cu_h, L.map.batch, tile_tokens(L.map, L.p->num_q_heads / hkv), idx != nullptr,
+                                        L.p->topk_total, dense_below);
+    const rules::GenericForm form = rules::generic_form(sizeof(T) == 2, D, hkv, x);
+    if constexpr (sizeof(T) == 2)
+        if (form.groups == 2)
+            return form.ahead ? launch_cg<T, D, 2, true>(L, q, k, v, idx, dense_below, out, lse)
+                              : launch_cg<T, D, 2, false>(L, q, k, v, idx, dense_below, out, lse);
+    return form.ahead ? launch_cg<T, D, 1, true>(L, q, k, v, idx, dense_below, out, lse)
+                      : launch_cg<T, D, 1, false>(L, q, k, v, idx, dense_below, out, lse);
 }
 
 }  // namespace
 
 int launch_attn_generic(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx,
-                        int dense_below, void *out, float *lse) {
+                        int dense_below, void *out, float *lse, const int32_t *cu_h) {
     const bool bf = L.p->dtype == INFLLMV2_BF16;
     if (L.p->head_dim == 128)
-        return bf ? launch_t<bf16_t, 128>(L, q, k, v, idx, dense_below, out, lse)
-                  : launch_t<float, 128>(L, q, k, v, idx, dense_below, out, lse);
-    return bf ? launch_t<bf16_t, 64>(L, q, k, v, idx, dense_below, out, lse)
-              : launch_t<float, 64>(L, q, k, v, idx, dense_below, out, lse);
+        return bf ? launch_t<bf16_t, 128>(L, q, k, v, idx, dense_below, out, lse, cu_h)
+                  : launch_t<float, 128>(L, q, k, v, idx, dense_below, out, lse, cu_h);
+    return bf ? launch_t<bf16_t, 64>(L, q, k, v, idx, dense_below, out, lse, cu_h)
+              : launch_t<float, 64>(L, q, k, v, idx, dense_below, out, lse, cu_h);
 }
 
 }  // namespace ifv2

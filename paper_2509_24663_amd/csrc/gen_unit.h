@@ -338,6 +338,10 @@ struct Union {
         }
         __syncthreads();
     }
+    // half blocks (32 keys) of the list; no token of the tile sees the last one if that starts behind all of them
+    __device__ inline int half_blocks(const Tile &t) const {
+        return 2 * count - (count > 0 && list[count - 1].x * kBlock + 32 > t.t0 + t.ntok - 1 ? 1 : 0);
+    }
 };
 
 }  // namespace gen

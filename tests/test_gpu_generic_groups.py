@@ -19,6 +19,12 @@ pytestmark = pytest.mark.gpu
     ("fp32", 8, 2, 64, [705]), ("fp32", 8, 2, 128, [1195]), ("fp32", 8, 2, 128, [1000, 210]),
     ("fp32", 24, 4, 128, [331]),                                              # G = 6: two tokens per group, 12 columns
     ("bf16", 48, 4, 128, [101, 17]),                                          # G = 12: one token per group
+    # many workgroups, rows not requested ahead: one group and two; walks that end in the first half of a block
+    ("bf16", 40, 8, 128, [96, 33, 5, 64, 65, 130]), ("bf16", 40, 8, 64, [31, 32, 200, 1]), ("bf16", 40, 8, 128, [400]),
+    ("bf16", 40, 8, 64, [801]), ("fp32", 40, 8, 128, [100, 33, 5]), ("fp32", 40, 8, 64, [130, 31]),
+    # (no sequence of 3 tokens among these: Delta = <dO, O> of a bf16 O is off by 2^-9 |O| sqrt(64 / 3) = 0.006, dQ by scale |K|
+    # times that = 6e-4, and with three tokens the largest dQ is 0.3: 2e-3 of it on average, as much as the comparison allows)
+    ("bf16", 8, 8, 64, [40, 65, 33] * 14),
 ])
 def test_both_sides_of_the_rules(m, oracle, dtype, hq, hkv, d, lens):  # noqa: F811
     w = synth.make_varlen(lens, hq, hkv, d, seed=2800 + sum(lens) + d, dtype=dtype)

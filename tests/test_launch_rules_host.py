@@ -1,0 +1,58 @@
+"""Which form of a kernel a call takes (csrc/launch_rules.h), compiled for the host: rules that depend on a batch's lengths."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+HARNESS = r"""
+#include "launch_rules.h"
+using namespace ifv2::rules;
+extern "C" void generic(int bf16, int d, int hkv, int tokens, const int *cu, int batch, int sparse, int topk, int below, int *r) {
+    const Walks x = walks(cu, batch, tokens, sparse, topk, below);
+    const GenericForm f = generic_form(bf16, d, hkv, x);
+    r[0] = f.groups;
+    r[1] = f.ahead;
+    r[2] = generic_dq_two_groups(bf16, d, hkv, x);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src = d / "rules.cpp"
+    src.write_text(HARNESS)
+    lib = d / "rules.so"
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2509_24663_amd", "csrc"),
+                           "-o", str(lib), str(src)])
+    return ctypes.CDLL(str(lib))
+
+
+def _cu(lens):
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    return (ctypes.c_int * len(cu))(*cu)
+
+
+def _generic(rules, bf16, d, hq, hkv, lens, topk=16, sparse=1, below=0):
+    r = (ctypes.c_int * 3)()
+    rules.generic(bf16, d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), sparse, topk, below, r)
+    return tuple(r)
+
+
+def test_many_short_sequences_take_one_column_group(rules):
+    """Tiles that end with their sequence have nothing for a second group: the number of sequences alone must not choose it."""
+    for lens in ([4] * 500, [1] * 2000, [10] * 200, [33] * 242, [100] * 40):
+        for bf16, d in ((1, 128), (1, 64), (0, 128), (0, 64)):
+            assert _generic(rules, bf16, d, 8, 2, lens)[:2] == (1, 0), (lens[:1], bf16, d)
+    assert _generic(rules, 1, 128, 8, 2, [4] * 500)[2] == 0 and _generic(rules, 1, 64, 8, 2, [4] * 500)[2] == 0
+    # a long sequence keeps the form it has alone
+    assert _generic(rules, 1, 128, 8, 2, [1985]) == (2, 1, 1)
+    assert _generic(rules, 1, 128, 8, 2, [1985, 3, 5]) == (2, 1, 1)
+    assert _generic(rules, 0, 64, 4, 1, [2048], topk=8) == (1, 1, 1)
+    assert _generic(rules, 1, 128, 8, 2, [6000]) == (2, 0, 1)
+    assert _generic(rules, 1, 128, 8, 2, []) == (1, 1, 0)
