@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(256) bwd_delta_kernel(BwdArgs<T> a) {
     if (lane == 0) a.delta[qhead_row(a.map, qh, a.hq, row)] = s;
 }
 
-template <typename T, int D, int CG>
+template <typename T, int D, int CG, bool AHEAD>
 __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
     constexpr int N = D / 16;
     __shared__ Union un;
@@ -121,13 +121,18 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
                 return ent.x * kBlock + 32 * (it & 1);
             };
             int u0 = 0;
-            if (w < items) {
+            if (AHEAD && w < items) {
                 u0 = key_of(w);
                 krows.frags(kf, u0, m, g);
                 vrows.frags(vf, u0, m, g);
                 krows.spread(kr, u0, m, g);
             }
             for (int it = w; it < items; it += NW) {
+                if (!AHEAD) {
+                    u0 = key_of(it);
+                    krows.frags(kf, u0, m, g);
+                    vrows.frags(vf, u0, m, g);
+                }
                 f32x4 s[CG][2], dp[CG][2];
 #pragma unroll
                 for (int x = 0; x < CG; ++x)
@@ -138,7 +143,8 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
                     }
                 const int here = u0;
                 const uint32_t takers = (uint32_t)ent.y;
-                const bool more = it + NW < items;
+                const bool more = AHEAD && it + NW < items;
+                if (!AHEAD) krows.spread(kr, u0, m, g);
                 if (more) {                              // the next half block's rows, while this one's weights are formed
                     u0 = key_of(it + NW);
                     krows.frags(kf, u0, m, g);
@@ -364,11 +370,11 @@ __global__ void __launch_bounds__(256) bwd_zero_kernel(float4 *dk, float4 *dv, i
         p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-template <typename T, int D, int CG>
+template <typename T, int D, int CG, bool AHEAD>
 void launch_dq(const Launch &L, const BwdArgs<T> &a) {
     const int tokens = CG * tile_tokens(L.map, a.hq / L.map.num_kv_heads);
     // at most this many tiles (every sequence may end with a partial one)
-    hipLaunchKernelGGL((bwd_dq_kernel<T, D, CG>), dim3((unsigned)(L.map.total_rows / tokens + L.map.batch), L.map.num_kv_heads),
+    hipLaunchKernelGGL((bwd_dq_kernel<T, D, CG, AHEAD>), dim3((unsigned)(L.map.total_rows / tokens + L.map.batch), L.map.num_kv_heads),
                        dim3(NW * 64), 0, L.stream, a);
 }
 
@@ -387,13 +393,15 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 8192), 2), dim3(256), 0, L.stream,
                        (float4 *)a.dk, (float4 *)a.dv, n4);
     hipLaunchKernelGGL((bwd_delta_kernel<T, D>), dim3((unsigned)((rows * a.hq + 3) / 4)), dim3(256), 0, L.stream, a);
+    const rules::GenericForm form = rules::generic_dq_form(
+        sizeof(T) == 2, D, hkv, rules::walks(cu_h, L.map.batch, tile_tokens(L.map, a.hq / hkv), a.idx != nullptr, a.topk_total, a.dense_below));
     bool two = false;
     if constexpr (D * sizeof(T) < 512) {
-        two = rules::generic_dq_two_groups(sizeof(T) == 2, D, hkv, rules::walks(cu_h, L.map.batch, tile_tokens(L.map, a.hq / hkv),
-                                                                               a.idx != nullptr, a.topk_total, a.dense_below));
-        if (two) launch_dq<T, D, 2>(L, a);
+        two = form.groups == 2;
+        if (two) launch_dq<T, D, 2, true>(L, a);
     }
-    if (!two) launch_dq<T, D, 1>(L, a);
+    if (!two && form.ahead) launch_dq<T, D, 1, true>(L, a);
+    else if (!two) launch_dq<T, D, 1, false>(L, a);
     // Tokens per dkv workgroup: as many (256 at most) as leave 256 workgroups with work, but not so many that these make little
     // more than the two rounds of 256 that the chip takes at once.  Training step with 256 / 128 / 64 / 32, 8 heads on 2, bf16:
     // 300 tokens 106 / 68 / 50 / 41 us, 1000 tokens 133 / 97 / 88 / 100, 1985 tokens 209 / 217 / 237 / 247, 2500 tokens 268 /

@@ -29,33 +29,38 @@ inline Walks walks(const int32_t *cu_h, int batch, int tokens, bool sparse, int 
     return r;
 }
 
-// Generic attention: column groups per wavefront, and whether a wavefront requests the next half block's rows ahead.
+// Generic attention and dQ: column groups per wavefront, and whether a wavefront requests the next half block's rows ahead.
+//
+// Rows requested ahead shorten a wavefront's walk, but their registers leave a SIMD one wavefront fewer: worth it while the
+// 256 CUs go round fewer times than one of a tile's four wavefronts has half blocks.  fp32 attention, 8 heads on 2, d 128, ahead /
+// not: 600 tokens 20.0 / 25.1 us, 1000 tokens 35.5 / 49.8, 11 x 700 105 / 90, 80 x 100 51 / 41, 2000 x 4 191 / 137; whole backward
+// call, bf16, 8 heads on 2: d 128, 114 x 70 tokens 121 / 110, 500 x 4 53 / 49; d 64, 2000 x 4 223 / 196.
 struct GenericForm {
     int groups;
     bool ahead;
 };
+inline bool rows_ahead(int64_t workgroups, int most, const Walks &x) {
+    return workgroups <= std::min(256. / 4 * x.half_blocks, (double)most);
+}
 inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
-    // Rows requested ahead shorten a wavefront's walk, but their registers leave a SIMD one wavefront fewer: worth it while the
-    // 256 CUs go round fewer times than one of a tile's four wavefronts has half blocks.  fp32, 8 heads on 2, d 128, ahead / not:
-    // 600 tokens 20.0 / 25.1 us, 1000 tokens 35.5 / 49.8, 11 x 700 105 / 90, 80 x 100 51 / 41, 2000 x 4 191 / 137.
-    auto ahead = [&](int64_t tiles, int most) { return tiles * hkv <= std::min(256. / 4 * x.half_blocks, (double)most); };
     // Two column groups: a K or V row read (and a V row spread) serves twice the columns, for half as many wavefronts; worth it
     // for walks of several half blocks.  bf16, 8 heads on 2, d 128, one / two groups: 600 tokens (300 tiles times KV heads) 12.0 /
     // 13.8 us, 1000 tokens (500) 22.3 / 18.4, 4000 tokens 127 / 95, 80 x 100 tokens 36.6 / 38.8, 500 x 4 17.5 / 20.1; d 64: 1000
     // tokens 14.8 / 14.9, 1300 tokens 19.0 / 18.7.  Two groups with rows ahead / without, d 128: 1700 tokens (426 workgroups) 31 /
     // 39, 2000 tokens (500) 38.8 / 47.7, 2500 tokens (626) 59 / 56, 4000 tokens (1000) 118 / 95; d 64: 4000 tokens 65 / 70, 6000
     // tokens (1500) 140 / 126.  fp32 is bound by its products (d 64, 1200 tiles 84 / 88; d 128: the registers do not suffice).
-    if (bf16 && x.half_blocks >= 6 && x.one * hkv > (d == 128 ? 380 : 600)) return {2, ahead(x.two, d == 128 ? 512 : 1024)};
-    return {1, ahead(x.one, 1024)};
+    if (bf16 && x.half_blocks >= 6 && x.one * hkv > (d == 128 ? 380 : 600))
+        return {2, rows_ahead(x.two * hkv, d == 128 ? 512 : 1024, x)};
+    return {1, rows_ahead(x.one * hkv, 1024, x)};
 }
-
-// Generic dQ: two column groups per wavefront (fp32 d 128: two groups need 54 registers more than there are).  By tiles of one
-// group times KV heads, one / two groups: bf16 d 128: 250 tiles 15.0 / 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1;
-// fp32 d 64: 400 38 / 34, 800 74 / 58.  Short walks are too little work per workgroup: whole call, 8 heads on 2, bf16 d 128:
-// 500 x 4 tokens 49 / 63, 57 x 140 tokens (walks of 3 half blocks) 133 / 144, 40 x 200 172 / 180, 6 x 300 64 / 63, 8 x 1000
-// 418 / 389; d 64: 800 x 10 tokens 97 / 102, 10 x 200 39.6 / 35.6.
-inline bool generic_dq_two_groups(bool bf16, int d, int hkv, const Walks &x) {
-    return (bf16 || d == 64) && x.half_blocks >= (d == 128 ? 4 : 2) && x.one * hkv > (bf16 ? 280 : 350);
+// dQ reads K twice, so two groups pay earlier.  By tiles of one group times KV heads, one / two groups: bf16 d 128: 250 tiles 15.0 /
+// 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1; fp32 d 64: 400 38 / 34, 800 74 / 58 (d 128: two groups need 54 registers
+// more than there are).  Short walks are too little work per workgroup: whole call, 8 heads on 2, bf16 d 128: 500 x 4 tokens 49 / 63,
+// 57 x 140 tokens (walks of 3 half blocks) 133 / 144, 40 x 200 172 / 180, 6 x 300 64 / 63, 8 x 1000 418 / 389; d 64: 800 x 10 tokens
+// 97 / 102, 10 x 200 39.6 / 35.6.  Two groups without rows ahead are slower everywhere (d 128, 4000 tokens 394 / 432, 26 x 300 208 / 213).
+inline GenericForm generic_dq_form(bool bf16, int d, int hkv, const Walks &x) {
+    if ((bf16 || d == 64) && x.half_blocks >= (d == 128 ? 4 : 2) && x.one * hkv > (bf16 ? 280 : 350)) return {2, true};
+    return {1, rows_ahead(x.one * hkv, 1024, x)};
 }
 
 }  // namespace rules

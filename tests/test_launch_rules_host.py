@@ -12,10 +12,11 @@ HARNESS = r"""
 using namespace ifv2::rules;
 extern "C" void generic(int bf16, int d, int hkv, int tokens, const int *cu, int batch, int sparse, int topk, int below, int *r) {
     const Walks x = walks(cu, batch, tokens, sparse, topk, below);
-    const GenericForm f = generic_form(bf16, d, hkv, x);
+    const GenericForm f = generic_form(bf16, d, hkv, x), g = generic_dq_form(bf16, d, hkv, x);
     r[0] = f.groups;
     r[1] = f.ahead;
-    r[2] = generic_dq_two_groups(bf16, d, hkv, x);
+    r[2] = g.groups;
+    r[3] = g.ahead;
 }
 """
 
@@ -39,7 +40,7 @@ def _cu(lens):
 
 
 def _generic(rules, bf16, d, hq, hkv, lens, topk=16, sparse=1, below=0):
-    r = (ctypes.c_int * 3)()
+    r = (ctypes.c_int * 4)()
     rules.generic(bf16, d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), sparse, topk, below, r)
     return tuple(r)
 
@@ -48,11 +49,12 @@ def test_many_short_sequences_take_one_column_group(rules):
     """Tiles that end with their sequence have nothing for a second group: the number of sequences alone must not choose it."""
     for lens in ([4] * 500, [1] * 2000, [10] * 200, [33] * 242, [100] * 40):
         for bf16, d in ((1, 128), (1, 64), (0, 128), (0, 64)):
-            assert _generic(rules, bf16, d, 8, 2, lens)[:2] == (1, 0), (lens[:1], bf16, d)
-    assert _generic(rules, 1, 128, 8, 2, [4] * 500)[2] == 0 and _generic(rules, 1, 64, 8, 2, [4] * 500)[2] == 0
+            f = _generic(rules, bf16, d, 8, 2, lens)
+            assert f[:2] == (1, 0) and (lens[0] > 33 or f[2:] == (1, 0)), (lens[:1], bf16, d)
     # a long sequence keeps the form it has alone
-    assert _generic(rules, 1, 128, 8, 2, [1985]) == (2, 1, 1)
-    assert _generic(rules, 1, 128, 8, 2, [1985, 3, 5]) == (2, 1, 1)
-    assert _generic(rules, 0, 64, 4, 1, [2048], topk=8) == (1, 1, 1)
-    assert _generic(rules, 1, 128, 8, 2, [6000]) == (2, 0, 1)
-    assert _generic(rules, 1, 128, 8, 2, []) == (1, 1, 0)
+    assert _generic(rules, 1, 128, 8, 2, [1985]) == (2, 1, 2, 1)
+    assert _generic(rules, 1, 128, 8, 2, [1985, 3, 5]) == (2, 1, 2, 1)
+    assert _generic(rules, 0, 64, 4, 1, [2048], topk=8) == (1, 1, 2, 1)
+    assert _generic(rules, 1, 128, 8, 2, [6000]) == (2, 0, 2, 1)
+    assert _generic(rules, 0, 128, 8, 2, [600]) == (1, 1, 1, 1)
+    assert _generic(rules, 1, 128, 8, 2, []) == (1, 1, 1, 1)
