@@ -12,7 +12,7 @@
 //   dq    : the workgroup and block walk of the generic forward kernel: per block S^T = K Q^T and dP^T = V dO^T
 //           (keys x columns), dZ^T in registers, dQ^T += K^T dZ^T
 //   dkv   : one workgroup of 4 wavefronts per (KV block, chunk of later tokens, KV head): lists the tokens of its chunk
-//           that selected the block and takes 16 / G of them at a time, 16 rows of Q and dO (bf16: twice that); wavefront w holds keys
+//           that selected the block and takes 16 / G of them at a time, 16 rows of Q and dO (bf16: mostly twice that); wavefront w holds keys
 //           16 w .. 16 w + 15 (their K and V rows stay in registers): S = Q K^T, dP = dO V^T (rows x keys), then
 //           dV += P^T dO and dK += dZ^T Q, contracted over the 16 rows.  The block's 64 rows of dK and dV are added to
 //           the float32 result with atomics (one add per element and workgroup; the order of the adds, and with it
@@ -213,10 +213,10 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
     }
 }
 
-template <typename T, int D>
+template <typename T, int D, int RG>
 __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chunk) {
     constexpr int N = D / 16;
-    constexpr int RG = sizeof(T) == 2 ? 2 : 1, ROWS = RG * kCols;      // groups of 16 rows of Q and dO per step
+    constexpr int ROWS = RG * kCols;                                   // RG groups of 16 rows of Q and dO per step
     __shared__ __attribute__((aligned(16))) T rows_s[2][2][ROWS][D + 16 / sizeof(T)];      // [buffer][Q, dO][row]
     __shared__ float lse_s[2][ROWS], delta_s[2][ROWS];
     __shared__ int t_s[2][ROWS];
@@ -327,6 +327,13 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
         if constexpr (RG == 2) {
             weighted_rows32<true, true, D>(acc_v, p[0], p[1], gr[0], gr[1]);
             weighted_rows32<true, true, D>(acc_k, dz[0], dz[1], qr[0], qr[1]);
+        } else if constexpr (sizeof(T) == 2) {                 // 16 of the 32 indices; the others are 0 times 0
+            const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+            Spread<T, D> zeros[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) zeros[r].zero();
+            weighted_rows32<true, true, D>(acc_v, p[0], none, gr[0], zeros);
+            weighted_rows32<true, true, D>(acc_k, dz[0], none, qr[0], zeros);
         } else {
             weighted_rows<true, D>(acc_v, p[0], gr[0]);
             weighted_rows<true, D>(acc_k, dz[0], qr[0]);
@@ -402,31 +409,13 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     }
     if (!two && form.ahead) launch_dq<T, D, 1, true>(L, a);
     else if (!two) launch_dq<T, D, 1, false>(L, a);
-    // Tokens per dkv workgroup: as many (256 at most) as leave 256 workgroups with work, but not so many that these make little
-    // more than the two rounds of 256 that the chip takes at once.  Training step with 256 / 128 / 64 / 32, 8 heads on 2, bf16:
-    // 300 tokens 106 / 68 / 50 / 41 us, 1000 tokens 133 / 97 / 88 / 100, 1985 tokens 209 / 217 / 237 / 247, 2500 tokens 268 /
-    // 276 / 310 / 367, 3300 tokens (728 workgroups with 256) 428 / 414 / 452 / 553, 4000 tokens 713 / 738 / 719 / 831; fp32, 1000
-    // tokens 282 / 200 / 191 / 201.  The smaller workgroups of d 64 are better shorter: 1400 fp32 tokens 221 / 176 / 154 / 165,
-    // 4000 bf16 tokens 405 / 410 / 375 / 423.
-    // So are lists that leave blocks out, whose workgroups differ more: 1985 bf16 tokens with 16 blocks each 203 with 256, 197 with 64.
-    auto busy = [&](int c) {                     // workgroups whose chunk does not end before their block (causal)
-        int64_t n = 0;
-        for (int s = 0; s < L.map.batch; ++s) {
-            const int64_t len = cu_h[s + 1] - cu_h[s];
-            n += (len + c - 1) / c * ((len + kBlock - 1) / kBlock + std::max(c / kBlock, 1)) / 2 * hkv;
-        }
-        return n;
-    };
-    int chunk = BWD_CHUNK;
-    if (D == 128 && (L.max_len + kBlock - 1) / kBlock <= L.p->topk_total) {
-        while (chunk > 32 && busy(chunk) < 256) chunk /= 2;
-        if (chunk == BWD_CHUNK && busy(chunk) > 512 && busy(chunk) <= 768) chunk /= 2;
-    } else {
-        while (chunk > 64 && nblocks * ((L.max_len + chunk - 1) / chunk) * hkv < 2048) chunk /= 2;
-        if (chunk == 64 && busy(chunk) < 256) chunk = 32;
-    }
-    const unsigned chunks = (unsigned)((L.max_len + chunk - 1) / chunk);
-    hipLaunchKernelGGL((bwd_dkv_kernel<T, D>), dim3(chunks, (unsigned)nblocks, hkv), dim3(NW * 64), 0, L.stream, a, chunk);
+    const rules::DkvForm dkv = rules::generic_dkv_form(sizeof(T) == 2, D, hkv, a.hq / hkv, cu_h, L.map.batch, a.idx != nullptr,
+                                                       a.topk_total, a.dense_below);
+    const dim3 grid((unsigned)((L.max_len + dkv.chunk - 1) / dkv.chunk), (unsigned)nblocks, hkv);
+    if constexpr (sizeof(T) == 2)
+        if (dkv.row_groups == 2) hipLaunchKernelGGL((bwd_dkv_kernel<T, D, 2>), grid, dim3(NW * 64), 0, L.stream, a, dkv.chunk);
+    if constexpr (sizeof(T) == 4 || D == 64)
+        if (dkv.row_groups == 1) hipLaunchKernelGGL((bwd_dkv_kernel<T, D, 1>), grid, dim3(NW * 64), 0, L.stream, a, dkv.chunk);
     return hip_status(hipGetLastError());
 }
 

@@ -24,7 +24,7 @@ pytestmark = pytest.mark.gpu
     ("bf16", 40, 8, 64, [801]), ("fp32", 40, 8, 128, [100, 33, 5]), ("fp32", 40, 8, 64, [130, 31]),
     # (no sequence of 3 tokens among these: Delta = <dO, O> of a bf16 O is off by 2^-9 |O| sqrt(64 / 3) = 0.006, dQ by scale |K|
     # times that = 6e-4, and with three tokens the largest dQ is 0.3: 2e-3 of it on average, as much as the comparison allows)
-    ("bf16", 8, 8, 64, [40, 65, 33] * 14),
+    ("bf16", 8, 8, 64, [40, 65, 33] * 16),
 ])
 def test_both_sides_of_the_rules(m, oracle, dtype, hq, hkv, d, lens):  # noqa: F811
     w = synth.make_varlen(lens, hq, hkv, d, seed=2800 + sum(lens) + d, dtype=dtype)
@@ -87,6 +87,7 @@ def test_strided_rows(m, oracle):  # noqa: F811
 @pytest.mark.parametrize("dtype,hq,hkv,d,lens", [
     ("bf16", 8, 2, 128, [33]), ("bf16", 8, 2, 128, [31, 300, 32, 1]), ("fp32", 8, 2, 128, [289]), ("bf16", 8, 2, 64, [97, 160]),
     ("fp32", 8, 2, 64, [350]), ("bf16", 8, 8, 128, [500]), ("bf16", 16, 16, 128, [700, 65]),
+    ("bf16", 40, 8, 64, [64, 130, 65] * 8), ("bf16", 16, 8, 64, [129, 63, 64] * 9),       # one group of 16 rows per step
 ])
 def test_token_chunks_of_dkv(m, oracle, dtype, hq, hkv, d, lens):  # noqa: F811
     """Chunks from 32 to 256 tokens, with ends inside and at the edge of a chunk."""
