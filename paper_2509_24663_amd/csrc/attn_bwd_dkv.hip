@@ -22,10 +22,9 @@
 // this one replaced (four wavefronts of 16 keys, two tokens per barrier) took 6.2 ms with the order of chunks above.  Four
 // wavefronts sharing a block and adding up in LDS: 5.4 ms; without the copies 3.7 ms; all rows L2 hits 4.6 ms; copies
 // spread over the products instead of early: 5.8 ms; chunks of 512 / 256 tokens: 5.1 / 5.3 ms.
-#include <algorithm>
-
 #include "attn_bwd.h"
 #include "attn_unit.h"
+#include "launch_rules.h"
 
 namespace ifv2 {
 
@@ -40,7 +39,7 @@ using attn_unit::u32x4;
 
 constexpr int D = 128, G = 16;
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr int MAX_CHUNK = 1024;                        // tokens per workgroup at most
+constexpr int MAX_CHUNK = 1024;                        // tokens per workgroup at most (launch_rules.h)
 constexpr uint32_t kTokBytes = 2 * G * D * 2;          // a token's Q rows, then its dO rows
 constexpr uint32_t kMatBytes = G * D * 2;
 constexpr uint32_t kPairBytes = 2 * kTokBytes + 256;   // two tokens, then lse and Delta of their heads
@@ -359,54 +358,14 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
 
 }  // namespace
 
-// Microseconds a launch with chunks of c tokens takes, up to what does not depend on c: a workgroup 35 for its keys and its
-// adds (every chunk of a block adds to the same rows) and 1.7 per pair of tokens (a fifth less while SIMDs are idle), on 128
-// SIMDs of the XCD that has most of them, and half of the longest list where the others end; or the longest list.
-// From the backward call at 264 shapes (1 to 8 KV heads, 700 to 24000 tokens, dense, budgets of 16 to 96 blocks, packed)
-// times six chunks: the one it prefers is 0.7 % from the best on average and 3.5 % at most, where the rule before it (as
-// many chunks as make 4096 workgroups) was 7.1 % off.
-static float dkv_cost(const BwdM &a, const int32_t *cu_h, int32_t max_len, int c) {
-    constexpr float kPair = 1.7f, kFixed = 35.f;
-    const int hkv = a.map.num_kv_heads;
-    const int64_t groups = ((int64_t)max_len + c - 1) / c * hkv;
-    const bool each = groups * a.map.batch <= 512;         // which XCD a workgroup is on matters while there are few
-    double wgs = 0, tokens = 0, xcd[8] = {};
-    for (int s = 0; s < a.map.batch; ++s) {
-        const double len = cu_h[s + 1] - cu_h[s], nb = (cu_h[s + 1] - cu_h[s] + kBlock - 1) / kBlock;
-        const double chunks = (cu_h[s + 1] - cu_h[s] + c - 1) / c, most = a.topk_total;
-        wgs += hkv * chunks * (nb + std::max(c / kBlock, 1)) / 2;
-        // entries of the lists: a token selects every block up to its own, or the budget
-        tokens += hkv * (a.idx == nullptr || len < a.dense_below || nb <= most
-                             ? len * (nb + 1) / 2 : kBlock * most * (most + 1) / 2 + (len - kBlock * most) * most);
-        if (each)
-            for (int64_t g = 0; g < groups && g / hkv * c < len; ++g)
-                xcd[(g - s) & 7] += (std::min<int64_t>(g / hkv * c + c, (int64_t)len) - 1) / kBlock + 1;
-    }
-    if (wgs == 0) return 0.f;
-    const double rounds = (each ? *std::max_element(xcd, xcd + 8) * 8 : wgs) / 1024;
-    const double pair = kPair * (rounds < 1 ? 0.8 + 0.2 * rounds : 1.0);
-    const double longest = std::min(c, max_len) * pair / 2 + kFixed, mean = tokens / wgs * pair / 2 + kFixed;
-    return (float)(rounds <= 1 ? longest : std::max(longest, rounds * mean + longest / 2));
-}
-
 int launch_bwd_dkv(const BwdM &a, const int32_t *cu_h, int32_t max_len, hipStream_t stream) {
-    // One sequence on 2 KV heads, training step with chunks of 32 / 64 / 128 / 256 / 512: 500 tokens 87 / 114 / 168 / 276 / 486
-    // us, 1500 tokens 283 / 235 / 270 / 370 / 581, 2000 tokens 376 / 360 / 321 / 408 / 619, 3000 tokens 580 / 539 / 551 / 499
-    // / 716, 8000 tokens 2.63 / 2.09 / 2.04 / 2.07 / 2.15 ms, 16000 tokens - / 5.53 / 4.86 / 4.68 / 4.77, 32768 tokens
-    // - / - / 12.5 / 11.15 / 11.0, with chunks of 1024 10.94.
-    // Every sequence gets the chunks of the longest (those past its end leave at once: 440000 of them beside a sequence of 32768
-    // tokens do not show), and a launch has fewer than 2^32 threads in x, which bounds the chunks from below.
-    auto groups = [&](int c) { return (max_len + c - 1) / c * a.map.num_kv_heads; };
-    auto launched = [&](int c) { return 8ll * ((groups(c) + 7) / 8) * a.nblocks; };
-    constexpr int64_t kMost = 0xffffffffll / 64;
-    if (launched(MAX_CHUNK) > kMost) return INFLLMV2_ERR_UNSUPPORTED;
-    int chunk = MAX_CHUNK;
-    float best = dkv_cost(a, cu_h, max_len, chunk);
-    for (int c = MAX_CHUNK / 2; c >= 32 && launched(c) <= kMost; c /= 2) {
-        const float cost = dkv_cost(a, cu_h, max_len, c);
-        if (cost <= best) { best = cost; chunk = c; }
-    }
-    hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3((unsigned)launched(chunk)), dim3(64), 0, stream, a, chunk, groups(chunk));
+    const int hkv = a.map.num_kv_heads;
+    // (a launch has fewer than 2^32 threads in x)
+    const int chunk = rules::dkv_chunk({cu_h, a.map.batch, max_len, hkv, a.nblocks, a.idx != nullptr, a.topk_total, a.dense_below},
+                                       0xffffffffll / 64);
+    if (chunk == 0) return INFLLMV2_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3((unsigned)rules::dkv_workgroups(max_len, hkv, a.nblocks, chunk)), dim3(64), 0, stream,
+                       a, chunk, (max_len + chunk - 1) / chunk * hkv);
     return hip_status(hipGetLastError());
 }
 

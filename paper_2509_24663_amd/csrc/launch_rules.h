@@ -116,5 +116,82 @@ inline DkvForm generic_dkv_form(bool bf16, int d, int hkv, int G, const int32_t 
     return {chunk, one ? 1 : 2};
 }
 
+// dK/dV of the matrix-core path: tokens per workgroup, 32 to 1024.
+//
+// Every sequence gets the chunks of the longest, and its workgroups go round the eight XCDs (see attn_bwd_dkv.hip): this many
+// are launched, most of the short sequences' to leave at once.
+inline int64_t dkv_workgroups(int max_len, int hkv, int64_t nblocks, int chunk) {
+    const int64_t groups = ((int64_t)max_len + chunk - 1) / chunk * hkv;
+    return 8 * ((groups + 7) / 8) * nblocks;
+}
+// Of one sequence and KV head, the workgroups that have tokens: chunks i of 32 << K tokens, blocks up to a chunk's last token.
+// (Lengths of this path are below 2^19, so everything fits 32 bits; a batch of thousands of sequences is counted for each call.)
+template <int K>
+inline uint32_t dkv_busy(uint32_t len) {
+    const uint32_t q = len >> (5 + K), full = K > 0 ? (q * (q + 1) / 2) << (K > 0 ? K - 1 : 0) : (q + 1) / 2 * (q / 2 + 1);
+    return full + (len & ((32u << K) - 1) ? (len + kKeys - 1) / kKeys : 0u);
+}
+struct DkvBatch {
+    const int32_t *cu_h;
+    int batch, max_len, hkv;
+    int64_t nblocks;
+    bool sparse;
+    int topk, dense_below;
+};
+// The cheapest chunk by a model of the launch, in microseconds: a workgroup takes 33 for its keys and its adds (every chunk of a
+// block adds to the same rows) and 1.9 per pair of tokens (down to 1.05 while SIMDs are idle), on the 128 SIMDs of each XCD, of
+// which the one that has most of them counts while there are few; where they go round more than once, 0.45 of the longest
+// list for the end; and one that leaves at once 3, more where it looks for its sequence among many.
+// From the backward call with every chunk at 521 shapes (1 to 8 KV heads, 40 to 24000 tokens, dense, budgets of 16 to 96
+// blocks, packed batches of up to 5000 sequences): the one the model prefers is 0.7 % from the best on average, more than 5 % at
+// 30 of them and 15 % at most (4000 tokens, 32 blocks, 1 KV head).  One sequence on 2 KV heads, training step with 32 /
+// 64 / 128 / 256 / 512: 500 tokens 87 / 114 / 168 / 276 / 486 us, 1500 tokens 283 / 235 / 270 / 370 / 581, 3000 tokens 580 / 539 / 551 /
+// 499 / 716, 8000 tokens 2.63 / 2.09 / 2.04 / 2.07 / 2.15 ms, 32768 tokens - / - / 12.5 / 11.15 / 11.0, with 1024 10.94; backward of
+// 100 x 300 tokens 884 / 812 / 814 / 876 / 867, on 4 KV heads 1658 / 1481 / 1403 / 1555 / 1564.
+// 0: no chunk makes a launch of at most `most` workgroups.
+inline int dkv_chunk(const DkvBatch &b, int64_t most) {
+    constexpr int N = 6;
+    constexpr double kPair = 1.9, kIdlePair = 0.55, kFixed = 33, kTail = 0.45, kLeave = 3;
+    int64_t busy[N] = {};                                   // by the chunk's size, 32 first
+    double entries = 0;                                     // of the lists: every block up to the token's own, or the budget
+    for (int s = 0; s < b.batch; ++s) {
+        const uint32_t len = (uint32_t)(b.cu_h[s + 1] - b.cu_h[s]);
+        const uint32_t most_of = b.sparse && (int)len >= b.dense_below ? (uint32_t)b.topk : ~0u;
+        const uint32_t full = std::min(len / kKeys, most_of);
+        busy[0] += dkv_busy<0>(len);
+        busy[1] += dkv_busy<1>(len);
+        busy[2] += dkv_busy<2>(len);
+        busy[3] += dkv_busy<3>(len);
+        busy[4] += dkv_busy<4>(len);
+        busy[5] += dkv_busy<5>(len);
+        entries += (double)kKeys * (full * (full + 1) / 2) + (double)(len - kKeys * full) * std::min(full + 1, most_of);
+    }
+    int chunk = 0;
+    double best = 0;
+    for (int i = N - 1; i >= 0; --i) {
+        const int c = 32 << i;
+        const int64_t launched = dkv_workgroups(b.max_len, b.hkv, b.nblocks, c);
+        if (launched > most) break;
+        const double wgs = (double)busy[i] * b.hkv;
+        double load = wgs;
+        const int64_t groups = ((int64_t)b.max_len + c - 1) / c * b.hkv;
+        if (groups * b.batch <= 512) {                      // which XCD a workgroup is on matters while there are few
+            double xcd[8] = {};
+            for (int s = 0; s < b.batch; ++s) {
+                const int64_t len = b.cu_h[s + 1] - b.cu_h[s];
+                for (int64_t g = 0; g < groups && g / b.hkv * c < len; ++g)
+                    xcd[(g - s) & 7] += (double)((std::min(g / b.hkv * c + c, len) - 1) / kKeys + 1);
+            }
+            load = 8 * *std::max_element(xcd, xcd + 8);
+        }
+        const double rounds = load / 1024, pair = kPair * (rounds < 1 ? kIdlePair + (1 - kIdlePair) * rounds : 1);
+        const double longest = std::min(c, b.max_len) * pair / 2 + kFixed, mean = wgs > 0 ? entries * b.hkv / wgs * pair / 2 + kFixed : 0;
+        const double cost = (rounds <= 1 ? longest : std::max(longest, rounds * mean + kTail * longest)) +
+                            (launched - wgs) / 1024 * kLeave * (1 + b.batch / 128.);
+        if (chunk == 0 || cost <= best) { best = cost; chunk = c; }
+    }
+    return chunk;
+}
+
 }  // namespace rules
 }  // namespace ifv2

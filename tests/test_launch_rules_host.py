@@ -23,6 +23,13 @@ extern "C" void generic_dkv(int bf16, int d, int hkv, int G, const int *cu, int 
     r[0] = f.chunk;
     r[1] = f.row_groups;
 }
+extern "C" long long busy(int len, int c) {
+    return c == 32 ? dkv_busy<0>(len) : c == 64 ? dkv_busy<1>(len) : c == 128 ? dkv_busy<2>(len) : c == 256 ? dkv_busy<3>(len)
+           : c == 512 ? dkv_busy<4>(len) : dkv_busy<5>(len);
+}
+extern "C" int chunk(const int *cu, int batch, int max_len, int hkv, long long nblocks, int sparse, int topk, int below, long long most) {
+    return dkv_chunk({cu, batch, max_len, hkv, nblocks, sparse != 0, topk, below}, most);
+}
 """
 
 
@@ -89,3 +96,32 @@ def test_dkv_chunks(rules):
         assert _dkv(rules, 1, 64, 8, 2, lens)[1] == 1
     assert _dkv(rules, 1, 64, 8, 2, [700] * 4)[1] == 2 and _dkv(rules, 1, 128, 8, 2, [4] * 500)[1] == 2
     assert _dkv(rules, 1, 128, 8, 2, [])[0] >= 32
+
+
+def _chunk(rules, lens, hkv=2, sparse=0, topk=16, below=0, most=0xffffffff // 64):
+    nblocks = sum((n + 63) // 64 for n in lens)
+    return rules.chunk(_cu(lens), len(lens), max(lens), hkv, ctypes.c_longlong(nblocks), sparse, topk, below, ctypes.c_longlong(most))
+
+
+def test_matrix_core_dkv_workgroups_are_counted_exactly(rules):
+    rules.busy.restype = ctypes.c_longlong
+    for c in (32, 64, 128, 256, 512, 1024):
+        for n in list(range(0, 700)) + [1023, 1024, 1025, 4095, 4100, 262144]:
+            want = sum((min(i + c, n) - 1) // 64 + 1 for i in range(0, n, c))
+            assert rules.busy(n, c) == want, (n, c)
+
+
+def test_matrix_core_dkv_chunks(rules):
+    # chunks longer than every sequence are the same work: never better than the shortest of them
+    for lens in ([300] * 100, [100] * 400, [64] * 1000, [200] * 8, [500] * 30):
+        for hkv in (1, 2, 4, 8):
+            for sparse in (0, 1):
+                c = _chunk(rules, lens, hkv, sparse)
+                assert c < 2 * lens[0], (lens[0], hkv, c)
+    for lens, hkv, good in (([300] * 100, 2, (64, 128)), ([300] * 100, 4, (128,)), ([500] * 30, 8, (64, 128, 256)), ([65] * 300, 1, (32,)),
+                            ([500], 2, (32,)), ([1000] * 10, 2, (256,)), ([200] * 8, 1, (32,))):
+        assert _chunk(rules, lens, hkv) in good, (lens[0], hkv)
+    assert _chunk(rules, [32768], 2, sparse=1, topk=64) == 1024 and _chunk(rules, [8000], 2, sparse=1, topk=64) == 256
+    # a launch's limit: chunks that are too many are left out, and 0 says that none is few enough
+    assert _chunk(rules, [100000] + [1] * 60000, 8, most=8 * 98 * (1563 + 60000)) == 1024
+    assert _chunk(rules, [100000] + [1] * 60000, 8, most=8 * 98 * (1563 + 60000) - 1) == 0
