@@ -200,12 +200,14 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
     // token of a chunk when it is an initial block, of all of them first, then group by group from the last block down
     // (the blocks next to the chunk have the next longest lists).  The groups move on by one XCD from sequence to sequence:
     // those of a batch of short sequences are few and unlike (40 sequences of 777 tokens: eight, between 117 and 2688 entries
-    // per sequence; 1148 -> 667 us).
+    // per sequence; 1148 -> 667 us); and by one more from eight sequences to the next: of one group per sequence every
+    // eighth of an XCD's workgroups would have tokens, which an XCD of 32 CUs deals to four of them (1000 x 64 tokens on 1 KV
+    // head, whole backward, 1362 -> 1170 us, 400 x 100 656 -> 558).
     const int per_xcd = (groups + 7) >> 3, slot = (int)blockIdx.x >> 3;
     const int ord = slot < per_xcd ? 0 : 1 + (slot - per_xcd) % max(nb - 1, 1);
     int j;
     const int seq = find_seq_tile(a.map.cu, a.map.batch, kBlock, ord == 0 ? 0 : nb - ord, j, s_tile);
-    const int grp = (slot < per_xcd ? slot : (slot - per_xcd) / max(nb - 1, 1)) * 8 + (((int)blockIdx.x + seq) & 7);
+    const int grp = (slot < per_xcd ? slot : (slot - per_xcd) / max(nb - 1, 1)) * 8 + (((int)blockIdx.x + seq + (seq >> 3)) & 7);
     if (seq >= a.map.batch || grp >= groups) return;
     const int h = grp % a.map.num_kv_heads, c0 = grp / a.map.num_kv_heads * chunk;
     const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;

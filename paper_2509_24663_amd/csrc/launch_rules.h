@@ -180,7 +180,7 @@ inline int dkv_chunk(const DkvBatch &b, int64_t most) {
             for (int s = 0; s < b.batch; ++s) {
                 const int64_t len = b.cu_h[s + 1] - b.cu_h[s];
                 for (int64_t g = 0; g < groups && g / b.hkv * c < len; ++g)
-                    xcd[(g - s) & 7] += (double)((std::min(g / b.hkv * c + c, len) - 1) / kKeys + 1);
+                    xcd[(g - s - (s >> 3)) & 7] += (double)((std::min(g / b.hkv * c + c, len) - 1) / kKeys + 1);
             }
             load = 8 * *std::max_element(xcd, xcd + 8);
         }
