@@ -33,14 +33,19 @@ struct BwdM {
     float *dk, *dv;
 };
 
-// words of the selection bitmap before sequence seq
-__device__ inline int64_t sel_base(const RowMap &m, int seq) {
-    int64_t w = 0;
-    for (int s = 0; s < seq; ++s) {
+// Words of the selection bitmap before sequence seq, by a whole wavefront: 64 sequences per step (a walk of one after the other,
+// which every wavefront of the bitmap kernel makes, took 6.3 of the 15.9 ms of a backward call for 5000 sequences of 20
+// tokens).  Fewer than 2^31 in all: at most 65535 blocks of at most 8192 words.
+__device__ inline int sel_base(const RowMap &m, int seq) {
+    if (seq == 0) return 0;
+    int w = 0;
+    for (int s = (int)threadIdx.x & 63; s < seq; s += 64) {
         const int len = m.cu[s + 1] - m.cu[s];
-        w += (int64_t)((len + kBlock - 1) / kBlock) * ((len + 31) / 32);
+        w += (len + kBlock - 1) / kBlock * ((len + 31) / 32);
     }
-    return w;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) w += __shfl_xor(w, o);
+    return __builtin_amdgcn_readfirstlane(w);
 }
 
 // dQ: the forward's tile kernel with another unit (attn_mfma.hip)

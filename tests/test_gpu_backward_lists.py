@@ -10,7 +10,8 @@ from test_gpu_parity import _params, m  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("lens,topk,threshold", [([4700], 70, 0), ([5000, 31, 4400], 65, 0), ([300, 4800, 257], 130, 280), ([33], 66, 0)])
+@pytest.mark.parametrize("lens,topk,threshold", [([4700], 70, 0), ([5000, 31, 4400], 65, 0), ([300, 4800, 257], 130, 280), ([33], 66, 0),
+                                                 ([17, 70, 64, 200] * 50, 16, 65)])       # sequences looked for 64 at a time
 def test_long_lists(m, oracle, lens, topk, threshold):  # noqa: F811
     w = synth.make_varlen(lens, 32, 2, 128, seed=2700 + topk, dtype="bf16")
     gp, _ = _params(m, oracle, "bf16", 32, 2, 128, n_init=1, n_local=2, topk_total=topk, dense_threshold=threshold)
