@@ -50,7 +50,7 @@ __device__ inline int sel_base(const RowMap &m, int seq) {
 
 // dQ: the forward's tile kernel with another unit (attn_mfma.hip)
 int launch_bwd_dq(const Launch &L, const BwdM &a, const int32_t *cu_h);
-// dK, dV (attn_bwd_dkv.hip)
-int launch_bwd_dkv(const BwdM &a, const int32_t *cu_h, int32_t max_len, hipStream_t stream);
+// dK, dV with `chunk` tokens per workgroup (attn_bwd_dkv.hip)
+int launch_bwd_dkv(const BwdM &a, int chunk, int32_t max_len, hipStream_t stream);
 
 }  // namespace ifv2

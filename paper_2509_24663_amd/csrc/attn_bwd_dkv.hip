@@ -360,12 +360,8 @@ __global__ void __launch_bounds__(64, 1) bwd_dkv_mfma_kernel(BwdM a, int chunk, 
 
 }  // namespace
 
-int launch_bwd_dkv(const BwdM &a, const int32_t *cu_h, int32_t max_len, hipStream_t stream) {
+int launch_bwd_dkv(const BwdM &a, int chunk, int32_t max_len, hipStream_t stream) {
     const int hkv = a.map.num_kv_heads;
-    // (a launch has fewer than 2^32 threads in x)
-    const int chunk = rules::dkv_chunk({cu_h, a.map.batch, max_len, hkv, a.nblocks, a.idx != nullptr, a.topk_total, a.dense_below},
-                                       0xffffffffll / 64);
-    if (chunk == 0) return INFLLMV2_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3((unsigned)rules::dkv_workgroups(max_len, hkv, a.nblocks, chunk)), dim3(64), 0, stream,
                        a, chunk, (max_len + chunk - 1) / chunk * hkv);
     return hip_status(hipGetLastError());

@@ -11,9 +11,8 @@
 // Measured at 32768 tokens, 64 selected blocks, 2 KV heads: dq 3.5 ms, dkv 5.1 ms (the forward attention kernel: 2.35 ms for
 // 2/7 of their flops).  dq took 5.5 ms as a kernel of its own that walked the union one block per barrier with K, V and a
 // transposed copy of K staged through registers.
-#include <algorithm>
-
 #include "attn_bwd.h"
+#include "launch_rules.h"
 
 namespace ifv2 {
 
@@ -125,6 +124,10 @@ int launch_attn_bwd_mfma(const Launch &L, const void *q, const void *k, const vo
     // What follows is for sequences whose bitmap rows fit LDS and for token strides of which three, in bytes, fit 32 bits (a
     // card holds 500 tokens of the others); the rest takes the generic kernels.
     if (L.max_len > 262144 || L.map.kv_tok_stride >= (1 << 28)) return INFLLMV2_ERR_UNSUPPORTED;
+    // (a launch has fewer than 2^32 threads in x; the dK/dV kernel's are 64 per workgroup)
+    const int chunk = rules::dkv_chunk({cu_h, L.map.batch, L.max_len, hkv, nblocks, idx != nullptr, p->topk_total, dense_below},
+                                       0xffffffffll / 64);
+    if (chunk == 0) return INFLLMV2_ERR_UNSUPPORTED;
     const size_t b_f = align256((size_t)rows * hq * sizeof(float));
     // selection bitmap (block-major): only when block lists exist and it stays moderate (it grows with len^2 / 512
     // bytes per sequence and KV head: 32 MB at 128K tokens); otherwise the dK/dV kernel searches the lists
@@ -173,7 +176,7 @@ int launch_attn_bwd_mfma(const Launch &L, const void *q, const void *k, const vo
     if (hipGetLastError() != hipSuccess) return INFLLMV2_ERR_HIP;
     const int rc = launch_bwd_dq(L, a, cu_h);
     if (rc != INFLLMV2_OK) return rc;
-    return launch_bwd_dkv(a, cu_h, L.max_len, L.stream);
+    return launch_bwd_dkv(a, chunk, L.max_len, L.stream);
 }
 
 }  // namespace ifv2
