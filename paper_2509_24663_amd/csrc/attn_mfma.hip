@@ -36,6 +36,7 @@
 
 #include "attn_bwd.h"
 #include "attn_unit.h"
+#include "launch_rules.h"
 #include "pair_entries.h"
 
 namespace ifv2 {
@@ -534,29 +535,16 @@ template <bool BWD>
 int launch_tiles(const Launch &L, const AttnArgs &a, const int32_t *cu_h) {
     // Two entries per interval when the four LDS stages that needs fit next to the block masks (with block lists:
     // sequences up to about 384K tokens; dense calls keep no masks), else one.
-    // Tiles of 16 tokens, or of 8 or 4 while even those leave CUs without a workgroup (one fits a CU): a block in LDS
-    // then serves fewer tokens, but there is nobody else to serve, and an interval takes as long as its units.
-    // (777 tokens, 2 KV heads: 28.9 us with 16, 20.7 with 8; dense, 1000 tokens: 36.4 and 27.4, 200 tokens 17.3 and,
-    // with 4, 13.5)
-    // A sequence of more than 1024 tokens takes tiles of 8 up to two for each CU: they start with the longest, so the CUs with
-    // the short ones of the first head take the long ones of the next.  16 / 8 tokens, 2 KV heads: 1400 tokens 44.4 / 33.0 us (dQ
-    // 71.0 / 45.8), 2040 tokens 62.6 / 55.1 (102 / 79), 2500 tokens 76.4 / 86.2 (125 / 119).  Below, a workgroup's start weighs
-    // more (500 tokens on 8 KV heads, whole call, 29.5 / 32.2), and packed sequences do not start with the longest tiles (2 x
-    // 1000 tokens 40.8 / 44.2).
-    const int64_t most = 256 / L.p->num_kv_heads;
-    int64_t tiles4 = 0, tiles8 = 0;
-    for (int s = 0; s < L.map.batch; ++s) {
-        tiles4 += (cu_h[s + 1] - cu_h[s] + 3) / 4;
-        tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
-    }
     int rc = INFLLMV2_ERR_UNSUPPORTED;
     if constexpr (BWD)
         if (L.map.kv_tok_stride >= kWideStride) {
             rc = launch_tile<16, 2, true, true>(L, a, cu_h);
             return rc == INFLLMV2_ERR_UNSUPPORTED ? launch_tile<16, 1, true, true>(L, a, cu_h) : rc;
         }
-    if (tiles4 <= most) rc = launch_tile<4, 2, BWD>(L, a, cu_h);
-    else if (tiles8 <= (L.map.batch == 1 && L.max_len > 1024 ? 2 * most : most)) rc = launch_tile<8, 2, BWD>(L, a, cu_h);
+    const int tokens = rules::attn_tile_tokens(cu_h, L.map.batch, L.max_len, L.p->num_kv_heads, a.idx != nullptr, a.topk_total,
+                                               a.dense_below, BWD);
+    if (tokens == 4) rc = launch_tile<4, 2, BWD>(L, a, cu_h);
+    else if (tokens == 8) rc = launch_tile<8, 2, BWD>(L, a, cu_h);
     if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 2, BWD>(L, a, cu_h);
     if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 1, BWD>(L, a, cu_h);
     return rc;

@@ -116,6 +116,38 @@ inline DkvForm generic_dkv_form(bool bf16, int d, int hkv, int G, const int32_t 
     return {chunk, one ? 1 : 2};
 }
 
+// Tile kernel of attention and dQ (bf16, G = 16, d 128): tokens per workgroup.
+//
+// Sixteen, or 8 or 4 while even those leave CUs without a workgroup (one fits a CU): a block in LDS then serves fewer tokens,
+// but there is nobody else to serve, and an interval takes as long as its units.  (777 tokens, 2 KV heads: 28.9 us with 16,
+// 20.7 with 8; dense, 1000 tokens: 36.4 and 27.4, 200 tokens 17.3 and, with 4, 13.5)
+//
+// A sequence of more than 1024 tokens that makes up most of the batch takes 8 up to two tiles for each CU: tiles start with the
+// longest, so the CUs with the short ones of the first head take the long ones of the next.  16 / 8, dense or with 64 blocks, 2
+// KV heads: 1400 tokens 44.4 / 33.0 us (dQ 71.0 / 45.8), 2040 tokens 62.6 / 55.1 (102 / 79), 2500 tokens 76.4 / 86.2 (125 /
+// 119); 1 KV head: 2049 tokens 58.3 / 42.7, 3100 tokens 82.9 / 58.8, 4096 tokens 107 / 86.  Below 1024 a workgroup's start weighs more
+// (500 tokens on 8 KV heads, whole call, 29.5 / 32.2).  Beside the long sequence, with 16 blocks: 1400 + 10 tokens on 2 KV heads
+// 42.7 / 33.7, 1400 + 300 42.9 / 39.7, 1400 + 600 44.4 / 44.2, 2 x 1024 41.5 / 45.2; 1200 + 2800 on 1 55.0 / 57.7.
+// Budgets cut the long tiles down to one length, and those behind the first 256 then begin when all of these end: they pay
+// while they have few blocks themselves.  Attention, 1 KV head (4096 tokens: 32 such blocks): 16 blocks, 2800 tokens 54.0 / 43.7, 3400
+// 57.5 / 57.9, 4096 63.5 / 68.5; 8 blocks, 2800 tokens 41.7 / 40.2, 3600 46.6 / 48.7; 2 KV heads (2048 tokens: 16): 4 blocks, 1200
+// tokens 27.7 / 26.0, 1400 29.3 / 30.1, 12 blocks, 1600 41.0 / 38.5, 2040 46.6 / 48.8.  dQ, which does more for a block, gains there too (16
+// blocks, 1 KV head, 4096 tokens, whole backward 283 / 229).
+inline int attn_tile_tokens(const int32_t *cu_h, int batch, int max_len, int hkv, bool sparse, int topk, int dense_below, bool bwd) {
+    const int64_t cus = 256 / hkv;
+    int64_t tiles4 = 0, tiles8 = 0;
+    for (int s = 0; s < batch; ++s) {
+        tiles4 += (cu_h[s + 1] - cu_h[s] + 3) / 4;
+        tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
+    }
+    if (tiles4 <= cus) return 4;
+    if (tiles8 <= cus) return 8;
+    const int64_t total = batch > 0 ? cu_h[batch] - cu_h[0] : 0;
+    if (tiles8 > 2 * cus || max_len <= 1024 || 4 * (int64_t)max_len < 3 * total) return 16;
+    const bool budget = !bwd && sparse && max_len >= dense_below;
+    return budget && (max_len + kKeys - 1) / kKeys - 8 * cus / kKeys > topk * 3 / 4 + cus * 3 / kKeys - 4 ? 16 : 8;
+}
+
 // dK/dV of the matrix-core path: tokens per workgroup, 32 to 1024.
 //
 // Every sequence gets the chunks of the longest, and its workgroups go round the eight XCDs (see attn_bwd_dkv.hip): this many

@@ -23,6 +23,9 @@ extern "C" void generic_dkv(int bf16, int d, int hkv, int G, const int *cu, int 
     r[0] = f.chunk;
     r[1] = f.row_groups;
 }
+extern "C" int tile(const int *cu, int batch, int max_len, int hkv, int sparse, int topk, int below, int bwd) {
+    return attn_tile_tokens(cu, batch, max_len, hkv, sparse, topk, below, bwd);
+}
 extern "C" long long busy(int len, int c) {
     return c == 32 ? dkv_busy<0>(len) : c == 64 ? dkv_busy<1>(len) : c == 128 ? dkv_busy<2>(len) : c == 256 ? dkv_busy<3>(len)
            : c == 512 ? dkv_busy<4>(len) : dkv_busy<5>(len);
@@ -125,3 +128,18 @@ def test_matrix_core_dkv_chunks(rules):
     # a launch's limit: chunks that are too many are left out, and 0 says that none is few enough
     assert _chunk(rules, [100000] + [1] * 60000, 8, most=8 * 98 * (1563 + 60000)) == 1024
     assert _chunk(rules, [100000] + [1] * 60000, 8, most=8 * 98 * (1563 + 60000) - 1) == 0
+
+
+def test_attention_tiles(rules):
+    def tile(lens, hkv=2, sparse=1, topk=64, below=0, bwd=0):
+        return rules.tile(_cu(lens), len(lens), max(lens, default=0), hkv, sparse, topk, below, bwd)
+    assert [tile([n]) for n in (1, 512, 513, 1024, 1025, 2048, 2049)] == [4, 4, 8, 8, 8, 8, 16]
+    assert [tile([n], 1) for n in (1024, 1025, 2048, 2049, 4096, 4097)] == [4, 8, 8, 8, 8, 16]
+    assert [tile([n], 8) for n in (128, 129, 256, 257, 2000)] == [4, 8, 8, 16, 16]
+    # a short sequence beside a long one changes nothing; two alike do
+    assert tile([1400, 10]) == tile([10, 1400]) == tile([1400]) == 8 and tile([1024, 1024]) == tile([1200, 800]) == 16
+    # lists with small budgets: the gradient keeps the small tiles, dense calls and sequences under the threshold too
+    for n, hkv, topk, want in ((4096, 1, 16, 16), (2800, 1, 12, 8), (3600, 1, 8, 16), (2040, 2, 12, 16), (1400, 2, 12, 8), (2040, 2, 64, 8)):
+        assert tile([n], hkv, topk=topk) == want, (n, hkv, topk)
+        assert tile([n], hkv, topk=topk, bwd=1) == tile([n], hkv, sparse=0, topk=topk) == tile([n], hkv, topk=topk, below=n + 1) == 8
+    assert tile([]) == 4
