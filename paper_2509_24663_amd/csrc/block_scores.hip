@@ -922,7 +922,12 @@ int launch_block_scores(const Launch &L, const void *q, const float *kc, float *
         }
         if (tiles16 * L.p->num_kv_heads <= 512) {
             if (a.lse_mode == 0) return launch_scores_pool<8, 2, true>(L, a, cu_h, pooled ? pool.pad : -1);
-            return launch_scores_pool<8, 2>(L, a, cu_h, pooled ? pool.pad : -1);
+            // Packed prompts of up to 2000 tokens have so few coarse key tiles that a workgroup's start is most of what it does:
+            // with more workgroups than CUs, two / four tokens per wavefront (kernels of the call): 4 x 700 tokens 19.8 / 19.1 us,
+            // 4 x 1000 21.3 / 19.9, 2 x 1000 on 4 KV heads 21.4 / 19.7, 4 x 2000 on 1 23.5 / 22.2; but 2 x 3600 on 1 23.8 / 25.7,
+            // one of 3800 tokens 24.7 / 26.4, 3 x 400 on 4 (300 workgroups) 18.3 / 19.7.
+            if (L.map.batch == 1 || L.max_len > 2000 || tiles16 * L.p->num_kv_heads <= 340)
+                return launch_scores_pool<8, 2>(L, a, cu_h, pooled ? pool.pad : -1);
         }
         return launch_scores_pool<8, 4>(L, a, cu_h, pooled ? pool.pad : -1);
     }
