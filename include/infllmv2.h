@@ -281,7 +281,10 @@ int infllmv2_dense_attn_fwd(const infllmv2_params *p, const void *q_d, const voi
  *   ctx_lens_h/d   host / device int32 [batch], each >= 1
  *   block_idx_out_d device out int32 [batch, num_kv_heads, topk_total] or NULL
  *   out_d          device out dtype [batch, num_q_heads, head_dim];  lse_d float32 [batch, num_q_heads] or NULL
- *   workspace_d    device scratch of at least infllmv2_decode_workspace_bytes(...) bytes, 256-byte aligned
+ *   workspace_d    device scratch, 256-byte aligned; infllmv2_decode_workspace_bytes(...) bytes always suffice
+ * With few sequences somewhat fewer bytes are accepted as well, down to what the step needs with its work split least
+ * (there is no query for that size); below it the call returns INFLLMV2_ERR_WORKSPACE_TOO_SMALL.  The number of splits,
+ * and with it the last bits of out and lse (never the block lists), can therefore depend on workspace_bytes.
  * Contexts longer than 262144 tokens are supported only for bf16 data with 16 query heads per KV head and
  * head_dim 128 (with the LSE Approximation up to about 419000 tokens; longer ones return INFLLMV2_ERR_UNSUPPORTED).
  * Sequences shorter than dense_threshold attend densely.
@@ -293,8 +296,7 @@ int infllmv2_sparse_decode(const infllmv2_params *p, const void *q_d, const void
                            int32_t *block_idx_out_d, void *out_d, float *lse_d,
                            void *workspace_d, size_t workspace_bytes, void *stream);
 
-/* Bytes of scratch infllmv2_sparse_decode makes use of for `batch` sequences of at most max_ctx_len tokens; with few
- * sequences it also accepts somewhat less and then splits the work more coarsely
+/* Bytes of scratch infllmv2_sparse_decode can make use of for `batch` sequences of at most max_ctx_len tokens
  * (= infllmv2_workspace_bytes(INFLLMV2_OP_SPARSE_DECODE, p, batch, 0, max_ctx_len)). */
 size_t infllmv2_decode_workspace_bytes(const infllmv2_params *p, int32_t batch, int32_t max_ctx_len);
 
@@ -304,7 +306,8 @@ size_t infllmv2_decode_workspace_bytes(const infllmv2_params *p, int32_t batch, 
  * errors as infllmv2_sparse_decode without (workspace_d, workspace_bytes): the scratch is a fixed array of
  * infllmv2_sparse_decode_static_capacity() bytes (16 MiB: batch 16 with contexts up to 65536 tokens fits) inside the
  * library's device image, which every GPU the library runs on holds until the process ends.  A step that needs
- * more (infllmv2_decode_workspace_bytes) returns INFLLMV2_ERR_WORKSPACE_TOO_SMALL before anything is launched.  The
+ * more with its work split least returns INFLLMV2_ERR_WORKSPACE_TOO_SMALL before anything is launched (one for which
+ * infllmv2_decode_workspace_bytes is at most the capacity never does).  The
  * call allocates and frees nothing.  All calls on one GPU share that GPU's array: calls that overlap in time on one
  * GPU (different streams or threads) race and give undefined results; calls on one stream, or ordered by events,
  * are fine.  The first call on a GPU looks the array's address up once (a host-side query).

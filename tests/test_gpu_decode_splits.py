@@ -33,6 +33,10 @@ def test_few_sequences(m, oracle, batch, n_local, topk):  # noqa: F811
             break
         tried += 1
         assert (buf[size:] == 0x5A).all() and torch.equal(idx, got[2])
-        assert_out_close(to_np(got[0]), to_np(out), "bf16") and (got[1] - lse).abs().max() < 1e-5
+        assert_out_close(to_np(got[0]), to_np(out), "bf16")
+        # the same keys in sums of other lengths: a few fp32 roundings of log2 of ~1000 summands, around lse < 16
+        assert (got[1] - lse).abs().max() < 1e-5
+    else:
+        pytest.fail("no size was refused")
     # 55 blocks: 7 splits at least, 11 at most; the other budgets and 24 pairs have one form
     assert (tried > 0) == ((n_local, topk) == (8, 64) and batch <= 9)
