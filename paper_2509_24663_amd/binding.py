@@ -126,8 +126,14 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # (not part of torch's documented interface)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 # `op` of infllmv2_workspace_bytes (enum infllmv2_op)

@@ -248,3 +248,28 @@ def test_library_sources_allocate_nothing_and_keep_no_state():
         # the one static array a source may hold is the documented, fixed-size device scratch of the entry point
         # for callers that cannot allocate; it is declared at file scope, not inside a function
         assert not static_state.search(code), (name, static_state.search(code).group(0))
+
+
+def test_stream_number_without_torchs_internal_names(m, monkeypatch):
+    """The stream's number is asked through two internal names of torch; a torch without them takes the public way."""
+    import types
+
+    import torch
+
+    from paper_2509_24663_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    for name in ("_raw_stream", "_device"):
+        with monkeypatch.context() as mp:
+            mp.setattr(binding, name, None)
+            assert binding._stream() == 1234
+
+
+@pytest.mark.gpu
+def test_stream_number_is_the_current_streams(m):
+    import torch
+
+    from paper_2509_24663_amd import binding
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.default_stream(), side):
+        with torch.cuda.stream(stream):
+            assert binding._stream() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
