@@ -57,6 +57,48 @@ def test_infinite_rows_stay_with_the_tokens_that_see_them(m, oracle, dtype, n): 
     assert torch.isfinite(lse).all()
 
 
+# column groups of attention and dQ, a: rows requested ahead: 1 1, 2a 2a, 1a 1a, 2 2a, 1a 1a, 1 2a, and 2a 2a with 32 tokens per tile
+@pytest.mark.parametrize("dtype,hq,hkv,d,lens", [
+    ("bf16", 40, 8, 128, [96, 130, 65, 100]), ("bf16", 8, 2, 128, [1100]), ("bf16", 8, 2, 128, [400]), ("bf16", 40, 8, 128, [400, 430]),
+    ("fp32", 8, 2, 128, [300]), ("fp32", 40, 8, 64, [130, 100, 97]), ("bf16", 8, 8, 128, [800]),
+])
+@pytest.mark.parametrize("bad", ["nan", "inf", "one inf"])
+def test_key_rows_that_are_not_finite(m, oracle, dtype, hq, hkv, d, lens, bad):  # noqa: F811
+    """A K row of NaN, of infinities or with one infinity, in the second half of a block: tokens that do not see it, in the same
+    tiles as tokens that do, keep output, log-sum-exp and dQ."""
+    T, G = sum(lens), hq // hkv
+    w = synth.make_varlen(lens, hq, hkv, d, seed=2970 + T, dtype=dtype)
+    gp, _ = _params(m, oracle, dtype, hq, hkv, d, n_init=1, n_local=1, topk_total=3)
+    q, k, v = (to_dev(w[x], dtype) for x in ("q", "k", "v"))
+    cu = w["cu_seqlens"]
+    idx = m.sparse_prefill(gp, q, k, v, cu)["block_idx"]
+    clean, lse = m.sparse_attn_fwd(gp, q, k, v, idx, cu)
+    torch.manual_seed(T)
+    dout = torch.randn_like(q)
+    want = m.sparse_attn_bwd(gp, q, k, v, idx, clean, lse, dout, cu)[0]
+    sees = torch.zeros(hkv, T, dtype=torch.bool, device="cuda")
+    for a, n in zip(cu[:-1].tolist(), lens):
+        hit = min(64 * (n // 128) + 41, n - 2)
+        k[:, a + hit] = float("nan") if bad == "nan" else k[:, a + hit]
+        if bad == "inf":
+            k[:, a + hit] = float("inf")
+        if bad == "one inf":
+            k[:, a + hit, 5] = float("inf")
+        sees[:, a + hit:a + n] = (idx[:, a + hit:a + n] == hit // 64).any(-1)
+    assert sees.any() and not sees.all()
+    out, lse2 = m.sparse_attn_fwd(gp, q, k, v, idx, cu)
+    got = m.sparse_attn_bwd(gp, q, k, v, idx, out, lse2, dout, cu)[0]
+    for h in range(hkv):
+        heads, rest = slice(h * G, h * G + G), ~sees[h]
+        if bad == "nan":
+            assert not torch.isfinite(out[sees[h], heads]).any()
+        assert_out_close(to_np(out[rest, heads]), to_np(clean[rest, heads]), dtype, "out")
+        assert (lse2[heads][:, rest] - lse[heads][:, rest]).abs().max() <= 1e-5
+        # the same sums in another order, of another (rounded) output: a rounding of dQ
+        scale = max(float(want.float().abs().max()), 0.1)
+        assert (got[rest, heads].float() - want[rest, heads].float()).abs().max() <= (2.0**-7 if dtype == "bf16" else 1e-5) * scale
+
+
 def test_strided_rows(m, oracle):  # noqa: F811
     """Rows 192 elements apart, and 2^25 elements apart (64-bit row distances), against rows side by side."""
     n, hq, hkv, d = 780, 8, 2, 128
@@ -68,7 +110,7 @@ def test_strided_rows(m, oracle):  # noqa: F811
     dout = torch.flip(out, (0,)).contiguous()
     want = m.sparse_attn_bwd(gp, q, k, v, idx, out, lse, dout, [0, n])
     for stride in (192, 1 << 25):
-        buf = torch.zeros(n * stride + 2048, dtype=torch.bfloat16, device="cuda")
+        buf = torch.empty(n * stride + 2048 if stride > 1000 else 0, dtype=torch.bfloat16, device="cuda")     # (only the rows are touched)
         ks, vs = (torch.as_strided(buf, (hkv, n, d), (d if stride > 1000 else n * stride, stride, 1), o) for o in (0, 1024)) \
             if stride > 1000 else (torch.zeros(hkv, n, stride, dtype=torch.bfloat16, device="cuda")[:, :, :d] for _ in range(2))
         ks.copy_(k)
