@@ -63,6 +63,13 @@ inline GenericForm generic_dq_form(bool bf16, int d, int hkv, const Walks &x) {
     return {1, rows_ahead(x.one * hkv, 1024, x)};
 }
 
+// Of one sequence and KV head, the workgroups that have tokens: chunks i of 32 << K tokens, blocks up to a chunk's last token.
+// (Everything fits 32 bits for lengths below 2^20; a batch of thousands of sequences is counted for each call.)
+template <int K>
+inline uint32_t dkv_busy(uint32_t len) {
+    const uint32_t q = len >> (5 + K), full = K > 0 ? (q * (q + 1) / 2) << (K > 0 ? K - 1 : 0) : (q + 1) / 2 * (q / 2 + 1);
+    return full + (len & ((32u << K) - 1) ? (len + kKeys - 1) / kKeys : 0u);
+}
 // Generic dK/dV: tokens per workgroup, and groups of 16 rows of Q and dO per step.
 struct DkvForm {
     int chunk, row_groups;
@@ -87,14 +94,24 @@ inline DkvForm generic_dkv_form(bool bf16, int d, int hkv, int G, const int32_t 
     int chunk = 256;
     if (d == 128 && (!sparse || max_len < dense_below || (max_len + kKeys - 1) / kKeys <= topk)) {
         // Every block is selected.  As many tokens as leave 256 workgroups with work, not more than a third of the longest sequence
-        // (its last chunk is short) where that is several steps.  Whole backward, bf16, 8 heads on 2, chunks of 256 / 128 / 64 / 32:
+        // (its last chunk is short) where that is several steps and does not make half as many workgroups again.  Whole backward, bf16, 8 heads on 2, chunks of 256 / 128 / 64 / 32:
         // 300 tokens 92 / 56 / 38 / 30 us, 1000 tokens 116 / 80 / 70 / 81, 1985 tokens 166 / 173 / 193 / 200, 2500 tokens 224 / 235 / 269 /
-        // 330, 26 x 300 tokens 201 / 186 / 177 / 211.
+        // 330, 26 x 300 tokens 201 / 186 / 177 / 211, but 20 x 400 (1.7 times the workgroups with 128) 216 / 225 / 204 and 114 x 70 (1.5
+        // times with 64) 107 / 107 / 132.
         // 512 to 768 workgroups of 256 are a little more than the two rounds of 256 that the chip takes at once: 3000 tokens (612)
         // 1.07 / 1 / 1.16 / 1.41, 4000 tokens (1072) 1.02 / 1.06 / 1 / 1.22 of the best.  Steps of less than 8 tokens make twice the
         // steps of a chunk: 16 heads on 2, 2300 tokens 348 / 339 / 321 / 358, fp32, 8 heads on 2, 2300 tokens 1.06 / 1.06 / 1 / 1.10.
         const int most = std::max(max_len / 3, 8 * step);
-        while (chunk > 64 && (chunk > most || busy(chunk) < 256)) chunk /= 2;
+        auto few_more = [&] {                               // halving: less than half as many workgroups again
+            int64_t now = 0, then = 0;
+            for (int s = 0; s < batch; ++s) {
+                const uint32_t len = (uint32_t)(cu_h[s + 1] - cu_h[s]);
+                now += chunk == 256 ? dkv_busy<3>(len) : dkv_busy<2>(len);
+                then += chunk == 256 ? dkv_busy<2>(len) : dkv_busy<1>(len);
+            }
+            return 20 * then < 29 * now;
+        };
+        while (chunk > 64 && (busy(chunk) < 256 || (chunk > most && few_more()))) chunk /= 2;
         if (chunk == 256 && step <= 8 && busy(chunk) <= 768) {
             if (busy(chunk) > 512) chunk = 128;
             else if (step < 8) chunk = 64;
@@ -156,13 +173,6 @@ inline int64_t dkv_workgroups(int max_len, int hkv, int64_t nblocks, int chunk) 
     const int64_t groups = ((int64_t)max_len + chunk - 1) / chunk * hkv;
     return 8 * ((groups + 7) / 8) * nblocks;
 }
-// Of one sequence and KV head, the workgroups that have tokens: chunks i of 32 << K tokens, blocks up to a chunk's last token.
-// (Lengths of this path are below 2^19, so everything fits 32 bits; a batch of thousands of sequences is counted for each call.)
-template <int K>
-inline uint32_t dkv_busy(uint32_t len) {
-    const uint32_t q = len >> (5 + K), full = K > 0 ? (q * (q + 1) / 2) << (K > 0 ? K - 1 : 0) : (q + 1) / 2 * (q / 2 + 1);
-    return full + (len & ((32u << K) - 1) ? (len + kKeys - 1) / kKeys : 0u);
-}
 struct DkvBatch {
     const int32_t *cu_h;
     int batch, max_len, hkv;
@@ -174,9 +184,9 @@ struct DkvBatch {
 // block adds to the same rows) and 1.9 per pair of tokens (down to 1.05 while SIMDs are idle), on the 128 SIMDs of each XCD, of
 // which the one that has most of them counts while there are few; where they go round more than once, 0.45 of the longest
 // list for the end; and one that leaves at once 3, more where it looks for its sequence among many.
-// From the backward call with every chunk at 521 shapes (1 to 8 KV heads, 40 to 24000 tokens, dense, budgets of 16 to 96
-// blocks, packed batches of up to 5000 sequences): the one the model prefers is 0.7 % from the best on average, more than 5 % at
-// 30 of them and 15 % at most (4000 tokens, 32 blocks, 1 KV head).  One sequence on 2 KV heads, training step with 32 /
+// From the backward call with every chunk at 629 shapes (1 to 8 KV heads, 40 to 24000 tokens, dense, budgets of 16 to 96
+// blocks, packed batches of up to 5000 sequences; profiles/backward_chunk_timings.txt): the one the model prefers is 0.9 % from
+// the best on average, more than 5 % at 43 of them and 22 % at most (1300 tokens beside four sequences of 50 to 80). One sequence on 2 KV heads, training step with 32 /
 // 64 / 128 / 256 / 512: 500 tokens 87 / 114 / 168 / 276 / 486 us, 1500 tokens 283 / 235 / 270 / 370 / 581, 3000 tokens 580 / 539 / 551 /
 // 499 / 716, 8000 tokens 2.63 / 2.09 / 2.04 / 2.07 / 2.15 ms, 32768 tokens - / - / 12.5 / 11.15 / 11.0, with 1024 10.94; backward of
 // 100 x 300 tokens 884 / 812 / 814 / 876 / 867, on 4 KV heads 1658 / 1481 / 1403 / 1555 / 1564.

@@ -95,6 +95,8 @@ def test_dkv_chunks(rules):
     assert _dkv(rules, 1, 128, 4, 4, [600], topk=64) == (64, 2)       # 32 tokens per step: a chunk of 32 is one step
     for lens in ([300] * 26, [333] * 12):                             # chunks no longer than a third of the sequences
         assert _dkv(rules, 1, 128, 8, 2, lens, topk=64)[0] <= 128
+    # ... unless that only cuts off ends: a chunk and a few tokens stay one
+    assert _dkv(rules, 0, 128, 8, 2, [70] * 114, topk=64)[0] >= 128 and _dkv(rules, 1, 128, 28, 4, [400] * 20, topk=64)[0] == 256
     for lens in ([4] * 500, [300] * 26, [70] * 114):                  # many workgroups with few steps each
         assert _dkv(rules, 1, 64, 8, 2, lens)[1] == 1
     assert _dkv(rules, 1, 64, 8, 2, [700] * 4)[1] == 2 and _dkv(rules, 1, 128, 8, 2, [4] * 500)[1] == 2
