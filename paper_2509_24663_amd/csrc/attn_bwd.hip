@@ -408,7 +408,8 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
         if (two) launch_dq<T, D, 2, true>(L, a);
     }
     if (!two && form.ahead) launch_dq<T, D, 1, true>(L, a);
-    else if (!two) launch_dq<T, D, 1, false>(L, a);
+    if constexpr (D * sizeof(T) < 512)
+        if (!two && !form.ahead) launch_dq<T, D, 1, false>(L, a);
     const rules::DkvForm dkv = rules::generic_dkv_form(sizeof(T) == 2, D, hkv, a.hq / hkv, cu_h, L.map.batch, a.idx != nullptr,
                                                        a.topk_total, a.dense_below);
     const dim3 grid((unsigned)((L.max_len + dkv.chunk - 1) / dkv.chunk), (unsigned)nblocks, hkv);

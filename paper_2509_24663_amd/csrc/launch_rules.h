@@ -60,7 +60,8 @@ inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
 // 97 / 102, 10 x 200 39.6 / 35.6.  Two groups without rows ahead are slower everywhere (d 128, 4000 tokens 394 / 432, 26 x 300 208 / 213).
 inline GenericForm generic_dq_form(bool bf16, int d, int hkv, const Walks &x) {
     if ((bf16 || d == 64) && x.half_blocks >= (d == 128 ? 4 : 2) && x.one * hkv > (bf16 ? 280 : 350)) return {2, true};
-    return {1, rows_ahead(x.one * hkv, 1024, x)};
+    // (fp32 d 128 has one wavefront per SIMD either way: 28 heads on 4, 400 x 20 tokens, ahead / not 870 / 938)
+    return {1, (!bf16 && d == 128) || rows_ahead(x.one * hkv, 1024, x)};
 }
 
 // Of one sequence and KV head, the workgroups that have tokens: chunks i of 32 << K tokens, blocks up to a chunk's last token.
