@@ -911,22 +911,30 @@ int launch_block_scores(const Launch &L, const void *q, const float *kc, float *
         // 19.9 / 19.8 / 21.3, 4000 tokens 28.2 / 24.8 / 26.0, 4500 tokens 31.8 / 34.1 / 31.5.  With one and two (and the exact
         // normalisation) a workgroup also converts the few key tiles it needs: the kernel then takes as long (777 tokens 7.8 ->
         // 8.0 us, 2000 tokens 12.2 -> 13.4, 4000 tokens 25 -> 29), and a pre-pass of 3.9 to 4.9 us and its launch are gone.
-        int64_t tiles8 = 0, tiles16 = 0;
+        int64_t tiles8 = 0, tiles16 = 0, tiles16_long = 0;
         for (int s = 0; s < L.map.batch; ++s) {
-            tiles8 += (cu_h[s + 1] - cu_h[s] + 7) / 8;
-            tiles16 += (cu_h[s + 1] - cu_h[s] + 15) / 16;
+            const int len = cu_h[s + 1] - cu_h[s];
+            tiles8 += (len + 7) / 8;
+            tiles16 += (len + 15) / 16;
+            if (len > 1750) tiles16_long += (len + 15) / 16;
         }
         if (tiles8 * L.p->num_kv_heads <= 384) {
             if (a.lse_mode == 0) return launch_scores_pool<8, 1, true>(L, a, cu_h, pooled ? pool.pad : -1);
             return launch_scores_pool<8, 1>(L, a, cu_h, pooled ? pool.pad : -1);
         }
-        if (tiles16 * L.p->num_kv_heads <= 512) {
+        // Just below the line sequences of 1751 to 2048 tokens (two key tiles, nearly full) are better off with four tokens
+        // already, if most tiles are theirs.  Calls with two / four: 4 x 2000 on 1 KV head 23.5 / 21.2 us, 2 x 1900 on 2
+        // 23.1 / 21.1, 1850 tokens on 4 22.4 / 20.4, 2040 on 4 22.9 / 20.9, with the LSE Approximation 22.9 / 20.0; but 1700
+        // tokens on 4 20.3 / 24.3, 1900 beside twenty of 300 on 1 22.9 / 29.5, 16 x 400 on 1 18.8 / 20.2.
+        const bool two_tiles = L.max_len <= 2048 && tiles16 * L.p->num_kv_heads > 440 && 2 * tiles16_long > tiles16;
+        if (tiles16 * L.p->num_kv_heads <= 512 && !two_tiles) {
             if (a.lse_mode == 0) return launch_scores_pool<8, 2, true>(L, a, cu_h, pooled ? pool.pad : -1);
-            // Packed prompts of up to 2000 tokens have so few coarse key tiles that a workgroup's start is most of what it does:
-            // with more workgroups than CUs, two / four tokens per wavefront (kernels of the call): 4 x 700 tokens 19.8 / 19.1 us,
-            // 4 x 1000 21.3 / 19.9, 2 x 1000 on 4 KV heads 21.4 / 19.7, 4 x 2000 on 1 23.5 / 22.2; but 2 x 3600 on 1 23.8 / 25.7,
-            // one of 3800 tokens 24.7 / 26.4, 3 x 400 on 4 (300 workgroups) 18.3 / 19.7.
-            if (L.map.batch == 1 || L.max_len > 2000 || tiles16 * L.p->num_kv_heads <= 340)
+            // Prompts of up to 2048 tokens have so few coarse key tiles that a workgroup's start is most of what it does: with
+            // more workgroups than CUs, two / four tokens per wavefront (calls): 4 x 700 tokens on 2 KV heads 19.8 / 17.4 us,
+            // 4 x 1000 20.7 / 17.6, 2 x 1000 on 4 21.0 / 17.7, 4 x 2000 on 1 23.3 / 20.3, one of 600, 1000 tokens on 8
+            // 20.4 / 17.0, 20.4 / 17.6, 400 on 16 20.3 / 17.1, 1400 on 4 20.3 / 18.6; but 1100, 1200 tokens on 4 (276 and 300
+            // workgroups) 18.1 / 19.0, 19.4 / 20.4, 2 x 3600 on 1 23.8 / 25.7, one of 3800 24.7 / 26.4.
+            if (L.max_len > 2048 || tiles16 * L.p->num_kv_heads <= 300)
                 return launch_scores_pool<8, 2>(L, a, cu_h, pooled ? pool.pad : -1);
         }
         return launch_scores_pool<8, 4>(L, a, cu_h, pooled ? pool.pad : -1);

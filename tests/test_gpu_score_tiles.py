@@ -17,7 +17,7 @@ RTOL = 10 * 8.5e-5
 
 
 @pytest.mark.parametrize("lens", [[1535], [1536], [1537], [4095], [4096], [4097], [37, 1200, 1, 290], [2300, 33, 1800],
-                                  [700, 701, 31, 699, 703]])
+                                  [700, 701, 31, 699, 703], [1801, 1850], [1750, 33, 1801], [1751, 600, 610, 640], [2048, 2047]])
 @pytest.mark.parametrize("window", [(32, 16), (24, 12), (25, 5)])
 @pytest.mark.parametrize("lse_mode", [0, 1])
 def test_scores(m, oracle, lens, window, lse_mode):  # noqa: F811
