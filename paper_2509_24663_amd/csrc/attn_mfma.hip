@@ -383,8 +383,8 @@ struct TileKernel {
                 if (u0) unit_bwd<OWN>(st, stage, kx, vx, lane, t0 + w - j0 * kBlock, issue_now);
                 if (u1) unit_bwd<false>(st, stage + STAGE_ELEMS * 2, kx, vx, lane, 0, issue_now);
             } else {
-                if (u0) unit<OWN>(st, stage, kx, vx, lane, t0 + w - j0 * kBlock, issue_now);
-                if (u1) unit<false>(st, stage + STAGE_ELEMS * 2, kx, vx, lane, 0, issue_now);
+                if (u0) unit<OWN, false>(st, stage, kx, vx, lane, t0 + w - j0 * kBlock, issue_now);
+                if (u1) unit<false, false>(st, stage + STAGE_ELEMS * 2, kx, vx, lane, 0, issue_now);
             }
 #ifdef ATTN_TIMING_CLOCK
             const uint64_t ck2 = wall_clock64();
@@ -543,14 +543,20 @@ int launch_tiles(const Launch &L, const AttnArgs &a, const int32_t *cu_h) {
         }
     const int tokens = rules::attn_tile_tokens(cu_h, L.map.batch, L.max_len, L.p->num_kv_heads, a.idx != nullptr, a.topk_total,
                                                a.dense_below, BWD);
-    if (tokens == 4) rc = launch_tile<4, 2, BWD>(L, a, cu_h);
-    else if (tokens == 8) rc = launch_tile<8, 2, BWD>(L, a, cu_h);
+    // (forward calls with so few tiles of 4 belong to attn_short.hip)
+    if constexpr (BWD)
+        if (tokens == 4) rc = launch_tile<4, 2, true>(L, a, cu_h);
+    if (tokens == 8) rc = launch_tile<8, 2, BWD>(L, a, cu_h);
     if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 2, BWD>(L, a, cu_h);
     if (rc == INFLLMV2_ERR_UNSUPPORTED) rc = launch_tile<16, 1, BWD>(L, a, cu_h);
     return rc;
 }
 
 }  // namespace
+
+// short prompts (attn_short.hip); INFLLMV2_ERR_UNSUPPORTED: not its case
+int launch_attn_short(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, void *out,
+                      float *lse, const int32_t *cu_h);
 
 bool attn_mfma_supported(const infllmv2_params *p) {
     return p->dtype == INFLLMV2_BF16 && p->head_dim == D && p->num_q_heads / p->num_kv_heads == G;
@@ -588,6 +594,8 @@ int launch_attn_mfma(const Launch &L, const void *q, const void *k, const void *
     void *ws = L.ws;
     if (ws == nullptr || L.ws_bytes < (size_t)nblk_total * L.p->num_kv_heads * VT_TILE_ELEMS * sizeof(uint16_t))
         return INFLLMV2_ERR_WORKSPACE_TOO_SMALL;
+    const int st = launch_attn_short(L, q, k, v, idx, dense_below, out, lse, cu_h);
+    if (st != INFLLMV2_ERR_UNSUPPORTED) return st;
     a.vt = (const uint16_t *)ws;
     a.nblk_total = (int)nblk_total;
     hipLaunchKernelGGL(vt_transpose_kernel, dim3((unsigned)nblk_total, L.p->num_kv_heads), dim3(256), 0, L.stream,

@@ -317,6 +317,9 @@ __device__ inline float prob_step(f32x4 &a0, f32x4 &a1, int e, float (&p)[2], u3
 // that an exponent was large (or this is the token's first half block) is the reference moved to the half block's
 // maximum, everything accumulated so far rescaled, and the half block's probabilities redone from the exponents,
 // which are still in a0, a1.
+// SHARED: several wavefronts hold one token, each with some of its half blocks.  A half block whose exponents are all -infinity
+// then leaves the reference unset, so that it does not turn into NaN what the other wavefronts have.
+template <bool SHARED = false>
 __device__ inline float move_reference(Tok &t, f32x4 &a0, f32x4 &a1, u32x4 &pb) {
     float mx = fmaxf(fmaxf(a0[0], a0[1]), a0[2]);
     mx = fmaxf(fmaxf(mx, a0[3]), a1[0]);
@@ -329,7 +332,8 @@ __device__ inline float move_reference(Tok &t, f32x4 &a0, f32x4 &a1, u32x4 &pb) 
         delta = fmaxf(delta, 0.f);         // never down once there is history
         alpha = fast_exp2(-delta);
     }
-    t.slack = kSumSlack;
+    if (SHARED && t.slack <= 0.f && mx == -INFINITY) delta = 0.f;
+    else t.slack = kSumSlack;
     t.nr -= delta;
     t.l *= alpha;
 #pragma unroll
@@ -340,102 +344,18 @@ __device__ inline float move_reference(Tok &t, f32x4 &a0, f32x4 &a1, u32x4 &pb) 
     return ls;
 }
 
-// One token against one block.  OWN: the block is the token's own and keys past key_limit are masked.
-//
-// The block is handled as two halves of 32 keys so that the vector work of the softmax always has matrix work
-// of the same wave to hide under: the exponentials of the first half are issued between the S^T products of the
-// second half, those of the second half between the PV products of the first.  (With the whole block's softmax
-// between the two groups of products, the waves of a workgroup, which start every unit together after a barrier,
-// all reach the softmax at the same time and the matrix core idles meanwhile.)  The order below is the issue
-// order: a scheduling fence after every step keeps the compiler from regrouping it.
-struct NoMid {
-    __device__ inline void operator()() const {}
-};
-
-// `mid` is called once, after the second group of products (the S^T half of the unit) has been issued: work of the
-// caller that must not delay the start of the unit but should be under way well before its end (the tile kernel
-// issues its copies there).
-template <bool OWN, class Mid = NoMid>
-__device__ inline void unit(Tok &t, uint32_t stage, uint32_t kx, uint32_t vx, int lane, int key_limit, Mid mid = Mid()) {
-    const int key0 = 8 * (lane >> 4);
-    const uint32_t kb = stage + kx, vb = stage + vx;
-    constexpr int W = 4;               // operand fetches run W products ahead, through all four groups of products
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4 acc[4];
-    u32x4 pb[2];
-    bf16x8 f[W];
-    float p[2];
-    // fragment n of the unit: 0-7 K rows of the first half (key tile n & 1, k-step n >> 1), 8-15 of the second
-    // half, 16-23 V^T k-step 0 (dim tile n & 7), 24-31 V^T k-step 1
-    auto frag = [&](int n) -> bf16x8 {
-        if (n < 16) return k_frag(kb, 2 * (n >> 3) + (n & 1), (n >> 1) & 3);
-        return v_frag(vb, n & 7, (n >> 3) & 1);
-    };
+// words of an operand of eight keys with those behind key `last` taken as 0
+__device__ inline u32x4 keep_mask(int last) {
+    u32x4 x;
 #pragma unroll
-    for (int n = 0; n < W; ++n) f[n] = frag(n);
-    // Products are issued in pairs, the later-fetched fragment first: LDS reads return in order, so the one wait
-    // for that fragment covers the pair (16 waits per unit instead of 32; a lone wave on a SIMD is bound by the
-    // number of instructions it has to issue).  The two products of a pair write different accumulators.
-    // ---- exponents of the first half (8 products, 2 accumulators)
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-        const int s = i >> 1;
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(i + 1) % W], t.qf[s], s == 0 ? zero : acc[1], 0, 0, 0);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % W], t.qf[s], s == 0 ? zero : acc[0], 0, 0, 0);
-        f[i % W] = frag(i + W);
-        f[(i + 1) % W] = frag(i + 1 + W);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    // ---- second half's exponents || first half's probabilities
-    float ls = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-        const int s = i >> 1;
-        acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(8 + i + 1) % W], t.qf[s], s == 0 ? zero : acc[3], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(8 + i) % W], t.qf[s], s == 0 ? zero : acc[2], 0, 0, 0);
-        f[(8 + i) % W] = frag(8 + i + W);
-        f[(8 + i + 1) % W] = frag(8 + i + 1 + W);
-        ls += prob_step<OWN>(acc[0], acc[1], i, p, pb[0], t.cm, t.nr, key0, key_limit);
-        ls += prob_step<OWN>(acc[0], acc[1], i + 1, p, pb[0], t.cm, t.nr, key0, key_limit);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (__any(!(ls < t.slack))) ls = move_reference(t, acc[0], acc[1], pb[0]);
-    t.l += ls;
-    mid();
-    // ---- O^T += V^T P^T of the first half || second half's probabilities
-    ls = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-        t.o[i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(16 + i + 1) % W], __builtin_bit_cast(bf16x8, pb[0]), t.o[i + 1], 0, 0, 0);
-        t.o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(16 + i) % W], __builtin_bit_cast(bf16x8, pb[0]), t.o[i], 0, 0, 0);
-        f[(16 + i) % W] = frag(16 + i + W);
-        f[(16 + i + 1) % W] = frag(16 + i + 1 + W);
-        ls += prob_step<OWN>(acc[2], acc[3], i, p, pb[1], t.cm, t.nr, key0 + 32, key_limit);
-        ls += prob_step<OWN>(acc[2], acc[3], i + 1, p, pb[1], t.cm, t.nr, key0 + 32, key_limit);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (__any(!(ls < t.slack))) ls = move_reference(t, acc[2], acc[3], pb[1]);
-    t.l += ls;
-    // ---- second half
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-        t.o[i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(24 + i + 1) % W], __builtin_bit_cast(bf16x8, pb[1]), t.o[i + 1], 0, 0, 0);
-        t.o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(24 + i) % W], __builtin_bit_cast(bf16x8, pb[1]), t.o[i], 0, 0, 0);
-        if (i + W < 8) {
-            f[(24 + i) % W] = frag(24 + i + W);
-            f[(24 + i + 1) % W] = frag(24 + i + 1 + W);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int i = 0; i < 4; ++i) x[i] = (uint32_t)((1ull << (16 * min(max(last + 1 - 2 * i, 0), 2))) - 1ull);
+    return x;
 }
+__device__ inline bf16x8 keep_keys(bf16x8 f, u32x4 mask) { return __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, f) & mask); }
 
-// =====================================================================================================
-// Backward unit (dQ): one K/V block against the token held by this wave.  Per half of 32 keys S^T = K Q^T and dP^T = V dO^T
-// (keys x heads, seeded with -lse / scale and -Delta, so that the products come out subtracted), dZ = P dP, and
-// dQ^T += K^T dZ^T, whose first operand is the K tile read back transposed.  Key rows are assigned to product rows as in
-// the prefill unit, so a lane's eight dZ are the eight consecutive keys it must supply.  Both tiles are row-major, 256-byte
-// rows, 16-byte chunk c of row r at chunk c ^ bwd_swizzle(r): the sixteen rows of an operand read take sixteen positions,
-// and so do the 8 rows x 2 chunks that half a wave touches in a transposing read.
+// Row-major tiles (backward unit; prefill unit of short prompts): K and V with 256-byte rows, 16-byte chunk c of row r at chunk
+// c ^ bwd_swizzle(r): the sixteen rows of an operand read take sixteen positions, and so do the 8 rows x 2 chunks that half a
+// wave touches in a transposing read.
 __device__ inline int bwd_swizzle(int r) { return 4 * (r & 3) + 2 * ((r >> 3) & 1) + ((r >> 4) & 1); }
 
 // K or V piece q (rows 4q .. 4q+3 of the block): lane l fills (row 4q + l / 16, physical chunk l % 16)
@@ -471,6 +391,116 @@ __device__ inline bf16x8 visible_keys(bf16x8 f, int last) {
     return __builtin_bit_cast(bf16x8, x);
 }
 
+// One token against one block.  OWN: the block is the token's own and keys past key_limit are masked.
+//
+// The block is handled as two halves of 32 keys so that the vector work of the softmax always has matrix work
+// of the same wave to hide under: the exponentials of the first half are issued between the S^T products of the
+// second half, those of the second half between the PV products of the first.  (With the whole block's softmax
+// between the two groups of products, the waves of a workgroup, which start every unit together after a barrier,
+// all reach the softmax at the same time and the matrix core idles meanwhile.)  The order below is the issue
+// order: a scheduling fence after every step keeps the compiler from regrouping it.
+struct NoMid {
+    __device__ inline void operator()() const {}
+};
+
+// `mid` is called once, after the second group of products (the S^T half of the unit) has been issued: work of the
+// caller that must not delay the start of the unit but should be under way well before its end (the tile kernel
+// issues its copies there).
+//
+// ROWS: the V tile is row-major like the K tile (see above) and V^T comes from transposing reads; kx and vx are then
+// bwd_row_bytes and bwd_trans_bytes plus a tile, and keys that the token does not see stay out of the V products as well (their
+// probability is 0, but 0 times an infinity in their V rows would not be).
+template <bool OWN, bool ROWS = false, class Mid = NoMid>
+__device__ inline void unit(Tok &t, uint32_t stage, uint32_t kx, uint32_t vx, int lane, int key_limit, Mid mid = Mid()) {
+    const int key0 = 8 * (lane >> 4);
+    const uint32_t kb = stage + kx, vb = stage + vx;
+    constexpr int W = 4;               // operand fetches run W products ahead, through all four groups of products
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[4];
+    u32x4 pb[2];
+    bf16x8 f[W];
+    float p[2];
+    // fragment n of the unit: 0-7 K rows of the first half (key tile n & 1, k-step n >> 1), 8-15 of the second
+    // half, 16-23 V^T k-step 0 (dim tile n & 7), 24-31 V^T k-step 1
+    auto frag = [&](int n) -> bf16x8 {
+        if (n < 16) return k_frag(kb, 2 * (n >> 3) + (n & 1), (n >> 1) & 3);
+        if (ROWS) return bwd_kt_frag(vb, n & 7, (n >> 3) & 1);
+        return v_frag(vb, n & 7, (n >> 3) & 1);
+    };
+#pragma unroll
+    for (int n = 0; n < W; ++n) f[n] = frag(n);
+    // Products are issued in pairs, the later-fetched fragment first: LDS reads return in order, so the one wait
+    // for that fragment covers the pair (16 waits per unit instead of 32; a lone wave on a SIMD is bound by the
+    // number of instructions it has to issue).  The two products of a pair write different accumulators.
+    // ---- exponents of the first half (8 products, 2 accumulators)
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        const int s = i >> 1;
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(i + 1) % W], t.qf[s], s == 0 ? zero : acc[1], 0, 0, 0);
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % W], t.qf[s], s == 0 ? zero : acc[0], 0, 0, 0);
+        f[i % W] = frag(i + W);
+        f[(i + 1) % W] = frag(i + 1 + W);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // ---- second half's exponents || first half's probabilities
+    float ls = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        const int s = i >> 1;
+        acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(8 + i + 1) % W], t.qf[s], s == 0 ? zero : acc[3], 0, 0, 0);
+        acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(8 + i) % W], t.qf[s], s == 0 ? zero : acc[2], 0, 0, 0);
+        f[(8 + i) % W] = frag(8 + i + W);
+        f[(8 + i + 1) % W] = frag(8 + i + 1 + W);
+        ls += prob_step<OWN>(acc[0], acc[1], i, p, pb[0], t.cm, t.nr, key0, key_limit);
+        ls += prob_step<OWN>(acc[0], acc[1], i + 1, p, pb[0], t.cm, t.nr, key0, key_limit);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (__any(!(ls < t.slack))) ls = move_reference<ROWS>(t, acc[0], acc[1], pb[0]);
+    t.l += ls;
+    mid();
+    // ---- O^T += V^T P^T of the first half || second half's probabilities
+    ls = 0.f;
+    u32x4 keep = {};
+    if (OWN && ROWS) keep = keep_mask(key_limit - key0);
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        if (OWN && ROWS) {
+            f[(16 + i + 1) % W] = keep_keys(f[(16 + i + 1) % W], keep);
+            f[(16 + i) % W] = keep_keys(f[(16 + i) % W], keep);
+        }
+        t.o[i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(16 + i + 1) % W], __builtin_bit_cast(bf16x8, pb[0]), t.o[i + 1], 0, 0, 0);
+        t.o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(16 + i) % W], __builtin_bit_cast(bf16x8, pb[0]), t.o[i], 0, 0, 0);
+        f[(16 + i) % W] = frag(16 + i + W);
+        f[(16 + i + 1) % W] = frag(16 + i + 1 + W);
+        ls += prob_step<OWN>(acc[2], acc[3], i, p, pb[1], t.cm, t.nr, key0 + 32, key_limit);
+        ls += prob_step<OWN>(acc[2], acc[3], i + 1, p, pb[1], t.cm, t.nr, key0 + 32, key_limit);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (__any(!(ls < t.slack))) ls = move_reference<ROWS>(t, acc[2], acc[3], pb[1]);
+    t.l += ls;
+    // ---- second half
+    if (OWN && ROWS) keep = keep_mask(key_limit - key0 - 32);
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        if (OWN && ROWS) {
+            f[(24 + i + 1) % W] = keep_keys(f[(24 + i + 1) % W], keep);
+            f[(24 + i) % W] = keep_keys(f[(24 + i) % W], keep);
+        }
+        t.o[i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(24 + i + 1) % W], __builtin_bit_cast(bf16x8, pb[1]), t.o[i + 1], 0, 0, 0);
+        t.o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[(24 + i) % W], __builtin_bit_cast(bf16x8, pb[1]), t.o[i], 0, 0, 0);
+        if (i + W < 8) {
+            f[(24 + i) % W] = frag(24 + i + W);
+            f[(24 + i + 1) % W] = frag(24 + i + 1 + W);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// =====================================================================================================
+// Backward unit (dQ): one K/V block against the token held by this wave.  Per half of 32 keys S^T = K Q^T and dP^T = V dO^T
+// (keys x heads, seeded with -lse / scale and -Delta, so that the products come out subtracted), dZ = P dP, and
+// dQ^T += K^T dZ^T, whose first operand is the K tile read back transposed.  Key rows are assigned to product rows as in
+// the prefill unit, so a lane's eight dZ are the eight consecutive keys it must supply.  Both tiles are row-major.
 struct TokBwd {
     bf16x8 qf[4], gf[4];   // Q_t and dO_t as second operands: head = lane % 16, dims ks*32 + (lane/16)*8 ..
     f32x4 o[8];            // dQ_t^T / scale: dim tile dt, dims dt*16 + 4*(lane/16) + r, head = lane % 16

@@ -134,6 +134,40 @@ inline DkvForm generic_dkv_form(bool bf16, int d, int hkv, int G, const int32_t 
     return {chunk, one ? 1 : 2};
 }
 
+// Attention of short prompts (attn_short.hip; bf16, G = 16, d 128): wavefronts per token, or 0 where the tile kernel is faster.
+//
+// Tiles of four tokens read a block for fewer tokens than the tile kernel's, but their chain is shorter, which wins while a
+// CU gets few of them.  Two wavefronts per token take a whole CU (128 KB of LDS): the choice while one round of workgroups is all there is,
+// or one and a half where the rest are the short tiles of long walks; with one wavefront two workgroups share a CU.  Microseconds of the call,
+// tile kernel / two / one: 2 KV heads, 64 blocks, 300 tokens (150 workgroups) 14.3 / 10.1 / 10.7, 700 (350) 21.6 / 16.4 / 18.7, 1000 (500) 27.1 /
+// 23.9 / 25.1, 1200 (600) 30.4 / 34.7 / 28.9, 1400 33.7 / 41.0 / 33.0, 2000 52.5 / 69.6 / 61.5; 1 KV head, 1700 (425) 36.9 / 29.3 / 37.4, 2000
+// (500) 42.0 / 35.9 / 43.3, 2400 (600) 48.3 / 53.2 / 51.0; 4 KV heads, 300 (300) 16.3 / 12.8 / 11.8, 500 (500) 19.6 / 17.9 / 15.9.
+// Budgets that leave blocks out shorten the walks, so that the second round weighs more: 1 KV head, 16 blocks, 1700 tokens 32.3 / 29.5 / 35.1, 2000
+// 34.5 / 36.1 / 38.8; 8 blocks, 1300 tokens (325) 23.4 / 20.4 / 24.7, 1700 25.4 / 27.1 / 25.1; 4 blocks, 1300 tokens 17.5 / 18.9 / 14.4; 2 KV
+// heads, 8 blocks, 777 tokens (390) 21.4 / 19.0 / 19.9, 1000 23.1 / 23.8 / 22.8.
+// One wavefront against the tile kernel: up to 600 tokens whatever the batch (100 x 300 tokens 298 / 317, 16 x 520 100 / 102, 1000 x 10 108 / 520);
+// up to 1024 tokens the tile kernel's time goes up by rounds of 256 tiles of 16 (4 x 777 tokens 50.1 / 55.0, 5 x 777 62.3 / 58.7; on 1 KV head 3 x
+// 777 23.7 / 32.5, 4 x 777 33.4 / 33.5, 6 x 700 37.9 / 33.9; 8 KV heads, 850 tokens 53.0 / 57.8, 8 blocks, 900 tokens 55.8 / 54.1; 4 KV
+// heads, 1000 tokens 38.3 / 39.8, 8 blocks 35.3 / 33.1).
+inline int short_attn_waves(const int32_t *cu_h, int batch, int max_len, int hkv, bool sparse, int topk, int dense_below) {
+    int64_t wgs = 0, tiles16 = 0;
+    for (int s = 0; s < batch; ++s) {
+        wgs += (int64_t)((cu_h[s + 1] - cu_h[s] + 3) / 4) * hkv;
+        tiles16 += (int64_t)((cu_h[s + 1] - cu_h[s] + 15) / 16) * hkv;
+    }
+    const int blocks = (max_len + kKeys - 1) / kKeys;
+    const int walk = sparse && max_len >= dense_below ? std::min(topk, blocks) : blocks;
+    const bool every = walk == blocks;
+    if (wgs <= 256) return 2;
+    if (wgs <= 512 && max_len > 600 && max_len <= 2048) {
+        if (walk < 6) return 1;
+        if (walk < 10 ? wgs <= 400 : every || max_len <= 1728) return 2;
+    }
+    if (max_len <= 600) return 1;
+    const int64_t rounds = std::max<int64_t>((tiles16 - 16 + 255) / 256, 1);
+    return max_len <= 1024 && rounds <= 2 && wgs <= (batch == 1 && every ? 1000 : 768) * rounds ? 1 : 0;
+}
+
 // Tile kernel of attention and dQ (bf16, G = 16, d 128): tokens per workgroup.
 //
 // Sixteen, or 8 or 4 while even those leave CUs without a workgroup (one fits a CU): a block in LDS then serves fewer tokens,
