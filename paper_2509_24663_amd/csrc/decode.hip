@@ -24,6 +24,8 @@
 //   merge   : grid (pairs)              log-sum-exp merge of the per-split partial outputs, writes O and lse
 // K^{C1} is float32; it is split into a bf16 high part and a bf16 residual in registers and both products
 // are accumulated, so the logits carry ~16 mantissa bits of K^{C1}.
+#include <algorithm>
+
 #include "attn_unit.h"
 #include "topk_row.h"
 
@@ -60,7 +62,7 @@ struct DecArgs {
     int pk_cap;
     int fsplit;        // partial-output slots taken by the forced blocks (attended beside the scores)
     int nslot;         // fsplit + nsplit
-    int bpw;           // blocks per attend workgroup (<= its number of waves): list entries split * bpw .. + bpw - 1
+    int bpw;           // blocks per attend workgroup: list entries split * bpw .. + bpw - 1
 };
 
 // Which blocks the newest token of an L-token sequence always keeps (Eq. 2: the first n_init and the last n_local
@@ -433,12 +435,13 @@ __global__ void __launch_bounds__(SEL_THREADS) dec_select_kernel(DecArgs a, int 
 // ------------------------------------------------------------------------------------------ attend + merge
 constexpr int AW = 8;              // waves (= selected blocks) per attend workgroup
 
-// Up to NWV waves of a workgroup attend to one block each (j < 0: none) for the newest token of (sequence b, KV head
-// h); the partial results are merged in LDS and written as partial `slot` of the pair.  Every thread of the
+// Up to NWV waves of a workgroup attend to `rounds` blocks each, block_of(0), block_of(1), .. (< 0: no more), for the newest token
+// of (sequence b, KV head h); the partial results are merged in LDS and written as partial `slot` of the pair.  Every thread of the
 // workgroup calls this (barriers inside); waves past NWV only help with the final sum.  smem: NWV tiles of 16 KB.
-template <int NWV>
-__device__ inline void attend_partial(const DecArgs &a, int pair, int L, int slot, int j, uint16_t *smem, float (*wm)[16],
-                                      float (*wl)[16]) {
+// MANY: rounds may be more than one.
+template <int NWV, bool MANY, class Blocks>
+__device__ inline void attend_partial(const DecArgs &a, int pair, int L, int slot, int rounds, Blocks block_of, uint16_t *smem,
+                                      float (*wm)[16], float (*wl)[16]) {
     // (L = ctx[b] comes from the caller: read again here, after the caller's stores, it would be a second trip to memory
     // in front of the K/V loads)
     const int b = pair / a.hkv, h = pair - b * a.hkv;
@@ -453,19 +456,26 @@ __device__ inline void attend_partial(const DecArgs &a, int pair, int L, int slo
     for (int dt = 0; dt < 8; ++dt) st.o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     st.m = -INFINITY;
     st.l = 0.f;
-    if (w < NWV && j >= 0) {
+    int j = w < NWV ? block_of(0) : -1;
+    if (j >= 0) {
         uint16_t *vtile = smem + w * TILE_ELEMS;
-#pragma unroll
-        for (int qi = 0; qi < 16; ++qi) load_piece(vb, a.kv_tok_stride, j, L, vtile, qi, lane);
         // K fragments as MFMA A operands, straight from global memory: row 16*kt + m16, dims 32*s + 8*g ..
         bf16x8 kf[4][4];
+        auto load_k = [&](int j1) {
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            const int tok = min(j * kBlock + 16 * kt + m16, L - 1);
-            const uint16_t *kr = kb + (int64_t)tok * a.kv_tok_stride + g * 8;
+            for (int kt = 0; kt < 4; ++kt) {
+                const int tok = min(j1 * kBlock + 16 * kt + m16, L - 1);
+                const uint16_t *kr = kb + (int64_t)tok * a.kv_tok_stride + g * 8;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) kf[kt][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(kr + s * 32));
-        }
+                for (int s = 0; s < 4; ++s) kf[kt][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(kr + s * 32));
+            }
+        };
+        auto load_v = [&](int j1) {
+#pragma unroll
+            for (int qi = 0; qi < 16; ++qi) load_piece(vb, a.kv_tok_stride, j1, L, vtile, qi, lane);
+        };
+        load_v(j);
+        load_k(j);
         const uint16_t *qp = a.q + ((int64_t)b * a.hq + h * G + m16) * D + g * 8;
 #pragma unroll
         for (int s = 0; s < 4; ++s) st.qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qp + s * 32));
@@ -473,17 +483,30 @@ __device__ inline void attend_partial(const DecArgs &a, int pair, int L, int slo
         // last third of the K fragments one at a time between the products: a chain of trips to memory)
         __builtin_amdgcn_sched_barrier(0);
         const LaneOffs lo = lane_offsets(lane);
-        f32x4 acc[4];
+        for (int r = 1;; ++r) {
+            f32x4 acc[4];
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            acc[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int kt = 0; kt < 4; ++kt) {
+                acc[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                acc[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kt][s], st.qf[s], acc[kt], 0, 0, 0);
+                for (int s = 0; s < 4; ++s)
+                    acc[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kt][s], st.qf[s], acc[kt], 0, 0, 0);
+            }
+            const int next = MANY && r < rounds ? block_of(r) : -1;
+            if (next >= 0) {                                      // its K rows while this block's softmax and V products run
+                __builtin_amdgcn_sched_barrier(0);
+                load_k(next);
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("s_waitcnt vmcnt(16)" ::: "memory"); // this block's V tile, requested before them, has landed in LDS
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            softmax_pv<MANY>(st, acc, vtile, lo, lane, j == bt, t - j * kBlock, c);
+            if (next < 0) break;
+            j = next;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the tile has been read
+            load_v(j);
         }
-        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);          // this wave's V tile has landed in LDS
-        asm volatile("" ::: "memory");
-        softmax_pv(st, acc, vtile, lo, lane, j == bt, t - j * kBlock, c);
         st.l += __shfl_xor(st.l, 16);
         st.l += __shfl_xor(st.l, 32);
     }
@@ -542,7 +565,7 @@ __global__ void __launch_bounds__(AW * 64) dec_attn_kernel(DecArgs a) {
     if (L < a.tk.dense_below) j = e <= bt ? e : -1;
     else if (e < a.tk.topk_total) j = a.idx[(int64_t)pair * a.tk.topk_total + e];
     if (j > bt) j = -1;
-    attend_partial<AW>(a, pair, L, split, j, smem, wm, wl);
+    attend_partial<AW, false>(a, pair, L, split, 1, [&](int) { return j; }, smem, wm, wl);
 }
 
 // =========================================================================================== three-stage form
@@ -579,7 +602,7 @@ __global__ void __launch_bounds__(256, 4) dec_front_kernel(DecArgs a) {
     const int e = f * FW + (int)(threadIdx.x >> 6);
     // (dense sequences attend to every block in the attend kernel; their forced slots stay empty)
     const int j = (L >= a.tk.dense_below && (int)(threadIdx.x >> 6) < FW && e < fo.n_forced) ? fo.forced_block(e) : -1;
-    attend_partial<FW>(a, pair, L, f, j, smem, wm, wl);
+    attend_partial<FW, false>(a, pair, L, f, 1, [&](int) { return j; }, smem, wm, wl);
 }
 
 __global__ void __launch_bounds__(256) dec_pool_kernel(DecArgs a) {
@@ -716,8 +739,9 @@ constexpr int kPkLds = 4096;                // pooled keys a workgroup keeps in 
 
 // The selection of one pair by a workgroup of NW waves: on return (after a barrier) sel[0 .. kr) holds the top-k blocks
 // without the forced ones, ascending.  hist: [4][256] of LDS.
-template <int NW>
-__device__ inline void pick_blocks(const DecArgs &a, int pair, const Forced &fo, int *sel, int (*hist)[256], int *wave_tot,
+// pk: the pair's pooled keys, in memory or in LDS.
+template <int NW, class Keys>
+__device__ inline void pick_blocks(const Keys *pk, const Forced &fo, int *sel, int (*hist)[256], int *wave_tot,
                                    uint32_t *s_prefix, int *s_k) {
     constexpr int NT = NW * 64;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -728,7 +752,6 @@ __device__ inline void pick_blocks(const DecArgs &a, int pair, const Forced &fo,
         // wave reduces the histogram of a pass by itself (data-parallel scan, no LDS round trips), so a pass costs
         // one barrier.
         constexpr int KPT = kPkLds / NT;
-        const uint32_t *pk = a.pk + (int64_t)pair * a.pk_cap;
         const int per = (fo.nblk + NT - 1) / NT, jb0 = tid * per;
         uint32_t kreg[KPT];
         uint32_t live = 0u;                              // bit u: block jb0 + u exists and takes part in the top-k
@@ -809,7 +832,6 @@ __device__ inline void pick_blocks(const DecArgs &a, int pair, const Forced &fo,
         __syncthreads();
     } else {
         // the same for rows too long for the registers: every pass re-reads the pooled keys from memory
-        const uint32_t *pk = a.pk + (int64_t)pair * a.pk_cap;
         for (int i = tid; i < 4 * 256; i += NT) (&hist[0][0])[i] = 0;
         if (tid == 0) { *s_prefix = 0u; *s_k = fo.kr; }
         __syncthreads();
@@ -866,6 +888,99 @@ __device__ inline void pick_blocks(const DecArgs &a, int pair, const Forced &fo,
     }
 }
 
+// Normaliser, group sums and max-pool of a whole row by one workgroup of NT threads: pk[j], j < nblk, as dec_pool_kernel leaves them,
+// in LDS (ends with a barrier).  At most kRowKeys visible keys and kRowBlocks blocks.  The logits of the first ZPT NT keys and the chunk
+// partials are requested up front: one trip to memory.
+constexpr int kRowKeys = 8192, kRowBlocks = 2048;
+struct RowLds {
+    float sh[kRowKeys], red[64][16][2], lse2[16];
+    uint32_t pk[kRowBlocks];
+};
+template <int NT, int ZPT>
+__device__ inline void pool_row(const DecArgs &a, int pair, int L, const Forced &fo, RowLds &r) {
+    constexpr int NG = NT / 16;                          // thread groups per head of the normaliser's merge
+    const int tid = threadIdx.x;
+    const int v = visible_cmp(L - 1, a.tk.lc, a.tk.sc);
+    const float *zb = a.z + (int64_t)pair * a.zs * G;
+    float4 zr[ZPT][4];
+#pragma unroll
+    for (int u = 0; u < ZPT; ++u) {
+        const float4 *zk = reinterpret_cast<const float4 *>(zb + (int64_t)min(tid + u * NT, max(v - 1, 0)) * G);
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) zr[u][q4] = zk[q4];
+    }
+    {
+        const int head = tid & 15, pg = tid >> 4;
+        const float *pp = a.part + (int64_t)pair * a.nchunk * 32 + head * 2;
+        constexpr int PQ = 64 / NG;                      // contexts up to 131072 tokens
+        float2 pq[PQ];
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) pq[q] = *reinterpret_cast<const float2 *>(pp + min(pg + NG * q, a.nchunk - 1) * 32);
+        float mm = -INFINITY, ll = 0.f;
+#pragma unroll
+        for (int q = 0; q < PQ; ++q)
+            if (pg + NG * q < a.nchunk) mm = fmaxf(mm, pq[q].x);
+        {
+            const float ms = mm == -INFINITY ? 0.f : mm;
+#pragma unroll
+            for (int q = 0; q < PQ; ++q)
+                if (pg + NG * q < a.nchunk) ll += pq[q].y * fast_exp2(pq[q].x - ms);
+        }
+        for (int ch = pg + NG * PQ; ch < a.nchunk; ch += NG) {
+            const float mo = pp[ch * 32], lo = pp[ch * 32 + 1];
+            const float mn = fmaxf(mm, mo);
+            const float ms = mn == -INFINITY ? 0.f : mn;
+            ll = ll * fast_exp2(mm - ms) + lo * fast_exp2(mo - ms);
+            mm = mn;
+        }
+        r.red[pg][head][0] = mm;
+        r.red[pg][head][1] = ll;
+        __syncthreads();
+        // NG -> 1: a wavefront per head (or per two heads), one thread group per lane, merged with lane moves
+        const int lane = tid & 63, w = tid >> 6;
+        for (int hd = w; hd < G; hd += NT / 64) {
+            const float mk = lane < NG ? r.red[lane][hd][0] : -INFINITY, lk = lane < NG ? r.red[lane][hd][1] : 0.f;
+            const float m2 = rows_max(row_all_max(mk));
+            const float l2 = rows_sum(row_all_sum(mk == -INFINITY ? 0.f : lk * fast_exp2(mk - m2)));
+            if (lane == 0) r.lse2[hd] = l2 > 0.f ? m2 + __log2f(l2) : INFINITY;
+        }
+        __syncthreads();
+    }
+    // S^shared[i] = sum over the 16 heads of 2^(z[g][i] - lse2[g])
+    float nl[G];
+#pragma unroll
+    for (int gq = 0; gq < G; ++gq) nl[gq] = r.lse2[gq];
+    auto group_sum = [&](const float4 (&z4)[4]) -> float {
+        float sum = 0.f;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+            sum += (fast_exp2(z4[q4].x - nl[4 * q4]) + fast_exp2(z4[q4].y - nl[4 * q4 + 1])) +
+                   (fast_exp2(z4[q4].z - nl[4 * q4 + 2]) + fast_exp2(z4[q4].w - nl[4 * q4 + 3]));
+        return sum;
+    };
+#pragma unroll
+    for (int u = 0; u < ZPT; ++u)
+        if (tid + u * NT < v) r.sh[tid + u * NT] = group_sum(zr[u]);
+    for (int i = tid + ZPT * NT; i < v; i += NT) {
+        const float4 *zk = reinterpret_cast<const float4 *>(zb + (int64_t)i * G);
+        const float4 z4[4] = {zk[0], zk[1], zk[2], zk[3]};
+        r.sh[i] = group_sum(z4);
+    }
+    __syncthreads();
+    for (int j = tid; j < fo.nblk; j += NT) {
+        float m = 0.f;
+        if (!fo.is_forced(j)) {
+            const int lo = a.tk.pool_stride * j - a.tk.pool_pad;
+            for (int u = 0; u < a.tk.pool_len; ++u) {
+                const int i = lo + u;
+                if (i >= 0 && i < v) m = fmaxf(m, r.sh[i]);
+            }
+        }
+        r.pk[j] = __float_as_uint(m);
+    }
+    __syncthreads();
+}
+
 // The whole list of a sparse pair, ascending: initial blocks, the top-k, the local blocks, then -1 (sel: nullptr when every
 // block up to the query's is kept).
 __device__ inline void write_list(const Forced &fo, const int *sel, int32_t *out, int topk_total, int nt) {
@@ -880,28 +995,37 @@ __device__ inline void write_list(const Forced &fo, const int *sel, int32_t *out
     }
 }
 
-// The selection as a kernel of its own, one workgroup per pair (see DecLayout::aw).
-__global__ void __launch_bounds__(AW * 64) dec_pick_kernel(DecArgs a) {
-    __shared__ int sel[kSelMax], hist[4][256], wave_tot[AW], s_k;
+// The selection as a kernel of its own, one workgroup per pair (see DecLayout::aw).  ROW: from the logits, without dec_pool_kernel.
+template <int NW, bool ROW>
+__global__ void __launch_bounds__(NW * 64, 8) dec_pick_kernel(DecArgs a) {
+    __shared__ int sel[kSelMax], hist[4][256], wave_tot[NW], s_k;
     __shared__ uint32_t s_prefix;
     const int pair = blockIdx.x, L = a.ctx[pair / a.hkv];
     const Forced fo(a.tk, L);
     int32_t *out = a.idx + (int64_t)pair * a.tk.topk_total;
     if (L < a.tk.dense_below) {
-        for (int i = threadIdx.x; i < a.tk.topk_total; i += AW * 64) out[i] = -1;
+        for (int i = threadIdx.x; i < a.tk.topk_total; i += NW * 64) out[i] = -1;
     } else if (fo.kr == fo.n_rest) {
-        write_list(fo, nullptr, out, a.tk.topk_total, AW * 64);
+        write_list(fo, nullptr, out, a.tk.topk_total, NW * 64);
     } else {
-        if (fo.kr > 0) pick_blocks<AW>(a, pair, fo, sel, hist, wave_tot, &s_prefix, &s_k);
-        write_list(fo, sel, out, a.tk.topk_total, AW * 64);
+        if (fo.kr > 0) {
+            if constexpr (ROW) {
+                __shared__ RowLds row;
+                pool_row<NW * 64, 2>(a, pair, L, fo, row);
+                pick_blocks<NW>(row.pk, fo, sel, hist, wave_tot, &s_prefix, &s_k);
+            } else {
+                pick_blocks<NW>(a.pk + (int64_t)pair * a.pk_cap, fo, sel, hist, wave_tot, &s_prefix, &s_k);
+            }
+        }
+        write_list(fo, sel, out, a.tk.topk_total, NW * 64);
     }
 }
 
-// NW waves (= blocks) per workgroup: 8 when the launch has at most one workgroup per CU anyway, and every workgroup then
-// selects for itself; 4 when it has more (64 KB of V tiles instead of 128, so that two workgroups share a CU), behind
-// dec_pick_kernel, which has written the lists to a.idx.
-template <int NW>
-__global__ void __launch_bounds__(NW * 64) dec_attn2_kernel(DecArgs a) {
+// NW waves per workgroup: 8 with one block each when the launch has at most one workgroup per CU anyway, and every workgroup then
+// selects for itself (ROW: it also pools the row, there is no dec_pool_kernel in front); 4 with several blocks each when it has more (64 KB of
+// V tiles instead of 128), behind dec_pick_kernel, which has written the lists to a.idx.
+template <int NW, bool ROW>
+__global__ void __launch_bounds__(NW * 64, 2) dec_attn2_kernel(DecArgs a) {
     constexpr bool PICKED = NW < AW;
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];     // NW V tiles of 16 KB, one per wave
     __shared__ float wm[NW][16], wl[NW][16];
@@ -921,8 +1045,10 @@ __global__ void __launch_bounds__(NW * 64) dec_attn2_kernel(DecArgs a) {
     const bool dense = L < a.tk.dense_below;
     int32_t *list = a.idx != nullptr ? a.idx + (int64_t)pair * a.tk.topk_total : nullptr;
     int32_t *out = !PICKED && split == 0 ? list : nullptr;       // this workgroup writes the pair's list
+    // entry of the top-k part that this wave takes: PICKED, lane r's for round r
     int j = -1;
-    const int e = w < a.bpw ? split * a.bpw + w : 1 << 30;       // (waves past bpw attend to nothing)
+    const int nth = PICKED ? (tid & 63) * NW + w : w;
+    const int e = nth < a.bpw ? split * a.bpw + nth : 1 << 30;   // (waves past bpw attend to nothing)
     if (dense) {
         j = e <= fo.bt ? e : -1;
         if (out != nullptr)
@@ -934,13 +1060,23 @@ __global__ void __launch_bounds__(NW * 64) dec_attn2_kernel(DecArgs a) {
     } else if (PICKED) {
         j = e < fo.kr ? list[fo.f_init + e] : -1;
     } else if (split * a.bpw < fo.kr || out != nullptr) {         // (otherwise nothing here: an empty partial)
-        if (fo.kr > 0) pick_blocks<NW>(a, pair, fo, sel, hist, wave_tot, &s_prefix, &s_k);
+        if (fo.kr > 0) {
+            if constexpr (ROW) {
+                RowLds &row = *reinterpret_cast<RowLds *>(hist + 4);
+                static_assert((kSelMax + 4 * 256) * 4 + sizeof(RowLds) <= NW * TILE_ELEMS * 2, "the row must fit in the V tiles");
+                pool_row<NT, 2>(a, pair, L, fo, row);
+                pick_blocks<NW>(row.pk, fo, sel, hist, wave_tot, &s_prefix, &s_k);
+            } else {
+                pick_blocks<NW>(a.pk + (int64_t)pair * a.pk_cap, fo, sel, hist, wave_tot, &s_prefix, &s_k);
+            }
+        }
         j = e < fo.kr ? sel[e] : -1;
         if (out != nullptr) write_list(fo, sel, out, a.tk.topk_total, NT);
         __syncthreads();                                         // the V tiles may overwrite the selection's state now
     }
     if (j > fo.bt) j = -1;
-    attend_partial<NW>(a, pair, L, a.fsplit + split, j, smem, wm, wl);
+    const int rounds = PICKED ? (a.bpw + NW - 1) / NW : 1;
+    attend_partial<NW, PICKED>(a, pair, L, a.fsplit + split, rounds, [&](int r) { return PICKED ? __builtin_amdgcn_readlane(j, r) : j; }, smem, wm, wl);
 }
 
 // ------------------------------------------------------------------------------------------ merge
@@ -1009,7 +1145,7 @@ struct DecLayout {
     // three-stage form
     bool staged;
     int aw;                     // waves per attend workgroup: AW, or AW / 2 behind a selection kernel
-    int bpw;                    // blocks per attend workgroup (<= aw)
+    int bpw;                    // blocks per attend workgroup (aw == AW: at most aw)
     int fsplit, nslot, pk_cap;
     size_t off_pk;
 };
@@ -1071,6 +1207,17 @@ DecLayout dec_layout(const infllmv2_params *p, int batch, int max_ctx, int dense
     d.off_ml = off;
     off += align_up(pairs * d.nslot * 32 * sizeof(float), 256);
     d.total = off;
+    if (d.staged && d.aw != AW) {
+        // Behind a selection kernel a workgroup takes as many blocks, in rounds of its four waves, as leave a workgroup for every CU (one
+        // round of them, and of partial results to merge, instead of several): attend 96 -> 81 us at batch 128, step of 32 / 64 / 128 / 256
+        // sequences 58 -> 52, 121 -> 109, 221 -> 199, 299 -> 260 us (four blocks each / this).  More than 512 pairs: two workgroups for each
+        // (batch 400: 425 / 409 with one, 397).  Rounds are counted in a lane's number and dense sequences may be long: 16 at most.
+        // (The scratch that a call asks for stays that of four blocks each, which grows with the batch.)
+        const int most = 16 * d.aw, ns = std::max({pairs > 512 ? 2 : (int)(256 / (pairs ? pairs : 1)), (entries + most - 1) / most, 1});
+        d.bpw = (entries + ns * d.aw - 1) / (ns * d.aw) * d.aw;
+        d.nsplit = std::min(d.nsplit, std::max((entries + d.bpw - 1) / d.bpw, 1));
+        d.nslot = d.fsplit + d.nsplit;
+    }
     return d;
 }
 
@@ -1139,18 +1286,27 @@ int launch_decode_mfma(const infllmv2_params *p, const void *q, const void *k, c
         // Larger-than-default dynamic LDS has to be enabled per kernel; the same fixed limit is set on every call,
         // so nothing has to be remembered between calls.
         const bool picked = d.aw != AW;
-        const auto attn = picked ? dec_attn2_kernel<AW / 2> : dec_attn2_kernel<AW>;
+        // Rows that fit one workgroup are pooled where they are picked from, a launch less: by the selection kernel while its workgroups (16
+        // waves, two on a CU) are one round (with it / behind dec_pool_kernel, batch 64 116 / 121 us, 128 213 / 221, 200 217 / 217, 400 429 /
+        // 424), by every attend workgroup while the row is short (one sequence: 4096 tokens 16.2 / 17.8 us, 16384 22.9 / 23.7, 32776
+        // 24.2 / 24.2, 65536 27.4 / 24.7; 16 sequences of up to 8192 tokens 28.9 / 30.9, 32768 35.3 / 35.6) or a pair has two of them at
+        // most (16 blocks, 32768 tokens: 64 sequences 47.3 / 51.4, 128 74.8 / 82.4; 16 sequences, 7 of them for each pair, 28.5 / 28.3).
+        const int max_nc = num_cmp(max_ctx, p->cmp_len, p->cmp_stride), max_nb = (max_ctx + kBlock - 1) / kBlock;
+        const bool row = max_nc <= kRowKeys && max_nb <= kRowBlocks &&
+                         (picked ? pairs <= 512 : d.nsplit <= 2 || (max_nc <= 1024 && max_nb <= 512));
+        const auto attn = picked ? dec_attn2_kernel<AW / 2, false> : row ? dec_attn2_kernel<AW, true> : dec_attn2_kernel<AW, false>;
         const size_t lds = attn_lds / (AW / d.aw);
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(attn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
             hipSuccess)
             return INFLLMV2_ERR_HIP;
         // written by the attend kernel only when the caller wants the list; by the pick kernel always
         a.idx = idx_out || !picked ? idx_out : (int32_t *)(base + d.off_idx);
-        const int groups = ((max_ctx + kBlock - 1) / kBlock + PB - 1) / PB;
+        const int groups = (max_nb + PB - 1) / PB;
         hipLaunchKernelGGL(dec_front_kernel, dim3(d.nchunk + d.fsplit, pairs), dim3(256),
                            (size_t)FW * TILE_ELEMS * sizeof(uint16_t), stream, a);
-        hipLaunchKernelGGL(dec_pool_kernel, dim3(groups, pairs), dim3(256), 0, stream, a);
-        if (picked) hipLaunchKernelGGL(dec_pick_kernel, dim3(pairs), dim3(AW * 64), 0, stream, a);
+        if (!row) hipLaunchKernelGGL(dec_pool_kernel, dim3(groups, pairs), dim3(256), 0, stream, a);
+        if (picked && row) hipLaunchKernelGGL((dec_pick_kernel<2 * AW, true>), dim3(pairs), dim3(2 * AW * 64), 0, stream, a);
+        if (picked && !row) hipLaunchKernelGGL((dec_pick_kernel<AW, false>), dim3(pairs), dim3(AW * 64), 0, stream, a);
         hipLaunchKernelGGL(attn, dim3(d.nsplit, pairs), dim3(d.aw * 64), lds, stream, a);
         hipLaunchKernelGGL(dec_merge_kernel, dim3(pairs), dim3(kMergeThreads), 0, stream, a);
         return hip_status(hipGetLastError());
