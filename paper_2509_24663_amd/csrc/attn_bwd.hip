@@ -12,19 +12,19 @@
 //   dq    : the workgroup and block walk of the generic forward kernel: per block S^T = K Q^T and dP^T = V dO^T
 //           (keys x columns), dZ^T in registers, dQ^T += K^T dZ^T
 //   dkv   : one workgroup of 4 wavefronts per (KV block, chunk of later tokens, KV head): lists the tokens of its chunk
-//           that selected the block and takes 16 / G of them at a time, 16 rows of Q and dO (bf16: mostly twice that); wavefront w holds keys
+//           that selected the block and takes 16 / G of them at a time, 16 rows of Q and dO (bf16: twice that); wavefront w holds keys
 //           16 w .. 16 w + 15 (their K and V rows stay in registers): S = Q K^T, dP = dO V^T (rows x keys), then
-//           dV += P^T dO and dK += dZ^T Q, contracted over the 16 rows.  The block's 64 rows of dK and dV are added to
+//           dV += P^T dO and dK += dZ^T Q, contracted over the rows.  The block's 64 rows of dK and dV are added to
 //           the float32 result with atomics (one add per element and workgroup; the order of the adds, and with it
 //           the last bits of dK and dV, can differ from run to run).
 // Measured, bf16, 1985 tokens, 8 heads on 2, d 128, 16 blocks: dq 87 -> 55 us (bound by the rows' trips from the L2, as the
-// forward kernel: two column groups per wavefront, half blocks requested ahead), dkv 108 -> 103 (products over 32 rows, the
-// products' operands and sums in vector registers instead of copied to and from accumulators, which took the fp32 kernel
-// from 346 to 251 us at 2000 tokens; with its atomic adds as the accumulators lie in registers instead of through LDS dkv took
-// 490 us).
+// forward kernel: two column groups per wavefront, half blocks requested ahead), dkv 108 -> 103 -> 55 (bf16 kernel of its own, 79 us of it by
+// its steps, 91 -> 55 by launching only the workgroups that have work); fp32, 2000 tokens, dkv 346 -> 251 with the products' operands and
+// sums in vector registers.
 #include <algorithm>
 
 #include "attn_bwd.h"
+#include "chunk_pairs.h"
 #include "gen_unit.h"
 #include "launch_rules.h"
 
@@ -213,29 +213,58 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
     }
 }
 
-template <typename T, int D, int RG>
-__global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chunk) {
+// Workgroups of the dkv kernels: (token chunk, KV block) pairs with at least one token that can see the block.  Nothing else is
+// launched: in a grid of all pairs half of the workgroups are empty, and as these come at regular intervals while workgroups are
+// dealt out in turn to the dies and to the engines of a die, some engines got several times the work of others (1985 tokens, 8 heads on
+// 2, chunks of 64: the workgroups' times sum up to 42 us of the chip and took 91 from first to last; whole backward 149 -> 140 us).
+// Sequence (>= batch past the last pair), chunk and block of this workgroup; s_tile: 3 ints of LDS.
+__device__ inline int dkv_place(const RowMap &m, int shift, int &chunk, int &block, int *s_tile) {
+    int nth, before;
+    const int seq = find_seq_count(m.cu, m.batch, (int)(blockIdx.y * gridDim.x + blockIdx.x), nth, before, s_tile,
+                                   [&](int n) { return sequence_pairs(n, shift); }, [](int) { return 0; });
+    if (seq < m.batch) pair_at(nth, shift, chunk, block);
+    return seq;
+}
+
+// is block j in the list e[0 .. n)?  Short lists whole (a search is a chain of five or six trips to memory)
+__device__ inline bool selected(const int32_t *e, int n, int j) {
+    if (n > 64) return list_has(e, n, j);
+    typedef int32_t Four __attribute__((ext_vector_type(4), aligned(4)));
+    bool hit = false;
+    int i = 0;
+    for (; i + 16 <= n; i += 16) {
+        Four x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const Four *>(e + i + 4 * u);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) hit |= x[u][0] == j || x[u][1] == j || x[u][2] == j || x[u][3] == j;
+    }
+    for (; i < n; ++i) hit |= e[i] == j;
+    return hit;
+}
+
+template <typename T, int D>
+__global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int shift) {
     constexpr int N = D / 16;
-    constexpr int ROWS = RG * kCols;                                   // RG groups of 16 rows of Q and dO per step
+    constexpr int ROWS = kCols;                                        // of Q and dO per step
     __shared__ __attribute__((aligned(16))) T rows_s[2][2][ROWS][D + 16 / sizeof(T)];      // [buffer][Q, dO][row]
     __shared__ float lse_s[2][ROWS], delta_s[2][ROWS];
     __shared__ int t_s[2][ROWS];
     __shared__ int s_tile[3], s_list[BWD_CHUNK], s_wave_cnt[NW];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int h = blockIdx.z, G = a.hq / a.map.num_kv_heads;
-    int j;
-    const int seq = find_seq_tile(a.map.cu, a.map.batch, kBlock, blockIdx.y, j, s_tile);
+    int j, at;
+    const int seq = dkv_place(a.map, shift, at, j, s_tile);
     if (seq >= a.map.batch) return;
     const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;
     // tokens of this chunk that can see the block: [max(chunk start, 64 j), min(chunk end, len))
-    const int c0 = blockIdx.x * chunk, c1 = min(c0 + chunk, len);
-    if (c1 <= j * kBlock || c0 >= len) return;
+    const int c0 = at << shift, c1 = min(c0 + (1 << shift), len);
     const bool dense = a.idx == nullptr || len < a.dense_below;
 
     // ---- which tokens of the chunk selected the block (in token order); a chunk has at most one token per thread
     const int t_mine = c0 + tid;
     bool sel = t_mine < c1 && t_mine >= j * kBlock;
-    if (sel && !dense) sel = list_has(a.idx + head_row(a.map, h, tok0 + t_mine) * a.topk_total, a.topk_total, j);
+    if (sel && !dense) sel = selected(a.idx + head_row(a.map, h, tok0 + t_mine) * a.topk_total, a.topk_total, j);
     const uint64_t bal = __ballot(sel);
     if (lane == 0) s_wave_cnt[w] = __popcll(bal);
     __syncthreads();
@@ -259,84 +288,70 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
 #pragma unroll
     for (int i = 0; i < N; ++i) acc_k[i] = acc_v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // A group is the list's next `tokens` entries with their G heads: row x is entry x / G, head x % G.  The four
+    // A step is the list's next `tokens` entries with their G heads: row x is entry x / G, head x % G.  The four
     // wavefronts need the same rows of Q and dO twice (as row operands and spread over lanes), so they pass through
-    // LDS once: thread (row, part) brings a sixteenth of its row of every group, the next step's in flight in registers while
-    // the current one is computed; one barrier per step.  Unused rows hold zeros and see no key.  bf16 rows: two groups per
-    // step, whose 32 rows are one contraction.
+    // LDS once: thread (row, part) brings a sixteenth of its row, the next step's in flight in registers while
+    // the current one is computed; one barrier per step.  Unused rows hold zeros and see no key.
     const int tokens = kCols / G;
     const int x_row = tid >> 4, x_slot = x_row / G, x_head = h * G + x_row - x_slot * G;
-    struct Pre { Spread<T, D> q[RG], g[RG]; float lse[RG], delta[RG]; int t[RG]; };
+    struct Pre { Spread<T, D> q, g; float lse, delta; int t; };
     auto fetch = [&](int it) -> Pre {
         Pre pr;
-#pragma unroll
-        for (int i = 0; i < RG; ++i) {
-            const int e = it + i * tokens + x_slot;
-            const bool used = x_slot < tokens && e < total;
-            const int t = s_list[used ? e : 0];
-            const int64_t off = ((int64_t)(tok0 + t) * a.hq + (used ? x_head : h * G)) * D;
-            pr.q[i].load(a.q + off, tid & 15);
-            pr.g[i].load(a.dout + off, tid & 15);
-            const int64_t lr = qhead_row(a.map, used ? x_head : h * G, a.hq, tok0 + t);
-            pr.lse[i] = a.lse[lr];
-            pr.delta[i] = a.delta[lr];
-            pr.t[i] = used ? t : -1;
-            if (!used) { pr.q[i].zero(); pr.g[i].zero(); }
-        }
+        const int e = it + x_slot;
+        const bool used = x_slot < tokens && e < total;
+        const int t = s_list[used ? e : 0];
+        const int64_t off = ((int64_t)(tok0 + t) * a.hq + (used ? x_head : h * G)) * D;
+        pr.q.load(a.q + off, tid & 15);
+        pr.g.load(a.dout + off, tid & 15);
+        const int64_t lr = qhead_row(a.map, used ? x_head : h * G, a.hq, tok0 + t);
+        pr.lse = a.lse[lr];
+        pr.delta = a.delta[lr];
+        pr.t = used ? t : -1;
+        if (!used) { pr.q.zero(); pr.g.zero(); }
         return pr;
     };
     auto stage = [&](int buf, const Pre &pr) {
-#pragma unroll
-        for (int i = 0; i < RG; ++i) {
-            const int row = i * kCols + x_row;
-            pr.q[i].store_lds(&rows_s[buf][0][row][0], tid & 15);
-            pr.g[i].store_lds(&rows_s[buf][1][row][0], tid & 15);
-            if ((tid & 15) == 0) {
-                lse_s[buf][row] = pr.lse[i];
-                delta_s[buf][row] = pr.delta[i];
-                t_s[buf][row] = pr.t[i];
-            }
+        pr.q.store_lds(&rows_s[buf][0][x_row][0], tid & 15);
+        pr.g.store_lds(&rows_s[buf][1][x_row][0], tid & 15);
+        if ((tid & 15) == 0) {
+            lse_s[buf][x_row] = pr.lse;
+            delta_s[buf][x_row] = pr.delta;
+            t_s[buf][x_row] = pr.t;
         }
     };
     stage(0, fetch(0));
     __syncthreads();
     int buf = 0;
-    for (int it = 0; it < total; it += RG * tokens, buf ^= 1) {
-        const bool more = it + RG * tokens < total;
+    for (int it = 0; it < total; it += tokens, buf ^= 1) {
+        const bool more = it + tokens < total;
         Pre nxt = {};
-        if (more) nxt = fetch(it + RG * tokens);
-        f32x4 p[RG], dz[RG];
-        Spread<T, D> qr[RG][4], gr[RG][4];
+        if (more) nxt = fetch(it + tokens);
+        RowFrag<T, D> qf, gf;
+        qf.load_lds(&rows_s[buf][0][m][0], g);
+        gf.load_lds(&rows_s[buf][1][m][0], g);
+        const f32x4 s = row_product<D>(qf, kf);
+        const f32x4 dp = row_product<D>(gf, vf);
+        f32x4 p, dz;
+        Spread<T, D> qr[4], gr[4];
 #pragma unroll
-        for (int i = 0; i < RG; ++i) {
-            RowFrag<T, D> qf, gf;
-            qf.load_lds(&rows_s[buf][0][i * kCols + m][0], g);
-            gf.load_lds(&rows_s[buf][1][i * kCols + m][0], g);
-            const f32x4 s = row_product<D>(qf, kf);
-            const f32x4 dp = row_product<D>(gf, vf);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int x = i * kCols + 4 * g + r;
-                const bool vis = key <= t_s[buf][x];
-                p[i][r] = vis ? exp2_fast(__builtin_fmaf(s[r], a.scale, -lse_s[buf][x]) * kLog2e) : 0.f;
-                dz[i][r] = vis ? p[i][r] * (dp[r] - delta_s[buf][x]) : 0.f;
-                qr[i][r].load_lds(&rows_s[buf][0][x][0], m);
-                gr[i][r].load_lds(&rows_s[buf][1][x][0], m);
-            }
+        for (int r = 0; r < 4; ++r) {
+            const int x = 4 * g + r;
+            const bool vis = key <= t_s[buf][x];
+            p[r] = vis ? exp2_fast(__builtin_fmaf(s[r], a.scale, -lse_s[buf][x]) * kLog2e) : 0.f;
+            dz[r] = vis ? p[r] * (dp[r] - delta_s[buf][x]) : 0.f;
+            qr[r].load_lds(&rows_s[buf][0][x][0], m);
+            gr[r].load_lds(&rows_s[buf][1][x][0], m);
         }
-        if constexpr (RG == 2) {
-            weighted_rows32<true, true, D>(acc_v, p[0], p[1], gr[0], gr[1]);
-            weighted_rows32<true, true, D>(acc_k, dz[0], dz[1], qr[0], qr[1]);
-        } else if constexpr (sizeof(T) == 2) {                 // 16 of the 32 indices; the others are 0 times 0
+        if constexpr (sizeof(T) == 2) {                        // 16 of the 32 indices; the others are 0 times 0
             const f32x4 none = {0.f, 0.f, 0.f, 0.f};
             Spread<T, D> zeros[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) zeros[r].zero();
-            weighted_rows32<true, true, D>(acc_v, p[0], none, gr[0], zeros);
-            weighted_rows32<true, true, D>(acc_k, dz[0], none, qr[0], zeros);
+            weighted_rows32<true, true, D>(acc_v, p, none, gr, zeros);
+            weighted_rows32<true, true, D>(acc_k, dz, none, qr, zeros);
         } else {
-            weighted_rows<true, D>(acc_v, p[0], gr[0]);
-            weighted_rows<true, D>(acc_k, dz[0], qr[0]);
+            weighted_rows<true, D>(acc_v, p, gr);
+            weighted_rows<true, D>(acc_k, dz, qr);
         }
         if (more) stage(buf ^ 1, nxt);
         __syncthreads();
@@ -366,6 +381,220 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int chun
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
+        }
+    }
+}
+
+// dK and dV of bf16 rows.  As above, with everything arranged for few instructions: with two wavefronts on a SIMD a step of 32 rows in the form
+// above took 2.84 us, 500 vector instructions per wavefront; this one 2.5 us, 310 (2.1 without its loads from memory):
+//   * a step is 32 rows, 32 / 16 times 16 / G tokens, staged in LDS as 256-byte rows with 16-byte chunk c of row r at chunk c ^ swizzle(r);
+//   * row x of product tile kt is row 8 (x / 4) + 4 kt + x % 4, so that a lane's eight weights are rows 8 g .. 8 g + 7, the operand of
+//     the second products as it is, whose other operand (the same rows, transposed) comes from transposing LDS reads: no
+//     spread rows, no byte permutes;
+//   * dP starts at -Delta; keys are hidden only in steps with tokens of the block itself; weights are checked for infinities
+//     once per step and cut into pieces without checks otherwise;
+//   * an accumulator register holds 16 consecutive dims of 4 keys, whole 64-byte pieces, so the adds leave the registers as they are.
+constexpr int kRowBytes = 256;                                         // (d 64: half of it used)
+__device__ inline uint32_t row_swizzle(int r) { return 4 * (r & 3) + 2 * ((r >> 3) & 1) + ((r >> 4) & 1); }
+typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
+typedef short short4v __attribute__((ext_vector_type(4)));
+
+template <int D>
+__global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t> a, int shift) {
+    constexpr int N = D / 16, ROWS = 32;
+    constexpr uint32_t kTile = ROWS * kRowBytes, kBuf = 2 * kTile;     // Q rows, then dO rows
+    __shared__ __attribute__((aligned(1024))) char rows_s[2 * kBuf];
+    __shared__ __attribute__((aligned(16))) float lse_s[2][ROWS], delta_s[2][ROWS];      // -lse and -Delta
+    __shared__ __attribute__((aligned(16))) int t_s[2][ROWS];
+    __shared__ int s_tile[3], s_list[BWD_CHUNK], s_wave_cnt[NW], s_own_cnt[NW];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = blockIdx.z, G = a.hq / a.map.num_kv_heads;
+    int j, at;
+    const int seq = dkv_place(a.map, shift, at, j, s_tile);
+    if (seq >= a.map.batch) return;
+    const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;
+    // tokens of this chunk that can see the block: [max(chunk start, 64 j), min(chunk end, len))
+    const int c0 = at << shift, c1 = min(c0 + (1 << shift), len);
+    const bool dense = a.idx == nullptr || len < a.dense_below;
+
+    // ---- which tokens of the chunk selected the block (in token order); a chunk has at most one token per thread
+    const int t_mine = c0 + tid;
+    bool sel = t_mine < c1 && t_mine >= j * kBlock;
+    if (sel && !dense) sel = selected(a.idx + head_row(a.map, h, tok0 + t_mine) * a.topk_total, a.topk_total, j);
+    // the wavefront's 16 keys: K and V rows as operands (past the end of the sequence: the last row, never visible)
+    const int m = lane & 15, g = lane >> 4;
+    const int key = j * kBlock + 16 * w + m;
+    const int64_t kv_off = (int64_t)(tok0 + min(key, len - 1)) * a.map.kv_tok_stride + (int64_t)h * a.map.kv_head_stride;
+    RowFrag<bf16_t, D> kf, vf;
+    kf.load(a.k + kv_off, g);
+    vf.load(a.v + kv_off, g);
+    const uint64_t bal = __ballot(sel);
+    const uint64_t own_bal = __ballot(sel && t_mine < (j + 1) * kBlock);
+    if (lane == 0) {
+        s_wave_cnt[w] = __popcll(bal);
+        s_own_cnt[w] = __popcll(own_bal);
+    }
+    __syncthreads();
+    int base = 0, total = 0, own = 0;                         // own: tokens of the block itself, the first of the list
+    for (int x = 0; x < NW; ++x) {
+        if (x < w) base += s_wave_cnt[x];
+        total += s_wave_cnt[x];
+        own += s_own_cnt[x];
+    }
+    if (sel) s_list[base + __popcll(bal & ((1ull << lane) - 1ull))] = t_mine;
+    total = __builtin_amdgcn_readfirstlane(total);
+    own = __builtin_amdgcn_readfirstlane(own);
+    if (total == 0) return;
+    __syncthreads();
+
+    f32x4 acc_k[N], acc_v[N];                                  // keys 16 w + 4 g + r, dim 16 i + m
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc_k[i] = acc_v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // Thread (x, part) brings sixteenth `part` of rows x and 16 + x: head x % G of the list's entries x / G and tokens + x / G behind the
+    // step's first.  The next step's are in flight in registers while the current one is computed; one barrier per step.
+    // Unused rows hold zeros and see no key.
+    const int tokens = kCols / G;
+    const int x_row = tid >> 4, part = tid & 15, x_slot = x_row / G, x_head = h * G + (x_slot < tokens ? x_row - x_slot * G : 0);
+    typedef uint32_t Part __attribute__((ext_vector_type(D / 32), aligned(2)));             // a sixteenth of a row, wherever it lies
+    struct Pre { Part q[2], g[2]; float lse[2], delta[2]; int t[2]; };
+    const int64_t row0 = ((int64_t)tok0 * a.hq + x_head) * D + part * N, lr0 = (int64_t)x_head * a.map.total_rows + tok0;
+    const bf16_t *qp = a.q + row0, *gp = a.dout + row0;
+    const float *lp = a.lse + lr0, *dp0 = a.delta + lr0;
+    const int t_step = a.hq * D;                               // elements from token to token
+    auto whole = [&](int it) { return it + 2 * tokens <= total && tokens * G == kCols; };     // no unused rows
+    auto fetch = [&](int it) -> Pre {
+        Pre pr;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int t = s_list[min(it + i * tokens + x_slot, total - 1)];
+            pr.q[i] = *reinterpret_cast<const Part *>(qp + (int64_t)t * t_step);
+            pr.g[i] = *reinterpret_cast<const Part *>(gp + (int64_t)t * t_step);
+            pr.lse[i] = -lp[t];
+            pr.delta[i] = -dp0[t];
+            pr.t[i] = t;
+        }
+        return pr;
+    };
+    auto drop_unused = [&](int it, Pre &pr) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (x_slot >= tokens || it + i * tokens + x_slot >= total) {
+                pr.q[i] = pr.g[i] = 0u;
+                pr.t[i] = -1;
+            }
+    };
+    auto stage = [&](int buf, const Pre &pr) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int row = i * kCols + x_row;
+            typedef uint32_t LPart __attribute__((ext_vector_type(D / 32), aligned(D / 8)));
+            char *p = rows_s + buf * kBuf + row * kRowBytes + (((D == 128 ? part : part >> 1) ^ row_swizzle(row)) << 4) + (D == 128 ? 0 : part & 1) * 8;
+            *reinterpret_cast<LPart *>(p) = pr.q[i];
+            *reinterpret_cast<LPart *>(p + kTile) = pr.g[i];
+            if (part == 0) {
+                lse_s[buf][row] = pr.lse[i];
+                delta_s[buf][row] = pr.delta[i];
+                t_s[buf][row] = pr.t[i];
+            }
+        }
+    };
+    // operand addresses of a lane in a tile: row 8 (m / 4) + m % 4 (+ 4 for the second tile), chunk 4 s + g; transposing read: rows 8 g + m / 4
+    // (+ 4), dims 16 i + 4 (m % 4) ..
+    const int r0 = 8 * (m >> 2) + (m & 3), r1 = 8 * g + (m >> 2);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)rows_s;
+    const uint32_t row_at = lds0 + r0 * kRowBytes + ((g ^ row_swizzle(r0)) << 4);
+    const uint32_t trans_at = lds0 + r1 * kRowBytes + ((((m & 3) >> 1) ^ row_swizzle(r1)) << 4) + (m & 1) * 8;
+    auto row_frag = [&](uint32_t at, int kt, int s) -> bf16x8 {
+        return *(lds_frag *)(uintptr_t)((at ^ (uint32_t)(64 * s)) + (uint32_t)(4 * kt * kRowBytes));
+    };
+    auto trans_frag = [&](uint32_t at, int i) -> bf16x8 {
+        typedef __attribute__((address_space(3))) short4v lds_s4;
+        const uint32_t x = at ^ (uint32_t)(32 * i);
+        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)x);
+        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)(x + 4 * kRowBytes));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    // acc += weights^T x rows, weights in three exact pieces (see weighted_rows32)
+    auto accumulate = [&](f32x4 (&acc)[N], f32x4 w0, f32x4 w1, uint32_t at) {
+        float top = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) top = fmaxf(top, fmaxf(fabsf(w0[r]), fabsf(w1[r])));
+        bf16x8 p0, p1, p2;
+        if (__any(top == INFINITY)) {
+            p0 = take_piece32<true>(w0, w1);
+            p1 = take_piece32<true>(w0, w1);
+            p2 = take_piece32<true>(w0, w1);
+        } else {
+            p0 = take_piece32<false>(w0, w1);
+            p1 = take_piece32<false>(w0, w1);
+            p2 = take_piece32<false>(w0, w1);
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const bf16x8 rows = trans_frag(at, i);
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p2, rows, acc[i], 0, 0, 0);
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, rows, acc[i], 0, 0, 0);
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, rows, acc[i], 0, 0, 0);
+        }
+    };
+    {
+        Pre first = fetch(0);
+        if (!whole(0)) drop_unused(0, first);
+        stage(0, first);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int it = 0; it < total; it += 2 * tokens, buf ^= 1) {
+        const bool more = it + 2 * tokens < total;
+        Pre nxt;
+        if (more) nxt = fetch(it + 2 * tokens);
+        const uint32_t ra = row_at + buf * kBuf, ta = trans_at + buf * kBuf;
+        f32x4 p[2], dz[2];
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+            f32x4 s = {0.f, 0.f, 0.f, 0.f};
+            f32x4 dp = *reinterpret_cast<const f32x4 *>(&delta_s[buf][8 * g + 4 * kt]);
+#pragma unroll
+            for (int ks = 0; ks < D / 32; ++ks) {
+                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_frag(ra, kt, ks), kf.x[ks], s, 0, 0, 0);
+                dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_frag(ra + kTile, kt, ks), vf.x[ks], dp, 0, 0, 0);
+            }
+            const f32x4 nl = *reinterpret_cast<const f32x4 *>(&lse_s[buf][8 * g + 4 * kt]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[kt][r] = exp2_fast(__builtin_fmaf(s[r], a.scale, nl[r]) * kLog2e);
+            dz[kt] = dp;
+        }
+        if (it < own || !whole(it)) {                          // hidden keys, unused rows
+
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool vis = key <= t_s[buf][8 * g + 4 * kt + r];
+                    p[kt][r] = vis ? p[kt][r] : 0.f;
+                    dz[kt][r] = vis ? dz[kt][r] : 0.f;
+                }
+        }
+        accumulate(acc_v, p[0], p[1], ta + kTile);
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) dz[kt] *= p[kt];
+        accumulate(acc_k, dz[0], dz[1], ta);
+        if (more) {
+            if (!whole(it + 2 * tokens)) drop_unused(it + 2 * tokens, nxt);
+            stage(buf ^ 1, nxt);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int u = j * kBlock + 16 * w + 4 * g + r;
+        if (u >= len) continue;
+        const int64_t at = ((int64_t)h * a.map.total_rows + tok0 + u) * D + m;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            unsafeAtomicAdd(a.dk + at + 16 * i, acc_k[i][r] * a.scale);      // the L2's own float add
+            unsafeAtomicAdd(a.dv + at + 16 * i, acc_v[i][r]);
         }
     }
 }
@@ -410,13 +639,21 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     if (!two && form.ahead) launch_dq<T, D, 1, true>(L, a);
     if constexpr (D * sizeof(T) < 512)
         if (!two && !form.ahead) launch_dq<T, D, 1, false>(L, a);
-    const rules::DkvForm dkv = rules::generic_dkv_form(sizeof(T) == 2, D, hkv, a.hq / hkv, cu_h, L.map.batch, a.idx != nullptr,
-                                                       a.topk_total, a.dense_below);
-    const dim3 grid((unsigned)((L.max_len + dkv.chunk - 1) / dkv.chunk), (unsigned)nblocks, hkv);
-    if constexpr (sizeof(T) == 2)
-        if (dkv.row_groups == 2) hipLaunchKernelGGL((bwd_dkv_kernel<T, D, 2>), grid, dim3(NW * 64), 0, L.stream, a, dkv.chunk);
-    if constexpr (sizeof(T) == 4 || D == 64)
-        if (dkv.row_groups == 1) hipLaunchKernelGGL((bwd_dkv_kernel<T, D, 1>), grid, dim3(NW * 64), 0, L.stream, a, dkv.chunk);
+    int64_t pairs;
+    const int shift = rules::generic_dkv_shift(sizeof(T) == 2, D, a.hq / hkv, {cu_h, L.map.batch, L.max_len, hkv, nblocks, a.idx != nullptr,
+                                               a.topk_total, a.dense_below}, pairs);
+    const int64_t gx = std::min<int64_t>(pairs, 1 << 20);
+    const dim3 grid((unsigned)gx, (unsigned)((pairs + gx - 1) / gx), hkv);
+    if constexpr (sizeof(T) == 2) {
+        // 16 rows per step where many workgroups have hardly more: d 64, 400 x 4 tokens, 8 heads on 2, whole backward 29.1 us, 33.8 with 32;
+        // 300 x 8 tokens 30.5 / 30.2
+        const bool few = D == 64 && L.max_len <= 4 &&
+                         rules::generic_dkv_form(true, D, hkv, a.hq / hkv, cu_h, L.map.batch, a.idx != nullptr, a.topk_total, a.dense_below).row_groups == 1;
+        if (few) hipLaunchKernelGGL((bwd_dkv_kernel<T, 64>), grid, dim3(NW * 64), 0, L.stream, a, shift);
+        else hipLaunchKernelGGL((bwd_dkv_bf16_kernel<D>), grid, dim3(NW * 64), 0, L.stream, a, shift);
+    } else {
+        hipLaunchKernelGGL((bwd_dkv_kernel<T, D>), grid, dim3(NW * 64), 0, L.stream, a, shift);
+    }
     return hip_status(hipGetLastError());
 }
 

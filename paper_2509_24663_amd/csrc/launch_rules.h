@@ -270,5 +270,40 @@ inline int dkv_chunk(const DkvBatch &b, int64_t most) {
     return chunk;
 }
 
+// Generic dK/dV: tokens per workgroup, 1 << the result, and the workgroups per KV head that this makes.
+//
+// The cheapest of 32 to 256 by a model of the launch, in steps (32 or 16 rows: as many tokens of G heads as that): a workgroup takes a fixed
+// time for its list, its keys and its adds, and its tokens' steps, of which the last is half empty; while all workgroups run at once
+// the longest counts, then the rounds of the average one and part of the longest.  From the backward call with every chunk at 650 forms
+// (60 to 6000 tokens, 1 to 8 KV heads, groups of 1, 4, 7 and 8, budgets of 8 to 32 blocks and dense, packed batches) the chosen chunk is 0.7 % (fp32 0.3 %)
+// from the best on average, 17 % (9 %) at most (profiles/generic_backward_chunk_timings.txt).  Whole backward, chunks of 32 / 64 / 128 / 256: bf16, 8 heads on 2, d 128, 16 blocks, 300 tokens 29 /
+// 35 / 48 / 76 us, 1000 tokens 80 / 63 / 69 / 97, 1985 tokens 180 / 140 / 112 / 132, 3000 tokens 357 / 266 / 216 / 212, 26 x 300 202 / 173 / 177 / 185;
+// d 64, 1985 tokens 114 / 94 / 84 / 104; fp32, d 128, 900 tokens 119 / 119 / 153 / 233.
+inline int generic_dkv_shift(bool bf16, int d, int G, const DkvBatch &b, int64_t &pairs) {
+    const double tokens = 16 / G * (bf16 ? 2 : 1), fixed = bf16 && d == 128 ? 5 : 2.5, slots = bf16 ? 384 : 512, kTail = 0.3;
+    int64_t busy[4] = {};                                   // by the chunk's size, 32 first
+    double entries = 0;
+    for (int s = 0; s < b.batch; ++s) {
+        const uint32_t len = (uint32_t)(b.cu_h[s + 1] - b.cu_h[s]);
+        const uint32_t most_of = b.sparse && (int)len >= b.dense_below ? (uint32_t)b.topk : ~0u;
+        const uint32_t full = std::min(len / kKeys, most_of);
+        busy[0] += dkv_busy<0>(len);
+        busy[1] += dkv_busy<1>(len);
+        busy[2] += dkv_busy<2>(len);
+        busy[3] += dkv_busy<3>(len);
+        entries += (double)kKeys * ((double)full * (full + 1) / 2) + (double)(len - kKeys * full) * std::min(full + 1, most_of);
+    }
+    int best_i = 3;
+    double best = 0;
+    for (int i = 3; i >= (b.max_len < 1 << 20 ? 0 : 3); --i) {     // (the counts fit 32 bits)
+        const double wgs = (double)busy[i] * b.hkv, rounds = wgs / slots;
+        const double longest = fixed + std::min(32 << i, b.max_len) / tokens, mean = fixed + (wgs > 0 ? entries * b.hkv / wgs / tokens : 0) + 0.5;
+        const double cost = rounds <= 1 ? longest : std::max(longest, rounds * mean + kTail * longest);
+        if (i == 3 || cost < best) { best = cost; best_i = i; }
+    }
+    pairs = busy[best_i];
+    return 5 + best_i;
+}
+
 }  // namespace rules
 }  // namespace ifv2
