@@ -53,6 +53,16 @@ inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
         return {2, rows_ahead(x.two * hkv, d == 128 ? 512 : 1024, x)};
     return {1, rows_ahead(x.one * hkv, 1024, x)};
 }
+// fp32 attention is bound by its products: rows requested ahead are worth their registers only where a CU has no other
+// workgroup's wavefronts to fill the waits with.  d 64 keeps two workgroups per CU with them and three without, d 128 one and two.
+// Attention alone, ahead / not: d 64, 4 heads on 1, topk 8: 1000 tokens (250 workgroups) 20.8 / 24.1 us, 2048 (512) 31.6 / 28.5,
+// 4096 (1024) 97 / 90; 8 on 2: 1000 (500) 28.0 / 25.4, 3300 (1650) 55.3 / 44.8; walks of fewer than six half blocks are over before a
+// second request would arrive.  d 128, 8 on 2: 600 tokens (300) 20.6 / 26.0, 1000 (500) 36.7 / 47.7, 2048 (1024) 103 / 92.  Over 228
+// batches the rule is within 0.2 % of the faster form in the mean, where rows_ahead lost 2.0 (d 128) and 2.9 % (d 64).
+inline bool fp32_rows_ahead(int d, int64_t workgroups, const Walks &x) {
+    if (d == 64) return workgroups <= 256 && x.half_blocks >= 6;
+    return x.half_blocks >= 4 && workgroups <= std::min(512., 64 * x.half_blocks);
+}
 // dQ reads K twice, so two groups pay earlier.  By tiles of one group times KV heads, one / two groups: bf16 d 128: 250 tiles 15.0 /
 // 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1; fp32 d 64: 400 38 / 34, 800 74 / 58 (d 128: two groups need 54 registers
 // more than there are).  Short walks are too little work per workgroup: whole call, 8 heads on 2, bf16 d 128: 500 x 4 tokens 49 / 63,

@@ -18,6 +18,10 @@ extern "C" void generic(int bf16, int d, int hkv, int tokens, const int *cu, int
     r[2] = g.groups;
     r[3] = g.ahead;
 }
+extern "C" int fp32_ahead(int d, int hkv, int tokens, const int *cu, int batch, int sparse, int topk, int below) {
+    const Walks x = walks(cu, batch, tokens, sparse, topk, below);
+    return fp32_rows_ahead(d, x.one * hkv, x);
+}
 extern "C" void generic_dkv(int bf16, int d, int hkv, int G, const int *cu, int batch, int sparse, int topk, int below, int *r) {
     const DkvForm f = generic_dkv_form(bf16, d, hkv, G, cu, batch, sparse, topk, below);
     r[0] = f.chunk;
@@ -145,3 +149,10 @@ def test_attention_tiles(rules):
         assert tile([n], hkv, topk=topk) == want, (n, hkv, topk)
         assert tile([n], hkv, topk=topk, bwd=1) == tile([n], hkv, sparse=0, topk=topk) == tile([n], hkv, topk=topk, below=n + 1) == 8
     assert tile([]) == 4
+
+
+@pytest.mark.parametrize("d,hq,hkv,lens,topk,ahead", [
+    (64, 4, 1, [1000], 8, 1), (64, 4, 1, [1024], 16, 1), (64, 4, 1, [1025], 16, 0), (64, 8, 2, [1000], 8, 0), (64, 4, 1, [300], 8, 0),
+    (128, 8, 2, [1000], 8, 1), (128, 8, 2, [1024], 8, 1), (128, 8, 2, [1025], 8, 0), (128, 4, 1, [150], 8, 0), (128, 4, 1, [], 8, 0)])
+def test_fp32_rows_ahead_only_where_a_cu_has_one_workgroup_to_run(rules, d, hq, hkv, lens, topk, ahead):
+    assert rules.fp32_ahead(d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, topk, 0) == ahead
