@@ -30,6 +30,7 @@ EXTRA_FLAGS = {
     "attn_bwd_dkv.hip": _VGPR_FORM,
     "attn_generic.hip": _VGPR_FORM,
     "attn_bwd.hip": _VGPR_FORM,
+    "attn_staged.hip": _VGPR_FORM,
 }
 
 

@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include "attn_bwd.h"
+#include "attn_staged.h"
 #include "chunk_pairs.h"
 #include "gen_unit.h"
 #include "launch_rules.h"
@@ -629,16 +630,19 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, 8192), 2), dim3(256), 0, L.stream,
                        (float4 *)a.dk, (float4 *)a.dv, n4);
     hipLaunchKernelGGL((bwd_delta_kernel<T, D>), dim3((unsigned)((rows * a.hq + 3) / 4)), dim3(256), 0, L.stream, a);
-    const rules::GenericForm form = rules::generic_dq_form(
-        sizeof(T) == 2, D, hkv, rules::walks(cu_h, L.map.batch, tile_tokens(L.map, a.hq / hkv), a.idx != nullptr, a.topk_total, a.dense_below));
-    bool two = false;
-    if constexpr (D * sizeof(T) < 512) {
-        two = form.groups == 2;
-        if (two) launch_dq<T, D, 2, true>(L, a);
+    const rules::Walks x = rules::walks(cu_h, L.map.batch, tile_tokens(L.map, a.hq / hkv), a.idx != nullptr, a.topk_total, a.dense_below);
+    const rules::GenericForm form = rules::generic_dq_form(sizeof(T) == 2, D, hkv, x);
+    const bool two = D * sizeof(T) < 512 && form.groups == 2;
+    if (sizeof(T) == 2 && rules::staged(true, D, x.two * hkv, x) && attn_staged_takes(L, a.k, a.v)) {
+        const int st = launch_dq_staged(L, a.q, a.k, a.v, a.idx, a.dense_below, a.lse, a.delta, a.dout, a.dq, x.two);
+        if (st != INFLLMV2_OK) return st;
+    } else {
+        if constexpr (D * sizeof(T) < 512)
+            if (two) launch_dq<T, D, 2, true>(L, a);
+        if (!two && form.ahead) launch_dq<T, D, 1, true>(L, a);
+        if constexpr (D * sizeof(T) < 512)
+            if (!two && !form.ahead) launch_dq<T, D, 1, false>(L, a);
     }
-    if (!two && form.ahead) launch_dq<T, D, 1, true>(L, a);
-    if constexpr (D * sizeof(T) < 512)
-        if (!two && !form.ahead) launch_dq<T, D, 1, false>(L, a);
     int64_t pairs;
     const int shift = rules::generic_dkv_shift(sizeof(T) == 2, D, a.hq / hkv, {cu_h, L.map.batch, L.max_len, hkv, nblocks, a.idx != nullptr,
                                                a.topk_total, a.dense_below}, pairs);

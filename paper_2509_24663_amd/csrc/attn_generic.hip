@@ -1,7 +1,7 @@
 // Stage 4, generic form: block-sparse causal attention over the selected blocks (Appendix Alg. 2) and dense causal
 // attention (Eq. 1 / Appendix Alg. 3) for any G <= 16, d in {64, 128}, fp32 or bf16 data, any stride and alignment,
-// prefill and single-row (decode) calls.  The bf16 G = 16 d = 128 shape has its own tile kernel; this one serves the
-// rest.
+// prefill and single-row (decode) calls.  The bf16 G = 16 d = 128 shape has its own tile kernel, and large bf16
+// calls with rows of 16-byte multiples pass theirs through LDS (attn_staged.hip); this one serves the rest.
 //
 // A workgroup owns a tile of one or two groups of 16 / G consecutive tokens of one KV head (16 columns each, see gen_unit.h)
 // and walks the union of their block lists; its wavefronts take the union's half blocks (32 keys) in turn, each with a
@@ -18,6 +18,7 @@
 // from 58 to 47 us.  Measured: fp32, 2048 tokens, 4 heads on 1, d 64, 8 blocks: 34 -> 30 us; bf16, 1985 tokens, 8 heads
 // on 2, d 128, 16 blocks: 58 -> 39 us; fp32, 600 / 2000 tokens, 8 heads on 2, d 128: 36 -> 20, 131 -> 113 us; bf16, 4000 tokens,
 // 8 heads on 2, d 128: 153 -> 95 us.  Taken back: the wavefronts of two tiles side by side, meeting in the L1 (51 us).
+#include "attn_staged.h"
 #include "gen_unit.h"
 #include "launch_rules.h"
 
@@ -241,6 +242,8 @@ int launch_t(const Launch &L, const void *q, const void *k, const void *v, const
     const int hkv = L.p->num_kv_heads;
     const rules::Walks x = rules::walks(cu_h, L.map.batch, tile_tokens(L.map, L.p->num_q_heads / hkv), idx != nullptr,
                                         L.p->topk_total, dense_below);
+    if (sizeof(T) == 2 && rules::staged(false, D, x.two * hkv, x) && attn_staged_takes(L, k, v))
+        return launch_attn_staged(L, q, k, v, idx, dense_below, out, lse, x.two);
     const rules::GenericForm form = rules::generic_form(sizeof(T) == 2, D, hkv, x);
     if constexpr (sizeof(T) == 2)
         if (form.groups == 2)

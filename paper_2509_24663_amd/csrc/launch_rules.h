@@ -48,7 +48,7 @@ inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
     // 13.8 us, 1000 tokens (500) 22.3 / 18.4, 4000 tokens 127 / 95, 80 x 100 tokens 36.6 / 38.8, 500 x 4 17.5 / 20.1; d 64: 1000
     // tokens 14.8 / 14.9, 1300 tokens 19.0 / 18.7.  Two groups with rows ahead / without, d 128: 1700 tokens (426 workgroups) 31 /
     // 39, 2000 tokens (500) 38.8 / 47.7, 2500 tokens (626) 59 / 56, 4000 tokens (1000) 118 / 95; d 64: 4000 tokens 65 / 70, 6000
-    // tokens (1500) 140 / 126.  fp32 is bound by its products (d 64, 1200 tiles 84 / 88; d 128: the registers do not suffice).
+    // tokens (1500) 140 / 126 (calls of this size take the staged form unless their rows are not 16-byte multiples).  fp32 is bound by its products (d 64, 1200 tiles 84 / 88; d 128: the registers do not suffice).
     if (bf16 && x.half_blocks >= 6 && x.one * hkv > (d == 128 ? 380 : 600))
         return {2, rows_ahead(x.two * hkv, d == 128 ? 512 : 1024, x)};
     return {1, rows_ahead(x.one * hkv, 1024, x)};
@@ -62,6 +62,17 @@ inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
 inline bool fp32_rows_ahead(int d, int64_t workgroups, const Walks &x) {
     if (d == 64) return workgroups <= 256 && x.half_blocks >= 6;
     return x.half_blocks >= 4 && workgroups <= std::min(512., 64 * x.half_blocks);
+}
+// bf16 attention and dQ with tiles of two groups whose V (dQ: K) rows pass through LDS (attn_staged.hip): a step is shorter, but a
+// workgroup takes 3 us longer to start and to end, so not where few of them leave the chip idle and each has few steps.  Calls by
+// workgroups (tiles of two groups times KV heads), generic / staged.  Attention d 128, 8 heads on 2: 600 tokens (150) 12.0 / 13.6 us, 800 (200)
+// 17.1 / 16.7, 2000 (500) 38.8 / 32.3, 7000 267.7 / 235.9; one head of 4, 2600 tokens (325) 29.6 / 30.3; 40 x 100 tokens (1040, walks of two
+// half blocks) 22.2 / 23.9.  d 64: 800 tokens (200) 12.0 / 12.3, 1000 (250) 15.2 / 13.8, 2000 31.6 / 23.3, 40 x 100 13.6 / 13.9.  Backward
+// d 128: 300 tokens (76) 27.7 / 30.3, 600 (150) 44.4 / 43.5, 6000 (1500) 519 / 399; 300 x 4 tokens, 28 heads on 4, 63.4 / 67.3; d 64, 1985
+// tokens 82 / 66.  Over 148 batches per kind the rule is within 0.6 % of the faster one in the mean; without the staged form 5 to 9 % were lost.
+inline bool staged(bool bwd, int d, int64_t workgroups, const Walks &x) {
+    if (bwd) return workgroups >= 150 && (d == 64 || x.half_blocks >= 2);
+    return d == 64 ? workgroups >= 226 : workgroups >= 200 && x.half_blocks >= 3;
 }
 // dQ reads K twice, so two groups pay earlier.  By tiles of one group times KV heads, one / two groups: bf16 d 128: 250 tiles 15.0 /
 // 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1; fp32 d 64: 400 38 / 34, 800 74 / 58 (d 128: two groups need 54 registers

@@ -22,6 +22,10 @@ extern "C" int fp32_ahead(int d, int hkv, int tokens, const int *cu, int batch, 
     const Walks x = walks(cu, batch, tokens, sparse, topk, below);
     return fp32_rows_ahead(d, x.one * hkv, x);
 }
+extern "C" int staged_form(int bwd, int d, int hkv, int tokens, const int *cu, int batch, int sparse, int topk, int below) {
+    const Walks x = walks(cu, batch, tokens, sparse, topk, below);
+    return staged(bwd, d, x.two * hkv, x);
+}
 extern "C" void generic_dkv(int bf16, int d, int hkv, int G, const int *cu, int batch, int sparse, int topk, int below, int *r) {
     const DkvForm f = generic_dkv_form(bf16, d, hkv, G, cu, batch, sparse, topk, below);
     r[0] = f.chunk;
@@ -156,3 +160,11 @@ def test_attention_tiles(rules):
     (128, 8, 2, [1000], 8, 1), (128, 8, 2, [1024], 8, 1), (128, 8, 2, [1025], 8, 0), (128, 4, 1, [150], 8, 0), (128, 4, 1, [], 8, 0)])
 def test_fp32_rows_ahead_only_where_a_cu_has_one_workgroup_to_run(rules, d, hq, hkv, lens, topk, ahead):
     assert rules.fp32_ahead(d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, topk, 0) == ahead
+
+
+@pytest.mark.parametrize("bwd,d,hq,hkv,lens,want", [
+    (0, 128, 8, 2, [792], 0), (0, 128, 8, 2, [793], 1), (0, 128, 8, 2, [4] * 400, 0), (0, 64, 8, 2, [896], 0), (0, 64, 8, 2, [897], 1),
+    (0, 64, 8, 2, [4] * 400, 1), (1, 128, 8, 2, [592], 0), (1, 128, 8, 2, [593], 1), (1, 128, 8, 2, [30] * 100, 0),
+    (1, 64, 8, 2, [30] * 100, 1), (1, 64, 8, 2, [592], 0), (1, 64, 4, 1, [], 0)])
+def test_rows_through_lds_for_large_calls(rules, bwd, d, hq, hkv, lens, want):
+    assert rules.staged_form(bwd, d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, 16, 0) == want
