@@ -15,7 +15,7 @@
 // fp32, the products (32 clocks each) and how evenly a tile's half blocks fall on its wavefronts.  Half as many vector
 // instructions (rows addressed by a scalar base and a constant lane offset, products over 32 keys, no checks for
 // infinities in the first pass, sums rescaled only when a logit is larger than all before) alone took the bf16 case below
-// from 58 to 47 us.  Measured: fp32, 2048 tokens, 4 heads on 1, d 64, 8 blocks: 34 -> 30 us; bf16, 1985 tokens, 8 heads
+// from 58 to 47 us.  Measured: fp32, 2048 tokens, 4 heads on 1, d 64, 8 blocks: 34 -> 27 us; bf16, 1985 tokens, 8 heads
 // on 2, d 128, 16 blocks: 58 -> 39 us; fp32, 600 / 2000 tokens, 8 heads on 2, d 128: 36 -> 20, 131 -> 113 us; bf16, 4000 tokens,
 // 8 heads on 2, d 128: 153 -> 95 us.  Taken back: the wavefronts of two tiles side by side, meeting in the L1 (51 us).
 #include "attn_staged.h"
@@ -29,6 +29,11 @@ namespace {
 using namespace gen;
 
 constexpr int NW = 4;             // wavefronts per workgroup
+
+// Workgroups per CU that the registers of a form allow
+template <typename T, int D, int CG, bool AHEAD>
+constexpr uint32_t kPerCu = (D == 64 ? 2 : 1) + (AHEAD ? 0 : 1) + (sizeof(T) == 2 && CG == 1 ? 1 : 0);
+
 template <typename T, int D, int CG, bool AHEAD>
 __global__ void __launch_bounds__(NW * 64)
 attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
@@ -38,11 +43,21 @@ attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *_
     __shared__ Union un;
     __shared__ float o_s[NW][CG * kCols][D + 4], m_s[NW][CG * kCols], l_s[NW][CG * kCols];
     __shared__ int s_tile[3];
-    const int h = blockIdx.y, G = hq / map.num_kv_heads;
+    // Late tiles first, for they have the most blocks, one head after the other; heads side by side and rows of 256 workgroups back and forth
+    // where all are on the chip at once.  fp32 d 64, one order / the other: 2048 tokens, 4 heads on 1 (512 workgroups) 29.3 / 26.8 us, with 16
+    // blocks 38.3 / 32.5, 1000 tokens on 2 (500) 25.7 / 19.9, 1500 (750) 34.7 / 31.3; beyond that nothing is gained (2048 tokens on 2, 1024
+    // workgroups, 45.6 / 50.0, 4096 102.9 / 99.9), and with one workgroup per CU the second row would start shortest first (36.5 / 44.1).
+    const uint32_t workgroups = gridDim.x * gridDim.y;
+    uint32_t h = blockIdx.y, nth = blockIdx.x;
+    if (workgroups > 256 && workgroups <= 256 * kPerCu<T, D, CG, AHEAD>) {
+        const uint32_t b = back_and_forth(blockIdx.y * gridDim.x + blockIdx.x, workgroups);
+        nth = b / gridDim.y;
+        h = b - nth * gridDim.y;
+    }
+    const int G = hq / map.num_kv_heads;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     Tile t;
-    // (late tiles first: they have the most blocks)
-    if (!find_tile(map, gridDim.x - 1 - blockIdx.x, CG * tile_tokens(map, G), t, s_tile)) return;
+    if (!find_tile(map, (int)(gridDim.x - 1 - nth), CG * tile_tokens(map, G), t, s_tile)) return;
     const bool dense = idx == nullptr || t.len < dense_below;
     const int32_t *lists = dense ? nullptr : idx + head_row(map, h, t.row0) * topk_total;
     const int nblk = (t.t0 + t.ntok - 1) / kBlock + 1;

@@ -130,10 +130,8 @@ __global__ void __launch_bounds__(NW * 64, D == 128 ? 2 : 3) attn_staged_kernel(
     __shared__ float m_s[NW][kTileCols], l_s[NW][kTileCols];
     __shared__ int s_tile[3], s_bad;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Longest tiles first, heads side by side.  Where all workgroups fit the chip at once (256 CUs, workgroups b and b + 256 on one), every
-    // second row of 256 goes backwards, so that long and short tiles share a CU.
-    uint32_t b = blockIdx.x;
-    if (gridDim.x <= a.resident && (b >> 8 & 1)) b = 2 * (b & ~255u) + min(255u, gridDim.x - 1 - (b & ~255u)) - b;
+    // longest tiles first, heads side by side
+    const uint32_t b = gridDim.x <= a.resident ? back_and_forth(blockIdx.x, gridDim.x) : blockIdx.x;
     const uint32_t hkv = (uint32_t)a.map.num_kv_heads, nth = b / hkv;
     const int h = (int)(b - nth * hkv), G = a.hq / (int)hkv;
     const int tokens = kCols / G;

@@ -301,6 +301,13 @@ __device__ inline bool find_tile(const RowMap &m, int tile, int tokens, Tile &t,
     return true;
 }
 
+// The b-th of n workgroups that are all on the chip at once, in an order of falling work: workgroups b and b + 256 share one of the 256 CUs,
+// so every second row of 256 goes backwards and long tiles have short ones beside them.
+__device__ inline uint32_t back_and_forth(uint32_t b, uint32_t n) {
+    const uint32_t row = b & ~255u;
+    return b & 256u ? 2 * row + min(255u, n - 1 - row) - b : b;
+}
+
 // The union of a tile's block lists, kChunk block numbers at a time: after build() the LDS list holds (block, mask of
 // the tokens that take it) in ascending order for the blocks [c0, c0 + kChunk).
 constexpr int kChunk = 1024;

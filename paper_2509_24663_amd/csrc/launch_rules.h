@@ -48,14 +48,16 @@ inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
     // 13.8 us, 1000 tokens (500) 22.3 / 18.4, 4000 tokens 127 / 95, 80 x 100 tokens 36.6 / 38.8, 500 x 4 17.5 / 20.1; d 64: 1000
     // tokens 14.8 / 14.9, 1300 tokens 19.0 / 18.7.  Two groups with rows ahead / without, d 128: 1700 tokens (426 workgroups) 31 /
     // 39, 2000 tokens (500) 38.8 / 47.7, 2500 tokens (626) 59 / 56, 4000 tokens (1000) 118 / 95; d 64: 4000 tokens 65 / 70, 6000
-    // tokens (1500) 140 / 126 (calls of this size take the staged form unless their rows are not 16-byte multiples).  fp32 is bound by its products (d 64, 1200 tiles 84 / 88; d 128: the registers do not suffice).
+    // tokens (1500) 140 / 126.  (Calls of this size take the
+    // staged form unless their rows are not 16-byte multiples.)  fp32 is bound by its products (d 64, 1200 tiles 84 / 88; d 128: the
+    // registers do not suffice).
     if (bf16 && x.half_blocks >= 6 && x.one * hkv > (d == 128 ? 380 : 600))
         return {2, rows_ahead(x.two * hkv, d == 128 ? 512 : 1024, x)};
     return {1, rows_ahead(x.one * hkv, 1024, x)};
 }
 // fp32 attention is bound by its products: rows requested ahead are worth their registers only where a CU has no other
 // workgroup's wavefronts to fill the waits with.  d 64 keeps two workgroups per CU with them and three without, d 128 one and two.
-// Attention alone, ahead / not: d 64, 4 heads on 1, topk 8: 1000 tokens (250 workgroups) 20.8 / 24.1 us, 2048 (512) 31.6 / 28.5,
+// Attention alone, ahead / not: d 64, 4 heads on 1, topk 8 (all in one order of workgroups): 1000 tokens (250 workgroups) 17.5 / 17.9 us, 2048 (512) 31.6 / 28.5,
 // 4096 (1024) 97 / 90; 8 on 2: 1000 (500) 28.0 / 25.4, 3300 (1650) 55.3 / 44.8; walks of fewer than six half blocks are over before a
 // second request would arrive.  d 128, 8 on 2: 600 tokens (300) 20.6 / 26.0, 1000 (500) 36.7 / 47.7, 2048 (1024) 103 / 92.  Over 228
 // batches the rule is within 0.2 % of the faster form in the mean, where rows_ahead lost 2.0 (d 128) and 2.9 % (d 64).
