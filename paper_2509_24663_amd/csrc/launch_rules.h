@@ -172,6 +172,9 @@ inline DkvForm generic_dkv_form(bool bf16, int d, int hkv, int G, const int32_t 
 // up to 1024 tokens the tile kernel's time goes up by rounds of 256 tiles of 16 (4 x 777 tokens 50.1 / 55.0, 5 x 777 62.3 / 58.7; on 1 KV head 3 x
 // 777 23.7 / 32.5, 4 x 777 33.4 / 33.5, 6 x 700 37.9 / 33.9; 8 KV heads, 850 tokens 53.0 / 57.8, 8 blocks, 900 tokens 55.8 / 54.1; 4 KV
 // heads, 1000 tokens 38.3 / 39.8, 8 blocks 35.3 / 33.1).
+// (Figures of one wavefront above are from when it took 250 registers; with 188 it is 6 to 9 % faster.)  One sequence of 501 to 600 tokens on 2 KV
+// heads has so few workgroups over one round that two are still better: two / one, 520 tokens (260) 13.3 / 15.0, 600 (300) 14.8 / 16.3; but
+// 4 x 300 on 2 (300) 21.9 / 15.8, 260 tokens on 4 (260) 12.0 / 10.9.
 inline int short_attn_waves(const int32_t *cu_h, int batch, int max_len, int hkv, bool sparse, int topk, int dense_below) {
     int64_t wgs = 0, tiles16 = 0;
     for (int s = 0; s < batch; ++s) {
@@ -182,7 +185,7 @@ inline int short_attn_waves(const int32_t *cu_h, int batch, int max_len, int hkv
     const int walk = sparse && max_len >= dense_below ? std::min(topk, blocks) : blocks;
     const bool every = walk == blocks;
     if (wgs <= 256) return 2;
-    if (wgs <= 512 && max_len > 600 && max_len <= 2048) {
+    if (wgs <= 512 && max_len > (batch == 1 && wgs <= 320 ? 500 : 600) && max_len <= 2048) {
         if (walk < 6) return 1;
         if (walk < 10 ? wgs <= 400 : every || max_len <= 1728) return 2;
     }

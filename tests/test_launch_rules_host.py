@@ -26,6 +26,9 @@ extern "C" int staged_form(int bwd, int d, int hkv, int tokens, const int *cu, i
     const Walks x = walks(cu, batch, tokens, sparse, topk, below);
     return staged(bwd, d, x.two * hkv, x);
 }
+extern "C" int short_waves(const int *cu, int batch, int max_len, int hkv, int sparse, int topk, int below) {
+    return short_attn_waves(cu, batch, max_len, hkv, sparse, topk, below);
+}
 extern "C" void generic_dkv(int bf16, int d, int hkv, int G, const int *cu, int batch, int sparse, int topk, int below, int *r) {
     const DkvForm f = generic_dkv_form(bf16, d, hkv, G, cu, batch, sparse, topk, below);
     r[0] = f.chunk;
@@ -168,3 +171,9 @@ def test_fp32_rows_ahead_only_where_a_cu_has_one_workgroup_to_run(rules, d, hq, 
     (1, 64, 8, 2, [30] * 100, 1), (1, 64, 8, 2, [592], 0), (1, 64, 4, 1, [], 0)])
 def test_rows_through_lds_for_large_calls(rules, bwd, d, hq, hkv, lens, want):
     assert rules.staged_form(bwd, d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, 16, 0) == want
+
+
+@pytest.mark.parametrize("hkv,lens,topk,want", [(2, [512], 16, 2), (2, [513], 16, 2), (2, [640], 16, 2), (2, [500, 13], 16, 1), (2, [300] * 4, 16, 1),
+                                                (4, [260], 16, 1), (2, [600], 4, 1), (3, [500], 16, 1)])
+def test_wavefronts_per_token_of_short_prompts(rules, hkv, lens, topk, want):
+    assert rules.short_waves(_cu(lens), len(lens), max(lens), hkv, 1, topk, 0) == want
