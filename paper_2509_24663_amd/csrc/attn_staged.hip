@@ -345,7 +345,11 @@ __global__ void __launch_bounds__(NW * 64, D == 128 ? 2 : 3) attn_staged_kernel(
                 wg[u] = exp2_fast((m_s[u][col] - base) * c);
                 L += l_s[u][col] * wg[u];
             }
-            lse_out = mm * a.scale + __logf(L);
+            // (in 64 bits, and the logarithm of the mantissa alone: a reference may lie 8 binary orders below the largest logit, and the terms
+            // are the larger for it.  Root mean square error, 1985 tokens: 1.7e-7; in 32 bits 3.2e-7, with the largest logit 3.0e-7)
+            int e;
+            const float f = frexpf(L, &e);
+            lse_out = (float)((double)mm * (double)a.scale + ((double)e * 0.6931471805599453 + (double)__logf(f)));
             const float inv = 1.f / L;
 #pragma unroll
             for (int u = 0; u < NW; ++u) wg[u] *= inv;
