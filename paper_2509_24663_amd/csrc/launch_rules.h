@@ -67,14 +67,16 @@ inline bool fp32_rows_ahead(int d, int64_t workgroups, const Walks &x) {
 }
 // bf16 attention and dQ with tiles of two groups whose V (dQ: K) rows pass through LDS (attn_staged.hip): a step is shorter, but a
 // workgroup takes 3 us longer to start and to end, so not where few of them leave the chip idle and each has few steps.  Calls by
-// workgroups (tiles of two groups times KV heads), generic / staged.  Attention d 128, 8 heads on 2: 600 tokens (150) 12.0 / 13.6 us, 800 (200)
-// 17.1 / 16.7, 2000 (500) 38.8 / 32.3, 7000 267.7 / 235.9; one head of 4, 2600 tokens (325) 29.6 / 30.3; 40 x 100 tokens (1040, walks of two
-// half blocks) 22.2 / 23.9.  d 64: 800 tokens (200) 12.0 / 12.3, 1000 (250) 15.2 / 13.8, 2000 31.6 / 23.3, 40 x 100 13.6 / 13.9.  Backward
-// d 128: 300 tokens (76) 27.7 / 30.3, 600 (150) 44.4 / 43.5, 6000 (1500) 519 / 399; 300 x 4 tokens, 28 heads on 4, 63.4 / 67.3; d 64, 1985
-// tokens 82 / 66.  Over 148 batches per kind the rule is within 0.6 % of the faster one in the mean; without the staged form 5 to 9 % were lost.
+// workgroups (tiles of two groups times KV heads), generic / staged.  Attention d 128, 8 heads on 2: 720 tokens (180) 13.6 / 16.6 us, 1020 (255)
+// 19.6 / 19.3, 1200 (300) 21.4 / 22.2, 1520 (380) 27.3 / 25.0, 2080 (520) 40.0 / 33.3, 7000 268 / 236; 28 on 4, 330 tokens 11.0 / 13.2, 380 18.2 / 13.4;
+// 40 x 100 tokens (1040, walks of two half blocks) 22.2 / 23.9.  d 64 (the generic form takes two groups beyond 300, for walks of six): 1200
+// tokens (300) 13.2 / 16.2, 1320 (330) 17.1 / 16.7, 2080 25.2 / 19.7; 28 on 4, 330 tokens (walks of five) 8.3 / 9.5; 8 x 300 (608) 13.6 / 12.4, 40 x 100
+// 13.6 / 13.9.  Backward d 128: 300 tokens (76) 27.7 / 30.3, 600 (150) 44.4 / 43.5, 6000 (1500) 519 / 399; 300 x 4 tokens, 28 heads on 4,
+// 63.4 / 67.3; d 64, 1985 tokens 82 / 66.
 inline bool staged(bool bwd, int d, int64_t workgroups, const Walks &x) {
     if (bwd) return workgroups >= 150 && (d == 64 || x.half_blocks >= 2);
-    return d == 64 ? workgroups >= 226 : workgroups >= 200 && x.half_blocks >= 3;
+    if (d == 64) return workgroups > 300 && x.half_blocks >= (workgroups > 512 ? 3 : 6);
+    return workgroups >= 340 && x.half_blocks >= 3;
 }
 // dQ reads K twice, so two groups pay earlier.  By tiles of one group times KV heads, one / two groups: bf16 d 128: 250 tiles 15.0 /
 // 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1; fp32 d 64: 400 38 / 34, 800 74 / 58 (d 128: two groups need 54 registers

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import synth
+import test_gpu_generic_groups as groups
 from helpers import assert_out_close, to_dev, to_np
 from test_gpu_parity import _check_backward, _params, _run_prefill_case, m  # noqa: F401
 
@@ -15,10 +16,10 @@ EDGES = [97, 127, 128, 129, 159, 160, 161, 191, 193, 223, 225, 255, 256, 257]
 
 
 @pytest.mark.parametrize("hq,hkv,d,lens,topk,threshold", [
-    (8, 2, 128, EDGES, 3, 0), (8, 2, 64, EDGES, 3, 190), (16, 8, 128, [129, 97, 161, 225], 2, 0),     # four and eight tokens per group
+    (8, 2, 128, EDGES, 3, 0), (8, 2, 64, EDGES, 3, 190), (16, 8, 128, [129, 97, 161, 225, 257], 2, 0),     # four and eight tokens per group
     (9, 3, 128, EDGES[:12], 4, 0), (9, 3, 64, EDGES[:12], 4, 160),                                    # G = 3: five tokens, 15 columns
-    (56, 8, 128, [97, 130], 2, 0), (12, 1, 64, EDGES[:6], 3, 0), (16, 1, 64, [200, 97, 130], 3, 0),   # two tokens and one per group
-    (8, 8, 128, EDGES[:9] + [511], 3, 0), (8, 8, 64, [1000], 5, 0),                                   # G = 1: 32 tokens per tile
+    (56, 8, 128, [197, 230], 3, 0), (12, 1, 64, EDGES[8:], 3, 0), (16, 1, 64, [300, 257, 500], 3, 0),   # two tokens and one per group
+    (8, 8, 128, EDGES[:9] + [511], 3, 0), (8, 8, 64, [1300], 5, 0),                                   # G = 1: 32 tokens per tile
     (8, 2, 128, [1985], 40, 0),                                                                       # walks of up to 62 half blocks
 ])
 def test_lengths_and_groups(m, oracle, hq, hkv, d, lens, topk, threshold):  # noqa: F811
@@ -36,7 +37,7 @@ def test_lengths_and_groups(m, oracle, hq, hkv, d, lens, topk, threshold):  # no
 def test_strides_and_alignments(m, d, how):  # noqa: F811
     """The same values wherever the rows lie: 16-byte strides take the same kernel, others the one without LDS rows; either way each
     result is within a bf16 rounding of the same sum."""
-    hq, hkv, n = 8, 2, 1100
+    hq, hkv, n = 8, 2, 1500
     w = synth.make_prefill(n, hq, hkv, d, seed=7500 + d, dtype="bf16")
     gp = m.Params.make("bf16", hq, hkv, d, n_init=1, n_local=1, topk_total=5)
     q, k, v = (to_dev(w[x], "bf16") for x in ("q", "k", "v"))
@@ -69,7 +70,7 @@ def test_strides_and_alignments(m, d, how):  # noqa: F811
 def test_references_that_move_late(m, d, size):  # noqa: F811
     """Keys whose logits grow along the sequence, from block to block by less and by more than a kept reference may fall behind, up to
     logits of thousands."""
-    hq, hkv, n = 8, 2, 1100
+    hq, hkv, n = 8, 2, 1500
     g = torch.Generator().manual_seed(7600 + d)
     q = torch.randn(n, hq, d, generator=g).abs().bfloat16()
     k = (torch.randn(hkv, n, d, generator=g).abs() * torch.linspace(0.1, 1.0, n)[None, :, None] * size).bfloat16()
@@ -84,3 +85,7 @@ def test_references_that_move_late(m, d, size):  # noqa: F811
         # a logit is a sum of at most 128 exact products in fp32, off by at most 2^-20 of its size here, where all terms are positive
         assert ((lse[h].double().cpu() - torch.logsumexp(s, -1)).abs() <= 2.0 ** -20 * top + 1e-5).all()
         assert_out_close(to_np(out[:, h]), (torch.softmax(s, -1) @ v[h // 4].double()).numpy(), "bf16", f"head {h}")
+
+
+def test_infinite_rows(m, oracle):  # noqa: F811
+    groups.test_infinite_rows_stay_with_the_tokens_that_see_them(m, oracle, "bf16", 1500)
