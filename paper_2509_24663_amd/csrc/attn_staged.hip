@@ -42,11 +42,11 @@ struct Stage {
     static constexpr uint32_t kBytes = 32 * D * 2;
     const char *src;                   // row lane / 16 of the tensor
     int64_t stride;                    // bytes from token to token
-    int len, lane;
+    int len;
     uint32_t lds0, row_at, trans_at;
 
-    __device__ inline Stage(const bf16_t *rows, int64_t tok_stride, int len_, int lane_, uint32_t lds)
-        : stride(tok_stride * 2), len(len_), lane(lane_), lds0(lds) {
+    __device__ inline Stage(const bf16_t *rows, int64_t tok_stride, int len_, int lane, uint32_t lds)
+        : stride(tok_stride * 2), len(len_), lds0(lds) {
         src = reinterpret_cast<const char *>(rows) + (lane >> 4) * stride;
         const int m = lane & 15, g = lane >> 4;
         // row x of product tile kt is row 8 (x / 4) + 4 kt + x % 4: a lane's eight weights are then rows 8 g .. 8 g + 7
@@ -61,8 +61,8 @@ struct Stage {
     __device__ inline void copy(int key0, int buf) const {
         constexpr int P = kBytes / 1024;
         const uint32_t dst = lds0 + buf * kBytes;
-        int l = lane;
-        asm volatile("" : "+v"(l));                      // (offsets are formed here, not kept in registers over the walk)
+        int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(l));                      // (the lane and its offsets are formed here, not kept in registers over the walk)
         const char *from = src + (int64_t)key0 * stride;
         const int c = (l & 15) ^ (4 * (l >> 4)), up = D == 128 ? 0 : 16 * (c >> 3);
         auto chunk_at = [&](int p) -> int { return ((c ^ (2 * ((p >> 1) & 1) + (p >> 2))) & (D / 8 - 1)) * 16; };
@@ -320,6 +320,9 @@ __global__ void __launch_bounds__(NW * 64, D == 128 ? 2 : 3) attn_staged_kernel(
     };
     // partial results of the wavefronts, merged and stored by eight threads per column; a 16-byte chunk of column m at chunk ^ m
     auto finish = [&]() -> bool {
+        int tid = w * 64 + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(tid));                    // (as above)
+        const int m = tid & 15, g = (tid >> 4) & 3;
         f32x4 *part = reinterpret_cast<f32x4 *>(smem);
 #pragma unroll
         for (int x = 0; x < CG; ++x) {
