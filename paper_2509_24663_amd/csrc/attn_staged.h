@@ -4,7 +4,8 @@
 
 namespace ifv2 {
 
-// bf16 prefill calls with rows and strides of 16-byte multiples and no more workgroups than a launch has
+// bf16 prefill calls with rows and strides of 16-byte multiples (whether there are workgroups enough, and not more than a launch holds:
+// rules::staged)
 bool attn_staged_takes(const Launch &L, const void *k, const void *v);
 
 // tiles: of two column groups, over the whole batch

@@ -410,8 +410,7 @@ int launch_t(const Launch &L, StagedArgs a, int64_t tiles) {
 
 bool attn_staged_takes(const Launch &L, const void *k, const void *v) {
     return L.p->dtype == INFLLMV2_BF16 && L.map.ctx == nullptr && (((uintptr_t)k | (uintptr_t)v) & 15) == 0 &&
-           L.map.kv_tok_stride % 8 == 0 && L.map.kv_head_stride % 8 == 0 &&
-           ((int64_t)L.map.total_rows + L.map.batch) * L.p->num_kv_heads <= 0x7fffffff;
+           L.map.kv_tok_stride % 8 == 0 && L.map.kv_head_stride % 8 == 0;
 }
 
 int launch_attn_staged(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, void *out,

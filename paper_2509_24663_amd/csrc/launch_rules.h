@@ -9,6 +9,10 @@ namespace rules {
 
 constexpr int kKeys = 64;         // keys of a selection block
 
+// Workgroups of 256 threads that a launch holds in x, which has fewer than 2^32 threads.  Kernels with tiles and heads both in x reach that
+// sooner than those with heads in y, which then serve the call.
+constexpr int64_t kMostInX = 0xffffffffll / 256;
+
 // Tiles of one and of two column groups (of `tokens` tokens) in a packed batch, and the half blocks (32 keys) that a tile walks
 // on average: a causal walk, or as far as one token's budget goes (neighbouring tokens share most of their blocks).
 struct Walks {
@@ -74,6 +78,7 @@ inline bool fp32_rows_ahead(int d, int64_t workgroups, const Walks &x) {
 // 13.6 / 13.9.  Backward d 128: 300 tokens (76) 27.7 / 30.3, 600 (150) 44.4 / 43.5, 6000 (1500) 519 / 399; 300 x 4 tokens, 28 heads on 4,
 // 63.4 / 67.3; d 64, 1985 tokens 82 / 66.
 inline bool staged(bool bwd, int d, int64_t workgroups, const Walks &x) {
+    if (workgroups > kMostInX) return false;
     if (bwd) return workgroups >= 150 && (d == 64 || x.half_blocks >= 2);
     if (d == 64) return workgroups > 300 && x.half_blocks >= (workgroups > 512 ? 3 : 6);
     return workgroups >= 340 && x.half_blocks >= 3;
@@ -183,6 +188,7 @@ inline int short_attn_waves(const int32_t *cu_h, int batch, int max_len, int hkv
         wgs += (int64_t)((cu_h[s + 1] - cu_h[s] + 3) / 4) * hkv;
         tiles16 += (int64_t)((cu_h[s + 1] - cu_h[s] + 15) / 16) * hkv;
     }
+    if (wgs > kMostInX) return 0;
     const int blocks = (max_len + kKeys - 1) / kKeys;
     const int walk = sparse && max_len >= dense_below ? std::min(topk, blocks) : blocks;
     const bool every = walk == blocks;

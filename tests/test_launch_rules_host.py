@@ -177,3 +177,13 @@ def test_rows_through_lds_for_large_calls(rules, bwd, d, hq, hkv, lens, want):
                                                 (4, [260], 16, 1), (2, [600], 4, 1), (3, [500], 16, 1)])
 def test_wavefronts_per_token_of_short_prompts(rules, hkv, lens, topk, want):
     assert rules.short_waves(_cu(lens), len(lens), max(lens), hkv, 1, topk, 0) == want
+
+
+def test_no_more_workgroups_than_a_launch_holds(rules):
+    """Tiles and heads side by side in x, 256 threads each: fewer than 2^32 threads, or the kernels with heads in y serve the call."""
+    for bwd in (0, 1):
+        for n, want in ((55924, 1), (55925, 0)):                      # sequences of 150 tiles on 2 KV heads: 16777200 and 16777500 workgroups
+            assert rules.staged_form(bwd, 64, 2, 1, _cu([300] * n), n, 0, 16, 0) == want
+    for n, want in ((8388607, 1), (8388608, 0)):
+        cu = (ctypes.c_int * (n + 1))(*range(n + 1))
+        assert rules.short_waves(cu, n, 1, 2, 0, 16, 0) == want
