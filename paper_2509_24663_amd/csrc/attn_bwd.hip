@@ -37,6 +37,7 @@ using namespace gen;
 
 constexpr int NW = 4;               // wavefronts per workgroup of the dq and dkv kernels
 constexpr int BWD_CHUNK = 256;      // most tokens a dkv workgroup looks at
+constexpr int kWaitVm0 = 0x0F70;    // s_waitcnt vmcnt(0), other counters untouched
 
 template <typename T>
 struct BwdArgs {
@@ -308,10 +309,11 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int shif
         pr.lse = a.lse[lr];
         pr.delta = a.delta[lr];
         pr.t = used ? t : -1;
-        if (!used) { pr.q.zero(); pr.g.zero(); }
         return pr;
     };
-    auto stage = [&](int buf, const Pre &pr) {
+    // (unused rows become zeros here: where they are requested it would mean to wait for them, half a microsecond of each step)
+    auto stage = [&](int buf, Pre &pr) {
+        if (pr.t < 0) { pr.q.zero(); pr.g.zero(); }
         pr.q.store_lds(&rows_s[buf][0][x_row][0], tid & 15);
         pr.g.store_lds(&rows_s[buf][1][x_row][0], tid & 15);
         if ((tid & 15) == 0) {
@@ -320,12 +322,18 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int shif
             t_s[buf][x_row] = pr.t;
         }
     };
-    stage(0, fetch(0));
+    {
+        Pre first = fetch(0);
+        stage(0, first);
+    }
+    // (the keys' own rows, requested first, are waited for here: left to the compiler that wait stands in the loop's first products, where it also
+    // waits for the rows just requested for the next step)
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __syncthreads();
     int buf = 0;
     for (int it = 0; it < total; it += tokens, buf ^= 1) {
         const bool more = it + tokens < total;
-        Pre nxt = {};
+        Pre nxt;
         if (more) nxt = fetch(it + tokens);
         RowFrag<T, D> qf, gf;
         qf.load_lds(&rows_s[buf][0][m][0], g);
@@ -337,11 +345,17 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int shif
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int x = 4 * g + r;
-            const bool vis = key <= t_s[buf][x];
-            p[r] = vis ? exp2_fast(__builtin_fmaf(s[r], a.scale, -lse_s[buf][x]) * kLog2e) : 0.f;
-            dz[r] = vis ? p[r] * (dp[r] - delta_s[buf][x]) : 0.f;
+            p[r] = exp2_fast(__builtin_fmaf(s[r], a.scale, -lse_s[buf][x]) * kLog2e);
+            dz[r] = p[r] * (dp[r] - delta_s[buf][x]);
+            asm volatile("" : "+v"(p[r]), "+v"(dz[r]));        // (no branch round the hidden ones: six waits for LDS, one after the other)
             qr[r].load_lds(&rows_s[buf][0][x][0], m);
             gr[r].load_lds(&rows_s[buf][1][x][0], m);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool vis = key <= t_s[buf][4 * g + r];
+            p[r] = vis ? p[r] : 0.f;
+            dz[r] = vis ? dz[r] : 0.f;
         }
         if constexpr (sizeof(T) == 2) {                        // 16 of the 32 indices; the others are 0 times 0
             const f32x4 none = {0.f, 0.f, 0.f, 0.f};
