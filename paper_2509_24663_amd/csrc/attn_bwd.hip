@@ -219,11 +219,15 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
 // launched: in a grid of all pairs half of the workgroups are empty, and as these come at regular intervals while workgroups are
 // dealt out in turn to the dies and to the engines of a die, some engines got several times the work of others (1985 tokens, 8 heads on
 // 2, chunks of 64: the workgroups' times sum up to 42 us of the chip and took 91 from first to last; whole backward 149 -> 140 us).
-// Sequence (>= batch past the last pair), chunk and block of this workgroup; s_tile: 3 ints of LDS.
-__device__ inline int dkv_place(const RowMap &m, int shift, int &chunk, int &block, int *s_tile) {
+// Sequence (>= batch past the last pair), chunk and block of this workgroup; s_tile: 3 ints of LDS.  ONE chunk holds every sequence: a
+// workgroup is a block, as cheap to find in a batch as a tile (2000 sequences of one token, 8 heads on 2, d 64, bf16: dkv 54 -> 49 us).
+__device__ inline int dkv_place(const RowMap &m, int shift, bool one, int &chunk, int &block, int *s_tile) {
+    const int at = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    chunk = 0;
+    if (one) return find_seq_tile(m.cu, m.batch, kBlock, at, block, s_tile);
     int nth, before;
-    const int seq = find_seq_count(m.cu, m.batch, (int)(blockIdx.y * gridDim.x + blockIdx.x), nth, before, s_tile,
-                                   [&](int n) { return sequence_pairs(n, shift); }, [](int) { return 0; });
+    const int seq = find_seq_count(m.cu, m.batch, at, nth, before, s_tile, [&](int n) { return sequence_pairs(n, shift); },
+                                   [](int) { return 0; });
     if (seq < m.batch) pair_at(nth, shift, chunk, block);
     return seq;
 }
@@ -246,7 +250,7 @@ __device__ inline bool selected(const int32_t *e, int n, int j) {
 }
 
 template <typename T, int D>
-__global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int shift) {
+__global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int shift, bool one) {
     constexpr int N = D / 16;
     constexpr int ROWS = kCols;                                        // of Q and dO per step
     __shared__ __attribute__((aligned(16))) T rows_s[2][2][ROWS][D + 16 / sizeof(T)];      // [buffer][Q, dO][row]
@@ -256,7 +260,7 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int shif
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int h = blockIdx.z, G = a.hq / a.map.num_kv_heads;
     int j, at;
-    const int seq = dkv_place(a.map, shift, at, j, s_tile);
+    const int seq = dkv_place(a.map, shift, one, at, j, s_tile);
     if (seq >= a.map.batch) return;
     const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;
     // tokens of this chunk that can see the block: [max(chunk start, 64 j), min(chunk end, len))
@@ -415,7 +419,7 @@ typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
 typedef short short4v __attribute__((ext_vector_type(4)));
 
 template <int D>
-__global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t> a, int shift) {
+__global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t> a, int shift, bool one) {
     constexpr int N = D / 16, ROWS = 32;
     constexpr uint32_t kTile = ROWS * kRowBytes, kBuf = 2 * kTile;     // Q rows, then dO rows
     __shared__ __attribute__((aligned(1024))) char rows_s[2 * kBuf];
@@ -425,7 +429,7 @@ __global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = blockIdx.z, G = a.hq / a.map.num_kv_heads;
     int j, at;
-    const int seq = dkv_place(a.map, shift, at, j, s_tile);
+    const int seq = dkv_place(a.map, shift, one, at, j, s_tile);
     if (seq >= a.map.batch) return;
     const int tok0 = a.map.cu[seq], len = a.map.cu[seq + 1] - tok0;
     // tokens of this chunk that can see the block: [max(chunk start, 64 j), min(chunk end, len))
@@ -660,6 +664,7 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     int64_t pairs;
     const int shift = rules::generic_dkv_shift(sizeof(T) == 2, D, a.hq / hkv, {cu_h, L.map.batch, L.max_len, hkv, nblocks, a.idx != nullptr,
                                                a.topk_total, a.dense_below}, pairs);
+    const bool one = L.max_len <= 1 << shift;
     const int64_t gx = std::min<int64_t>(pairs, 1 << 20);
     const dim3 grid((unsigned)gx, (unsigned)((pairs + gx - 1) / gx), hkv);
     if constexpr (sizeof(T) == 2) {
@@ -667,10 +672,10 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
         // 300 x 8 tokens 30.5 / 30.2
         const bool few = D == 64 && L.max_len <= 4 &&
                          rules::generic_dkv_form(true, D, hkv, a.hq / hkv, cu_h, L.map.batch, a.idx != nullptr, a.topk_total, a.dense_below).row_groups == 1;
-        if (few) hipLaunchKernelGGL((bwd_dkv_kernel<T, 64>), grid, dim3(NW * 64), 0, L.stream, a, shift);
-        else hipLaunchKernelGGL((bwd_dkv_bf16_kernel<D>), grid, dim3(NW * 64), 0, L.stream, a, shift);
+        if (few) hipLaunchKernelGGL((bwd_dkv_kernel<T, 64>), grid, dim3(NW * 64), 0, L.stream, a, shift, one);
+        else hipLaunchKernelGGL((bwd_dkv_bf16_kernel<D>), grid, dim3(NW * 64), 0, L.stream, a, shift, one);
     } else {
-        hipLaunchKernelGGL((bwd_dkv_kernel<T, D>), grid, dim3(NW * 64), 0, L.stream, a, shift);
+        hipLaunchKernelGGL((bwd_dkv_kernel<T, D>), grid, dim3(NW * 64), 0, L.stream, a, shift, one);
     }
     return hip_status(hipGetLastError());
 }
