@@ -314,7 +314,9 @@ inline int dkv_chunk(const DkvBatch &b, int64_t most) {
 // 35 / 48 / 76 us, 1000 tokens 80 / 63 / 69 / 97, 1985 tokens 180 / 140 / 112 / 132, 3000 tokens 357 / 266 / 216 / 212, 26 x 300 202 / 173 / 177 / 185;
 // d 64, 1985 tokens 114 / 94 / 84 / 104; fp32, d 128, 900 tokens 119 / 119 / 153 / 233.
 inline int generic_dkv_shift(bool bf16, int d, int G, const DkvBatch &b, int64_t &pairs) {
-    const double tokens = 16 / G * (bf16 ? 2 : 1), fixed = bf16 && d == 128 ? 5 : 2.5, slots = bf16 ? 384 : 512, kTail = 0.3;
+    const double tokens = 16 / G * (bf16 ? 2 : 1);
+    const double fixed = d == 128 ? (bf16 ? 3 : 4) : (bf16 ? 5 : 2), slots = d == 128 ? (bf16 ? 256 : 512) : (bf16 ? 768 : 512);
+    const double kTail = bf16 == (d == 128) ? 0.3 : 0.7;
     int64_t busy[4] = {};                                   // by the chunk's size, 32 first
     double entries = 0;
     for (int s = 0; s < b.batch; ++s) {
