@@ -308,15 +308,18 @@ inline int dkv_chunk(const DkvBatch &b, int64_t most) {
 //
 // The cheapest of 32 to 256 by a model of the launch, in steps (32 or 16 rows: as many tokens of G heads as that): a workgroup takes a fixed
 // time for its list, its keys and its adds, and its tokens' steps, of which the last is half empty; while all workgroups run at once
-// the longest counts, then the rounds of the average one and part of the longest.  From the backward call with every chunk at 650 forms
-// (60 to 6000 tokens, 1 to 8 KV heads, groups of 1, 4, 7 and 8, budgets of 8 to 32 blocks and dense, packed batches) the chosen chunk is 0.7 % (fp32 0.3 %)
-// from the best on average, 17 % (9 %) at most (profiles/generic_backward_chunk_timings.txt).  Whole backward, chunks of 32 / 64 / 128 / 256: bf16, 8 heads on 2, d 128, 16 blocks, 300 tokens 29 /
-// 35 / 48 / 76 us, 1000 tokens 80 / 63 / 69 / 97, 1985 tokens 180 / 140 / 112 / 132, 3000 tokens 357 / 266 / 216 / 212, 26 x 300 202 / 173 / 177 / 185;
-// d 64, 1985 tokens 114 / 94 / 84 / 104; fp32, d 128, 900 tokens 119 / 119 / 153 / 233.
+// the longest counts, then the rounds of the average one and part of the longest.  From the backward call with every chunk at 4150 forms
+// (60 to 6000 tokens, packed mixtures of up to 2000 sequences, 1 to 8 KV heads, groups of 1 to 16, budgets of 4 and 16 blocks and dense) the chosen chunk
+// is from the best on average / at the worst hundredth: bf16 d 128 0.8 / 10 %, d 64 0.6 / 8 %, fp32 0.7 / 10 and 0.3 / 8 %
+// (profiles/generic_backward_chunk_timings.txt).  Whole backward, chunks of 32 / 64 / 128 / 256: bf16, 8 heads on 2, d 128, 16 blocks, 300 tokens 29 /
+// 34 / 48 / 75 us, 1000 tokens 80 / 63 / 69 / 97, 1985 tokens 167 / 125 / 97 / 117, with 4 blocks 1000 tokens 63 / 48 / 58 / 87; d 64, 1985 tokens 98 / 75 /
+// 67 / 86; fp32, d 128, 1985 tokens 400 / 368 / 363 / 464, 4 heads on 4, 1000 tokens 134 / 115 / 100 / 107.
 inline int generic_dkv_shift(bool bf16, int d, int G, const DkvBatch &b, int64_t &pairs) {
+    // a workgroup's fixed time, what the average one takes beyond its tokens' steps, workgroups in a round, the part of the longest
+    struct Model { double fixed, end, slots, tail; };
+    const Model c = !bf16 ? (d == 64 ? Model{2, 0.5, 512, 0.3} : Model{4, 1, 480, 0.5})
+                          : d == 64 ? Model{4, 1, 512, 0.3} : G > 4 ? Model{5, 0.5, 512, 0.5} : Model{3, 0.5, 256, 0.3};
     const double tokens = 16 / G * (bf16 ? 2 : 1);
-    const double fixed = d == 128 ? (bf16 ? 3 : 4) : (bf16 ? 5 : 2), slots = d == 128 ? (bf16 ? 256 : 512) : (bf16 ? 768 : 512);
-    const double kTail = bf16 == (d == 128) ? 0.3 : 0.7;
     int64_t busy[4] = {};                                   // by the chunk's size, 32 first
     double entries = 0;
     for (int s = 0; s < b.batch; ++s) {
@@ -332,9 +335,9 @@ inline int generic_dkv_shift(bool bf16, int d, int G, const DkvBatch &b, int64_t
     int best_i = 3;
     double best = 0;
     for (int i = 3; i >= (b.max_len < 1 << 20 ? 0 : 3); --i) {     // (the counts fit 32 bits)
-        const double wgs = (double)busy[i] * b.hkv, rounds = wgs / slots;
-        const double longest = fixed + std::min(32 << i, b.max_len) / tokens, mean = fixed + (wgs > 0 ? entries * b.hkv / wgs / tokens : 0) + 0.5;
-        const double cost = rounds <= 1 ? longest : std::max(longest, rounds * mean + kTail * longest);
+        const double wgs = (double)busy[i] * b.hkv, rounds = wgs / c.slots;
+        const double longest = c.fixed + std::min(32 << i, b.max_len) / tokens, mean = c.fixed + (wgs > 0 ? entries * b.hkv / wgs / tokens : 0) + c.end;
+        const double cost = rounds <= 1 ? longest : std::max(longest, rounds * mean + c.tail * longest);
         if (i == 3 || cost < best) { best = cost; best_i = i; }
     }
     pairs = busy[best_i];
