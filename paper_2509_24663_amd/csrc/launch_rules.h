@@ -18,11 +18,14 @@ constexpr int64_t kMostInX = 0xffffffffll / 256;
 struct Walks {
     int64_t one = 0, two = 0;
     double half_blocks = 0;
+    double filled = 0;                // part of the tiles of one group that holds tokens
 };
 inline Walks walks(const int32_t *cu_h, int batch, int tokens, bool sparse, int topk, int dense_below) {
     Walks r;
+    int64_t total = 0;
     for (int s = 0; s < batch; ++s) {
         const int n = cu_h[s + 1] - cu_h[s];
+        total += n;
         const int64_t tiles = (n + (int64_t)tokens - 1) / tokens;
         const double far = (n + kKeys / 2.) / kKeys;
         r.one += tiles;
@@ -30,6 +33,7 @@ inline Walks walks(const int32_t *cu_h, int batch, int tokens, bool sparse, int 
         r.half_blocks += tiles * (sparse && n >= dense_below ? std::min(far, 2. * topk) : far);
     }
     if (r.one > 0) r.half_blocks /= r.one;
+    if (r.one > 0) r.filled = (double)total / ((double)r.one * tokens);
     return r;
 }
 
@@ -77,9 +81,18 @@ inline bool fp32_rows_ahead(int d, int64_t workgroups, const Walks &x) {
 // tokens (300) 13.2 / 16.2, 1320 (330) 17.1 / 16.7, 2080 25.2 / 19.7; 28 on 4, 330 tokens (walks of five) 8.3 / 9.5; 8 x 300 (608) 13.6 / 12.4, 40 x 100
 // 13.6 / 13.9.  Backward d 128: 300 tokens (76) 27.7 / 30.3, 600 (150) 44.4 / 43.5, 6000 (1500) 519 / 399; 300 x 4 tokens, 28 heads on 4,
 // 63.4 / 67.3; d 64, 1985 tokens 82 / 66.
+//
+// Where many tiles end with their sequences a second group is often empty, and short walks do not make up for it: attention d 128, 3000 tokens and
+// 300 x 4, 4 blocks, 4 heads on 1 (675) 22.2 / 26.5, 1000 tokens and 300 x 4, 4 on 4 (1328) 27.7 / 33.8, but 3000 + 300 x 4 with every block 79 / 100 of the
+// generic form's time; d 64, 1000 + 200 x 1, 4 on 1 (325) 11.3 / 14.4, on 2 with 4 blocks (650) 11.2 / 13.4, with every block 85 / 100.
+// Backward, d 64, sequences that fill neither group: 4000 / hkv sequences, staged / generic: 1 token on 8 heads of their own 1.15, 4 tokens 1.09, 12 tokens 0.98; 4
+// heads on 1, 1 token 1.11, 3 tokens 0.98, 4 tokens 0.94; 8 heads on 1, 1 token 0.88.
 inline bool staged(bool bwd, int d, int64_t workgroups, const Walks &x) {
     if (workgroups > kMostInX) return false;
-    if (bwd) return workgroups >= 150 && (d == 64 || x.half_blocks >= 2);
+    const bool partial = 9 * x.two > 5 * x.one;
+    if (bwd) return workgroups >= 150 && (d == 64 ? !(partial && x.filled < 0.45) : x.half_blocks >= 2);
+    const double least = d == 128 ? 6 : workgroups <= 450 ? 10 : workgroups <= 1100 ? 6 : 0;
+    if (partial && x.half_blocks < least) return false;
     if (d == 64) return workgroups > 300 && x.half_blocks >= (workgroups > 512 ? 3 : 6);
     return workgroups >= 340 && x.half_blocks >= 3;
 }

@@ -187,3 +187,13 @@ def test_no_more_workgroups_than_a_launch_holds(rules):
     for n, want in ((8388607, 1), (8388608, 0)):
         cu = (ctypes.c_int * (n + 1))(*range(n + 1))
         assert rules.short_waves(cu, n, 1, 2, 0, 16, 0) == want
+
+
+@pytest.mark.parametrize("bwd,d,hq,hkv,lens,topk,want", [
+    (0, 128, 4, 1, [3000] + [4] * 300, 4, 0), (0, 128, 4, 1, [3000] + [4] * 300, 16, 1), (0, 128, 4, 4, [1000] + [4] * 300, 16, 0),
+    (0, 128, 8, 2, [1000] + [1] * 200, 4, 0), (0, 128, 8, 2, [1000] + [1] * 200, 16, 1), (0, 64, 4, 1, [1000] + [1] * 200, 16, 0),
+    (0, 64, 8, 2, [1000] + [1] * 200, 4, 0), (0, 64, 8, 2, [1000] + [1] * 200, 16, 1), (0, 64, 8, 2, [3000] + [1] * 500, 4, 1),
+    (1, 64, 8, 8, [1] * 500, 16, 0), (1, 64, 8, 8, [16] * 500, 16, 1), (1, 64, 8, 2, [1] * 2000, 16, 0), (1, 64, 8, 2, [4] * 2000, 16, 1),
+    (1, 64, 8, 1, [1] * 2000, 16, 1)])
+def test_rows_through_lds_not_for_empty_second_groups(rules, bwd, d, hq, hkv, lens, topk, want):
+    assert rules.staged_form(bwd, d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, topk, 0) == want
