@@ -668,10 +668,7 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     const int64_t gx = std::min<int64_t>(pairs, 1 << 20);
     const dim3 grid((unsigned)gx, (unsigned)((pairs + gx - 1) / gx), hkv);
     if constexpr (sizeof(T) == 2) {
-        // 16 rows per step where many workgroups have hardly more: d 64, 400 x 4 tokens, 8 heads on 2, whole backward 29.1 us, 33.8 with 32;
-        // 300 x 8 tokens 30.5 / 30.2
-        const bool few = D == 64 && L.max_len <= 4 &&
-                         rules::generic_dkv_form(true, D, hkv, a.hq / hkv, cu_h, L.map.batch, a.idx != nullptr, a.topk_total, a.dense_below).row_groups == 1;
+        const bool few = rules::dkv_short_steps(D, a.hq / hkv, L.max_len, nblocks * hkv);
         if (few) hipLaunchKernelGGL((bwd_dkv_kernel<T, 64>), grid, dim3(NW * 64), 0, L.stream, a, shift, one);
         else hipLaunchKernelGGL((bwd_dkv_bf16_kernel<D>), grid, dim3(NW * 64), 0, L.stream, a, shift, one);
     } else {

@@ -114,68 +114,11 @@ inline uint32_t dkv_busy(uint32_t len) {
     const uint32_t q = len >> (5 + K), full = K > 0 ? (q * (q + 1) / 2) << (K > 0 ? K - 1 : 0) : (q + 1) / 2 * (q / 2 + 1);
     return full + (len & ((32u << K) - 1) ? (len + kKeys - 1) / kKeys : 0u);
 }
-// Generic dK/dV: tokens per workgroup, and groups of 16 rows of Q and dO per step.
-struct DkvForm {
-    int chunk, row_groups;
-};
-inline DkvForm generic_dkv_form(bool bf16, int d, int hkv, int G, const int32_t *cu_h, int batch, bool sparse, int topk, int dense_below) {
-    const int step = 16 / G * (bf16 ? 2 : 1);               // tokens
-    int64_t nblocks = 0;
-    int max_len = 0;
-    for (int s = 0; s < batch; ++s) {
-        const int len = cu_h[s + 1] - cu_h[s];
-        nblocks += (len + kKeys - 1) / kKeys;
-        max_len = std::max(max_len, len);
-    }
-    auto busy = [&](int c) {                                // workgroups whose chunk does not end before their block (causal)
-        int64_t n = 0;
-        for (int s = 0; s < batch; ++s) {
-            const int64_t len = cu_h[s + 1] - cu_h[s], nb = (len + kKeys - 1) / kKeys;
-            n += (len + c - 1) / c * (nb + std::max<int64_t>(std::min<int64_t>(c / kKeys, nb), 1)) / 2 * hkv;
-        }
-        return n;
-    };
-    int chunk = 256;
-    if (d == 128 && (!sparse || max_len < dense_below || (max_len + kKeys - 1) / kKeys <= topk)) {
-        // Every block is selected.  As many tokens as leave 256 workgroups with work, not more than a third of the longest sequence
-        // (its last chunk is short) where that is several steps and does not make half as many workgroups again.  Whole backward, bf16, 8 heads on 2, chunks of 256 / 128 / 64 / 32:
-        // 300 tokens 92 / 56 / 38 / 30 us, 1000 tokens 116 / 80 / 70 / 81, 1985 tokens 166 / 173 / 193 / 200, 2500 tokens 224 / 235 / 269 /
-        // 330, 26 x 300 tokens 201 / 186 / 177 / 211, but 20 x 400 (1.7 times the workgroups with 128) 216 / 225 / 204 and 114 x 70 (1.5
-        // times with 64) 107 / 107 / 132.
-        // 512 to 768 workgroups of 256 are a little more than the two rounds of 256 that the chip takes at once: 3000 tokens (612)
-        // 1.07 / 1 / 1.16 / 1.41, 4000 tokens (1072) 1.02 / 1.06 / 1 / 1.22 of the best.  Steps of less than 8 tokens make twice the
-        // steps of a chunk: 16 heads on 2, 2300 tokens 348 / 339 / 321 / 358, fp32, 8 heads on 2, 2300 tokens 1.06 / 1.06 / 1 / 1.10.
-        const int most = std::max(max_len / 3, 8 * step);
-        auto few_more = [&] {                               // halving: less than half as many workgroups again
-            int64_t now = 0, then = 0;
-            for (int s = 0; s < batch; ++s) {
-                const uint32_t len = (uint32_t)(cu_h[s + 1] - cu_h[s]);
-                now += chunk == 256 ? dkv_busy<3>(len) : dkv_busy<2>(len);
-                then += chunk == 256 ? dkv_busy<2>(len) : dkv_busy<1>(len);
-            }
-            return 20 * then < 29 * now;
-        };
-        while (chunk > 64 && (busy(chunk) < 256 || (chunk > most && few_more()))) chunk /= 2;
-        if (chunk == 256 && step <= 8 && busy(chunk) <= 768) {
-            if (busy(chunk) > 512) chunk = 128;
-            else if (step < 8) chunk = 64;
-        }
-    } else {
-        // Lists that leave blocks out, whose workgroups differ more, and the smaller workgroups of d 64 are better shorter: 1985 bf16
-        // tokens with 16 blocks each 167 us with 256 tokens, 160 with 64; d 64, 1400 fp32 tokens 221 / 176 / 154 / 165.
-        while (chunk > 64 && nblocks * ((max_len + chunk - 1) / chunk) * hkv < 2048) chunk /= 2;
-    }
-    // Below 256 workgroups chunks of 32; where those are one or two steps (groups of one or two heads), below 160.  64 / 32: 8 heads on
-    // 2, bf16: 300 tokens 38 / 30 us, 6 x 300 tokens (180 workgroups) 1.05 / 1; fp32, 900 tokens (240) 1.21 / 1; 4 heads on 4, bf16:
-    // 150 tokens 25 / 23 us, 600 tokens (220) 38 / 45, 40 x 100 tokens, d 64 (240) 29 / 32; fp32: 300 tokens (60) 1.04 / 1, 600
-    // tokens (220) 1 / 1.06.
-    if (chunk == 64 && busy(chunk) < (step >= 16 ? 160 : 256)) chunk = 32;
-    // Two groups of 16 rows in one contraction halve the products of bf16 rows, but at d 64 they cost a wavefront per SIMD, which many
-    // workgroups with few steps each feel more.  Whole backward, 8 heads on 2, d 64, two groups / one: 500 x 4 tokens 38.9 / 33.6 us,
-    // 26 x 300 107 / 97, 114 x 70 99 / 89; 4 x 700 (528 workgroups) 75 / 78, 16 heads on 2 112 / 122; 1300 tokens 8 heads on 1 62 / 68.
-    const bool one = !bf16 || (d == 64 && std::min(chunk, max_len) <= 64 && busy(chunk) > 600);
-    return {chunk, one ? 1 : 2};
-}
+// Generic dK/dV, bf16, d 64: 16 rows of Q and dO per step instead of 32 (bwd_dkv_kernel), whose workgroups are the smaller ones: where sequences have
+// hardly more rows and there are many of them.  blocks: KV blocks of the batch times KV heads.  Whole backward, 32 / 16 rows, blocks of about 700 / 1500 / 4000:
+// 4 heads on 1, 4 tokens 27.9 / 27.3, 54.9 / 51.4, 223 / 199 us, 12 tokens 41.8 / 41.6, 93.9 / 91.4, 371 / 348; 8 on 8, 8 tokens 20.2 / 19.6, 32.8 / 31.5,
+// 89 / 81, 20 tokens 25.0 / 25.3, 44.4 / 46.6, 112 / 111; 16 on 1, 2 tokens 29.2 / 30.0, 61.3 / 61.8, 242 / 226.
+inline bool dkv_short_steps(int d, int G, int max_len, int64_t blocks) { return d == 64 && max_len <= std::max(4, 16 / G) && blocks > 600; }
 
 // Attention of short prompts (attn_short.hip; bf16, G = 16, d 128): wavefronts per token, or 0 where the tile kernel is faster.
 //

@@ -31,8 +31,8 @@ def test_chunks_of_64_tokens_and_more(m, oracle, dtype, hq, hkv, lens):  # noqa:
         _check_backward(m, oracle, w, gp, op, dtype)
 
 
-@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 2, 64), (3, 1, 128), (16, 1, 64)])
-@pytest.mark.parametrize("lens", [[4] * 400, [2, 3, 1, 5] * 40, [9] * 30, [333]])
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 2, 64), (3, 1, 128), (16, 1, 64), (8, 8, 64), (6, 3, 64)])
+@pytest.mark.parametrize("lens", [[4] * 400, [2, 3, 1, 5] * 40, [9] * 30, [333], [16, 1, 15, 9] * 30, [8, 7] * 120])
 def test_the_same_values_as_fp32(m, hq, hkv, d, lens):  # noqa: F811
     """The fp32 kernels fed the bf16 call's inputs, outputs and Delta: dK and dV differ by fp32 roundings of sums over up to 333 x G rows."""
     w = synth.make_varlen(lens, hq, hkv, d, seed=7200 + len(lens) + hq, dtype="bf16")

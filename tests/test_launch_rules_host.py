@@ -29,11 +29,7 @@ extern "C" int staged_form(int bwd, int d, int hkv, int tokens, const int *cu, i
 extern "C" int short_waves(const int *cu, int batch, int max_len, int hkv, int sparse, int topk, int below) {
     return short_attn_waves(cu, batch, max_len, hkv, sparse, topk, below);
 }
-extern "C" void generic_dkv(int bf16, int d, int hkv, int G, const int *cu, int batch, int sparse, int topk, int below, int *r) {
-    const DkvForm f = generic_dkv_form(bf16, d, hkv, G, cu, batch, sparse, topk, below);
-    r[0] = f.chunk;
-    r[1] = f.row_groups;
-}
+extern "C" int short_steps(int d, int G, int max_len, long long blocks) { return dkv_short_steps(d, G, max_len, blocks); }
 extern "C" int tile(const int *cu, int batch, int max_len, int hkv, int sparse, int topk, int below, int bwd) {
     return attn_tile_tokens(cu, batch, max_len, hkv, sparse, topk, below, bwd);
 }
@@ -86,32 +82,10 @@ def test_many_short_sequences_take_one_column_group(rules):
     assert _generic(rules, 1, 128, 8, 2, []) == (1, 1, 1, 1)
 
 
-def _dkv(rules, bf16, d, hq, hkv, lens, topk=16, sparse=1, below=0):
-    r = (ctypes.c_int * 2)()
-    rules.generic_dkv(bf16, d, hkv, hq // hkv, _cu(lens), len(lens), sparse, topk, below, r)
-    return tuple(r)
-
-
-@pytest.mark.parametrize("lens", [[300], [1000], [1985], [2500], [4000], [300] * 26, [700] * 4])
-@pytest.mark.parametrize("bf16,hq,hkv", [(1, 8, 2), (0, 8, 2), (1, 16, 2), (1, 4, 4)])
-def test_dkv_chunks_do_not_depend_on_why_every_block_is_selected(rules, lens, bf16, hq, hkv):
-    want = _dkv(rules, bf16, 128, hq, hkv, lens, topk=64)             # lists with room for every block
-    assert _dkv(rules, bf16, 128, hq, hkv, lens, topk=16, sparse=0) == want
-    assert _dkv(rules, bf16, 128, hq, hkv, lens, topk=16, below=max(lens) + 1) == want
-
-
-def test_dkv_chunks(rules):
-    assert _dkv(rules, 1, 128, 8, 2, [1985], sparse=0) == (256, 2)
-    assert _dkv(rules, 1, 128, 8, 2, [1985]) == (64, 2)
-    assert _dkv(rules, 1, 128, 4, 4, [600], topk=64) == (64, 2)       # 32 tokens per step: a chunk of 32 is one step
-    for lens in ([300] * 26, [333] * 12):                             # chunks no longer than a third of the sequences
-        assert _dkv(rules, 1, 128, 8, 2, lens, topk=64)[0] <= 128
-    # ... unless that only cuts off ends: a chunk and a few tokens stay one
-    assert _dkv(rules, 0, 128, 8, 2, [70] * 114, topk=64)[0] >= 128 and _dkv(rules, 1, 128, 28, 4, [400] * 20, topk=64)[0] == 256
-    for lens in ([4] * 500, [300] * 26, [70] * 114):                  # many workgroups with few steps each
-        assert _dkv(rules, 1, 64, 8, 2, lens)[1] == 1
-    assert _dkv(rules, 1, 64, 8, 2, [700] * 4)[1] == 2 and _dkv(rules, 1, 128, 8, 2, [4] * 500)[1] == 2
-    assert _dkv(rules, 1, 128, 8, 2, [])[0] >= 32
+@pytest.mark.parametrize("d,G,max_len,blocks,want", [(64, 4, 4, 601, 1), (64, 4, 4, 600, 0), (64, 4, 5, 4000, 0), (64, 1, 16, 700, 1), (64, 1, 17, 4000, 0),
+                                                     (64, 2, 8, 700, 1), (64, 16, 4, 700, 1), (128, 1, 1, 4000, 0)])
+def test_dkv_in_steps_of_16_rows(rules, d, G, max_len, blocks, want):
+    assert rules.short_steps(d, G, max_len, ctypes.c_longlong(blocks)) == want
 
 
 def _chunk(rules, lens, hkv=2, sparse=0, topk=16, below=0, most=0xffffffff // 64):
