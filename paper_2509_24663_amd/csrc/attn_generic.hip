@@ -264,7 +264,7 @@ int launch_t(const Launch &L, const void *q, const void *k, const void *v, const
         if (form.groups == 2)
             return form.ahead ? launch_cg<T, D, 2, true>(L, q, k, v, idx, dense_below, out, lse)
                               : launch_cg<T, D, 2, false>(L, q, k, v, idx, dense_below, out, lse);
-    const bool ahead = sizeof(T) == 2 ? form.ahead : rules::fp32_rows_ahead(D, x.one * hkv, x);
+    const bool ahead = sizeof(T) == 2 ? form.ahead : rules::fp32_rows_ahead(D, hkv, x.one * hkv, x);
     return ahead ? launch_cg<T, D, 1, true>(L, q, k, v, idx, dense_below, out, lse)
                  : launch_cg<T, D, 1, false>(L, q, k, v, idx, dense_below, out, lse);
 }

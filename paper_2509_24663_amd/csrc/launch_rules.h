@@ -63,15 +63,23 @@ inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
         return {2, rows_ahead(x.two * hkv, d == 128 ? 512 : 1024, x)};
     return {1, rows_ahead(x.one * hkv, 1024, x)};
 }
-// fp32 attention is bound by its products: rows requested ahead are worth their registers only where a CU has no other
-// workgroup's wavefronts to fill the waits with.  d 64 keeps two workgroups per CU with them and three without, d 128 one and two.
-// Attention alone, ahead / not: d 64, 4 heads on 1, topk 8 (all in one order of workgroups): 1000 tokens (250 workgroups) 17.5 / 17.9 us, 2048 (512) 31.6 / 28.5,
-// 4096 (1024) 97 / 90; 8 on 2: 1000 (500) 28.0 / 25.4, 3300 (1650) 55.3 / 44.8; walks of fewer than six half blocks are over before a
-// second request would arrive.  d 128, 8 on 2: 600 tokens (300) 20.6 / 26.0, 1000 (500) 36.7 / 47.7, 2048 (1024) 103 / 92.  Over 228
-// batches the rule is within 0.2 % of the faster form in the mean, where rows_ahead lost 2.0 (d 128) and 2.9 % (d 64).
-inline bool fp32_rows_ahead(int d, int64_t workgroups, const Walks &x) {
-    if (d == 64) return workgroups <= 256 && x.half_blocks >= 6;
-    return x.half_blocks >= 4 && workgroups <= std::min(512., 64 * x.half_blocks);
+// fp32 attention is bound by its products: rows requested ahead are worth their registers only where a CU has no other workgroup's wavefronts to fill the
+// waits with.  The chip holds, ahead / not, 512 / 768 workgroups at d 64 and 256 / 512 at d 128.  Walks of fewer than six (d 128: four) half blocks are over
+// before a second request would arrive.  Attention alone, ahead / not, by workgroups:
+// d 64: one a CU and a few: 4 heads on 1, 1000 tokens (250) 17.5 / 17.9 us, 1050 (263) 18.5 / 19.7, 1450 (363) 24.6 / 25.2, 2048 (512) 31.6 / 28.5, 8 on 2, 1000 (500)
+// 28.0 / 25.4.
+// d 128: one or two KV heads, 4 heads on 1, 1600 tokens (400) 55 / 60, 1255 + 347 (401) 35 / 45, 1800 (450) 61.3 / 61.5, 3500 tokens on 2 of their own (438)
+// 91 / 107; 8 on 2, 800 (400) 27 / 28, 1000 (500) 36.7 / 34.5; just over 512 without is a second, nearly empty round: 1000 + 50 tokens (526) 39.4 / 49.8, 1100 (550) 45.7 / 52.9, 1200 (600) 47 / 49, 1300
+// (650) 57 / 54.  More heads come one after the other beyond 512 and their longest tiles late, all the later in long rounds: 16 on 4, 900 tokens (900) 62 / 69, 1000
+// (1000) 71 / 78, 4 on 4, 4000 (1000) 221 / 262; within one round without they share the CUs evenly: 8 on 8, 1000 (504) 58 / 35, 4 on 4, 1200 (300) 36 / 38,
+// 1600 (400) 66 / 52.
+// Over 1566 calls the rule is from the faster form in the mean 0.3 % (d 64) and 0.5 % (d 128), rows_ahead 5 % each.
+inline bool fp32_rows_ahead(int d, int hkv, int64_t workgroups, const Walks &x) {
+    const double hb = x.half_blocks;
+    if (d == 64) return hb >= 6 && workgroups <= (hb >= 12 ? 300 : 256);
+    if (hb < 4) return false;
+    if (hkv > 2) return workgroups <= std::min(300., 40 * hb) || (hb >= 12 && workgroups > 600 && workgroups <= 1024);
+    return workgroups <= std::min(512., 64 * hb) || (hb >= 12 && workgroups <= 600);
 }
 // bf16 attention and dQ with tiles of two groups whose V (dQ: K) rows pass through LDS (attn_staged.hip): a step is shorter, but a
 // workgroup takes 3 us longer to start and to end, so not where few of them leave the chip idle and each has few steps.  Calls by

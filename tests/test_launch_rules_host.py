@@ -20,7 +20,7 @@ extern "C" void generic(int bf16, int d, int hkv, int tokens, const int *cu, int
 }
 extern "C" int fp32_ahead(int d, int hkv, int tokens, const int *cu, int batch, int sparse, int topk, int below) {
     const Walks x = walks(cu, batch, tokens, sparse, topk, below);
-    return fp32_rows_ahead(d, x.one * hkv, x);
+    return fp32_rows_ahead(d, hkv, x.one * hkv, x);
 }
 extern "C" int staged_form(int bwd, int d, int hkv, int tokens, const int *cu, int batch, int sparse, int topk, int below) {
     const Walks x = walks(cu, batch, tokens, sparse, topk, below);
@@ -133,8 +133,10 @@ def test_attention_tiles(rules):
 
 
 @pytest.mark.parametrize("d,hq,hkv,lens,topk,ahead", [
-    (64, 4, 1, [1000], 8, 1), (64, 4, 1, [1024], 16, 1), (64, 4, 1, [1025], 16, 0), (64, 8, 2, [1000], 8, 0), (64, 4, 1, [300], 8, 0),
-    (128, 8, 2, [1000], 8, 1), (128, 8, 2, [1024], 8, 1), (128, 8, 2, [1025], 8, 0), (128, 4, 1, [150], 8, 0), (128, 4, 1, [], 8, 0)])
+    (64, 4, 1, [1000], 8, 1), (64, 4, 1, [1200], 16, 1), (64, 4, 1, [1201], 16, 0), (64, 4, 1, [1025], 4, 0), (64, 8, 2, [1000], 8, 0),
+    (64, 4, 1, [300], 8, 0), (128, 8, 2, [1000], 8, 1), (128, 8, 2, [1024], 8, 1), (128, 8, 2, [1025], 8, 1), (128, 8, 2, [1000, 50], 16, 1),
+    (128, 8, 2, [1300], 8, 0), (128, 4, 1, [1985], 16, 1), (128, 4, 1, [2100], 4, 0), (128, 4, 1, [1255, 347], 16, 1), (128, 4, 4, [4000], 16, 1), (128, 4, 4, [1600], 16, 0), (128, 8, 8, [1000], 16, 0),
+    (128, 16, 4, [1000], 16, 1), (128, 16, 4, [1000], 4, 0), (128, 4, 1, [150], 8, 0), (128, 4, 1, [], 8, 0)])
 def test_fp32_rows_ahead_only_where_a_cu_has_one_workgroup_to_run(rules, d, hq, hkv, lens, topk, ahead):
     assert rules.fp32_ahead(d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, topk, 0) == ahead
 
