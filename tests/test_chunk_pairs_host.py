@@ -77,7 +77,8 @@ def test_chunks(lib):
 
 @pytest.mark.parametrize("bf16,d,G,hkv,lens,topk,want", [
     (0, 128, 1, 4, [1000], 16, 128), (0, 128, 1, 4, [1000, 50], 16, 128), (0, 128, 4, 1, [1600], 16, 64), (0, 128, 1, 4, [1600], 64, 256),
-    (1, 128, 4, 2, [1000], 4, 64), (1, 128, 4, 2, [1000, 50], 4, 64), (1, 128, 4, 1, [1000, 1000], 4, 64), (1, 64, 4, 2, [1985], 16, 128)])
+    (1, 128, 4, 2, [1000], 4, 64), (1, 128, 4, 2, [1000, 50], 4, 64), (1, 128, 4, 1, [1000, 1000], 4, 64), (1, 64, 4, 2, [1985], 16, 128),
+    (1, 64, 2, 3, [800], 64, 64), (1, 64, 2, 3, [800], 4, 64), (1, 64, 8, 1, [265, 1167, 2164], 16, 64), (1, 128, 14, 1, [1094, 1374, 285, 401], 16, 64), (1, 128, 1, 4, [1985], 16, 256)])
 def test_chunks_of_small_groups_and_budgets(lib, bf16, d, G, hkv, lens, topk, want):
     """Whole backward with the chunk of this rule / with half or twice of it, the rule before: fp32, d 128, 4 heads on 4, 1000 tokens 105 / 118 us, 1600
     193 / 205; 4 heads on 1, 1600 tokens 167 / 179; bf16, d 128, 8 heads on 2, 4 blocks, 1000 tokens 48 / 63."""
