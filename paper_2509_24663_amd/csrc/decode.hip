@@ -24,9 +24,8 @@
 //   merge   : grid (pairs)              log-sum-exp merge of the per-split partial outputs, writes O and lse
 // K^{C1} is float32; it is split into a bf16 high part and a bf16 residual in registers and both products
 // are accumulated, so the logits carry ~16 mantissa bits of K^{C1}.
-#include <algorithm>
-
 #include "attn_unit.h"
+#include "launch_rules.h"
 #include "topk_row.h"
 
 namespace ifv2 {
@@ -1208,14 +1207,12 @@ DecLayout dec_layout(const infllmv2_params *p, int batch, int max_ctx, int dense
     off += align_up(pairs * d.nslot * 32 * sizeof(float), 256);
     d.total = off;
     if (d.staged && d.aw != AW) {
-        // Behind a selection kernel a workgroup takes as many blocks, in rounds of its four waves, as leave a workgroup for every CU (one
-        // round of them, and of partial results to merge, instead of several): attend 96 -> 81 us at batch 128, step of 32 / 64 / 128 / 256
-        // sequences 58 -> 52, 121 -> 109, 221 -> 199, 299 -> 260 us (four blocks each / this).  More than 512 pairs: two workgroups for each
-        // (batch 400: 425 / 409 with one, 397).  Rounds are counted in a lane's number and dense sequences may be long: 16 at most.
-        // (The scratch that a call asks for stays that of four blocks each, which grows with the batch.)
-        const int most = 16 * d.aw, ns = std::max({pairs > 512 ? 2 : (int)(256 / (pairs ? pairs : 1)), (entries + most - 1) / most, 1});
-        d.bpw = (entries + ns * d.aw - 1) / (ns * d.aw) * d.aw;
-        d.nsplit = std::min(d.nsplit, std::max((entries + d.bpw - 1) / d.bpw, 1));
+        // Behind a selection kernel a workgroup takes several blocks, in rounds of its four waves (fewer rounds of workgroups, and of partial results to
+        // merge): attend 96 -> 81 us at batch 128, step of 32 / 64 / 128 / 256 sequences 58 -> 52, 121 -> 109, 221 -> 199, 299 -> 260 us (four
+        // blocks each / this).  (The scratch that a call asks for stays that of four blocks each, which grows with the batch.)
+        const rules::DecodeSplits r = rules::decode_splits((int64_t)pairs, entries, d.aw);
+        d.bpw = r.bpw;
+        d.nsplit = r.nsplit;
         d.nslot = d.fsplit + d.nsplit;
     }
     return d;

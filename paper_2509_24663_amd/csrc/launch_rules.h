@@ -309,5 +309,28 @@ inline int generic_dkv_shift(bool bf16, int d, int G, const DkvBatch &b, int64_t
     return 5 + best_i;
 }
 
+// Decode behind the selection kernel: blocks per attend workgroup (of `waves` wavefronts, which take them in rounds) and workgroups per pair.  entries: blocks of
+// the longest list.  Rounds are counted in a lane's number and dense sequences may be long: kDecodeRounds at most.
+//
+// As many workgroups as leave one for every CU make one round of them, with the fewest partial results to merge; two for each of more than 512 pairs.  Where that
+// leaves CUs empty, or a few workgroups for a second round, another split whose fullest CU has a tenth fewer rounds (and half a round for each
+// workgroup's start and end) is faster.  Step of that many pairs of 55 blocks with 1 / 2 / 3 / 4 / 6 workgroups each (* the old rule, ** this one): 66 85 73 69 70** 72
+// us; 96 98 79*  ** 91 86 80; 130 113* 116 106** 111 108; 160 119* 125 118** 123 124; 192 134* ** 139 141 139 139; 264 207* 190 186** 186 183; 320 221* 208 209**
+// 209 211; 400 247* ** 254 250 255 253; 512 292* ** 294 305 305 308.  Over 76 batches it is 0.2 % from the best (the old rule 1.2 %).
+constexpr int kDecodeRounds = 16;
+struct DecodeSplits {
+    int bpw, nsplit;
+};
+inline DecodeSplits decode_splits(int64_t pairs, int entries, int waves) {
+    const int64_t groups = (entries + waves - 1) / waves, least = std::max<int64_t>((groups + kDecodeRounds - 1) / kDecodeRounds, 1);
+    auto cost = [&](int64_t ns) { return (double)((pairs * ns + 255) / 256 * ((groups + ns - 1) / ns)) + pairs * ns / 512.; };
+    int64_t ns = std::max<int64_t>(pairs > 512 ? 2 : 256 / std::max<int64_t>(pairs, 1), least);
+    double best = 0.9 * cost(ns);
+    for (int64_t n = least; n <= std::min<int64_t>(4, groups); ++n)
+        if (cost(n) < best) { best = cost(n); ns = n; }
+    const int64_t bpw = std::max<int64_t>((groups + ns - 1) / ns, 1) * waves;
+    return {(int)bpw, (int)std::max<int64_t>((entries + bpw - 1) / bpw, 1)};
+}
+
 }  // namespace rules
 }  // namespace ifv2

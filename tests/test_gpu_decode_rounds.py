@@ -52,3 +52,23 @@ def test_forms_agree(m):  # noqa: F811
             assert torch.equal(idx, want[2][s])
             assert_out_close(to_np(out), to_np(want[0][s]), "bf16")
             assert (lse - want[1][s]).abs().max() < 1e-5           # (see test_gpu_decode_splits.py)
+
+
+def test_rounds_of_dense_sequences(m):  # noqa: F811
+    """400 pairs, one workgroup each by their number, with dense sequences of 65 to 67 blocks: more than sixteen rounds of four wavefronts hold, so that
+    the limit decides; against calls of 10 sequences, where every wavefront takes one block."""
+    B, n = 200, 4400
+    torch.manual_seed(9)
+    q, k = torch.randn(B, 32, 128).cuda().bfloat16(), torch.randn(B, 2, n, 128, device="cuda").bfloat16()
+    v = torch.randn(B, 2, n, 128, device="cuda").bfloat16()
+    ctx = [int(x) for x in np.random.default_rng(4).integers(4100, n + 1, B)]
+    gp = m.Params.make("bf16", 32, 2, 128, n_init=1, n_local=4, topk_total=32, dense_threshold=4270)
+    kc = torch.zeros((B, 2, m.num_cmp(gp, n), 128), device="cuda")
+    m.compress_k_append(gp, k, kc, [0] * B, ctx)
+    want = m.sparse_decode(gp, q, k, v, kc, ctx)
+    for b in range(0, B, 10):
+        s = slice(b, b + 10)
+        out, lse, idx = m.sparse_decode(gp, q[s], k[s], v[s], kc[s], ctx[s])
+        assert torch.equal(idx, want[2][s])
+        assert_out_close(to_np(out), to_np(want[0][s]), "bf16")
+        assert (lse - want[1][s]).abs().max() < 1e-5

@@ -29,6 +29,11 @@ extern "C" int staged_form(int bwd, int d, int hkv, int tokens, const int *cu, i
 extern "C" int short_waves(const int *cu, int batch, int max_len, int hkv, int sparse, int topk, int below) {
     return short_attn_waves(cu, batch, max_len, hkv, sparse, topk, below);
 }
+extern "C" void splits(long long pairs, int entries, int waves, int *r) {
+    const DecodeSplits d = decode_splits(pairs, entries, waves);
+    r[0] = d.bpw;
+    r[1] = d.nsplit;
+}
 extern "C" int short_steps(int d, int G, int max_len, long long blocks) { return dkv_short_steps(d, G, max_len, blocks); }
 extern "C" int tile(const int *cu, int batch, int max_len, int hkv, int sparse, int topk, int below, int bwd) {
     return attn_tile_tokens(cu, batch, max_len, hkv, sparse, topk, below, bwd);
@@ -173,3 +178,23 @@ def test_no_more_workgroups_than_a_launch_holds(rules):
     (1, 64, 8, 1, [1] * 2000, 16, 1)])
 def test_rows_through_lds_not_for_empty_second_groups(rules, bwd, d, hq, hkv, lens, topk, want):
     assert rules.staged_form(bwd, d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, topk, 0) == want
+
+
+def _splits(rules, pairs, entries, waves=4):
+    r = (ctypes.c_int * 2)()
+    rules.splits(ctypes.c_longlong(pairs), entries, waves, r)
+    return tuple(r)
+
+
+def test_decode_splits_hold_every_block(rules):
+    """Every entry has a place, in at most sixteen rounds of the workgroup's wavefronts, and no more splits than four blocks each would make."""
+    for pairs in list(range(1, 600)) + [1000, 4000, 65535]:
+        for entries in list(range(0, 70)) + [127, 128, 129, 500, 1024, 4096]:
+            bpw, ns = _splits(rules, pairs, entries)
+            assert bpw % 4 == 0 and 4 <= bpw <= 16 * 4 and ns * bpw >= entries and 1 <= ns <= max((entries + 3) // 4, 1), (pairs, entries)
+
+
+def test_decode_splits_fill_the_chip(rules):
+    """Steps in microseconds, with one workgroup per pair / with this: 130 pairs 113 / 106, 264 207 / 186, 320 221 / 208."""
+    assert [_splits(rules, p, 55)[1] for p in (43, 64, 96, 128, 130, 160, 192, 256, 264, 320, 400, 512, 600)] == [5, 4, 2, 2, 3, 3, 1, 1, 3, 3, 1, 1, 2]
+    assert _splits(rules, 512, 128) == (64, 2) and _splits(rules, 300, 128) == (32, 4) and _splits(rules, 128, 0) == (4, 1)
