@@ -159,6 +159,7 @@ __global__ void __launch_bounds__(T * SH * 64) attn_short_kernel(ShortArgs a, in
     }
     const uint32_t rx = bwd_row_bytes(lane), tx = bwd_trans_bytes(lane) + kTileBytes;
     const int ni = (ne + SH - 1) / SH;
+    bool took = false;                                               // this wave has had a block
     for (int i = 0; i < ni; ++i) {
         __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);                     // this wave's copies of interval i have landed
         __syncthreads();                                             // everybody's have, and interval i - 1 has been consumed
@@ -181,6 +182,7 @@ __global__ void __launch_bounds__(T * SH * 64) attn_short_kernel(ShortArgs a, in
             continue;
         }
         const uint32_t at = lds0 + (uint32_t)((i & 1) * SH + share) * kStageBytes;
+        took = true;
         uint32_t kx = rx, vx = tx;
         asm volatile("" : "+v"(kx), "+v"(vx));        // (operand addresses are formed here, not kept over the loop)
         if (j == bt) unit<true, true>(st, at, kx, vx, lane, t0 + ti - j * kBlock, issue_now);
@@ -189,6 +191,8 @@ __global__ void __launch_bounds__(T * SH * 64) attn_short_kernel(ShortArgs a, in
     __syncthreads();
 
     // ---- merge the shares of a token (the stages are free now), normalise and store
+    // (a share whose blocks had no logit but minus infinity counts for nothing beside another's, so its sum is told apart from that of a share without
+    // blocks by its sign: with weight 0 it adds nothing, and a token that has nothing else is NaN, like any mean over such logits)
     float *part = reinterpret_cast<float *>(smem);
     const float ref = st.slack > 0.f ? -st.nr : -INFINITY;
     if (share > 0) {
@@ -196,7 +200,7 @@ __global__ void __launch_bounds__(T * SH * 64) attn_short_kernel(ShortArgs a, in
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f32x4 *>(p + (dt * 64 + lane) * 4) = st.o[dt];
         p[64 * 32 + lane] = ref;
-        p[64 * 33 + lane] = st.l;
+        p[64 * 33 + lane] = took && st.l == 0.f ? -1.f : st.l;
     }
     __syncthreads();
     if (share > 0 || ti >= ntok) return;
@@ -215,13 +219,16 @@ __global__ void __launch_bounds__(T * SH * 64) attn_short_kernel(ShortArgs a, in
     for (int s = 1; s < SH; ++s) {
         const float *p = part + ((s - 1) * T + ti) * kPart;
         wt = fast_exp2(refs[s] - base);
-        l += p[64 * 33 + lane] * wt;
+        const float ls = p[64 * 33 + lane];
+        took = took || ls != 0.f;
+        l += (ls < 0.f ? 0.f : ls) * wt;
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) st.o[dt] += *reinterpret_cast<const f32x4 *>(p + (dt * 64 + lane) * 4) * wt;
     }
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    const bool none = !(l > 0.f);
+    const float inv = !none ? 1.0f / l : took ? NAN : 0.f;
     int lane_end = lane;
     asm volatile("" : "+v"(lane_end));           // the address is formed here, not kept in registers over the loop
     uint16_t *op = a.out + ((int64_t)(row0 + ti) * a.hq + h * G + (lane_end & 15)) * D + (lane_end >> 4) * 4;
@@ -229,7 +236,7 @@ __global__ void __launch_bounds__(T * SH * 64) attn_short_kernel(ShortArgs a, in
     for (int dt = 0; dt < 8; ++dt)
         *reinterpret_cast<uint2 *>(op + dt * 16) = make_uint2(pack_bf16(st.o[dt][0] * inv, st.o[dt][1] * inv), pack_bf16(st.o[dt][2] * inv, st.o[dt][3] * inv));
     if (a.lse != nullptr && g == 0)
-        a.lse[(int64_t)(h * G + m16) * a.map.total_rows + row0 + ti] = (__log2f(l) + base) * 0.6931471805599453f;
+        a.lse[(int64_t)(h * G + m16) * a.map.total_rows + row0 + ti] = none && took ? NAN : (__log2f(l) + base) * 0.6931471805599453f;
 }
 
 template <int SH>

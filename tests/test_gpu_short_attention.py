@@ -87,3 +87,24 @@ def test_rows_that_are_not_finite(m, n):  # noqa: F811
     z = (q[n - 1, :16].float() @ keep[0][0].t().contiguous()) * 128 ** -0.5
     assert (torch.softmax(z, 1) @ keep[1][0] - out[n - 1, :16].float()).abs().max() <= 2e-2      # the forward bar
     assert (torch.logsumexp(z, 1) - lse2[:16, n - 1]).abs().max() <= 2e-3
+
+
+@pytest.mark.parametrize("hkv,n", [(1, 40), (2, 130), (4, 300), (2, 777), (2, 1500)])
+def test_logits_that_are_all_minus_infinity(m, hkv, n):  # noqa: F811
+    """A token that sees nothing but logits of minus infinity has no mean, NaN; one whose list is empty has nothing, 0 and minus infinity.
+    (One and two wavefronts per token, and the tile kernel.)"""
+    torch.manual_seed(n)
+    q, v = torch.randn(n, 16 * hkv, 128).abs().cuda().bfloat16(), torch.randn(hkv, n, 128).cuda().bfloat16()
+    k = torch.randn(hkv, n, 128).cuda().bfloat16()
+    gp = m.Params.make("bf16", 16 * hkv, hkv, 128, n_init=0, n_local=1, topk_total=2)
+    k[:, :min(n, 64)] = float("-inf")
+    idx = torch.full((hkv, n, 2), -1, dtype=torch.int32, device="cuda")
+    idx[:, :, 0] = 0                                              # block 0 alone: minus infinity throughout
+    idx[:, n // 2:, 0] = -1                                       # nothing
+    out, lse = m.sparse_attn_fwd(gp, q, k, v, idx, [0, n])
+    assert out[:n // 2].isnan().all() and lse[:, :n // 2].isnan().all()
+    assert (out[n // 2:] == 0).all() and (lse[:, n // 2:] == float("-inf")).all()
+    out, lse = m.dense_attn_fwd(gp, q, k, v, [0, n])
+    assert out[:min(n, 64)].isnan().all() and lse[:, :min(n, 64)].isnan().all()
+    if n <= 777:                                                  # (the tile kernel's tokens meet block 0 first and keep its NaN)
+        assert out[64:].isfinite().all() and lse[:, 64:].isfinite().all()
