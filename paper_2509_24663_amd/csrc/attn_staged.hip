@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(NW * 64, D == 128 ? 2 : 3) attn_staged_kernel(
     const int32_t *lists = dense ? nullptr : a.idx + head_row(a.map, h, t.row0) * a.topk_total;
     const int nblk = (t.t0 + t.ntok - 1) / kBlock + 1;
     const int64_t head_off = t.kv_base + (int64_t)h * a.map.kv_head_stride, stride = a.map.kv_tok_stride * 2;
-    const float c = a.scale * kLog2e, slack = c > 0.f ? fminf(8.f / c, 1e30f) : 0.f;
+    const float c = a.scale * kLog2e, lag = c > 0.f ? fminf(8.f / c, 1e30f) : 0.f;
 
     const int m = lane & 15, g = lane >> 4;
     int ti[CG];
@@ -169,10 +169,12 @@ __global__ void __launch_bounds__(NW * 64, D == 128 ? 2 : 3) attn_staged_kernel(
     float ref[CG], l_run[CG];                            // a column's largest logit when last moved, sum relative to it
     f32x4 acc[CG][N];                                    // O^T or dQ^T: dim 16 i + 4 g + r, this lane's column
     // One pass serves all tokens of the tile; a result that is not finite is computed again token by token (solo >= 0) with
-    // the rows that the token does not see taken as 0 (0 x infinity).
+    // the rows that the token does not see taken as 0 (0 x infinity), and with references that do not lag: sums of V of more than 1.3e36 overflow
+    // with weights of 2^8 where they do not with weights of 1.
     uint32_t all = t.ntok == 32 ? ~0u : (1u << t.ntok) - 1u;
     auto pass = [&](auto solo_pass, int solo) {
         constexpr bool SOLO = decltype(solo_pass)::value;
+        const float slack = SOLO ? 0.f : lag;
 #pragma unroll
         for (int x = 0; x < CG; ++x) {
             ref[x] = -INFINITY;
