@@ -62,7 +62,8 @@ __device__ inline void load_piece(const uint16_t *base, int64_t tok_stride, int 
 struct TokState {
     bf16x8 qf[4];      // Q_t as MFMA B operand: head = lane % 16, dims ks*32 + (lane/16)*8 .. +8
     f32x4 o[8];        // O_t^T: dim tile dt, dims dt*16 + 4*(lane/16) + r, head = lane % 16
-    float m, l;        // running max (raw logits) and this lane's share of the running sum
+    float m, l;        // reference (raw logits) and this lane's share of the running sum
+    float top;         // largest logit so far, where the reference may lie above it
 };
 
 struct LaneOffs {
@@ -120,7 +121,8 @@ constexpr float kMaxSlack = 8.0f;
 // ---- online softmax over the 64 logits of a block and O^T += V_blk^T P^T (V block in a swizzled LDS tile)
 // OWN_REF: the reference lies a whole number of powers of two above the block's largest logit, so that the weights are rounded to bf16
 // as if it were that logit (the largest weight, a power of two, not at all): a block's result is the same, up to fp32 sums, after
-// other blocks as alone.  (With a reference that only keeps within the slack the output of a decode step over 55 blocks is 2.3e-3 from
+// other blocks as alone.  It stands less than one binary order above the largest logit so far (top): counted from the reference before it would follow
+// blocks of falling logits down by up to half an order each, and sums of large V overflow.  (With a reference that only keeps within the slack the output of a decode step over 55 blocks is 2.3e-3 from
 // 64 bits instead of 2.0e-3.)
 template <bool OWN_REF = false>
 __device__ inline void softmax_pv(TokState &st, f32x4 (&acc)[4], const uint16_t *vt, const LaneOffs &lo, int lane,
@@ -137,7 +139,9 @@ __device__ inline void softmax_pv(TokState &st, f32x4 (&acc)[4], const uint16_t 
 #pragma unroll
     for (int kt = 1; kt < 4; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(acc[kt][0], acc[kt][1]), fmaxf(acc[kt][2], acc[kt][3])));
     if (OWN_REF) {
-        const float own = rows_max(mx), k = fmaxf(rintf((st.m - own) * c), 0.f);
+        const float own = rows_max(mx);
+        st.top = fmaxf(st.top, own);
+        const float k = fmaxf(ceilf((st.top - own) * c), 0.f);
         const float m_new = own == -INFINITY ? st.m : k > 0.f ? own + k / c : own;
         const float alpha = st.m == -INFINITY ? 0.f : fast_exp2((st.m - m_new) * c);
         st.m = m_new;

@@ -453,7 +453,7 @@ __device__ inline void attend_partial(const DecArgs &a, int pair, int L, int slo
     TokState st;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) st.o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    st.m = -INFINITY;
+    st.m = st.top = -INFINITY;
     st.l = 0.f;
     int j = w < NWV ? block_of(0) : -1;
     if (j >= 0) {
