@@ -604,6 +604,63 @@ __global__ void __launch_bounds__(256, 4) dec_front_kernel(DecArgs a) {
     attend_partial<FW, false>(a, pair, L, f, 1, [&](int) { return j; }, smem, wm, wl);
 }
 
+// ---- the row's normaliser and group sums, in one order of adds wherever they are formed: which kernel does it depends on the batch, and what is selected
+// must not.  (Compiled into several kernels, so the adds may not be regrouped and products are fused by hand.)
+constexpr int kPartsUpFront = 4;           // partials that a thread requests at once: contexts up to 131072 tokens
+// the chunk partials of thread t < 256: head t % 16, chunks t / 16, + 16, .. (one trip to memory; a loop that loads as it goes makes one per iteration)
+__device__ inline void load_partials(const DecArgs &a, int pair, int t, float2 (&pq)[kPartsUpFront]) {
+    const float *pp = a.part + (int64_t)pair * a.nchunk * 32 + (t & 15) * 2;
+#pragma unroll
+    for (int q = 0; q < kPartsUpFront; ++q) pq[q] = *reinterpret_cast<const float2 *>(pp + min((t >> 4) + 16 * q, a.nchunk - 1) * 32);
+}
+// log2 of sum_i 2^z per head from the chunk partials: 16 thread groups per head, then 16 -> 1.  By a whole workgroup (two barriers), of which 256 threads work.
+__device__ inline void row_normaliser(const DecArgs &a, int pair, int tid, const float2 (&pq)[kPartsUpFront], float (*red)[16][2], float *lse2) {
+#pragma clang fp reassociate(off) contract(off)
+    if (tid < 256) {
+        const int head = tid & 15, pg = tid >> 4;
+        const float *pp = a.part + (int64_t)pair * a.nchunk * 32 + head * 2;
+        float mm = -INFINITY, ll = 0.f;
+#pragma unroll
+        for (int q = 0; q < kPartsUpFront; ++q)
+            if (pg + 16 * q < a.nchunk) mm = fmaxf(mm, pq[q].x);
+        {
+            const float ms = mm == -INFINITY ? 0.f : mm;
+#pragma unroll
+            for (int q = 0; q < kPartsUpFront; ++q)
+                if (pg + 16 * q < a.nchunk) ll = __builtin_fmaf(pq[q].y, fast_exp2(pq[q].x - ms), ll);
+        }
+        for (int ch = pg + 16 * kPartsUpFront; ch < a.nchunk; ch += 16) {
+            const float mo = pp[ch * 32], lo = pp[ch * 32 + 1];
+            const float mn = fmaxf(mm, mo);
+            const float ms = mn == -INFINITY ? 0.f : mn;
+            ll = __builtin_fmaf(ll, fast_exp2(mm - ms), lo * fast_exp2(mo - ms));
+            mm = mn;
+        }
+        red[pg][head][0] = mm;
+        red[pg][head][1] = ll;
+    }
+    __syncthreads();
+    if (tid < 16) {
+        float m2 = -INFINITY;
+        for (int k = 0; k < 16; ++k) m2 = fmaxf(m2, red[k][tid][0]);
+        float l2 = 0.f;
+        for (int k = 0; k < 16; ++k)
+            if (red[k][tid][0] != -INFINITY) l2 = __builtin_fmaf(red[k][tid][1], fast_exp2(red[k][tid][0] - m2), l2);
+        lse2[tid] = l2 > 0.f ? m2 + __log2f(l2) : INFINITY;
+    }
+    __syncthreads();
+}
+// S^shared[i] = sum over the 16 heads of 2^(z[g][i] - lse2[g])
+__device__ inline float heads_sum(const float4 (&z)[4], const float (&nl)[G]) {
+#pragma clang fp reassociate(off) contract(off)
+    float sum = 0.f;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+        sum += (fast_exp2(z[q4].x - nl[4 * q4]) + fast_exp2(z[q4].y - nl[4 * q4 + 1])) +
+               (fast_exp2(z[q4].z - nl[4 * q4 + 2]) + fast_exp2(z[q4].w - nl[4 * q4 + 3]));
+    return sum;
+}
+
 __global__ void __launch_bounds__(256) dec_pool_kernel(DecArgs a) {
     __shared__ float red[16][16][2];
     __shared__ float lse2[16];
@@ -632,45 +689,9 @@ __global__ void __launch_bounds__(256) dec_pool_kernel(DecArgs a) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) zr[u][q4] = zk[q4];
     }
-    {   // log2 of sum_i 2^z per head from the chunk partials: 16 thread groups per head, then 16 -> 1
-        const int head = tid & 15, pg = tid >> 4;
-        const float *pp = a.part + (int64_t)pair * a.nchunk * 32 + head * 2;
-        // the first 64 chunks' partials (contexts up to 131072 tokens) are requested at once, beside the logits above:
-        // one trip to memory (a loop that loads as it goes makes one trip per iteration)
-        constexpr int PQ = 4;
-        float2 pq[PQ];
-#pragma unroll
-        for (int q = 0; q < PQ; ++q) pq[q] = *reinterpret_cast<const float2 *>(pp + min(pg + 16 * q, a.nchunk - 1) * 32);
-        float mm = -INFINITY, ll = 0.f;
-#pragma unroll
-        for (int q = 0; q < PQ; ++q)
-            if (pg + 16 * q < a.nchunk) mm = fmaxf(mm, pq[q].x);
-        {
-            const float ms = mm == -INFINITY ? 0.f : mm;
-#pragma unroll
-            for (int q = 0; q < PQ; ++q)
-                if (pg + 16 * q < a.nchunk) ll += pq[q].y * fast_exp2(pq[q].x - ms);
-        }
-        for (int ch = pg + 16 * PQ; ch < a.nchunk; ch += 16) {
-            const float mo = pp[ch * 32], lo = pp[ch * 32 + 1];
-            const float mn = fmaxf(mm, mo);
-            const float ms = mn == -INFINITY ? 0.f : mn;
-            ll = ll * fast_exp2(mm - ms) + lo * fast_exp2(mo - ms);
-            mm = mn;
-        }
-        red[pg][head][0] = mm;
-        red[pg][head][1] = ll;
-        __syncthreads();
-        if (tid < 16) {
-            float m2 = -INFINITY;
-            for (int k = 0; k < 16; ++k) m2 = fmaxf(m2, red[k][tid][0]);
-            float l2 = 0.f;
-            for (int k = 0; k < 16; ++k)
-                if (red[k][tid][0] != -INFINITY) l2 += red[k][tid][1] * fast_exp2(red[k][tid][0] - m2);
-            lse2[tid] = l2 > 0.f ? m2 + __log2f(l2) : INFINITY;
-        }
-        __syncthreads();
-    }
+    float2 pq[kPartsUpFront];
+    load_partials(a, pair, tid, pq);
+    row_normaliser(a, pair, tid, pq, red, lse2);
     // S^shared[i] = sum over the 16 heads of 2^(z[g][i] - lse2[g]) for this workgroup's keys
     float nl[G];
 #pragma unroll
@@ -688,12 +709,7 @@ __global__ void __launch_bounds__(256) dec_pool_kernel(DecArgs a) {
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) z4[q4] = zk[q4];
             }
-            float sum = 0.f;
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-                sum += (fast_exp2(z4[q4].x - nl[4 * q4]) + fast_exp2(z4[q4].y - nl[4 * q4 + 1])) +
-                       (fast_exp2(z4[q4].z - nl[4 * q4 + 2]) + fast_exp2(z4[q4].w - nl[4 * q4 + 3]));
-            sh[i - k0] = sum;
+            sh[i - k0] = heads_sum(z4, nl);
         }
     }
     __syncthreads();
@@ -892,12 +908,12 @@ __device__ inline void pick_blocks(const Keys *pk, const Forced &fo, int *sel, i
 // partials are requested up front: one trip to memory.
 constexpr int kRowKeys = 8192, kRowBlocks = 2048;
 struct RowLds {
-    float sh[kRowKeys], red[64][16][2], lse2[16];
+    float sh[kRowKeys], red[16][16][2], lse2[16];
     uint32_t pk[kRowBlocks];
 };
 template <int NT, int ZPT>
 __device__ inline void pool_row(const DecArgs &a, int pair, int L, const Forced &fo, RowLds &r) {
-    constexpr int NG = NT / 16;                          // thread groups per head of the normaliser's merge
+    static_assert(NT >= 256, "the normaliser is merged by 256 threads");
     const int tid = threadIdx.x;
     const int v = visible_cmp(L - 1, a.tk.lc, a.tk.sc);
     const float *zb = a.z + (int64_t)pair * a.zs * G;
@@ -908,62 +924,19 @@ __device__ inline void pool_row(const DecArgs &a, int pair, int L, const Forced 
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) zr[u][q4] = zk[q4];
     }
-    {
-        const int head = tid & 15, pg = tid >> 4;
-        const float *pp = a.part + (int64_t)pair * a.nchunk * 32 + head * 2;
-        constexpr int PQ = 64 / NG;                      // contexts up to 131072 tokens
-        float2 pq[PQ];
-#pragma unroll
-        for (int q = 0; q < PQ; ++q) pq[q] = *reinterpret_cast<const float2 *>(pp + min(pg + NG * q, a.nchunk - 1) * 32);
-        float mm = -INFINITY, ll = 0.f;
-#pragma unroll
-        for (int q = 0; q < PQ; ++q)
-            if (pg + NG * q < a.nchunk) mm = fmaxf(mm, pq[q].x);
-        {
-            const float ms = mm == -INFINITY ? 0.f : mm;
-#pragma unroll
-            for (int q = 0; q < PQ; ++q)
-                if (pg + NG * q < a.nchunk) ll += pq[q].y * fast_exp2(pq[q].x - ms);
-        }
-        for (int ch = pg + NG * PQ; ch < a.nchunk; ch += NG) {
-            const float mo = pp[ch * 32], lo = pp[ch * 32 + 1];
-            const float mn = fmaxf(mm, mo);
-            const float ms = mn == -INFINITY ? 0.f : mn;
-            ll = ll * fast_exp2(mm - ms) + lo * fast_exp2(mo - ms);
-            mm = mn;
-        }
-        r.red[pg][head][0] = mm;
-        r.red[pg][head][1] = ll;
-        __syncthreads();
-        // NG -> 1: a wavefront per head (or per two heads), one thread group per lane, merged with lane moves
-        const int lane = tid & 63, w = tid >> 6;
-        for (int hd = w; hd < G; hd += NT / 64) {
-            const float mk = lane < NG ? r.red[lane][hd][0] : -INFINITY, lk = lane < NG ? r.red[lane][hd][1] : 0.f;
-            const float m2 = rows_max(row_all_max(mk));
-            const float l2 = rows_sum(row_all_sum(mk == -INFINITY ? 0.f : lk * fast_exp2(mk - m2)));
-            if (lane == 0) r.lse2[hd] = l2 > 0.f ? m2 + __log2f(l2) : INFINITY;
-        }
-        __syncthreads();
-    }
-    // S^shared[i] = sum over the 16 heads of 2^(z[g][i] - lse2[g])
+    float2 pq[kPartsUpFront];
+    load_partials(a, pair, tid & 255, pq);
+    row_normaliser(a, pair, tid, pq, r.red, r.lse2);
     float nl[G];
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) nl[gq] = r.lse2[gq];
-    auto group_sum = [&](const float4 (&z4)[4]) -> float {
-        float sum = 0.f;
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-            sum += (fast_exp2(z4[q4].x - nl[4 * q4]) + fast_exp2(z4[q4].y - nl[4 * q4 + 1])) +
-                   (fast_exp2(z4[q4].z - nl[4 * q4 + 2]) + fast_exp2(z4[q4].w - nl[4 * q4 + 3]));
-        return sum;
-    };
 #pragma unroll
     for (int u = 0; u < ZPT; ++u)
-        if (tid + u * NT < v) r.sh[tid + u * NT] = group_sum(zr[u]);
+        if (tid + u * NT < v) r.sh[tid + u * NT] = heads_sum(zr[u], nl);
     for (int i = tid + ZPT * NT; i < v; i += NT) {
         const float4 *zk = reinterpret_cast<const float4 *>(zb + (int64_t)i * G);
         const float4 z4[4] = {zk[0], zk[1], zk[2], zk[3]};
-        r.sh[i] = group_sum(z4);
+        r.sh[i] = heads_sum(z4, nl);
     }
     __syncthreads();
     for (int j = tid; j < fo.nblk; j += NT) {

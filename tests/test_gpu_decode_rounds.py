@@ -72,3 +72,20 @@ def test_rounds_of_dense_sequences(m):  # noqa: F811
         assert torch.equal(idx, want[2][s])
         assert_out_close(to_np(out), to_np(want[0][s]), "bf16")
         assert (lse - want[1][s]).abs().max() < 1e-5
+
+
+def test_lists_do_not_depend_on_the_batch(m):  # noqa: F811
+    """Rows of up to 20 chunk partials, pooled by a kernel of their own (520 and 20 pairs), by the selection kernel (260) and by the attend
+    workgroups (200 and 120 pairs): the normaliser and the sums are added in one order, so the lists are the same."""
+    B, n = 260, 40000
+    torch.manual_seed(11)
+    q, k = torch.randn(B, 32, 128).cuda().bfloat16(), torch.empty(B, 2, n, 128, device="cuda", dtype=torch.bfloat16).normal_()
+    ctx = [int(x) for x in np.random.default_rng(5).integers(20000, n + 1, B)]
+    gp = m.Params.make("bf16", 32, 2, 128, n_init=1, n_local=8, topk_total=16)
+    kc = torch.zeros((B, 2, m.num_cmp(gp, n), 128), device="cuda")
+    m.compress_k_append(gp, k, kc, [0] * B, ctx)
+    want = m.sparse_decode(gp, q, k, k, kc, ctx)[2]
+    for part in (130, 100, 10):
+        for b in range(0, B, part):
+            s = slice(b, b + part)
+            assert torch.equal(m.sparse_decode(gp, q[s], k[s], k[s], kc[s], ctx[s])[2], want[s]), (part, b)
