@@ -1,15 +1,45 @@
 """The generic attention and gradient kernels with one and two column groups per wavefront: the token counts on both sides of
 each rule, tiles that end ragged, groups that do not divide 16, packed and switched sequences, strided rows and infinities in
 rows that only some of a tile's tokens see; against the CPU oracle."""
+import sys
+
 import numpy as np
 import pytest
 import torch
 
 import synth
+import test_gpu_parity
 from helpers import assert_out_close, to_dev, to_np
 from test_gpu_parity import _check_backward, _params, _run_prefill_case, m  # noqa: F401
 
 pytestmark = pytest.mark.gpu
+
+# Forms of the calls below, held on the host by test_launch_rules_host.py: dtype, heads, KV heads, d, lengths, blocks, threshold; whether attention and dQ of rows of
+# 16-byte multiples pass through LDS; and the generic form, which serves the rest and all rows that lie otherwise: column groups and rows requested ahead of
+# attention, the same of dQ.
+GENERIC_FORMS = [
+    ("bf16", 8, 2, 128, [555], 4, 0, (0, 0), (1, 1, 1, 1)), ("bf16", 8, 2, 128, [565], 4, 0, (0, 0), (1, 1, 2, 1)),
+    ("bf16", 8, 2, 128, [755], 4, 0, (0, 1), (1, 1, 2, 1)), ("bf16", 8, 2, 128, [769], 4, 0, (0, 1), (2, 1, 2, 1)),
+    ("bf16", 8, 2, 64, [3, 700, 66], 4, 67, (0, 1), (1, 1, 2, 1)), ("bf16", 24, 8, 64, [131, 120], 4, 67, (0, 1), (1, 0, 2, 1)),
+    ("bf16", 8, 8, 128, [777], 4, 0, (0, 1), (2, 1, 2, 1)), ("bf16", 40, 8, 128, [400], 4, 0, (1, 1), (2, 0, 2, 1)),
+    ("bf16", 40, 8, 64, [801], 4, 0, (1, 1), (2, 0, 2, 1)), ("bf16", 40, 8, 64, [31, 32, 200, 1], 4, 67, (0, 1), (1, 0, 2, 1)),
+    ("bf16", 8, 8, 64, [40, 65, 33] * 16, 4, 67, (0, 1), (1, 0, 1, 0)), ("bf16", 48, 4, 128, [101, 17], 4, 67, (0, 0), (1, 0, 1, 0)),
+    ("bf16", 40, 8, 128, [96, 33, 5, 64, 65, 130], 4, 67, (0, 0), (1, 0, 1, 0)), ("bf16", 40, 8, 64, [400, 430], 4, 67, (1, 1), (2, 0, 2, 1)),
+    ("fp32", 8, 2, 64, [705], 4, 0, (0, 0), (1, 0, 2, 1)), ("fp32", 8, 2, 128, [1195], 4, 0, (0, 0), (1, 0, 1, 1)),
+    ("fp32", 8, 2, 128, [1000, 210], 4, 67, (0, 0), (1, 0, 1, 1)), ("fp32", 24, 4, 128, [331], 4, 0, (0, 0), (1, 0, 1, 1)),
+    ("fp32", 40, 8, 128, [100, 33, 5], 4, 67, (0, 0), (1, 0, 1, 1)), ("fp32", 40, 8, 64, [130, 31], 4, 67, (0, 0), (1, 0, 2, 1)),
+    # rows that are not finite
+    ("bf16", 40, 8, 128, [96, 130, 65, 100], 3, 0, (0, 1), (1, 0, 1, 0)), ("bf16", 8, 2, 128, [1100], 3, 0, (0, 1), (2, 1, 2, 1)),
+    ("bf16", 8, 2, 128, [400], 3, 0, (0, 0), (1, 1, 1, 1)), ("bf16", 40, 8, 128, [400, 430], 3, 0, (1, 1), (2, 0, 2, 1)),
+    ("fp32", 8, 2, 128, [300], 3, 0, (0, 0), (1, 1, 1, 1)), ("fp32", 40, 8, 64, [130, 100, 97], 3, 0, (0, 0), (1, 0, 2, 1)),
+    ("bf16", 8, 8, 128, [800], 3, 0, (0, 1), (2, 1, 2, 1)),
+]
+
+
+def _off_by_one(a, dtype):
+    """The same values one element behind an aligned place: no row is a 16-byte multiple."""
+    x = to_dev(a, dtype)
+    return torch.zeros(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape).copy_(x)
 
 
 @pytest.mark.parametrize("dtype,hq,hkv,d,lens", [
@@ -57,7 +87,7 @@ def test_infinite_rows_stay_with_the_tokens_that_see_them(m, oracle, dtype, n): 
     assert torch.isfinite(lse).all()
 
 
-# column groups of attention and dQ, a: rows requested ahead: 1 1, 2a 2a, 1a 1a, 2 2a, 1a 1a, 1 2a, and 2a 2a with 32 tokens per tile
+# (which form each takes, also of the tests below: GENERIC_FORMS)
 @pytest.mark.parametrize("dtype,hq,hkv,d,lens", [
     ("bf16", 40, 8, 128, [96, 130, 65, 100]), ("bf16", 8, 2, 128, [1100]), ("bf16", 8, 2, 128, [400]), ("bf16", 40, 8, 128, [400, 430]),
     ("fp32", 8, 2, 128, [300]), ("fp32", 40, 8, 64, [130, 100, 97]), ("bf16", 8, 8, 128, [800]),
@@ -97,6 +127,23 @@ def test_key_rows_that_are_not_finite(m, oracle, dtype, hq, hkv, d, lens, bad): 
         # the same sums in another order, of another (rounded) output: a rounding of dQ
         scale = max(float(want.float().abs().max()), 0.1)
         assert (got[rest, heads].float() - want[rest, heads].float()).abs().max() <= (2.0**-7 if dtype == "bf16" else 1e-5) * scale
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [(40, 8, 128, [400]), (40, 8, 64, [801]), (40, 8, 64, [400, 430]), (8, 2, 128, [769]), (8, 2, 64, [3, 700, 66]),
+                                           (24, 8, 64, [131, 120]), (8, 8, 128, [777]), (8, 8, 64, [40, 65, 33] * 16)])
+def test_both_sides_of_the_rules_unaligned(m, oracle, monkeypatch, hq, hkv, d, lens):  # noqa: F811
+    """The generic two-group forms, and those whose aligned calls pass their rows through LDS."""
+    monkeypatch.setattr(test_gpu_parity, "to_dev", _off_by_one)
+    test_both_sides_of_the_rules(m, oracle, "bf16", hq, hkv, d, lens)
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [(40, 8, 128, [96, 130, 65, 100]), (8, 2, 128, [1100]), (40, 8, 128, [400, 430]), (8, 8, 128, [800])])
+@pytest.mark.parametrize("bad", ["nan", "inf", "one inf"])
+def test_key_rows_that_are_not_finite_unaligned(m, oracle, monkeypatch, hq, hkv, d, lens, bad):  # noqa: F811
+    aligned = to_dev
+    monkeypatch.setattr(sys.modules[__name__], "to_dev", lambda a, dtype: torch.zeros(aligned(a, dtype).numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(
+        a.shape).copy_(aligned(a, dtype)))
+    test_key_rows_that_are_not_finite(m, oracle, "bf16", hq, hkv, d, lens, bad)
 
 
 def test_strided_rows(m, oracle):  # noqa: F811

@@ -198,3 +198,19 @@ def test_decode_splits_fill_the_chip(rules):
     """Steps in microseconds, with one workgroup per pair / with this: 130 pairs 113 / 106, 264 207 / 186, 320 221 / 208."""
     assert [_splits(rules, p, 55)[1] for p in (43, 64, 96, 128, 130, 160, 192, 256, 264, 320, 400, 512, 600)] == [5, 4, 2, 2, 3, 3, 1, 1, 3, 3, 1, 1, 2]
     assert _splits(rules, 512, 128) == (64, 2) and _splits(rules, 300, 128) == (32, 4) and _splits(rules, 128, 0) == (4, 1)
+
+
+def _cases():
+    import test_gpu_generic_groups as g
+    return g.GENERIC_FORMS
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,lens,topk,below,lds,form", _cases())
+def test_forms_that_the_gpu_tests_count_on(rules, dtype, hq, hkv, d, lens, topk, below, lds, form):
+    """A rule that moves one of these calls to another form leaves the form it had without a test."""
+    bf16, tokens = dtype == "bf16", 16 // (hq // hkv)
+    got = _generic(rules, bf16, d, hq, hkv, lens, topk, 1, below)
+    if not bf16:
+        got = (1, rules.fp32_ahead(d, hkv, tokens, _cu(lens), len(lens), 1, topk, below)) + got[2:]
+    assert got == form
+    assert tuple(bf16 and rules.staged_form(b, d, hkv, tokens, _cu(lens), len(lens), 1, topk, below) for b in (0, 1)) == lds
