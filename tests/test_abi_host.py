@@ -273,3 +273,23 @@ def test_stream_number_is_the_current_streams(m):
     for stream in (torch.cuda.default_stream(), side):
         with torch.cuda.stream(stream):
             assert binding._stream() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
+
+
+def test_workgroups_per_cu_that_attention_counts_on():
+    """kPerCu of attn_generic.hip and `resident` of attn_staged.hip state how many workgroups of four wavefronts a CU takes: what the compiled kernels'
+    registers (and LDS) allow."""
+    import re
+
+    from paper_2509_24663_amd import build
+    res, seen = build.kernel_resources(), 0
+    for name, u in res["attn_generic.hip"].items():
+        t, d, groups, ahead = re.search(r"attn_generic_kernelI(f|NS_6bf16_tE)Li(\d+)ELi(\d)ELb(\d)", name).groups()
+        want = (2 if d == "64" else 1) + (ahead == "0") + (t != "f" and groups == "1")
+        assert u["Occupancy"] == want and want * u["LDS Size"] <= 160 * 1024, name
+        seen += 1
+    for name, u in res["attn_staged.hip"].items():
+        d = int(re.search(r"attn_staged_kernelILi(\d+)E", name).group(1))
+        want = 2 if d == 128 else 3
+        assert u["Occupancy"] == want and want * (u["LDS Size"] + 4 * 2 * 32 * d * 2) <= 160 * 1024, name
+        seen += 1
+    assert seen == 16

@@ -89,3 +89,47 @@ def test_references_that_move_late(m, d, size):  # noqa: F811
 
 def test_infinite_rows(m, oracle):  # noqa: F811
     groups.test_infinite_rows_stay_with_the_tokens_that_see_them(m, oracle, "bf16", 1500)
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(64, 4, 1), (128, 8, 2)])
+def test_walks_of_more_than_one_list(m, d, hq, hkv):  # noqa: F811
+    """More than 1024 blocks: a tile's list is built again and the wavefronts' buffers start again.  Sampled rows of attention and dQ against float64."""
+    n, topk, G = 65536 + 700, 6, hq // hkv
+    g = torch.Generator(device="cuda").manual_seed(7700 + d)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda").bfloat16()
+    q, k, v, dout = rnd(n, hq, d), rnd(hkv, n, d), rnd(hkv, n, d), rnd(n, hq, d)
+    own = torch.arange(n, device="cuda") // 64
+    idx = (torch.rand(hkv, n, topk, generator=g, device="cuda") * (own[None, :, None] + 1)).int()        # anywhere up to the own block
+    idx[..., 0] = own.int()
+    idx = idx.sort(-1).values
+    dup = torch.zeros_like(idx, dtype=torch.bool)
+    dup[..., 1:] = idx[..., 1:] == idx[..., :-1]
+    idx[dup] = 1 << 20
+    idx = idx.sort(-1).values
+    idx[idx == 1 << 20] = -1
+    gp = m.Params.make("bf16", hq, hkv, d, n_init=0, n_local=1, topk_total=topk)
+    for lists in (idx, None):
+        if lists is None and d == 128:
+            continue                                       # (every block of 66236 tokens: once is enough)
+        out, lse = m.sparse_attn_fwd(gp, q, k, v, lists, [0, n]) if lists is not None else m.dense_attn_fwd(gp, q, k, v, [0, n])
+        dq = m.sparse_attn_bwd(gp, q, k, v, lists, out, lse, dout, [0, n])[0]
+        worst = 0.0
+        for t in list(range(65520, 65560)) + list(range(n - 9, n)) + list(range(5, n, 2717)):
+            for h in range(hkv):
+                if lists is None:
+                    keys = torch.arange(t + 1, device="cuda")
+                else:
+                    have = lists[h, t][lists[h, t] >= 0].long()
+                    keys = (have[:, None] * 64 + torch.arange(64, device="cuda")).flatten()
+                    keys = keys[keys <= t]
+                K, V, s = k[h, keys].double(), v[h, keys].double(), slice(h * G, h * G + G)
+                z = q[t, s].double() @ K.t().contiguous() * gp.softmax_scale
+                assert (torch.logsumexp(z, 1) - lse[s, t].double()).abs().max() <= 2e-3
+                O = torch.softmax(z, 1) @ V
+                assert (O - out[t, s].double()).abs().max() <= 2e-2                                   # the forward bar
+                dO = dout[t, s].double()
+                dz = (z - lse[s, t, None].double()).exp() * (dO @ V.t().contiguous() - (dO * out[t, s].double()).sum(1, keepdim=True))
+                want = gp.softmax_scale * dz @ K
+                # a bf16 rounding, and fp32 products and sums of terms that cancel
+                worst = max(worst, float((want - dq[t, s].double()).abs().max() / max(float(want.abs().max()), 0.1)))
+        assert worst <= 2.0 ** -7, worst
