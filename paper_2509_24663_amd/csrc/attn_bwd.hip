@@ -640,7 +640,8 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     int64_t nblocks = 0;
     for (int s = 0; s < L.map.batch; ++s) nblocks += (cu_h[s + 1] - cu_h[s] + kBlock - 1) / kBlock;
     const int hkv = L.p->num_kv_heads;
-    if (nblocks > 65535 || hkv > 65535) return INFLLMV2_ERR_UNSUPPORTED;      // grid.y / grid.z limits
+    // grid.z; and what the (chunk, block) pairs' 32 bits hold (one sequence of 65535 blocks: 537 million pairs with chunks of 256 tokens)
+    if (nblocks > 65535 || hkv > 65535) return INFLLMV2_ERR_UNSUPPORTED;
     void *ws = L.ws;         // <dO, O> per (row, head)
     if (ws == nullptr || L.ws_bytes < (size_t)rows * a.hq * sizeof(float)) return INFLLMV2_ERR_WORKSPACE_TOO_SMALL;
     a.delta = (float *)ws;

@@ -10,8 +10,8 @@
 //   * where a token's list can hold every block of the tile's walk, all blocks are walked: their copies start before the lists
 //     are read, which then only say who takes part; lists, queries and first blocks are requested together;
 //   * heads side by side in the launch, so that the longest tiles of every head start first (500 tokens on 8 KV heads 31.3 -> 25.6 us).
-// Measured, call with 64 blocks, tile kernel and pre-pass -> this: 2 KV heads, 60 tokens 10.5 -> 7.5 us, 300 14.3 -> 10.1, 777 23.7 ->
-// 19.3, 1000 27.1 -> 23.9; 1 KV head, 1400 tokens 32.1 -> 23.1; 8 KV heads, 700 tokens 52.0 -> 39.6; 500 x 60 tokens 595 -> 269.
+// Measured, call with 64 blocks, tile kernel and pre-pass -> this: 2 KV heads, 60 tokens 10.5 -> 7.5 us, 300 14.3 -> 10.4, 777 23.7 ->
+// 19.4, 1000 27.0 -> 24.0; 1 KV head, 1400 tokens 32.0 -> 23.3; 8 KV heads, 700 tokens 51.6 -> 37.5; 500 x 60 tokens 595 -> 269.
 // Measured and not built: rings of three or four intervals (no faster: the copies are not what an interval waits for; 4 tokens in 64 KB
 // leave room for a second workgroup on the CU), half blocks as a wavefront's share (777 tokens 20.7), tiles of two tokens (29.5; faster
 // below 300 tokens by 1 us), two tokens per wavefront with shared operands (half the LDS reads, but a lone wavefront per SIMD issues

@@ -133,19 +133,21 @@ inline bool dkv_short_steps(int d, int G, int max_len, int64_t blocks) { return 
 // Tiles of four tokens read a block for fewer tokens than the tile kernel's, but their chain is shorter, which wins while a
 // CU gets few of them.  Two wavefronts per token take a whole CU (128 KB of LDS): the choice while one round of workgroups is all there is,
 // or one and a half where the rest are the short tiles of long walks; with one wavefront two workgroups share a CU.  Microseconds of the call,
-// tile kernel / two / one: 2 KV heads, 64 blocks, 300 tokens (150 workgroups) 14.3 / 10.1 / 10.7, 700 (350) 21.6 / 16.4 / 18.7, 1000 (500) 27.1 /
-// 23.9 / 25.1, 1200 (600) 30.4 / 34.7 / 28.9, 1400 33.7 / 41.0 / 33.0, 2000 52.5 / 69.6 / 61.5; 1 KV head, 1700 (425) 36.9 / 29.3 / 37.4, 2000
-// (500) 42.0 / 35.9 / 43.3, 2400 (600) 48.3 / 53.2 / 51.0; 4 KV heads, 300 (300) 16.3 / 12.8 / 11.8, 500 (500) 19.6 / 17.9 / 15.9.
-// Budgets that leave blocks out shorten the walks, so that the second round weighs more: 1 KV head, 16 blocks, 1700 tokens 32.3 / 29.5 / 35.1, 2000
-// 34.5 / 36.1 / 38.8; 8 blocks, 1300 tokens (325) 23.4 / 20.4 / 24.7, 1700 25.4 / 27.1 / 25.1; 4 blocks, 1300 tokens 17.5 / 18.9 / 14.4; 2 KV
-// heads, 8 blocks, 777 tokens (390) 21.4 / 19.0 / 19.9, 1000 23.1 / 23.8 / 22.8.
-// One wavefront against the tile kernel: up to 600 tokens whatever the batch (100 x 300 tokens 298 / 317, 16 x 520 100 / 102, 1000 x 10 108 / 520);
-// up to 1024 tokens the tile kernel's time goes up by rounds of 256 tiles of 16 (4 x 777 tokens 50.1 / 55.0, 5 x 777 62.3 / 58.7; on 1 KV head 3 x
-// 777 23.7 / 32.5, 4 x 777 33.4 / 33.5, 6 x 700 37.9 / 33.9; 8 KV heads, 850 tokens 53.0 / 57.8, 8 blocks, 900 tokens 55.8 / 54.1; 4 KV
-// heads, 1000 tokens 38.3 / 39.8, 8 blocks 35.3 / 33.1).
-// (Figures of one wavefront above are from when it took 250 registers; with 188 it is 6 to 9 % faster.)  One sequence of 501 to 600 tokens on 2 KV
-// heads has so few workgroups over one round that two are still better: two / one, 520 tokens (260) 13.3 / 15.0, 600 (300) 14.8 / 16.3; but
-// 4 x 300 on 2 (300) 21.9 / 15.8, 260 tokens on 4 (260) 12.0 / 10.9.
+// tile kernel / two / one, all of the present kernels (workgroups): 2 KV heads, 64 blocks, 300 tokens (150) 14.2 / 10.4 / 10.5, 600 (300) 20.4 / 15.0 / 16.5, 700 (350)
+// 21.4 / 16.5 / 17.6, 777 (390) 23.7 / 19.4 / 19.9, 1000 (500) 27.0 / 24.0 / 23.6; 1 KV head, 1400 (350) 32.0 / 23.3 / 28.8, 1700 (425) 36.7 / 29.3 / 34.3, 2000
+// (500) 41.5 / 35.9 / 40.0; 4 KV heads, 300 (300) 16.0 / 13.3 / 11.8, 500 (500) 19.4 / 18.1 / 15.1.
+// Budgets that leave blocks out shorten the walks, so that the second round weighs more: 1 KV head, 16 blocks, 1700 tokens 32.8 / 29.5 / 33.7, 2000
+// 35.4 / 36.1 / 37.9; 8 blocks, 1300 tokens (325) 24.7 / 20.5 / 24.6, 1700 26.8 / 28.6 / 26.0; 4 blocks, 1300 tokens 20.1 / 20.0 / 16.4; 2 KV
+// heads, 8 blocks, 777 tokens (390) 22.3 / 19.3 / 19.5, 1000 24.2 / 24.1 / 22.4.
+// One wavefront against the tile kernel: up to 600 tokens whatever the batch (tile kernel / one: 16 x 300 tokens on 2 53.8 / 47.2, 4 x 600 46.8 / 33.5, 500 x 10 169 /
+// 48, 100 x 60 on 4 119 / 79); up to 1024 tokens while the tile kernel's time, which goes up by rounds of 256 tiles of 16, has had its
+// step (3 x 900 on 1 35.6 / 27.6, on 2 51.6 / 46.2; 777 tokens on 4 32.8 / 25.0, 1000 39.4 / 34.5).
+// The lines beyond 600 tokens were drawn when one wavefront took 250 registers; with 188 it is 6 to 9 % faster, and the tile kernel, which these
+// calls keep, is no longer the faster one for 1024 to 1500 tokens on 2 KV heads (1200 tokens 30.4 / 27.0, 1400 33.7 / 30.6, 1500 36.3 / 34.5; 1700 42.9 / 43.0), for
+// batches just over the lines (2 x 777 on 2 33.2 / 25.3, 4 x 777 55 / 47, 2 x 1024 41.2 / 36.1, 2 x 777 on 4 53.5 / 46.4; but 4 x 777 on 4 82 / 86, 3 x 900 78 / 82) and
+// for small budgets (8 blocks, 777 tokens on 4 30.3 / 24.0).
+// One sequence of 501 to 600 tokens on 2 KV heads has so few workgroups over one round that two are better: two / one, 520 tokens (260) 13.3 / 15.2, 600 (300) 15.0 /
+// 16.5; but 4 x 300 on 2 (300) 22.2 / 16.1, 300 tokens on 4 (300) 13.3 / 11.8.
 inline int short_attn_waves(const int32_t *cu_h, int batch, int max_len, int hkv, bool sparse, int topk, int dense_below) {
     int64_t wgs = 0, tiles16 = 0;
     for (int s = 0; s < batch; ++s) {
