@@ -28,6 +28,7 @@
 #include "chunk_pairs.h"
 #include "gen_unit.h"
 #include "launch_rules.h"
+#include "lds_rows.h"
 
 namespace ifv2 {
 
@@ -406,17 +407,13 @@ __global__ void __launch_bounds__(NW * 64) bwd_dkv_kernel(BwdArgs<T> a, int shif
 
 // dK and dV of bf16 rows.  As above, with everything arranged for few instructions: with two wavefronts on a SIMD a step of 32 rows in the form
 // above took 2.84 us, 500 vector instructions per wavefront; this one 2.5 us, 310 (2.1 without its loads from memory):
-//   * a step is 32 rows, 32 / 16 times 16 / G tokens, staged in LDS as 256-byte rows with 16-byte chunk c of row r at chunk c ^ swizzle(r);
-//   * row x of product tile kt is row 8 (x / 4) + 4 kt + x % 4, so that a lane's eight weights are rows 8 g .. 8 g + 7, the operand of
+//   * a step is 32 rows, 32 / 16 times 16 / G tokens, staged in LDS (lds_rows.h) so that a lane's eight weights are the operand of
 //     the second products as it is, whose other operand (the same rows, transposed) comes from transposing LDS reads: no
 //     spread rows, no byte permutes;
 //   * dP starts at -Delta; keys are hidden only in steps with tokens of the block itself; weights are checked for infinities
 //     once per step and cut into pieces without checks otherwise;
 //   * an accumulator register holds 16 consecutive dims of 4 keys, whole 64-byte pieces, so the adds leave the registers as they are.
-constexpr int kRowBytes = 256;                                         // (d 64: half of it used)
-__device__ inline uint32_t row_swizzle(int r) { return 4 * (r & 3) + 2 * ((r >> 3) & 1) + ((r >> 4) & 1); }
-typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
-typedef short short4v __attribute__((ext_vector_type(4)));
+using lds_rows::kRowBytes;                                             // (d 64: half of it used)
 
 template <int D>
 __global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t> a, int shift, bool one) {
@@ -508,7 +505,7 @@ __global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t
         for (int i = 0; i < 2; ++i) {
             const int row = i * kCols + x_row;
             typedef uint32_t LPart __attribute__((ext_vector_type(D / 32), aligned(D / 8)));
-            char *p = rows_s + buf * kBuf + row * kRowBytes + (((D == 128 ? part : part >> 1) ^ row_swizzle(row)) << 4) + (D == 128 ? 0 : part & 1) * 8;
+            char *p = rows_s + buf * kBuf + row * kRowBytes + (((D == 128 ? part : part >> 1) ^ lds_rows::swizzle(row)) << 4) + (D == 128 ? 0 : part & 1) * 8;
             *reinterpret_cast<LPart *>(p) = pr.q[i];
             *reinterpret_cast<LPart *>(p + kTile) = pr.g[i];
             if (part == 0) {
@@ -518,22 +515,9 @@ __global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t
             }
         }
     };
-    // operand addresses of a lane in a tile: row 8 (m / 4) + m % 4 (+ 4 for the second tile), chunk 4 s + g; transposing read: rows 8 g + m / 4
-    // (+ 4), dims 16 i + 4 (m % 4) ..
-    const int r0 = 8 * (m >> 2) + (m & 3), r1 = 8 * g + (m >> 2);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)rows_s;
-    const uint32_t row_at = lds0 + r0 * kRowBytes + ((g ^ row_swizzle(r0)) << 4);
-    const uint32_t trans_at = lds0 + r1 * kRowBytes + ((((m & 3) >> 1) ^ row_swizzle(r1)) << 4) + (m & 1) * 8;
-    auto row_frag = [&](uint32_t at, int kt, int s) -> bf16x8 {
-        return *(lds_frag *)(uintptr_t)((at ^ (uint32_t)(64 * s)) + (uint32_t)(4 * kt * kRowBytes));
-    };
-    auto trans_frag = [&](uint32_t at, int i) -> bf16x8 {
-        typedef __attribute__((address_space(3))) short4v lds_s4;
-        const uint32_t x = at ^ (uint32_t)(32 * i);
-        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)x);
-        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)(x + 4 * kRowBytes));
-        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    };
+    const uint32_t row_at = lds0 + lds_rows::offset(lds_rows::operand_row(m), g);
+    const uint32_t trans_at = lds0 + lds_rows::offset(lds_rows::piece_row(m, g), lds_rows::piece_chunk(m)) + lds_rows::piece_half(m);
     // acc += weights^T x rows, weights in three exact pieces (see weighted_rows32)
     auto accumulate = [&](f32x4 (&acc)[N], f32x4 w0, f32x4 w1, uint32_t at) {
         float top = 0.f;
@@ -551,7 +535,7 @@ __global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t
         }
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            const bf16x8 rows = trans_frag(at, i);
+            const bf16x8 rows = lds_rows::transposed(at ^ (uint32_t)(32 * i));
             acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p2, rows, acc[i], 0, 0, 0);
             acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, rows, acc[i], 0, 0, 0);
             acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, rows, acc[i], 0, 0, 0);
@@ -576,8 +560,8 @@ __global__ void __launch_bounds__(NW * 64, 2) bwd_dkv_bf16_kernel(BwdArgs<bf16_t
             f32x4 dp = *reinterpret_cast<const f32x4 *>(&delta_s[buf][8 * g + 4 * kt]);
 #pragma unroll
             for (int ks = 0; ks < D / 32; ++ks) {
-                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_frag(ra, kt, ks), kf.x[ks], s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_frag(ra + kTile, kt, ks), vf.x[ks], dp, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_rows::operand(ra, kt, ks), kf.x[ks], s, 0, 0, 0);
+                dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_rows::operand(ra + kTile, kt, ks), vf.x[ks], dp, 0, 0, 0);
             }
             const f32x4 nl = *reinterpret_cast<const f32x4 *>(&lse_s[buf][8 * g + 4 * kt]);
 #pragma unroll

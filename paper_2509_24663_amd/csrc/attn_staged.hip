@@ -16,6 +16,7 @@
 #include "attn_staged.h"
 #include "attn_unit.h"
 #include "gen_unit.h"
+#include "lds_rows.h"
 
 namespace ifv2 {
 
@@ -26,15 +27,12 @@ using namespace gen;
 constexpr int NW = 4;                  // wavefronts; each takes every fourth half block (32 keys) of the walk
 constexpr int CG = 2;                  // column groups
 constexpr int kTileCols = CG * kCols;
-constexpr uint32_t kRowBytes = 256;    // of LDS; d 64: rows r and 16 + r of the half block side by side
+using lds_rows::kRowBytes;             // of LDS; d 64: rows r and 16 + r of the half block side by side
 
 // 16 bytes per lane from global memory to LDS address lds + 16 lane; the caller waits before it reads them
 __device__ inline void copy16(const char *src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
 }
-
-// 16-byte chunk c of LDS row r lies at chunk c ^ row_swizzle(r)
-__device__ inline uint32_t row_swizzle(int r) { return 4 * (r & 3) + 2 * ((r >> 3) & 1) + ((r >> 4) & 1); }
 
 // Half blocks of K or V rows in LDS, two buffers of a wavefront's own: nobody else reads them, so a wait takes the place of a barrier.
 template <int D>
@@ -49,13 +47,11 @@ struct Stage {
         : stride(tok_stride * 2), len(len_), lds0(lds) {
         src = reinterpret_cast<const char *>(rows) + (lane >> 4) * stride;
         const int m = lane & 15, g = lane >> 4;
-        // row x of product tile kt is row 8 (x / 4) + 4 kt + x % 4: a lane's eight weights are then rows 8 g .. 8 g + 7
-        row_at = lds + address(8 * (m >> 2) + (m & 3), g);
-        trans_at = lds + address(8 * g + (m >> 2), (m & 3) >> 1) + (m & 1) * 8;
+        row_at = lds + address(lds_rows::operand_row(m), g);
+        trans_at = lds + address(lds_rows::piece_row(m, g), lds_rows::piece_chunk(m)) + lds_rows::piece_half(m);
     }
     static __device__ inline uint32_t address(int row, int chunk) {
-        const int r = D == 128 ? row : row & 15, c = D == 128 ? chunk : chunk + 8 * (row >> 4);
-        return r * kRowBytes + ((c ^ row_swizzle(r)) << 4);
+        return D == 128 ? lds_rows::offset(row, chunk) : lds_rows::offset(row & 15, chunk + 8 * (row >> 4));
     }
     // keys key0 .. + 31, 1 KB (four LDS rows) at a time
     __device__ inline void copy(int key0, int buf) const {
@@ -78,18 +74,9 @@ struct Stage {
             }
         }
     }
-    __device__ inline bf16x8 row_frag(int buf, int kt, int s) const {
-        typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
-        return *(lds_frag *)(uintptr_t)(((row_at + buf * kBytes) ^ (uint32_t)(64 * s)) + (uint32_t)(4 * kt) * kRowBytes);
-    }
+    __device__ inline bf16x8 row_frag(int buf, int kt, int s) const { return lds_rows::operand(row_at + buf * kBytes, kt, s); }
     // rows 8 g .. 8 g + 7 of dim 16 i + lane % 16
-    __device__ inline bf16x8 trans_frag(int buf, int i) const {
-        typedef __attribute__((address_space(3))) attn_unit::short4v lds_s4;
-        const uint32_t x = (trans_at + buf * kBytes) ^ (uint32_t)(32 * i);
-        const attn_unit::short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)x);
-        const attn_unit::short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)(x + 4 * kRowBytes));
-        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    }
+    __device__ inline bf16x8 trans_frag(int buf, int i) const { return lds_rows::transposed((trans_at + buf * kBytes) ^ (uint32_t)(32 * i)); }
 };
 
 struct StagedArgs {

@@ -6,6 +6,7 @@
 // bandwidth limits described there.
 #pragma once
 #include "common.h"
+#include "lds_rows.h"
 
 namespace ifv2 {
 namespace attn_unit {
@@ -370,33 +371,23 @@ __device__ inline u32x4 keep_mask(int last) {
 }
 __device__ inline bf16x8 keep_keys(bf16x8 f, u32x4 mask) { return __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, f) & mask); }
 
-// Row-major tiles (backward unit; prefill unit of short prompts): K and V with 256-byte rows, 16-byte chunk c of row r at chunk
-// c ^ bwd_swizzle(r): the sixteen rows of an operand read take sixteen positions, and so do the 8 rows x 2 chunks that half a
-// wave touches in a transposing read.
-__device__ inline int bwd_swizzle(int r) { return 4 * (r & 3) + 2 * ((r >> 3) & 1) + ((r >> 4) & 1); }
-
+// Row-major tiles (backward unit; prefill unit of short prompts): see lds_rows.h.
 // K or V piece q (rows 4q .. 4q+3 of the block): lane l fills (row 4q + l / 16, physical chunk l % 16)
 __device__ inline void bwd_piece_src(int q, int lane, int &row, int &chunk) {
     row = 4 * q + (lane >> 4);
-    chunk = (lane & 15) ^ bwd_swizzle(row);
+    chunk = (lane & 15) ^ lds_rows::swizzle(row);
 }
 // row operand of key tile 0, k-step 0 (as k_lane_bytes)
-__device__ inline uint32_t bwd_row_bytes(int lane) {
-    const int m16 = lane & 15, g = lane >> 4, row = 8 * (m16 >> 2) + (m16 & 3);
-    return (uint32_t)(row * D * 2 + ((g ^ bwd_swizzle(row)) << 4));
-}
-// transposing read of the 4 x 16 piece (rows 8 g + L / 4, dims 4 (L % 4) ..) of each 16-lane group
+__device__ inline uint32_t bwd_row_bytes(int lane) { return lds_rows::offset(lds_rows::operand_row(lane & 15), lane >> 4); }
+// transposing read of the lane's piece
 __device__ inline uint32_t bwd_trans_bytes(int lane) {
-    const int L = lane & 15, g = lane >> 4, row = 8 * g + (L >> 2);
-    return (uint32_t)(row * D * 2 + ((((L & 3) >> 1) ^ bwd_swizzle(row)) << 4) + (L & 1) * 8);
+    const int m = lane & 15;
+    return lds_rows::offset(lds_rows::piece_row(m, lane >> 4), lds_rows::piece_chunk(m)) + lds_rows::piece_half(m);
 }
 // K^T operand of dim tile dt and half h: keys 32 h + 8 g .. + 7 of dim 16 dt + lane % 16
 __device__ inline bf16x8 bwd_kt_frag(uint32_t tb, int dt, int h) {
-    typedef __attribute__((address_space(3))) short4v lds_s4;
-    const uint32_t x = (tb ^ (uint32_t)(32 * dt)) + (uint32_t)(32 * h * D * 2);
-    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)x);
-    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)(x + 4 * D * 2));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    static_assert(D * 2 == lds_rows::kRowBytes, "rows of a tile");
+    return lds_rows::transposed((tb ^ (uint32_t)(32 * dt)) + (uint32_t)(32 * h) * lds_rows::kRowBytes);
 }
 
 // an operand of the K^T products with the keys the token does not see taken as 0 (their dZ is 0, but 0 times an infinity in
