@@ -613,11 +613,13 @@ __device__ inline void load_partials(const DecArgs &a, int pair, int t, float2 (
 #pragma unroll
     for (int q = 0; q < kPartsUpFront; ++q) pq[q] = *reinterpret_cast<const float2 *>(pp + min((t >> 4) + 16 * q, a.nchunk - 1) * 32);
 }
-// log2 of sum_i 2^z per head from the chunk partials: 16 thread groups per head, then 16 -> 1.  By a whole workgroup (two barriers), of which 256 threads work.
-__device__ inline void row_normaliser(const DecArgs &a, int pair, int tid, const float2 (&pq)[kPartsUpFront], float (*red)[16][2], float *lse2) {
+// log2 of sum_i 2^z per head from the chunk partials: 16 thread groups per head, then 16 -> 1.  By a whole workgroup (two barriers) of 256 threads
+// or a multiple, whose further threads repeat what the first ones do: round a branch the compiler moves the partials' loads into it, behind the logits'
+// and their wait (decode step of one sequence 24.3 -> 24.6 us).
+__device__ inline void row_normaliser(const DecArgs &a, int pair, int tid, const float2 (&pq)[kPartsUpFront], float2 (*red)[16], float *lse2) {
 #pragma clang fp reassociate(off) contract(off)
-    if (tid < 256) {
-        const int head = tid & 15, pg = tid >> 4;
+    {
+        const int head = tid & 15, pg = (tid & 255) >> 4;
         const float *pp = a.part + (int64_t)pair * a.nchunk * 32 + head * 2;
         float mm = -INFINITY, ll = 0.f;
 #pragma unroll
@@ -636,16 +638,25 @@ __device__ inline void row_normaliser(const DecArgs &a, int pair, int tid, const
             ll = __builtin_fmaf(ll, fast_exp2(mm - ms), lo * fast_exp2(mo - ms));
             mm = mn;
         }
-        red[pg][head][0] = mm;
-        red[pg][head][1] = ll;
+        red[pg][head] = make_float2(mm, ll);
     }
     __syncthreads();
     if (tid < 16) {
-        float m2 = -INFINITY;
-        for (int k = 0; k < 16; ++k) m2 = fmaxf(m2, red[k][tid][0]);
-        float l2 = 0.f;
-        for (int k = 0; k < 16; ++k)
-            if (red[k][tid][0] != -INFINITY) l2 = __builtin_fmaf(red[k][tid][1], fast_exp2(red[k][tid][0] - m2), l2);
+        // (read four at a time, held by nobody in between, and added with selects: with a branch round each sum that is a trip to LDS each)
+        float m2 = -INFINITY, l2 = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) m2 = fmaxf(m2, red[k][tid].x);
+#pragma unroll
+        for (int k = 0; k < 16; k += 4) {
+            asm volatile("" ::: "memory");
+            const float2 r[4] = {red[k][tid], red[k + 1][tid], red[k + 2][tid], red[k + 3][tid]};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float sum = __builtin_fmaf(r[i].y, fast_exp2(r[i].x - m2), l2);
+                asm volatile("" : "+v"(sum));
+                l2 = r[i].x != -INFINITY ? sum : l2;
+            }
+        }
         lse2[tid] = l2 > 0.f ? m2 + __log2f(l2) : INFINITY;
     }
     __syncthreads();
@@ -662,7 +673,7 @@ __device__ inline float heads_sum(const float4 (&z)[4], const float (&nl)[G]) {
 }
 
 __global__ void __launch_bounds__(256) dec_pool_kernel(DecArgs a) {
-    __shared__ float red[16][16][2];
+    __shared__ float2 red[16][16];
     __shared__ float lse2[16];
     __shared__ float sh[kPoolKeysMax];
     const int pair = blockIdx.y;
@@ -678,7 +689,9 @@ __global__ void __launch_bounds__(256) dec_pool_kernel(DecArgs a) {
     // keys this workgroup pools: the union of its blocks' windows, clipped to the visible keys
     const int k0 = max(a.tk.pool_stride * j0 - a.tk.pool_pad, 0);
     const int k1 = min(a.tk.pool_stride * (j1 - 1) - a.tk.pool_pad + a.tk.pool_len, v);
-    // their logits are requested first, so that the trip overlaps the merge of the normaliser
+    // their logits are requested right behind the partials, so that the trip overlaps the merge of the normaliser
+    float2 pq[kPartsUpFront];
+    load_partials(a, pair, tid, pq);
     constexpr int KPT = kPoolKeysMax / 256;
     const float *zb = a.z + (int64_t)pair * a.zs * G;
     float4 zr[2][4];                                      // the first two keys of this thread, 16 heads each
@@ -689,8 +702,6 @@ __global__ void __launch_bounds__(256) dec_pool_kernel(DecArgs a) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) zr[u][q4] = zk[q4];
     }
-    float2 pq[kPartsUpFront];
-    load_partials(a, pair, tid, pq);
     row_normaliser(a, pair, tid, pq, red, lse2);
     // S^shared[i] = sum over the 16 heads of 2^(z[g][i] - lse2[g]) for this workgroup's keys
     float nl[G];
@@ -908,15 +919,18 @@ __device__ inline void pick_blocks(const Keys *pk, const Forced &fo, int *sel, i
 // partials are requested up front: one trip to memory.
 constexpr int kRowKeys = 8192, kRowBlocks = 2048;
 struct RowLds {
-    float sh[kRowKeys], red[16][16][2], lse2[16];
+    float sh[kRowKeys], lse2[16];
+    float2 red[16][16];
     uint32_t pk[kRowBlocks];
 };
 template <int NT, int ZPT>
 __device__ inline void pool_row(const DecArgs &a, int pair, int L, const Forced &fo, RowLds &r) {
-    static_assert(NT >= 256, "the normaliser is merged by 256 threads");
+    static_assert(NT % 256 == 0, "the normaliser is merged by 256 threads");
     const int tid = threadIdx.x;
     const int v = visible_cmp(L - 1, a.tk.lc, a.tk.sc);
     const float *zb = a.z + (int64_t)pair * a.zs * G;
+    float2 pq[kPartsUpFront];
+    load_partials(a, pair, tid & 255, pq);
     float4 zr[ZPT][4];
 #pragma unroll
     for (int u = 0; u < ZPT; ++u) {
@@ -924,8 +938,6 @@ __device__ inline void pool_row(const DecArgs &a, int pair, int L, const Forced 
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) zr[u][q4] = zk[q4];
     }
-    float2 pq[kPartsUpFront];
-    load_partials(a, pair, tid & 255, pq);
     row_normaliser(a, pair, tid, pq, r.red, r.lse2);
     float nl[G];
 #pragma unroll
