@@ -38,18 +38,16 @@ template <typename T, int D, int CG, bool AHEAD>
 __global__ void __launch_bounds__(NW * 64)
 attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
                     const int32_t *__restrict__ idx, int topk_total, int dense_below, RowMap map, int hq,
-                    float scale, T *__restrict__ out, float *__restrict__ lse) {
+                    float scale, T *__restrict__ out, float *__restrict__ lse, uint32_t back) {
     constexpr int N = D / 16;
     __shared__ Union un;
     __shared__ float o_s[NW][CG * kCols][D + 4], m_s[NW][CG * kCols], l_s[NW][CG * kCols];
     __shared__ int s_tile[3];
-    // Late tiles first, for they have the most blocks, one head after the other; heads side by side and rows of 256 workgroups back and forth
-    // where all are on the chip at once.  fp32 d 64, one order / the other: 2048 tokens, 4 heads on 1 (512 workgroups) 29.3 / 26.8 us, with 16
-    // blocks 38.3 / 32.5, 1000 tokens on 2 (500) 25.7 / 19.9, 1500 (750) 34.7 / 31.3; beyond that nothing is gained (2048 tokens on 2, 1024
-    // workgroups, 45.6 / 50.0, 4096 102.9 / 99.9), and with one workgroup per CU the second row would start shortest first (36.5 / 44.1).
+    // Late tiles first, for they have the most blocks, one head after the other; or heads side by side and rows of 256 workgroups back and forth
+    // (rules::back_and_forth).  (back: the launch's workgroups, or 0; as a flag it would have the grid's size fetched behind it, 0.3 us of every call.)
     const uint32_t workgroups = gridDim.x * gridDim.y;
     uint32_t h = blockIdx.y, nth = blockIdx.x;
-    if (workgroups > 256 && workgroups <= 256 * kPerCu<T, D, CG, AHEAD>) {
+    if (workgroups == back) {
         const uint32_t b = back_and_forth(blockIdx.y * gridDim.x + blockIdx.x, workgroups);
         nth = b / gridDim.y;
         h = b - nth * gridDim.y;
@@ -239,13 +237,15 @@ attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *_
 
 template <typename T, int D, int CG, bool AHEAD>
 int launch_cg(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, void *out,
-              float *lse) {
+              float *lse, const int32_t *cu_h, double half_blocks) {
     const int tokens = CG * tile_tokens(L.map, L.p->num_q_heads / L.p->num_kv_heads);
     // at most this many tiles (every sequence may end with a partial one)
     const unsigned tiles = L.map.ctx ? L.map.total_rows : L.map.total_rows / tokens + L.map.batch;
+    const bool back = rules::back_and_forth(cu_h, L.map.batch, tokens, tiles, L.p->num_kv_heads, idx != nullptr, L.p->topk_total, dense_below,
+                                            half_blocks, 256 * kPerCu<T, D, CG, AHEAD>);
     hipLaunchKernelGGL((attn_generic_kernel<T, D, CG, AHEAD>), dim3(tiles, L.p->num_kv_heads), dim3(NW * 64), 0, L.stream,
                        (const T *)q, (const T *)k, (const T *)v, idx, L.p->topk_total, dense_below, L.map,
-                       L.p->num_q_heads, L.p->softmax_scale, (T *)out, lse);
+                       L.p->num_q_heads, L.p->softmax_scale, (T *)out, lse, back ? tiles * L.p->num_kv_heads : 0);
     return hip_status(hipGetLastError());
 }
 
@@ -253,7 +253,7 @@ template <typename T, int D>
 int launch_t(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, void *out,
              float *lse, const int32_t *cu_h) {
     if (L.map.total_rows == 0) return INFLLMV2_OK;
-    if (L.map.ctx != nullptr) return launch_cg<T, D, 1, true>(L, q, k, v, idx, dense_below, out, lse);      // (one token per tile)
+    if (L.map.ctx != nullptr) return launch_cg<T, D, 1, true>(L, q, k, v, idx, dense_below, out, lse, nullptr, 0);      // (one token per tile)
     const int hkv = L.p->num_kv_heads;
     const rules::Walks x = rules::walks(cu_h, L.map.batch, tile_tokens(L.map, L.p->num_q_heads / hkv), idx != nullptr,
                                         L.p->topk_total, dense_below);
@@ -262,11 +262,11 @@ int launch_t(const Launch &L, const void *q, const void *k, const void *v, const
     const rules::GenericForm form = rules::generic_form(sizeof(T) == 2, D, hkv, x);
     if constexpr (sizeof(T) == 2)
         if (form.groups == 2)
-            return form.ahead ? launch_cg<T, D, 2, true>(L, q, k, v, idx, dense_below, out, lse)
-                              : launch_cg<T, D, 2, false>(L, q, k, v, idx, dense_below, out, lse);
+            return form.ahead ? launch_cg<T, D, 2, true>(L, q, k, v, idx, dense_below, out, lse, cu_h, x.half_blocks)
+                              : launch_cg<T, D, 2, false>(L, q, k, v, idx, dense_below, out, lse, cu_h, x.half_blocks);
     const bool ahead = sizeof(T) == 2 ? form.ahead : rules::fp32_rows_ahead(D, hkv, x.one * hkv, x);
-    return ahead ? launch_cg<T, D, 1, true>(L, q, k, v, idx, dense_below, out, lse)
-                 : launch_cg<T, D, 1, false>(L, q, k, v, idx, dense_below, out, lse);
+    return ahead ? launch_cg<T, D, 1, true>(L, q, k, v, idx, dense_below, out, lse, cu_h, x.half_blocks)
+                 : launch_cg<T, D, 1, false>(L, q, k, v, idx, dense_below, out, lse, cu_h, x.half_blocks);
 }
 
 }  // namespace

@@ -81,6 +81,43 @@ inline bool fp32_rows_ahead(int d, int hkv, int64_t workgroups, const Walks &x) 
     if (hkv > 2) return workgroups <= std::min(300., 40 * hb) || (hb >= 12 && workgroups > 600 && workgroups <= 1024);
     return workgroups <= std::min(512., 64 * hb) || (hb >= 12 && workgroups <= 600);
 }
+// Order of a generic attention launch's workgroups, which all take the tiles from the last one down: one head after the other, or, where all workgroups are on
+// the chip at once, heads side by side and rows of 256 back and forth, so that long and short tiles share a CU.  fp32 d 64, one order / the other: 2048
+// tokens, 4 heads on 1 (512 workgroups) 29.3 / 26.8 us, with 16 blocks 38.3 / 32.5, 1000 tokens on 2 (500) 25.7 / 19.9, 1500 (750) 34.7 / 31.3; with one
+// workgroup per CU the second row would start shortest first (36.5 / 44.1).
+//
+// Walks of a packed batch do not fall from tile to tile, so there the fullest CU is counted for both orders: fp32 d 64, 2 heads on 1, dense, 2463 + 2040 + 68 tokens
+// (572) 58.6 / 40.5 us but 2490 and 100 of one (412) 41.6 / 45.2, 16 blocks, 2675 + 10 x 100 (535) 29.8 / 35.2; d 128, 4 on 1, 4 blocks, 1217 + 10 x 43 (415) 20.8 /
+// 23.9.  127 packed calls are 0.5 % from the faster order, 1.1 % with the second for all, six instead of fifteen of them 3 % and more slower than
+// with the first.
+// Where walks are shorter than four half blocks the call is over before the count on the host pays (2 us: 500 sequences of 4 tokens 9.1 -> 12.0 us).
+// tiles: launched, of `tokens` tokens (the sequences' partial ones may be fewer: empty ones come first); resident: workgroups that the chip holds.  cu_h: nullptr
+// where a tile is a token of its own.
+inline bool back_and_forth(const int32_t *cu_h, int batch, int tokens, int64_t tiles, int hkv, bool sparse, int topk, int dense_below, double half_blocks,
+                           int resident) {
+    const int64_t workgroups = tiles * hkv;
+    if (workgroups <= 256 || workgroups > resident || resident > 1024) return false;
+    if (cu_h == nullptr || batch == 1 || half_blocks < 4) return true;
+    const int n = (int)workgroups;
+    int work[1024];                                          // half blocks of the launch's nth tile, and a start and an end worth four
+    int nth = (int)tiles;
+    for (int s = 0; s < batch; ++s) {
+        const int len = cu_h[s + 1] - cu_h[s], most = sparse && len >= dense_below ? 2 * topk : len;
+        for (int t = 0; t < len && nth > 0; t += tokens) work[--nth] = 4 + std::min((std::min(t + tokens, len) + kKeys / 2 - 1) / (kKeys / 2), most);
+    }
+    while (nth > 0) work[--nth] = 0;
+    int straight[256] = {}, back[256] = {};
+    int b = 0, e = 0;
+    for (int h = 0; h < hkv; ++h)
+        for (int t = 0; t < (int)tiles; ++t) straight[b++ & 255] += work[t];
+    for (int t = 0; t < (int)tiles; ++t)
+        for (int h = 0; h < hkv; ++h, ++e) {
+            const int row = e & ~255, last = std::min(255, n - 1 - row), at = e - row;
+            back[e & 256 ? last - at : at] += work[t];
+        }
+    return *std::max_element(back, back + 256) < *std::max_element(straight, straight + 256);
+}
+
 // bf16 attention and dQ with tiles of two groups whose V (dQ: K) rows pass through LDS (attn_staged.hip): a step is shorter, but a
 // workgroup takes 3 us longer to start and to end, so not where few of them leave the chip idle and each has few steps.  Calls by
 // workgroups (tiles of two groups times KV heads), generic / staged.  Attention d 128, 8 heads on 2: 720 tokens (180) 13.6 / 16.6 us, 1020 (255)
