@@ -311,18 +311,21 @@ inline int dkv_chunk(const DkvBatch &b, int64_t most) {
 //
 // The cheapest of 32 to 256 by a model of the launch, in steps (32 or 16 rows: as many tokens of G heads as that): a workgroup takes a fixed
 // time for its list, its keys and its adds, and its tokens' steps, of which the last is half empty; while all workgroups run at once
-// the longest counts, then the rounds of the average one and part of the longest.  From the backward call with every chunk at 4830 forms
-// (60 to 6000 tokens, packed mixtures of up to 2000 sequences, 1 to 8 KV heads, groups of 1 to 16, budgets of 4 and 16 blocks and dense) the chosen chunk
-// is from the best on average / at the worst hundredth: bf16 d 128 0.7 / 9 %, d 64 0.4 / 8 %, fp32 0.6 / 10 and 0.4 / 9 %
-// (profiles/generic_backward_chunk_timings.txt).  Whole backward, chunks of 32 / 64 / 128 / 256: bf16, 8 heads on 2, d 128, 16 blocks, 300 tokens 29 /
-// 34 / 48 / 75 us, 1000 tokens 80 / 63 / 69 / 97, 1985 tokens 167 / 125 / 97 / 117, with 4 blocks 1000 tokens 63 / 48 / 58 / 87; d 64, 1985 tokens 98 / 75 /
-// 67 / 86; fp32, d 128, 1985 tokens 400 / 368 / 363 / 464, 4 heads on 4, 1000 tokens 134 / 115 / 100 / 107.
+// the longest counts, then the rounds of the average one and part of the longest.  From the backward call with every chunk at 8000 forms
+// (60 to 6000 tokens, packed mixtures of up to 2000 sequences, 1 to 8 KV heads, groups of 1 to 16, budgets of 4 to 32 blocks and dense) the chosen chunk
+// is from the best on average / at the worst hundredth: bf16 d 128 0.5 / 8 %, d 64 0.5 / 8 %, fp32 0.4 / 7 and 0.4 / 8 % (with one set of constants for all
+// groups 1.8 / 20, 1.2 / 16, 0.9 / 13 and 0.9 / 12; profiles/generic_backward_chunk_timings.txt).  Whole backward, chunks of 32 / 64 / 128 / 256: bf16, 8 heads on 2, d 128, 16
+// blocks, 346 tokens 30 / 35 / 48 / 75 us, 873 tokens 59 / 53 / 62 / 91, 1971 tokens 146 / 106 / 90 / 108; 2 heads on 1, 4 blocks, 2795 + 1317 + 794 + 648 tokens 93 / 75 / 70 / 74; fp32,
+// d 128, 2 on 1, 4 blocks, 1558 tokens 61 / 77 / 82 / 123, 8 on 1, 5531 tokens 478 / 461 / 546 / 731.
 inline int generic_dkv_shift(bool bf16, int d, int G, const DkvBatch &b, int64_t &pairs) {
     // a workgroup's fixed time, what the average one takes beyond its tokens' steps, workgroups in a round, the part of the longest
     struct Model { double fixed, end, slots, tail; };
-    const Model c = !bf16     ? (d == 64 ? Model{2, 0.5, 512, 0.3} : Model{4, 1, 480, 0.5})
-                    : d == 64 ? (G > 4 ? Model{4, 1, 512, 0.3} : Model{1.5, 0.5, 256, 0.3})
-                              : (G > 4 ? Model{5, 0.5, 512, 0.5} : G > 2 ? Model{3, 0.5, 256, 0.3} : Model{3, 0.5, 192, 0.5});
+    // by heads of a group: one, two, up to four, more
+    static const Model fp32_64[4] = {{2.5, 0.5, 448, 0.3}, {1, 2, 640, 0.5}, {2.5, 0.5, 768, 0.7}, {1, 0, 512, 0.3}};
+    static const Model fp32_128[4] = {{1.5, 0.5, 256, 0.5}, {2, 1, 512, 0.5}, {1.5, 2, 512, 0.7}, {1, 0.5, 512, 0.5}};
+    static const Model bf16_64[4] = {{1, 0, 160, 0.3}, {1, 0, 192, 0.2}, {1, 3, 512, 0.3}, {2.5, 2, 640, 0.5}};
+    static const Model bf16_128[4] = {{1.5, 0.5, 128, 0.3}, {1, 1, 160, 0.3}, {2, 3, 384, 0.3}, {2, 3, 512, 0.5}};
+    const Model c = (bf16 ? d == 64 ? bf16_64 : bf16_128 : d == 64 ? fp32_64 : fp32_128)[G <= 2 ? G - 1 : G <= 4 ? 2 : 3];
     const double tokens = 16 / G * (bf16 ? 2 : 1);
     int64_t busy[4] = {};                                   // by the chunk's size, 32 first
     double entries = 0;
