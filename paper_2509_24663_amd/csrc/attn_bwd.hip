@@ -223,13 +223,12 @@ __global__ void __launch_bounds__(NW * 64) bwd_dq_kernel(BwdArgs<T> a) {
 // Sequence (>= batch past the last pair), chunk and block of this workgroup; s_tile: 3 ints of LDS.  ONE chunk holds every sequence: a
 // workgroup is a block, as cheap to find in a batch as a tile (2000 sequences of one token, 8 heads on 2, d 64, bf16: dkv 54 -> 49 us).
 __device__ inline int dkv_place(const RowMap &m, int shift, bool one, int &chunk, int &block, int *s_tile) {
-    const int at = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    chunk = 0;
-    if (one) return find_seq_tile(m.cu, m.batch, kBlock, at, block, s_tile);
     int nth, before;
-    const int seq = find_seq_count(m.cu, m.batch, at, nth, before, s_tile, [&](int n) { return sequence_pairs(n, shift); },
-                                   [](int) { return 0; });
-    if (seq < m.batch) pair_at(nth, shift, chunk, block);
+    const int seq = find_seq_count(m.cu, m.batch, (int)(blockIdx.y * gridDim.x + blockIdx.x), nth, before, s_tile,
+                                   [&](int n) { return one ? (n + kBlock - 1) / kBlock : sequence_pairs(n, shift); }, [](int) { return 0; });
+    chunk = 0;
+    block = nth;
+    if (!one && seq < m.batch) pair_at(nth, shift, chunk, block);
     return seq;
 }
 
