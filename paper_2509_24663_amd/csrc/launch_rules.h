@@ -322,7 +322,7 @@ inline int generic_dkv_shift(bool bf16, int d, int G, const DkvBatch &b, int64_t
     struct Model { double fixed, end, slots, tail; };
     // by heads of a group: one, two, up to four, more
     static const Model fp32_64[4] = {{2.5, 0.5, 448, 0.3}, {1, 2, 640, 0.5}, {2.5, 0.5, 768, 0.7}, {1, 0, 512, 0.3}};
-    static const Model fp32_128[4] = {{1.5, 0.5, 256, 0.5}, {2, 1, 512, 0.5}, {1.5, 2, 512, 0.7}, {1, 0.5, 512, 0.5}};
+    static const Model fp32_128[4] = {{1, 2, 384, 0.2}, {2, 1, 512, 0.5}, {1.5, 2, 512, 0.7}, {1, 0.5, 512, 0.5}};
     static const Model bf16_64[4] = {{1, 0, 160, 0.3}, {1, 0, 192, 0.2}, {1, 3, 512, 0.3}, {2.5, 2, 640, 0.5}};
     static const Model bf16_128[4] = {{1.5, 0.5, 128, 0.3}, {1, 1, 160, 0.3}, {2, 3, 384, 0.3}, {2, 3, 512, 0.5}};
     const Model c = (bf16 ? d == 64 ? bf16_64 : bf16_128 : d == 64 ? fp32_64 : fp32_128)[G <= 2 ? G - 1 : G <= 4 ? 2 : 3];
