@@ -127,6 +127,9 @@ inline bool back_and_forth(const int32_t *cu_h, int batch, int tokens, int64_t t
 // 13.6 / 13.9.  Backward d 128: 300 tokens (76) 27.7 / 30.3, 600 (150) 44.4 / 43.5, 6000 (1500) 519 / 399; 300 x 4 tokens, 28 heads on 4,
 // 63.4 / 67.3; d 64, 1985 tokens 82 / 66.
 //
+// d 128, packed sequences with walks of less than five half blocks, staged / generic: 16 x 189, 4 heads on 1 (384) 12.3 / 10.7 us, 12 x 238 (360) 13.2 / 11.5, 234 + 121 + 216 +
+// 177, 14 on 1 (375) 14.2 / 10.9, but 4 x 211 (424) 0.92 of the generic form's time, 4 x 224, 16 on 4 (448) 0.80, 12 x 192, 6 on 3 (432) 0.79; with longer walks 6 x 309 (360) 0.98.
+//
 // Where many tiles end with their sequences a second group is often empty, and short walks do not make up for it: attention d 128, 3000 tokens and
 // 300 x 4, 4 blocks, 4 heads on 1 (675) 22.2 / 26.5, 1000 tokens and 300 x 4, 4 on 4 (1328) 27.7 / 33.8, but 3000 + 300 x 4 with every block 79 / 100 of the
 // generic form's time; d 64, 1000 + 200 x 1, 4 on 1 (325) 11.3 / 14.4, on 2 with 4 blocks (650) 11.2 / 13.4, with every block 85 / 100.
@@ -139,7 +142,7 @@ inline bool staged(bool bwd, int d, int64_t workgroups, const Walks &x) {
     const double least = d == 128 ? 6 : workgroups <= 450 ? 10 : workgroups <= 1100 ? 6 : 0;
     if (partial && x.half_blocks < least) return false;
     if (d == 64) return workgroups > 300 && x.half_blocks >= (workgroups > 512 ? 3 : 6);
-    return workgroups >= 340 && x.half_blocks >= 3;
+    return workgroups >= (x.half_blocks < 5 ? 400 : 340) && x.half_blocks >= 3;
 }
 // dQ reads K twice, so two groups pay earlier.  By tiles of one group times KV heads, one / two groups: bf16 d 128: 250 tiles 15.0 /
 // 17.2 us, 300 20.0 / 18.8, 994 80 / 55; d 64: 400 17.7 / 16.1; fp32 d 64: 400 38 / 34, 800 74 / 58 (d 128: two groups need 54 registers

@@ -197,7 +197,8 @@ def test_fp32_rows_ahead_only_where_a_cu_has_one_workgroup_to_run(rules, d, hq, 
 @pytest.mark.parametrize("bwd,d,hq,hkv,lens,want", [
     (0, 128, 8, 2, [1352], 0), (0, 128, 8, 2, [1353], 1), (0, 128, 8, 2, [4] * 400, 0), (0, 64, 8, 2, [1200], 0), (0, 64, 8, 2, [1201], 1),
     (0, 64, 8, 2, [4] * 400, 0), (0, 64, 8, 2, [300] * 6, 0), (0, 64, 8, 2, [300] * 8, 1), (1, 128, 8, 2, [592], 0), (1, 128, 8, 2, [593], 1), (1, 128, 8, 2, [30] * 100, 0),
-    (1, 64, 8, 2, [30] * 100, 1), (1, 64, 8, 2, [592], 0), (1, 64, 4, 1, [], 0)])
+    (1, 64, 8, 2, [30] * 100, 1), (1, 64, 8, 2, [592], 0), (1, 64, 4, 1, [], 0),
+    (0, 128, 4, 1, [189] * 16, 0), (0, 128, 4, 1, [238] * 12, 0), (0, 128, 16, 4, [200] * 4, 1), (0, 128, 6, 3, [309] * 6, 1)])
 def test_rows_through_lds_for_large_calls(rules, bwd, d, hq, hkv, lens, want):
     assert rules.staged_form(bwd, d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, 16, 0) == want
 
