@@ -11,7 +11,7 @@
 // as the registers of this one's are free (AHEAD), or, in launches of many workgroups, as late as they are needed: fewer
 // registers, one wavefront more per SIMD (launch_rules.h).
 //
-// What bounds it: bf16, the trips of the rows from the L2 to the CUs (12 TB/s), which is why two column groups share them;
+// What bounds it: bf16, the trips of the rows from the L2 to the CUs (255 MB in the case below, 6.5 TB/s), which is why two column groups share them;
 // fp32, the products (32 clocks each) and how evenly a tile's half blocks fall on its wavefronts.  Half as many vector
 // instructions (rows addressed by a scalar base and a constant lane offset, products over 32 keys, no checks for
 // infinities in the first pass, sums rescaled only when a logit is larger than all before) alone took the bf16 case below

@@ -6,9 +6,9 @@
 //     buffers: no barrier stands in the walk;
 //   * softmax references move only when a logit exceeds them by a factor of 2^8 (forward): fewer rescales, the same 24 bits;
 //   * long and short tiles share a CU (see the order of the workgroups).
-// What bounds it: the rows' way from the L2 to the CUs (17 TB/s; a wavefront's requests for a step take 1100 clocks of its 4200 to go
-// out, the 64 products with their LDS reads 1500, the softmax 1250) and, per workgroup, 3.6 us of chained requests before its first
-// step and 2.5 after the last.  Measured, 1985 tokens, 8 heads on 2, 16 blocks: attention d 128 40 -> 31 us (37.8 without the order of
+// What bounds it: the chain of a wavefront's step (its requests take 1100 clocks of 4200 to go out, the 64 products with their LDS reads 1500, the
+// softmax 1250; two wavefronts per SIMD) and, per workgroup, 3.6 us of chained requests before its first step and 2.5 after the last.  In the
+// case below rows come at 8 TB/s (255 MB, nine tenths from the L2) and the matrix cores are busy for a sixth of the time.  Measured, 1985 tokens, 8 heads on 2, 16 blocks: attention d 128 40 -> 31 us (37.8 without the order of
 // the workgroups), d 64 30 -> 22.4; backward call d 128 109 -> 97, d 64 82 -> 66.  6000 tokens, d 128: attention 181 -> 158, backward 517 -> 390.
 // Measured and not built: tiles of four groups in eight wavefronts with K and V in LDS (half the traffic, but a barrier per interval keeps
 // the wavefronts of a SIMD in step: 44 us); first copies before the lists where a walk has all blocks (2 us slower: registers);
