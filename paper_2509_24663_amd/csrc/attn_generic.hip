@@ -45,9 +45,9 @@ attn_generic_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *_
     __shared__ int s_tile[3];
     // Late tiles first, for they have the most blocks, one head after the other; or heads side by side and rows of 256 workgroups back and forth
     // (rules::back_and_forth).  (back: the launch's workgroups, or 0; as a flag it would have the grid's size fetched behind it, 0.3 us of every call.)
-    const uint32_t workgroups = gridDim.x * gridDim.y;
+    const uint32_t workgroups = gridDim.x * gridDim.y;                  // (modulo 2^32)
     uint32_t h = blockIdx.y, nth = blockIdx.x;
-    if (workgroups == back) {
+    if ((workgroups == back) & (back != 0)) {
         const uint32_t b = back_and_forth(blockIdx.y * gridDim.x + blockIdx.x, workgroups);
         nth = b / gridDim.y;
         h = b - nth * gridDim.y;
