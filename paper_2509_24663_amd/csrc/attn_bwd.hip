@@ -636,7 +636,7 @@ int launch_t(const Launch &L, BwdArgs<T> a, const int32_t *cu_h) {
     const rules::GenericForm form = rules::generic_dq_form(sizeof(T) == 2, D, hkv, x);
     const bool two = D * sizeof(T) < 512 && form.groups == 2;
     if (sizeof(T) == 2 && rules::staged(true, D, x.two * hkv, x) && attn_staged_takes(L, a.k, a.v)) {
-        const int st = launch_dq_staged(L, a.q, a.k, a.v, a.idx, a.dense_below, a.lse, a.delta, a.dout, a.dq, x.two);
+        const int st = launch_dq_staged(L, a.q, a.k, a.v, a.idx, a.dense_below, a.lse, a.delta, a.dout, a.dq, cu_h, x);
         if (st != INFLLMV2_OK) return st;
     } else {
         if constexpr (D * sizeof(T) < 512)

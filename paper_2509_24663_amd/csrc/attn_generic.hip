@@ -242,7 +242,7 @@ int launch_cg(const Launch &L, const void *q, const void *k, const void *v, cons
     // at most this many tiles (every sequence may end with a partial one)
     const unsigned tiles = L.map.ctx ? L.map.total_rows : L.map.total_rows / tokens + L.map.batch;
     const bool back = rules::back_and_forth(cu_h, L.map.batch, tokens, tiles, L.p->num_kv_heads, idx != nullptr, L.p->topk_total, dense_below,
-                                            half_blocks, 256 * kPerCu<T, D, CG, AHEAD>);
+                                            half_blocks, 256 * kPerCu<T, D, CG, AHEAD>, false);
     hipLaunchKernelGGL((attn_generic_kernel<T, D, CG, AHEAD>), dim3(tiles, L.p->num_kv_heads), dim3(NW * 64), 0, L.stream,
                        (const T *)q, (const T *)k, (const T *)v, idx, L.p->topk_total, dense_below, L.map,
                        L.p->num_q_heads, L.p->softmax_scale, (T *)out, lse, back ? tiles * L.p->num_kv_heads : 0);
@@ -258,7 +258,7 @@ int launch_t(const Launch &L, const void *q, const void *k, const void *v, const
     const rules::Walks x = rules::walks(cu_h, L.map.batch, tile_tokens(L.map, L.p->num_q_heads / hkv), idx != nullptr,
                                         L.p->topk_total, dense_below);
     if (sizeof(T) == 2 && rules::staged(false, D, x.two * hkv, x) && attn_staged_takes(L, k, v))
-        return launch_attn_staged(L, q, k, v, idx, dense_below, out, lse, x.two);
+        return launch_attn_staged(L, q, k, v, idx, dense_below, out, lse, cu_h, x);
     const rules::GenericForm form = rules::generic_form(sizeof(T) == 2, D, hkv, x);
     if constexpr (sizeof(T) == 2)
         if (form.groups == 2)

@@ -1,6 +1,7 @@
 // Generic attention and dQ of bf16 rows that pass through LDS (attn_staged.hip).
 #pragma once
 #include "common.h"
+#include "launch_rules.h"
 
 namespace ifv2 {
 
@@ -8,11 +9,11 @@ namespace ifv2 {
 // rules::staged)
 bool attn_staged_takes(const Launch &L, const void *k, const void *v);
 
-// tiles: of two column groups, over the whole batch
+// walks: of the batch's tiles of one column group (rules::walks); cu_h: host cu_seqlens
 int launch_attn_staged(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, void *out,
-                       float *lse, int64_t tiles);
+                       float *lse, const int32_t *cu_h, const rules::Walks &walks);
 // delta: <dO, O> per (query head, row)
 int launch_dq_staged(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, const float *lse,
-                     const float *delta, const void *dout, void *dq, int64_t tiles);
+                     const float *delta, const void *dout, void *dq, const int32_t *cu_h, const rules::Walks &walks);
 
 }  // namespace ifv2

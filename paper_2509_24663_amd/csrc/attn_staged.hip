@@ -89,7 +89,7 @@ struct StagedArgs {
     float *lse;                 // forward: output (or nullptr); backward: input
     const bf16_t *dout;         // backward
     const float *delta;
-    uint32_t resident;          // workgroups that the chip holds at once
+    uint32_t resident;          // workgroups that the chip holds at once, or 0: in the plain order
 };
 
 // acc[x] += (weights of column group x) x (the half block's rows), weights in three exact pieces (see weighted_rows32); x of [X0, X1)
@@ -384,14 +384,17 @@ __global__ void __launch_bounds__(NW * 64, D == 128 ? 2 : 3) attn_staged_kernel(
 }
 
 template <int D, bool BWD>
-int launch_t(const Launch &L, StagedArgs a, int64_t tiles) {
+int launch_t(const Launch &L, StagedArgs a, const int32_t *cu_h, const rules::Walks &walks) {
     constexpr size_t lds = (size_t)NW * 2 * Stage<D>::kBytes;
     static_assert(lds == (size_t)NW * kTileCols * D * sizeof(float), "the partial results take the stages' place");
-    a.resident = D == 128 ? 512 : 768;
+    const int64_t tiles = walks.two;
+    const int resident = D == 128 ? 512 : 768, hkv = L.p->num_kv_heads;
+    a.resident = rules::back_and_forth(cu_h, L.map.batch, CG * tile_tokens(L.map, a.hq / hkv), tiles, hkv, a.idx != nullptr, a.topk_total, a.dense_below,
+                                       walks.half_blocks, resident, true) ? resident : 0;
     void (*kern)(StagedArgs, int) = attn_staged_kernel<D, BWD>;
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return INFLLMV2_ERR_HIP;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * L.p->num_kv_heads)), dim3(NW * 64), lds, L.stream, a, (int)tiles);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * hkv)), dim3(NW * 64), lds, L.stream, a, (int)tiles);
     return hip_status(hipGetLastError());
 }
 
@@ -403,17 +406,17 @@ bool attn_staged_takes(const Launch &L, const void *k, const void *v) {
 }
 
 int launch_attn_staged(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, void *out,
-                       float *lse, int64_t tiles) {
+                       float *lse, const int32_t *cu_h, const rules::Walks &walks) {
     const StagedArgs a{(const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, idx, L.p->topk_total, dense_below, L.p->num_q_heads,
                        L.p->softmax_scale, L.map, (bf16_t *)out, lse, nullptr, nullptr, 0};
-    return L.p->head_dim == 128 ? launch_t<128, false>(L, a, tiles) : launch_t<64, false>(L, a, tiles);
+    return L.p->head_dim == 128 ? launch_t<128, false>(L, a, cu_h, walks) : launch_t<64, false>(L, a, cu_h, walks);
 }
 
 int launch_dq_staged(const Launch &L, const void *q, const void *k, const void *v, const int32_t *idx, int dense_below, const float *lse,
-                     const float *delta, const void *dout, void *dq, int64_t tiles) {
+                     const float *delta, const void *dout, void *dq, const int32_t *cu_h, const rules::Walks &walks) {
     const StagedArgs a{(const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, idx, L.p->topk_total, dense_below, L.p->num_q_heads,
                        L.p->softmax_scale, L.map, (bf16_t *)dq, const_cast<float *>(lse), (const bf16_t *)dout, delta, 0};
-    return L.p->head_dim == 128 ? launch_t<128, true>(L, a, tiles) : launch_t<64, true>(L, a, tiles);
+    return L.p->head_dim == 128 ? launch_t<128, true>(L, a, cu_h, walks) : launch_t<64, true>(L, a, cu_h, walks);
 }
 
 }  // namespace ifv2

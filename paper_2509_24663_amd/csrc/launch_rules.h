@@ -81,8 +81,8 @@ inline bool fp32_rows_ahead(int d, int hkv, int64_t workgroups, const Walks &x) 
     if (hkv > 2) return workgroups <= std::min(300., 40 * hb) || (hb >= 12 && workgroups > 600 && workgroups <= 1024);
     return workgroups <= std::min(512., 64 * hb) || (hb >= 12 && workgroups <= 600);
 }
-// Order of a generic attention launch's workgroups, which all take the tiles from the last one down: one head after the other, or, where all workgroups are on
-// the chip at once, heads side by side and rows of 256 back and forth, so that long and short tiles share a CU.  fp32 d 64, one order / the other: 2048
+// Order of a generic attention launch's workgroups, which all take the tiles from the last one down: one head after the other (SIDE_BY_SIDE, the staged form: heads side by
+// side), or, where all workgroups are on the chip at once, heads side by side and rows of 256 back and forth, so that long and short tiles share a CU.  fp32 d 64, one order / the other: 2048
 // tokens, 4 heads on 1 (512 workgroups) 29.3 / 26.8 us, with 16 blocks 38.3 / 32.5, 1000 tokens on 2 (500) 25.7 / 19.9, 1500 (750) 34.7 / 31.3; with one
 // workgroup per CU the second row would start shortest first (36.5 / 44.1).
 //
@@ -90,11 +90,13 @@ inline bool fp32_rows_ahead(int d, int hkv, int64_t workgroups, const Walks &x) 
 // (572) 58.6 / 40.5 us but 2490 and 100 of one (412) 41.6 / 45.2, 16 blocks, 2675 + 10 x 100 (535) 29.8 / 35.2; d 128, 4 on 1, 4 blocks, 1217 + 10 x 43 (415) 20.8 /
 // 23.9.  127 packed calls are 0.5 % from the faster order, 1.1 % with the second for all, six instead of fifteen of them 3 % and more slower than
 // with the first.
+// Staged form, bf16, plain / back and forth: d 128, 4 on 4, 16 blocks, 2389 + 434 + 509 tokens (420) 32.1 / 38.0, 4 on 1, dense, 2496 + 5 x 269 (482) 41.0 / 46.0; 652 packed calls 0.4 % from
+// the faster order (0.9 % and 2.1 % with one order for all), eight instead of 63 of them 3 % and more slower than with the plain one.
 // Where walks are shorter than four half blocks the call is over before the count on the host pays (2 us: 500 sequences of 4 tokens 9.1 -> 12.0 us).
 // tiles: launched, of `tokens` tokens (the sequences' partial ones may be fewer: empty ones come first); resident: workgroups that the chip holds.  cu_h: nullptr
 // where a tile is a token of its own.
 inline bool back_and_forth(const int32_t *cu_h, int batch, int tokens, int64_t tiles, int hkv, bool sparse, int topk, int dense_below, double half_blocks,
-                           int resident) {
+                           int resident, bool side_by_side) {
     const int64_t workgroups = tiles * hkv;
     if (workgroups <= 256 || workgroups > resident || resident > 1024) return false;
     if (cu_h == nullptr || batch == 1 || half_blocks < 4) return true;
@@ -108,10 +110,11 @@ inline bool back_and_forth(const int32_t *cu_h, int batch, int tokens, int64_t t
     while (nth > 0) work[--nth] = 0;
     int straight[256] = {}, back[256] = {};
     int b = 0, e = 0;
-    for (int h = 0; h < hkv; ++h)
+    for (int h = 0; h < hkv && !side_by_side; ++h)
         for (int t = 0; t < (int)tiles; ++t) straight[b++ & 255] += work[t];
     for (int t = 0; t < (int)tiles; ++t)
         for (int h = 0; h < hkv; ++h, ++e) {
+            if (side_by_side) straight[e & 255] += work[t];
             const int row = e & ~255, last = std::min(255, n - 1 - row), at = e - row;
             back[e & 256 ? last - at : at] += work[t];
         }

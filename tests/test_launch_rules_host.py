@@ -22,9 +22,9 @@ extern "C" int fp32_ahead(int d, int hkv, int tokens, const int *cu, int batch, 
     const Walks x = walks(cu, batch, tokens, sparse, topk, below);
     return fp32_rows_ahead(d, hkv, x.one * hkv, x);
 }
-extern "C" int back(const int *cu, int batch, int tokens, int tiles, int hkv, int sparse, int topk, int below, int resident) {
+extern "C" int back(const int *cu, int batch, int tokens, int tiles, int hkv, int sparse, int topk, int below, int resident, int side) {
     const double far = cu ? walks(cu, batch, tokens, sparse, topk, below).half_blocks : 0;
-    return back_and_forth(cu, batch, tokens, tiles, hkv, sparse, topk, below, far, resident);
+    return back_and_forth(cu, batch, tokens, tiles, hkv, sparse, topk, below, far, resident, side);
 }
 extern "C" int staged_form(int bwd, int d, int hkv, int tokens, const int *cu, int batch, int sparse, int topk, int below) {
     const Walks x = walks(cu, batch, tokens, sparse, topk, below);
@@ -91,9 +91,9 @@ def test_many_short_sequences_take_one_column_group(rules):
     assert _generic(rules, 1, 128, 8, 2, []) == (1, 1, 1, 1)
 
 
-def _back(rules, lens, tokens, hkv, resident, topk=16, sparse=1, below=0):
-    tiles = sum(lens) // tokens + len(lens)
-    return tiles, rules.back(_cu(lens), len(lens), tokens, tiles, hkv, sparse, topk, below, resident)
+def _back(rules, lens, tokens, hkv, resident, topk=16, sparse=1, below=0, side=0):
+    tiles = sum(-(-n // tokens) for n in lens) if side else sum(lens) // tokens + len(lens)      # (the staged form launches no empty ones)
+    return tiles, rules.back(_cu(lens), len(lens), tokens, tiles, hkv, sparse, topk, below, resident, side)
 
 
 def test_order_of_generic_attention_workgroups(rules):
@@ -101,16 +101,17 @@ def test_order_of_generic_attention_workgroups(rules):
     assert _back(rules, [1020], 4, 1, 768)[1] == 0 and _back(rules, [1024], 4, 1, 768)[1] == 1        # 256 and 257 workgroups
     assert _back(rules, [3068], 4, 1, 768)[1] == 1 and _back(rules, [3072], 4, 1, 768)[1] == 0        # 768 and 769
     assert _back(rules, [1024], 4, 1, 256)[1] == 0 and _back(rules, [2000], 4, 1, 2048)[1] == 0
-    assert rules.back(None, 300, 1, 300, 2, 1, 16, 0, 768) == 1 and rules.back(None, 2, 1, 1 << 30, 4, 1, 16, 0, 768) == 0   # (2^32 workgroups)
+    assert rules.back(None, 300, 1, 300, 2, 1, 16, 0, 768, 0) == 1 and rules.back(None, 2, 1, 1 << 30, 4, 1, 16, 0, 768, 0) == 0   # (2^32 workgroups)
     assert _back(rules, [2463, 2040, 68], 8, 1, 768, sparse=0)[1] == 1
     assert _back(rules, [2490] + [1] * 100, 8, 1, 768, sparse=0)[1] == 0 and _back(rules, [2675] + [100] * 10, 8, 1, 768)[1] == 0
     import random
     rng, seen = random.Random(3), set()
-    for _ in range(300):
-        tokens, hkv = rng.choice([1, 2, 4, 8, 16, 32]), rng.choice([1, 2, 3, 8])
+    assert _back(rules, [2389, 434, 509], 32, 4, 512, side=1)[1] == 0 and _back(rules, [3000], 8, 1, 512, side=1)[1] == 1
+    for i in range(500):
+        tokens, hkv, side = rng.choice([1, 2, 4, 8, 16, 32]), rng.choice([1, 2, 3, 8]), i % 2
         lens = [rng.choice([0, 1, rng.randint(1, 90), rng.randint(100, 3000)]) for _ in range(rng.randint(2, 40))]
         topk, sparse, below = rng.choice([1, 4, 16]), rng.randint(0, 1), rng.choice([0, 500])
-        tiles, got = _back(rules, lens, tokens, hkv, 768, topk, sparse, below)
+        tiles, got = _back(rules, lens, tokens, hkv, 768, topk, sparse, below, side)
         n = tiles * hkv
         if not 256 < n <= 768:
             assert not got
@@ -125,14 +126,14 @@ def test_order_of_generic_attention_workgroups(rules):
             most = 2 * topk if sparse and L >= below else 1 << 30
             work += [4 + min((min(t + tokens, L) + 31) // 32, most) for t in range(0, L, tokens)]
         work = [0] * (tiles - len(work)) + work[::-1]
-        one = [work[b % tiles] for b in range(n)]
         order = [w for w in work for _ in range(hkv)]                # heads side by side
+        one = order if side else [work[b % tiles] for b in range(n)]
         rows = [order[i:i + 256] for i in range(0, n, 256)]
         two = sum((r[::-1] if i % 2 else r for i, r in enumerate(rows)), [])
         fullest = [max(sum(x[c::256]) for c in range(256)) for x in (one, two)]
         assert got == (fullest[1] < fullest[0]), (lens, tokens, hkv)
-        seen.add(got)
-    assert seen == {0, 1}
+        seen.add((side, got))
+    assert len(seen) == 4
 
 
 @pytest.mark.parametrize("d,G,max_len,blocks,want", [(64, 4, 4, 601, 1), (64, 4, 4, 600, 0), (64, 4, 5, 4000, 0), (64, 1, 16, 700, 1), (64, 1, 17, 4000, 0),
