@@ -72,13 +72,14 @@ inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
 // 91 / 107; 8 on 2, 800 (400) 27 / 28, 1000 (500) 36.7 / 34.5; just over 512 without is a second, nearly empty round: 1000 + 50 tokens (526) 39.4 / 49.8, 1100 (550) 45.7 / 52.9, 1200 (600) 47 / 49, 1300
 // (650) 57 / 54.  More heads come one after the other beyond 512 and their longest tiles late, all the later in long rounds: 16 on 4, 900 tokens (900) 62 / 69, 1000
 // (1000) 71 / 78, 4 on 4, 4000 (1000) 221 / 262; within one round without they share the CUs evenly: 8 on 8, 1000 (504) 58 / 35, 4 on 4, 1200 (300) 36 / 38,
-// 1600 (400) 66 / 52.
+// 1600 (400) 66 / 52; of three heads beyond 370: 3 on 3, dense, 1642 tokens (309) 39 / 47, 1765 (333) 48 / 58, 1962 (369) 60 / 65, 6 on 3, 834 (315) 26 / 30, 917 (345) 29 / 31, 1008
+// (378) 1.14 of the time, but 4 on 4, 1290 (324) 1.04, 8 on 8, 640 (320) 1.2.
 // Over 1566 calls the rule is from the faster form in the mean 0.3 % (d 64) and 0.5 % (d 128), rows_ahead 5 % each.
 inline bool fp32_rows_ahead(int d, int hkv, int64_t workgroups, const Walks &x) {
     const double hb = x.half_blocks;
     if (d == 64) return hb >= 6 && workgroups <= (hb >= 12 ? 300 : 256);
     if (hb < 4) return false;
-    if (hkv > 2) return workgroups <= std::min(300., 40 * hb) || (hb >= 12 && workgroups > 600 && workgroups <= 1024);
+    if (hkv > 2) return workgroups <= std::min(hkv == 3 && hb >= 12 ? 370. : 300., 40 * hb) || (hb >= 12 && workgroups > 600 && workgroups <= 1024);
     return workgroups <= std::min(512., 64 * hb) || (hb >= 12 && workgroups <= 600);
 }
 // Order of a generic attention launch's workgroups, which all take the tiles from the last one down: one head after the other (SIDE_BY_SIDE, the staged form: heads side by

@@ -190,7 +190,8 @@ def test_attention_tiles(rules):
     (64, 4, 1, [1000], 8, 1), (64, 4, 1, [1200], 16, 1), (64, 4, 1, [1201], 16, 0), (64, 4, 1, [1025], 4, 0), (64, 8, 2, [1000], 8, 0),
     (64, 4, 1, [300], 8, 0), (128, 8, 2, [1000], 8, 1), (128, 8, 2, [1024], 8, 1), (128, 8, 2, [1025], 8, 1), (128, 8, 2, [1000, 50], 16, 1),
     (128, 8, 2, [1300], 8, 0), (128, 4, 1, [1985], 16, 1), (128, 4, 1, [2100], 4, 0), (128, 4, 1, [1255, 347], 16, 1), (128, 4, 4, [4000], 16, 1), (128, 4, 4, [1600], 16, 0), (128, 8, 8, [1000], 16, 0),
-    (128, 16, 4, [1000], 16, 1), (128, 16, 4, [1000], 4, 0), (128, 4, 1, [150], 8, 0), (128, 4, 1, [], 8, 0)])
+    (128, 16, 4, [1000], 16, 1), (128, 16, 4, [1000], 4, 0), (128, 4, 1, [150], 8, 0), (128, 4, 1, [], 8, 0),
+    (128, 3, 3, [1968], 16, 1), (128, 3, 3, [1969], 16, 0), (128, 6, 3, [834], 16, 1), (128, 6, 3, [834], 4, 0), (128, 4, 4, [1290], 16, 0)])
 def test_fp32_rows_ahead_only_where_a_cu_has_one_workgroup_to_run(rules, d, hq, hkv, lens, topk, ahead):
     assert rules.fp32_ahead(d, hkv, 16 // (hq // hkv), _cu(lens), len(lens), 1, topk, 0) == ahead
 
