@@ -74,7 +74,7 @@ inline GenericForm generic_form(bool bf16, int d, int hkv, const Walks &x) {
 // (1000) 71 / 78, 4 on 4, 4000 (1000) 221 / 262; within one round without they share the CUs evenly: 8 on 8, 1000 (504) 58 / 35, 4 on 4, 1200 (300) 36 / 38,
 // 1600 (400) 66 / 52; of three heads beyond 370: 3 on 3, dense, 1642 tokens (309) 39 / 47, 1765 (333) 48 / 58, 1962 (369) 60 / 65, 6 on 3, 834 (315) 26 / 30, 917 (345) 29 / 31, 1008
 // (378) 1.14 of the time, but 4 on 4, 1290 (324) 1.04, 8 on 8, 640 (320) 1.2.
-// Over 1566 calls the rule is from the faster form in the mean 0.3 % (d 64) and 0.5 % (d 128), rows_ahead 5 % each.
+// Over 2015 calls, half of them near these lines, the rule is from the faster form in the mean 0.2 % (d 64) and 0.9 % (d 128), rows_ahead 4 % each.
 inline bool fp32_rows_ahead(int d, int hkv, int64_t workgroups, const Walks &x) {
     const double hb = x.half_blocks;
     if (d == 64) return hb >= 6 && workgroups <= (hb >= 12 ? 300 : 256);
